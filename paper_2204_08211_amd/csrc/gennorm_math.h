@@ -25,13 +25,13 @@ namespace co3 {
 constexpr double kBetaMin = 0.1;    // range the moment fit searches; the kurtosis falls from
 constexpr double kBetaMax = 64.0;   // about 3.3e4 to 1.8 (the uniform limit) over it
 
-// Regularised incomplete gamma functions P(a, x) and Q(a, x) = 1 - P(a, x): power series for
+// Regularised incomplete gamma functions P(a, x) and Q(a, x) = 1 - P(a, x), lga = lgamma(a): power series for
 // x < a + 1, continued fraction (modified Lentz) otherwise.
-CO3_HD inline void inc_gamma(double a, double x, double *P, double *Q)
+CO3_HD inline void inc_gamma(double a, double x, double lga, double *P, double *Q)
 {
     if (x <= 0.0) { *P = 0.0; *Q = 1.0; return; }
     if (isinf(x)) { *P = 1.0; *Q = 0.0; return; }
-    const double lead = exp(a * log(x) - x - lgamma(a));
+    const double lead = exp(a * log(x) - x - lga);
     if (x < a + 1.0) {
         double term = 1.0 / a, sum = term, ap = a;
         for (int n = 0; n < 2000; ++n) {
@@ -66,22 +66,27 @@ CO3_HD inline void inc_gamma(double a, double x, double *P, double *Q)
 CO3_HD inline void gennorm_cdf(double x, double mu, double alpha, double beta, double *F, double *S)
 {
     double P, Q;
-    inc_gamma(1.0 / beta, pow(fabs(x - mu) / alpha, beta), &P, &Q);
+    inc_gamma(1.0 / beta, pow(fabs(x - mu) / alpha, beta), lgamma(1.0 / beta), &P, &Q);
     if (x >= mu) { *F = 0.5 + 0.5 * P; *S = 0.5 * Q; }
     else { *F = 0.5 * Q; *S = 0.5 + 0.5 * P; }
 }
 
-// Probability of (lo, hi], taken on the tail that keeps precision.
-CO3_HD inline double gennorm_mass(double lo, double hi, double mu, double alpha, double beta)
+// Probability of (lo, hi] from F and 1 - F at its ends, taken on the tail that keeps precision.
+CO3_HD inline double mass_between(double Flo, double Slo, double Fhi, double Shi)
 {
-    double Flo, Slo, Fhi, Shi;
-    gennorm_cdf(lo, mu, alpha, beta, &Flo, &Slo);
-    gennorm_cdf(hi, mu, alpha, beta, &Fhi, &Shi);
     double p;
     if (Fhi <= 0.5) p = Fhi - Flo;
     else if (Slo <= 0.5) p = Slo - Shi;
     else p = Fhi - Flo;
     return p < 0.0 ? 0.0 : p;
+}
+
+CO3_HD inline double gennorm_mass(double lo, double hi, double mu, double alpha, double beta)
+{
+    double Flo, Slo, Fhi, Shi;
+    gennorm_cdf(lo, mu, alpha, beta, &Flo, &Slo);
+    gennorm_cdf(hi, mu, alpha, beta, &Fhi, &Shi);
+    return mass_between(Flo, Slo, Fhi, Shi);
 }
 
 // Magnitude of magnitude code k (exponent field k >> M, mantissa field below) for one bias.
@@ -108,6 +113,17 @@ CO3_HD inline bool symbol_cell(uint32_t s, int E, int M, int bias, double *lo, d
     return true;
 }
 
+// The factor alpha^k Gamma((k+1)/beta) / (2 Gamma(1/beta)) of the partial moments below, from the two log-gammas, and
+// the factor times the difference of P between two places, taken on the tail that keeps precision.
+CO3_HD inline double moment_scale(int k, double alpha, double lg_shape, double lg_zero)
+{
+    return 0.5 * exp((double)k * log(alpha) + lg_shape - lg_zero);
+}
+CO3_HD inline double moment_between(double ck, double Pa, double Qa, double Pb, double Qb)
+{
+    return ck * (Pa > 0.5 ? Qa - Qb : Pb - Pa);
+}
+
 // int_a^b y^k f_Y(y) dy for the zero-location density f_Y and 0 <= a <= b <= infinity:
 //   alpha^k Gamma((k+1)/beta) / (2 Gamma(1/beta)) [P((k+1)/beta, (b/alpha)^beta) - P(.., (a/alpha)^beta)],
 // the difference taken on the tail that keeps precision.
@@ -115,11 +131,11 @@ CO3_HD inline double interval_moment_pos(int k, double a, double b, double alpha
 {
     if (!(b > a)) return 0.0;
     const double shape = ((double)k + 1.0) / beta;
-    const double ck = 0.5 * exp((double)k * log(alpha) + lgamma(shape) - lgamma(1.0 / beta));
+    const double lg = lgamma(shape), ck = moment_scale(k, alpha, lg, lgamma(1.0 / beta));
     double Pa, Qa, Pb, Qb;
-    inc_gamma(shape, pow(a / alpha, beta), &Pa, &Qa);
-    inc_gamma(shape, pow(b / alpha, beta), &Pb, &Qb);
-    return ck * (Pa > 0.5 ? Qa - Qb : Pb - Pa);
+    inc_gamma(shape, pow(a / alpha, beta), lg, &Pa, &Qa);
+    inc_gamma(shape, pow(b / alpha, beta), lg, &Pb, &Qb);
+    return moment_between(ck, Pa, Qa, Pb, Qb);
 }
 
 // The same for any a <= b: the part on the negative axis is the mirrored integral with sign (-1)^k.
@@ -129,6 +145,9 @@ CO3_HD inline double interval_moment(int k, double a, double b, double alpha, do
     const double neg = interval_moment_pos(k, -b > 0.0 ? -b : 0.0, -a > 0.0 ? -a : 0.0, alpha, beta);
     return (k & 1) ? pos - neg : pos + neg;
 }
+
+// int (y - c)^2 f_Y(y) dy over a cell from the cell's moments
+CO3_HD inline double sq_error_of_moments(double c, double j0, double j1, double j2) { return j2 - 2.0 * c * j1 + c * c * j0; }
 
 // Share of symbol s in E (Q_fp(X) - X)^2 for X ~ GenNorm(mu, alpha, beta) and one exponent bias:
 // the integral of (x - r)^2 f(x) over the cell of its representative r (0 if Q_fp cannot produce s).
@@ -142,7 +161,7 @@ CO3_HD inline double sq_error_of_symbol(uint32_t s, int E, int M, int bias, doub
     const double j0 = interval_moment(0, a, b, alpha, beta);
     const double j1 = interval_moment(1, a, b, alpha, beta);
     const double j2 = interval_moment(2, a, b, alpha, beta);
-    return j2 - 2.0 * c * j1 + c * c * j0;
+    return sq_error_of_moments(c, j0, j1, j2);
 }
 
 // E (Q_fp(X) - X)^2: the objective of eq. (exp bias), Sec. IV-A (i), summed over the symbols.

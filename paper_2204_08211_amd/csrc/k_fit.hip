@@ -8,7 +8,7 @@
 //                    lane adds its elements in index order, the wavefront folds the lanes in a
 //                    fixed order: the sums do not depend on scheduling
 //   k_fit_params     per (user, layer): folds the chunk sums in a fixed order, central moments,
-//                    beta from the kurtosis by bisection, alpha from the variance
+//                    beta from the kurtosis by bisection (its steps evaluated ahead), alpha from the variance
 //   k_model_weights  per code table: the element-count-weighted mixture of the quantized models
 //                    of the (user, layer) pairs the table serves -> integer Huffman weights
 //
@@ -92,14 +92,59 @@ __global__ __launch_bounds__(kMoThreads) void k_moments(Layout lay, const float 
     }
 }
 
+// beta_of_kurtosis() by the workgroup: the same bisection, kFitDepth steps at a time.  An evaluation is three
+// log-gammas, some 2 us that depend on the step before, so the midpoints of the next kFitDepth steps, whichever way
+// those turn out, are evaluated side by side: thread k takes node k of the binary tree of intervals (heap order), and
+// every thread then walks down the tree with the answers.  Midpoints and decisions are the serial bisection's, bit
+// for bit; it ends once a whole walk leaves the interval as it was, which the serial one's remaining steps would, too.
+// (One thread, 80 evaluations one after the other: k_fit_params 168 us; this way 40 us.)
+constexpr int kFitDepth = 8;
+static_assert(kFitThreads == 1 << kFitDepth, "a thread per node of the tree");
+__device__ inline double fit_beta_of_kurtosis(double kappa, uint32_t t, uint8_t *s_flag)
+{
+    if (!(kappa == kappa) || isinf(kappa)) return kBetaMin;   // the same in every thread
+    const double lk = log(kappa);
+    if ((t & 63u) == 0u && t < 128u) s_flag[t >> 6] = t ? lk <= log_kurtosis_of_beta(kBetaMax) : lk >= log_kurtosis_of_beta(kBetaMin);
+    __syncthreads();
+    const bool at_min = s_flag[0], at_max = s_flag[1];
+    __syncthreads();
+    if (at_min) return kBetaMin;
+    if (at_max) return kBetaMax;
+    double lo = log(kBetaMin), hi = log(kBetaMax);
+    for (int i = 0; i < 80; i += kFitDepth) {
+        if (t) {
+            double a = lo, b = hi;
+            for (int l = 30 - __clz((int)t); l >= 0; --l) {   // from the bit below the leading one of t down
+                const double mid = 0.5 * (a + b);
+                if ((t >> l) & 1u) a = mid; else b = mid;
+            }
+            s_flag[t] = log_kurtosis_of_beta(exp(0.5 * (a + b))) > lk;
+        }
+        __syncthreads();
+        const double lo0 = lo, hi0 = hi;
+        uint32_t node = 1;
+        for (int l = 0; l < kFitDepth; ++l) {
+            const double mid = 0.5 * (lo + hi);
+            const uint32_t right = s_flag[node];
+            if (right) lo = mid; else hi = mid;
+            node = 2 * node + right;
+        }
+        __syncthreads();
+        if (lo == lo0 && hi == hi0) break;
+    }
+    return exp(0.5 * (lo + hi));
+}
+
 __global__ __launch_bounds__(kFitThreads) void k_fit_params(Layout lay, const double *__restrict__ partial,
                                                             co3_gennorm_params *__restrict__ params)
 {
     __shared__ double s_red[4][kFitThreads];
+    __shared__ uint8_t s_flag[kFitThreads];
     const uint32_t seg = blockIdx.x, u = blockIdx.y, t = threadIdx.x;
     const uint64_t cs = lay.segs[seg].chunk_start, ce = lay.segs[seg + 1].chunk_start;
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (uint64_t c = cs + t; c < ce; c += kFitThreads) {
+#pragma unroll 8
+    for (uint64_t c = cs + t; c < ce; c += kFitThreads) {   // eight chunks' sums requested together, added in order
         const double *p = partial + ((uint64_t)u * lay.nchunks + c) * 4;
 #pragma unroll
         for (int j = 0; j < 4; ++j) a[j] += p[j];
@@ -114,10 +159,9 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_params(Layout lay, const do
         }
         __syncthreads();
     }
-    if (t != 0) return;
     co3_gennorm_params out = {0.0, 0.0, 0.0, 0.0};
     const uint64_t n = lay.segs[seg].length;
-    if (n > 0) {
+    if (n > 0) {   // the same in every thread, like everything below
         const double dn = (double)n;
         const double S1 = s_red[0][0], S2 = s_red[1][0], S3 = s_red[2][0], S4 = s_red[3][0];
         const double mean = S1 / dn, ms = S2 / dn;
@@ -127,39 +171,80 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_params(Layout lay, const do
         // a variance below 2^-40 of the mean square is rounding noise of the raw sums: constant layer
         if (m2 > ms * 9.094947017729282e-13) {
             out.kurtosis = m4 / (m2 * m2);
-            out.beta = beta_of_kurtosis(out.kurtosis);
+            out.beta = fit_beta_of_kurtosis(out.kurtosis, t, s_flag);
             out.alpha = sqrt(m2 / variance_factor(out.beta));
         }
     }
-    params[(uint64_t)u * lay.nseg + seg] = out;
+    if (t == 0) params[(uint64_t)u * lay.nseg + seg] = out;
 }
 
-__global__ __launch_bounds__(kMaxA) void k_model_weights(Layout lay, const co3_gennorm_params *__restrict__ params,
-                                                         uint64_t *__restrict__ weights)
+// Weights of code table b: the masses of its (user, layer) pairs are summed per symbol in the order of the pairs.  What
+// bounds it is the length of one evaluation (a power and an incomplete gamma function in fp64, some microseconds),
+// not their number, so an evaluation gets a thread: a workgroup takes kMwSymbols symbols and kMwPairs pairs at a time,
+// two neighbouring threads the two ends of a cell.  (Thread per symbol, ends and pairs one after the other: 121
+// against 15 us for eight users in [1,5,2], 1.05 ms for sixteen in [1,5,6].)
+constexpr int kMwSymbols = 16;
+constexpr int kMwPairs = 8;
+constexpr int kMwThreads = 2 * kMwSymbols * kMwPairs;
+__global__ __launch_bounds__(kMwThreads) void k_model_weights(Layout lay, const co3_gennorm_params *__restrict__ params,
+                                                              uint64_t *__restrict__ weights)
 {
-    const uint32_t b = blockIdx.x;
-    const uint32_t u_first = lay.per_user_books ? b / lay.books_per_user : 0u;
-    const uint32_t u_last = lay.per_user_books ? u_first : lay.U - 1u;
+    __shared__ uint64_t s_pair[kMwThreads];            // the pairs of a block of kMwThreads candidates that count, in order
+    __shared__ uint32_t s_cnt[kMwThreads / 64];
+    __shared__ double s_term[kMwPairs][kMwSymbols];
+    const uint32_t b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const uint32_t end = t & 1u, sl = (t >> 1) % kMwSymbols, slot = (t >> 1) / kMwSymbols;
+    const uint32_t s = blockIdx.y * kMwSymbols + sl;   // may lie beyond the alphabet (symbol_cell refuses it)
+    const uint64_t first = (lay.per_user_books ? (uint64_t)(b / lay.books_per_user) : 0u) * lay.nseg;
+    const uint64_t npair = lay.per_user_books ? (uint64_t)lay.nseg : (uint64_t)lay.U * lay.nseg;
     const int32_t book = (int32_t)(lay.per_user_books ? b % lay.books_per_user : b);
-    for (uint32_t s = threadIdx.x; s < lay.A; s += kMaxA) {   // one symbol per thread up to 8 bits, up to 16 above
-        double lo, hi;
-        const bool producible = symbol_cell(s, lay.E, lay.M, lay.bias[0], &lo, &hi);  // the same for every bias
-        double mass = 0.0, count = 0.0;
-        if (producible) {
-            for (uint32_t u = u_first; u <= u_last; ++u) {
-                for (uint32_t k = 0; k < lay.nseg; ++k) {
-                    const SegDev sd = lay.segs[k];
-                    if (sd.book != book || sd.length == 0) continue;
-                    const co3_gennorm_params p = params[(uint64_t)u * lay.nseg + k];
-                    if (!(p.alpha > 0.0) || !(p.beta > 0.0)) continue;
-                    symbol_cell(s, lay.E, lay.M, lay.bias[(uint64_t)u * lay.nseg + k], &lo, &hi);
-                    // with a real-valued scale the conversion sees y = v * gain: the model's location and scale times gain
-                    const double gn = (double)lay.gain[2 * ((uint64_t)u * lay.nseg + k)];
-                    mass += (double)sd.length * gennorm_mass(lo, hi, p.mu * gn, p.alpha * gn, p.beta);
-                    count += (double)sd.length;
-                }
-            }
+    double ends[2];
+    const bool producible = s < lay.A && symbol_cell(s, lay.E, lay.M, lay.bias[0], &ends[0], &ends[1]);  // the same for every bias
+    double mass = 0.0, count = 0.0;                    // of thread `sl`'s symbol, in the threads of slot 0
+    for (uint64_t base = 0; base < npair; base += kMwThreads) {
+        const uint64_t cand = first + base + t;
+        bool use = base + t < npair;
+        if (use) {
+            const SegDev sd = lay.segs[cand % lay.nseg];
+            const co3_gennorm_params p = params[cand];
+            use = sd.book == book && sd.length != 0 && p.alpha > 0.0 && p.beta > 0.0;
         }
+        const uint64_t mask = __ballot(use);
+        if (lane == 0) s_cnt[wave] = (uint32_t)__popcll(mask);
+        __syncthreads();
+        uint32_t pos = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull)), n = 0;
+        for (uint32_t k = 0; k < kMwThreads / 64; ++k) {
+            pos += k < wave ? s_cnt[k] : 0u;
+            n += s_cnt[k];
+        }
+        if (use) s_pair[pos] = cand;
+        __syncthreads();
+        for (uint32_t i0 = 0; i0 < n; i0 += kMwPairs) {
+            const uint32_t i = i0 + slot;
+            if (i < n) {                               // the same in both threads of a cell
+                const uint64_t pr = s_pair[i];
+                double F = 0.0, S = 0.0;
+                if (producible) {
+                    const co3_gennorm_params p = params[pr];
+                    symbol_cell(s, lay.E, lay.M, lay.bias[pr], &ends[0], &ends[1]);
+                    // with a real-valued scale the conversion sees y = v * gain: the model's location and scale times gain
+                    const double gn = (double)lay.gain[2 * pr];
+                    gennorm_cdf(ends[end], p.mu * gn, p.alpha * gn, p.beta, &F, &S);
+                }
+                const double Fhi = __shfl_xor(F, 1, 64), Shi = __shfl_xor(S, 1, 64);
+                if (end == 0) s_term[slot][sl] = (double)lay.segs[pr % lay.nseg].length * mass_between(F, S, Fhi, Shi);
+            }
+            __syncthreads();
+            const uint32_t nk = n - i0 < (uint32_t)kMwPairs ? n - i0 : (uint32_t)kMwPairs;
+            if (slot == 0)
+                for (uint32_t k = 0; k < nk; ++k) {
+                    mass += s_term[k][sl];
+                    count += (double)lay.segs[s_pair[i0 + k] % lay.nseg].length;
+                }
+            __syncthreads();
+        }
+    }
+    if (slot == 0 && end == 0 && s < lay.A) {
         uint64_t w = 0;
         if (producible) {
             w = 1;
@@ -174,24 +259,84 @@ __global__ __launch_bounds__(kMaxA) void k_model_weights(Layout lay, const co3_g
 
 // Exponent bias from the model, eq. (exp bias) with integer b.  The expected squared error of a candidate
 // bias is a sum of non-negative shares, one per symbol's cell, so any few shares bound it from below:
-//   k_model_bias_bounds  per (user, layer), thread per candidate: the shares of the zero cell and of the two
+//   k_model_bias_bounds  per (user, layer), kErrLanes threads per symbol: the shares of the zero cell and of the two
 //                        outermost cells (too coarse a set loses in the first, too narrow a one in the others)
 //   k_model_bias_ref     per (user, layer): the candidate with the smallest bound, evaluated in full; no
 //                        candidate whose bound exceeds that error can be the minimum or tie with it
-//   k_model_bias_errors  workgroup per (candidate bias, layer, user), thread per symbol: every thread
-//                        integrates (x - r)^2 f(x) over its symbol's cell, the workgroup folds the
-//                        shares in a fixed order -> expected squared error of the candidate; candidates
-//                        ruled out by their bound leave at once (a handful of the 226 remain)
-//   k_model_bias_pick    per (user, layer): the smallest bias whose error is within kBiasTie of the
+//   k_model_bias_errors  workgroup per (candidate bias, layer, user): the integral of (x - r)^2 f(x) over
+//                        every symbol's cell in closed form, folded in a fixed order -> expected squared
+//                        error of the candidate; candidates ruled out by their bound leave at once (a
+//                        handful of the 226 remain)
+//   k_model_bias_pick    wavefront per (user, layer): the smallest bias whose error is within kBiasTie of the
 //                        minimum (a format with many binades has a plateau of equally good biases;
 //                        the smallest has the most headroom).  No model (alpha = 0): the IEEE bias.
+// What bounds all of it is the length of one incomplete gamma function in fp64 (some microseconds each: a power, an
+// exponential, a series with a division per term), so the six that a cell needs - three moments at two ends - are
+// evaluated side by side by kErrLanes threads, and what they share, the log-gammas of the three shapes, once per
+// workgroup.  (Thread per symbol, the six one after the other, picks by one thread: 280 us for eight
+// users in [1,5,2]; this way 92 us.)
 constexpr int kBiasSlots = 256;  // error slots per (user, layer); candidates: at most 226
 constexpr double kBiasPrune = 1e-6;  // margin of the bound test, far above the rounding of the sums and the tie width
+constexpr int kErrLanes = 8;     // threads per symbol: moment (0, 1, 2) x end of the cell; two idle
+constexpr int kErrThreads = 1024;
+constexpr int kErrSyms = kErrThreads / kErrLanes;   // symbols a workgroup evaluates at a time
 
-// the workgroup's sum of one value per thread, folded in a fixed order
-__device__ inline double bias_fold(double *s_red, uint32_t t, double e)
+// What the cells of one (mu, alpha, beta) share: per moment the log-gamma of its shape and the moment's factor.
+struct ErrModel { double lg[3], ck[3]; };
+__device__ inline void err_log_gammas(ErrModel *em, uint32_t t, double beta)
 {
-    s_red[t] = e;
+    if (t < 3u) em->lg[t] = lgamma(((double)t + 1.0) / beta);
+    __syncthreads();
+}
+__device__ inline void err_factors(ErrModel *em, uint32_t t, double alpha)   // of this alpha; log-gammas are there
+{
+    if (t < 3u) em->ck[t] = moment_scale((int)t, alpha, em->lg[t], em->lg[0]);
+    __syncthreads();
+}
+
+// sq_error_of_symbol() by kErrLanes neighbouring threads, part = threadIdx.x % kErrLanes; all of them call it with the
+// same symbol.  The share is returned in the thread of part 0.
+__device__ inline double err_of_symbol(uint32_t s, int E, int M, int bias, double mu, double alpha, double beta,
+                                       const ErrModel *em, uint32_t part)
+{
+    const uint32_t k = part >> 1, end = part & 1u;
+    double lo, hi, j = 0.0, c = 0.0;
+    const bool cell = symbol_cell(s, E, M, bias, &lo, &hi);
+    if (cell) {
+        const int code = (int)(s & ((1u << (E + M)) - 1u));
+        const double r = ((s >> (E + M)) & 1u) ? -magnitude_of_code(code, M, bias) : magnitude_of_code(code, M, bias);
+        c = r - mu;
+        const double a = lo - mu, b = hi - mu;
+        double side[2] = {0.0, 0.0};   // the part on the positive axis, the mirrored part on the negative one
+#pragma unroll 1
+        for (int n = 0; n < 2; ++n) {
+            const double x0 = n ? -b : a, x1 = n ? -a : b;
+            const double p0 = x0 > 0.0 ? x0 : 0.0, p1 = x1 > 0.0 ? x1 : 0.0;
+            if (!(p1 > p0)) continue;  // the same for all threads of a symbol
+            double P = 0.0, Q = 0.0;
+            if (k < 3u) inc_gamma(((double)k + 1.0) / beta, pow((end ? p1 : p0) / alpha, beta), em->lg[k], &P, &Q);
+            const double Pb = __shfl_xor(P, 1, 64), Qb = __shfl_xor(Q, 1, 64);
+            if (k < 3u) side[n] = moment_between(em->ck[k], P, Q, Pb, Qb);   // right in the thread of end 0
+        }
+        j = (k & 1u) ? side[0] - side[1] : side[0] + side[1];
+    }
+    const double j1 = __shfl_down(j, 2, 64), j2 = __shfl_down(j, 4, 64);
+    return cell ? sq_error_of_moments(c, j, j1, j2) : 0.0;
+}
+
+// Expected squared error of one candidate by a workgroup of kErrThreads: the shares of symbols i, i + 256, ... are
+// added in this order (one symbol for alphabets of up to 8 bits), then the 256 sums in a fixed tree.
+__device__ inline double err_total(double *s_red, uint32_t t, uint32_t A, int E, int M, int bias, double mu, double alpha,
+                                   double beta, const ErrModel *em)
+{
+    static_assert(kMaxA == 2 * kErrSyms, "two symbols of a block of 256 per thread group");
+    const uint32_t part = t % kErrLanes, sl = t / kErrLanes;
+    double e0 = 0.0, e1 = 0.0;
+    for (uint32_t s0 = 0; s0 < A; s0 += kMaxA) {
+        if (s0 + sl < A) e0 += err_of_symbol(s0 + sl, E, M, bias, mu, alpha, beta, em, part);
+        if (s0 + kErrSyms + sl < A) e1 += err_of_symbol(s0 + kErrSyms + sl, E, M, bias, mu, alpha, beta, em, part);
+    }
+    if (part == 0) { s_red[sl] = e0; s_red[kErrSyms + sl] = e1; }
     __syncthreads();
     for (int o = kMaxA / 2; o > 0; o >>= 1) {
         if (t < (uint32_t)o) s_red[t] += s_red[t + o];
@@ -202,53 +347,75 @@ __device__ inline double bias_fold(double *s_red, uint32_t t, double e)
     return r;
 }
 
-__global__ __launch_bounds__(kMaxA) void k_model_bias_bounds(Layout lay, const co3_gennorm_params *__restrict__ params,
-                                                             double *__restrict__ bounds)
+constexpr int kBoundLanes = 4 * kErrLanes;   // threads per candidate: three symbols, kErrLanes threads idle
+constexpr int kBoundCands = 8;               // candidates per workgroup
+__global__ __launch_bounds__(kBoundLanes *kBoundCands) void k_model_bias_bounds(
+    Layout lay, const co3_gennorm_params *__restrict__ params, double *__restrict__ bounds)
 {
-    const uint32_t seg = blockIdx.x, u = blockIdx.y, cand = threadIdx.x;
-    const co3_gennorm_params p = params[(uint64_t)u * lay.nseg + seg];
-    const int ncand = kBiasMax - bias_min_supported(lay.E) + 1;
-    if ((int)cand >= ncand) return;
-    double lb = INFINITY;
-    if (p.alpha > 0.0 && p.beta > 0.0) {
-        const int bias = bias_min_supported(lay.E) + (int)cand;
+    __shared__ ErrModel s_em;
+    __shared__ double s_share[kBoundCands][3];
+    const uint32_t seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x;
+    const uint32_t cl = t / kBoundLanes, which = t % kBoundLanes / kErrLanes, part = t % kErrLanes;
+    const uint32_t cand = blockIdx.x * kBoundCands + cl;
+    const uint64_t pair = (uint64_t)u * lay.nseg + seg;
+    const co3_gennorm_params p = params[pair];
+    const uint32_t ncand = (uint32_t)(kBiasMax - bias_min_supported(lay.E) + 1);
+    const bool model = p.alpha > 0.0 && p.beta > 0.0;   // the same in every thread
+    if (model) {
+        err_log_gammas(&s_em, t, p.beta);
+        err_factors(&s_em, t, p.alpha);
         const uint32_t top = (((1u << lay.E) - 1u) << lay.M) - 1u;        // largest magnitude code
-        lb = sq_error_of_symbol(0u, lay.E, lay.M, bias, p.mu, p.alpha, p.beta) +
-             sq_error_of_symbol(top, lay.E, lay.M, bias, p.mu, p.alpha, p.beta) +
-             sq_error_of_symbol((1u << (lay.E + lay.M)) | top, lay.E, lay.M, bias, p.mu, p.alpha, p.beta);
+        if (cand < ncand && which < 3u) {
+            const uint32_t sy = which == 0u ? 0u : which == 1u ? top : (1u << (lay.E + lay.M)) | top;
+            const double e = err_of_symbol(sy, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em, part);
+            if (part == 0) s_share[cl][which] = e;
+        }
+        __syncthreads();
     }
-    bounds[((uint64_t)u * lay.nseg + seg) * kBiasSlots + cand] = lb;
+    if (cand < ncand && t % kBoundLanes == 0)
+        bounds[pair * kBiasSlots + cand] = model ? s_share[cl][0] + s_share[cl][1] + s_share[cl][2] : INFINITY;
 }
 
-__global__ __launch_bounds__(kMaxA) void k_model_bias_ref(Layout lay, const co3_gennorm_params *__restrict__ params,
-                                                          const double *__restrict__ bounds, double *__restrict__ ref)
+__global__ __launch_bounds__(kErrThreads) void k_model_bias_ref(Layout lay, const co3_gennorm_params *__restrict__ params,
+                                                                const double *__restrict__ bounds, double *__restrict__ ref)
 {
     __shared__ double s_red[kMaxA];
+    __shared__ ErrModel s_em;
     __shared__ int s_c0;
     const uint32_t seg = blockIdx.x, u = blockIdx.y, t = threadIdx.x;
-    const co3_gennorm_params p = params[(uint64_t)u * lay.nseg + seg];
-    const bool model = p.alpha > 0.0 && p.beta > 0.0;
-    const int ncand = kBiasMax - bias_min_supported(lay.E) + 1;
-    if (t == 0) {
-        const double *lb = bounds + ((uint64_t)u * lay.nseg + seg) * kBiasSlots;
-        int c0 = 0;
-        for (int c = 1; c < ncand; ++c) c0 = lb[c] < lb[c0] ? c : c0;
-        s_c0 = c0;
+    const uint64_t pair = (uint64_t)u * lay.nseg + seg;
+    const co3_gennorm_params p = params[pair];
+    if (!(p.alpha > 0.0 && p.beta > 0.0)) {   // the same in every thread
+        if (t == 0) ref[pair] = INFINITY;
+        return;
     }
-    __syncthreads();
-    double e = 0.0;   // the shares of symbols t, t + 256, ... in this order (one symbol for alphabets of up to 8 bits)
-    if (model)
-        for (uint32_t sy = t; sy < lay.A; sy += kMaxA)
-            e += sq_error_of_symbol(sy, lay.E, lay.M, bias_min_supported(lay.E) + s_c0, p.mu, p.alpha, p.beta);
-    const double total = bias_fold(s_red, t, e);
-    if (t == 0) ref[(uint64_t)u * lay.nseg + seg] = model ? total : INFINITY;
+    const int ncand = kBiasMax - bias_min_supported(lay.E) + 1;
+    if (t < 64u) {   // first candidate with the smallest bound
+        const double *lb = bounds + pair * kBiasSlots;
+        int c0 = 0;
+        double v0 = lb[0];
+        for (int c = (int)t; c < ncand; c += 64) {
+            if (lb[c] < v0) { v0 = lb[c]; c0 = c; }
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const double v = __shfl_xor(v0, o, 64);
+            const int c = __shfl_xor(c0, o, 64);
+            if (v < v0 || (v == v0 && c < c0)) { v0 = v; c0 = c; }
+        }
+        if (t == 0) s_c0 = c0;
+    }
+    err_log_gammas(&s_em, t, p.beta);
+    err_factors(&s_em, t, p.alpha);
+    const double total = err_total(s_red, t, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + s_c0, p.mu, p.alpha, p.beta, &s_em);
+    if (t == 0) ref[pair] = total;
 }
 
-__global__ __launch_bounds__(kMaxA) void k_model_bias_errors(Layout lay, const co3_gennorm_params *__restrict__ params,
-                                                             const double *__restrict__ bounds,
-                                                             const double *__restrict__ ref, double *__restrict__ errors)
+__global__ __launch_bounds__(kErrThreads) void k_model_bias_errors(Layout lay, const co3_gennorm_params *__restrict__ params,
+                                                                   const double *__restrict__ bounds,
+                                                                   const double *__restrict__ ref, double *__restrict__ errors)
 {
     __shared__ double s_red[kMaxA];
+    __shared__ ErrModel s_em;
     const uint32_t cand = blockIdx.x, seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
     const co3_gennorm_params p = params[pair];
@@ -258,32 +425,56 @@ __global__ __launch_bounds__(kMaxA) void k_model_bias_errors(Layout lay, const c
         if (t == 0) errors[pair * kBiasSlots + cand] = INFINITY;
         return;
     }
-    double e = 0.0;
-    for (uint32_t sy = t; sy < lay.A; sy += kMaxA)
-        e += sq_error_of_symbol(sy, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta);
-    const double total = bias_fold(s_red, t, e);
+    err_log_gammas(&s_em, t, p.beta);
+    err_factors(&s_em, t, p.alpha);
+    const double total = err_total(s_red, t, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em);
     if (t == 0) errors[pair * kBiasSlots + cand] = total;
 }
 
 __global__ __launch_bounds__(64) void k_model_bias_pick(Layout lay, const double *__restrict__ errors,
                                                         int32_t *__restrict__ bias_out, double *__restrict__ error_out)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (user, layer) pair
-    if (i >= (uint64_t)lay.U * lay.nseg) return;
+    const uint64_t i = blockIdx.x;  // (user, layer) pair
     const double *err = errors + i * kBiasSlots;
     const int b0 = bias_min_supported(lay.E);
     const int ncand = kBiasMax - b0 + 1;
+    const int lane = (int)threadIdx.x;
+    constexpr int kPer = kBiasSlots / 64;
+    double e[kPer], lowest = INFINITY;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int c = lane + 64 * r;
+        e[r] = c < ncand ? err[c] : INFINITY;
+        lowest = e[r] < lowest ? e[r] : lowest;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double v = __shfl_xor(lowest, o, 64);
+        lowest = v < lowest ? v : lowest;
+    }
     int best = (1 << (lay.E - 1)) - 1;
-    double best_err = 0.0, lowest = INFINITY;
-    for (int c = 0; c < ncand; ++c) lowest = err[c] < lowest ? err[c] : lowest;
+    double best_err = 0.0;
     if (lowest < INFINITY) {
         const double limit = lowest * (1.0 + kBiasTie);
-        for (int c = 0; c < ncand; ++c) {
-            if (err[c] <= limit) { best = b0 + c; best_err = err[c]; break; }
+        int first = ncand;          // the first candidate within the limit; there is one, the lowest itself
+        double first_err = 0.0;
+#pragma unroll
+        for (int r = kPer - 1; r >= 0; --r) {
+            if (e[r] <= limit) { first = lane + 64 * r; first_err = e[r]; }
         }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const int c = __shfl_xor(first, o, 64);
+            const double v = __shfl_xor(first_err, o, 64);
+            if (c < first) { first = c; first_err = v; }
+        }
+        best = b0 + first;
+        best_err = first_err;
     }
-    bias_out[i] = best;
-    if (error_out) error_out[i] = best_err;
+    if (lane == 0) {
+        bias_out[i] = best;
+        if (error_out) error_out[i] = best_err;
+    }
 }
 
 // errors and bounds per candidate, reference error per pair
@@ -297,11 +488,12 @@ hipError_t launch_model_bias(const Layout &lay, const co3_gennorm_params *params
     ProfScope prof(K_MODEL_BIAS, s);
     const uint64_t pairs = (uint64_t)lay.U * lay.nseg;
     double *bounds = errors_ws + pairs * kBiasSlots, *ref = bounds + pairs * kBiasSlots;
-    hipLaunchKernelGGL(k_model_bias_bounds, dim3(lay.nseg, lay.U), dim3(kMaxA), 0, s, lay, params, bounds);
-    hipLaunchKernelGGL(k_model_bias_ref, dim3(lay.nseg, lay.U), dim3(kMaxA), 0, s, lay, params, bounds, ref);
-    hipLaunchKernelGGL(k_model_bias_errors, dim3((uint32_t)ncand, lay.nseg, lay.U), dim3(kMaxA), 0, s, lay, params,
+    hipLaunchKernelGGL(k_model_bias_bounds, dim3((uint32_t)(ncand + kBoundCands - 1) / kBoundCands, lay.nseg, lay.U),
+                       dim3(kBoundLanes * kBoundCands), 0, s, lay, params, bounds);
+    hipLaunchKernelGGL(k_model_bias_ref, dim3(lay.nseg, lay.U), dim3(kErrThreads), 0, s, lay, params, bounds, ref);
+    hipLaunchKernelGGL(k_model_bias_errors, dim3((uint32_t)ncand, lay.nseg, lay.U), dim3(kErrThreads), 0, s, lay, params,
                        bounds, ref, errors_ws);
-    hipLaunchKernelGGL(k_model_bias_pick, dim3((uint32_t)((pairs + 63) / 64)), dim3(64), 0, s, lay, errors_ws, bias,
+    hipLaunchKernelGGL(k_model_bias_pick, dim3((uint32_t)pairs), dim3(64), 0, s, lay, errors_ws, bias,
                        error);
     return hipGetLastError();
 }
@@ -312,13 +504,14 @@ hipError_t launch_model_bias(const Layout &lay, const co3_gennorm_params *params
 // serves again.  The logarithm s = t - bias of the whole scale is scanned in steps of 1/16 binade over one and a
 // half binades to either side of the integer optimum and refined by a golden-section search between the scan
 // points next to the best one; bias = -round(s), t = s + bias in [-1/2, 1/2].  One workgroup per (user, layer),
-// thread per symbol, every evaluation folded in the same fixed order: all threads see the same numbers and take
+// every evaluation folded in the same fixed order: all threads see the same numbers and take
 // the same steps.  A real scale is taken only where it lowers the error by more than kBiasTie (relative).
-__global__ __launch_bounds__(kMaxA) void k_model_scale(Layout lay, const co3_gennorm_params *__restrict__ params,
+__global__ __launch_bounds__(kErrThreads) void k_model_scale(Layout lay, const co3_gennorm_params *__restrict__ params,
                                                        int32_t *bias_io, const double *__restrict__ err_int,
                                                        float *__restrict__ gain_pairs, double *error_out)
 {
     __shared__ double s_red[kMaxA];
+    __shared__ ErrModel s_em;
     const uint32_t seg = blockIdx.x, u = blockIdx.y, t = threadIdx.x;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
     const co3_gennorm_params p = params[pair];
@@ -330,6 +523,7 @@ __global__ __launch_bounds__(kMaxA) void k_model_scale(Layout lay, const co3_gen
     __syncthreads();   // every thread has read the integer result before thread 0 replaces it
     if (p.alpha > 0.0 && p.beta > 0.0) {   // the same in every thread
         const int bmin = bias_min_supported(lay.E), bmax = kBiasMax;
+        err_log_gammas(&s_em, t, p.beta);
         auto split = [&](double sc, int &b, double &tt) {
             b = (int)lround(-sc);
             b = b < bmin ? bmin : (b > bmax ? bmax : b);
@@ -337,10 +531,8 @@ __global__ __launch_bounds__(kMaxA) void k_model_scale(Layout lay, const co3_gen
         };
         auto err_at = [&](int b, double tt) {
             const double c = exp2(tt);
-            double e = 0.0;
-            for (uint32_t sy = t; sy < lay.A; sy += kMaxA)
-                e += sq_error_of_symbol(sy, lay.E, lay.M, b, p.mu / c, p.alpha / c, p.beta);
-            return c * c * bias_fold(s_red, t, e);
+            err_factors(&s_em, t, p.alpha / c);
+            return c * c * err_total(s_red, t, lay.A, lay.E, lay.M, b, p.mu / c, p.alpha / c, p.beta, &s_em);
         };
         auto f = [&](double sc) {
             int b;
@@ -398,7 +590,7 @@ hipError_t launch_model_scale(const Layout &lay, const co3_gennorm_params *param
     hipError_t e = launch_model_bias(lay, params, bias, err_int, ws_int, s);
     if (e != hipSuccess) return e;
     ProfScope prof(K_MODEL_BIAS, s);
-    hipLaunchKernelGGL(k_model_scale, dim3(lay.nseg, lay.U), dim3(kMaxA), 0, s, lay, params, bias, err_int, gain_pairs,
+    hipLaunchKernelGGL(k_model_scale, dim3(lay.nseg, lay.U), dim3(kErrThreads), 0, s, lay, params, bias, err_int, gain_pairs,
                        error);
     return hipGetLastError();
 }
@@ -424,7 +616,8 @@ hipError_t launch_model_weights(const Layout &lay, const co3_gennorm_params *par
 {
     if (lay.nbooks == 0) return hipSuccess;
     ProfScope prof(K_MODEL_WEIGHTS, s);
-    hipLaunchKernelGGL(k_model_weights, dim3(lay.nbooks), dim3(kMaxA), 0, s, lay, params, weights);
+    hipLaunchKernelGGL(k_model_weights, dim3(lay.nbooks, (lay.A + kMwSymbols - 1) / kMwSymbols), dim3(kMwThreads), 0, s,
+                       lay, params, weights);
     return hipGetLastError();
 }
 

@@ -101,6 +101,27 @@ def test_fit_layers_empty_constant_and_shared_tables(per_user):
     check_weights(w, fitm.pooled_model_weights(E, M, bias, ref, seg_len, seg_book, per_user))
 
 
+@pytest.mark.parametrize("E,M,nseg,U,per_user", [(2, 1, 100, 3, False), (4, 3, 129, 2, False), (3, 5, 5, 9, False), (4, 3, 300, 2, True)])
+def test_weights_of_tables_that_serve_many_pairs(E, M, nseg, U, per_user):
+    # more (user, layer) pairs than a workgroup looks at in one go (256), numbers of pairs off the multiples of
+    # those it evaluates at a time, pairs that do not count in between; alphabets of one tile of symbols to 32
+    import torch
+    from paper_2204_08211_amd import binding as B
+    rng = np.random.default_rng(7 * nseg + U)
+    seg_len = [int(x) for x in rng.integers(0, 40, nseg)]
+    seg_book = [int(x) for x in rng.integers(0, 2, nseg)]
+    bias = rng.integers(8, 20, (U, nseg)).astype(np.int32)
+    par = np.zeros((U, nseg, 4))
+    for idx in np.ndindex(U, nseg):
+        if rng.random() < 0.8:
+            a = 2.0 ** (-float(bias[idx])) * rng.uniform(0.5, 8.0)
+            par[idx] = [rng.uniform(-0.1, 0.1) * a, a, rng.uniform(0.5, 2.0), 3.0]
+    plan = B.Plan(E, M, U, sum(seg_len), bias, seg_len=seg_len, seg_book=seg_book, per_user_books=per_user)
+    w = B.co3_model_weights_device(plan, torch.from_numpy(par).to("cuda:0"))
+    check_weights(w.cpu().numpy().view(np.uint64),
+                  fitm.pooled_model_weights(E, M, bias, par, seg_len, seg_book, per_user))
+
+
 def test_fit_closed_form_samples():
     # {-1 (p), 0, +1 (p)} scaled: kurtosis 1/(2p) exactly; p = 1/12 is Laplace's 6, p = 1/6 the Normal's 3
     E, M = 4, 3
