@@ -119,20 +119,23 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     if (!segments) { segments = &whole; nseg = 1; }
     if (nseg == 0 || nseg > (1u << 20)) return CO3_ERR_ARG;
     std::vector<SegDev> segs(nseg + 1);
-    uint64_t off = 0, chunks = 0;
+    uint64_t off = 0, chunks = 0, wg = 0, wg_small = 0;
     int32_t max_book = 0;
     for (uint32_t k = 0; k < nseg; ++k) {
         if (segments[k].offset != off || segments[k].codebook < 0 || segments[k].codebook >= (1 << 16))
             return CO3_ERR_ARG;
         if (off + segments[k].length < off) return CO3_ERR_ARG;
-        segs[k] = {off, segments[k].length, chunks, segments[k].codebook, 0};
+        segs[k] = {off, segments[k].length, chunks, segments[k].codebook, (uint32_t)wg, (uint32_t)wg_small, 0};
+        const uint64_t n = (segments[k].length + kChunk - 1) / kChunk;
         off += segments[k].length;
-        chunks += (segments[k].length + kChunk - 1) / kChunk;
+        chunks += n;
+        wg += (n + kWgChunks - 1) / kWgChunks;   // never more than chunks, which is checked below
+        wg_small += (n + kWgChunksSmall - 1) / kWgChunksSmall;
         if (segments[k].codebook > max_book) max_book = segments[k].codebook;
     }
     if (off != d) return CO3_ERR_ARG;
     if (chunks >= (1ull << 31)) return CO3_ERR_ARG;  // one workgroup per chunk in grid.x
-    segs[nseg] = {d, 0, chunks, 0, 0};
+    segs[nseg] = {d, 0, chunks, 0, (uint32_t)wg, (uint32_t)wg_small, 0};
     int rc = check_bias_table(format, bias, (size_t)U * nseg);
     if (rc != CO3_OK) return rc;
 
@@ -158,6 +161,7 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     }
     Layout &l = p->lay;
     l.U = U; l.nseg = nseg; l.d = d; l.nchunks = chunks;
+    l.nwg = (uint32_t)wg; l.nwg_small = (uint32_t)wg_small;
     l.E = format.exp_bits; l.M = format.mant_bits;
     l.A = 1u << (1 + format.exp_bits + format.mant_bits);
     l.wide = l.A > (uint32_t)kMaxA ? 1u : 0u;

@@ -79,8 +79,11 @@ struct SegDev {
     uint64_t length;
     uint64_t chunk_start;  // index of the segment's first chunk within a user
     int32_t book;          // code table id within a user's (or the shared) set
-    int32_t pad;
+    uint32_t wg_start;     // first of the layer's workgroups of up to kWgChunks chunks (k_wide.hip's coder)
+    uint32_t wg_small_start;   // the same for workgroups of up to kWgChunksSmall chunks
+    uint32_t pad;
 };
+constexpr uint32_t kWgChunks = 16, kWgChunksSmall = 4;
 
 // Constants of Q_fp for one (format, bias), derived on the device from E, M and bias.
 struct Layout {
@@ -88,6 +91,7 @@ struct Layout {
     uint32_t nseg;
     uint64_t d;
     uint64_t nchunks;          // per user
+    uint32_t nwg, nwg_small;   // per user: workgroups of up to kWgChunks, kWgChunksSmall chunks of one layer
     int32_t E, M;
     uint32_t A;
     uint32_t books_per_user;   // 1 + max segment.codebook

@@ -3,9 +3,9 @@
 // The steps are those of the byte path (Algorithm 1 lines 8-10 and 13-14; Sec. IV-A (i)-(iii), Sec. II-B (iv))
 // and the container is the same; symbols are 16-bit words and a code table has up to 4096 entries, too many
 // for the per-wavefront LDS tables the byte kernels are built around: here a workgroup shares one copy of the
-// table of the layer it works on, and falls back to the table in device memory where its range of the vector
-// crosses into a layer with another table.  A fixed code without a symbol buffer ("single sweep" in the byte
-// path) runs the same three steps here with the symbols kept in the workspace.
+// table of the layer it works on, and loads the next one where its range of the vector crosses into a layer with
+// another table.  A fixed code without a symbol buffer ("single sweep" in the byte path) runs the same three steps
+// here with the symbols kept in the workspace.
 //
 //   k_quantize_wide      v = g + gamma m, Q_fp, m' = v - ghat, symbol; symbol counts in an LDS table per workgroup
 //                        (and, for a held code on layers that start on its tile grid, the chunks' coded sizes)
@@ -97,11 +97,16 @@ __device__ inline WChunk w_chunk(const Layout &lay, uint64_t c, uint32_t u)
 
 // ---- user side, step 1 ------------------------------------------------------------------------------------
 
-// A workgroup takes kWqTiles consecutive tiles of one user and counts their symbols in an LDS table of the code
+// A workgroup takes `tiles` consecutive tiles of one user and counts their symbols in an LDS table of the code
 // table in use (A entries), which it adds to one of the global partial tables when the code table changes (a layer
 // with another table begins) and at its end; the few elements of a tile that belong to another table than the
 // tile's first element are counted in global memory directly.
-constexpr int kWqTiles = 32;
+// The table's atomics into device memory at a workgroup's end are the price of many workgroups, the memory latency
+// that nothing covers the price of few: up to kWqTiles tiles per workgroup, fewer while there would be less than
+// kWqGrid workgroups (three users of 2 M elements: 93 workgroups 66 us, 1466 workgroups 25 us; sixteen users of
+// 25.6 M elements keep 32 tiles, 1.14 ms).
+constexpr uint32_t kWqTiles = 32;
+constexpr uint64_t kWqGrid = 1024;
 typedef float wf4 __attribute__((ext_vector_type(4)));
 typedef uint32_t wu2 __attribute__((ext_vector_type(2)));
 // kSR: the stochastic conversion (dither from Philox words of (element, user, seed)) instead of the closest
@@ -116,7 +121,7 @@ __global__ __launch_bounds__(kWqThreads) void k_quantize_wide(Layout lay, const 
                                                               uint64_t seed, uint64_t *__restrict__ hist_rep,
                                                               const BookWide *__restrict__ books,
                                                               uint32_t *__restrict__ chunk_bits,
-                                                              uint64_t *__restrict__ status)
+                                                              uint64_t *__restrict__ status, uint32_t tiles)
 {
     __shared__ uint32_t s_hist[kWideMaxA];
     __shared__ uint32_t s_len4[kBits ? kWideMaxA / 4 : 1];   // the code lengths of the table in use, four per word
@@ -146,8 +151,8 @@ __global__ __launch_bounds__(kWqThreads) void k_quantize_wide(Layout lay, const 
     int bias0 = 0;
     QConst qc0 = make_qconst(lay.E, lay.M, 0);
     float gain0 = 1.0f, inv_gain0 = 1.0f;
-    for (int tile = 0; tile < kWqTiles; ++tile) {
-        const uint64_t base = ((uint64_t)blockIdx.x * kWqTiles + (uint64_t)tile) * kWqTile;
+    for (uint32_t tile = 0; tile < tiles; ++tile) {
+        const uint64_t base = ((uint64_t)blockIdx.x * tiles + tile) * kWqTile;
         if (base >= lay.d) break;      // workgroup-uniform
         if (base >= seg_end) {         // the tile starts in another layer than the last one did: look it up
             seg0 = w_find_segment(lay.segs, lay.nseg, base);
@@ -534,11 +539,46 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
 
 // ---- user side, steps 2 and 3 -------------------------------------------------------------------------------
 
-// Both chunk kernels give a workgroup kWChunksPerWg consecutive chunks of one user (wavefront w takes chunks
-// w, w + kWWaves, ...) and keep the code table of the workgroup's first chunk in LDS; a chunk of another table
-// (a layer boundary inside the workgroup's range) reads its table from global memory instead.
-constexpr int kWChunksPerWave = 4;
-constexpr int kWChunksPerWg = kWWaves * kWChunksPerWave;
+// Both chunk kernels give a workgroup up to kWWaves * cpw consecutive chunks of one layer of one user, wavefront w
+// chunks w, w + kWWaves, ..., with the layer's code table in LDS; a layer's last workgroup has fewer.  (Workgroups
+// cut from the chunks of all layers kept the first layer's table only and coded another layer's chunks by rolled
+// loops from device memory: three users of 2 M elements in five layers, k_pack_wide 383 us, this way 16 us.)
+// A table is up to 36 KB to read, so a wavefront takes four chunks where that still leaves every CU several
+// workgroups, and one otherwise.
+static_assert(kWgChunksSmall == kWWaves && kWgChunks == 4 * kWWaves, "the plan's workgroup counts");
+constexpr uint64_t kWSmallGrid = 1024;   // workgroups of kWgChunks chunks below which they take kWgChunksSmall
+inline uint32_t w_chunks_per_wave(const Layout &lay)
+{
+    return (uint64_t)lay.nwg * lay.U < kWSmallGrid ? kWgChunksSmall / kWWaves : kWgChunks / kWWaves;
+}
+// first chunk of workgroup b and its first element, chunks and elements of the workgroup, the layer's code table
+struct WRange {
+    uint64_t first, e0;
+    uint32_t nck, n, book;
+    __device__ inline uint32_t count(uint32_t i) const   // elements of the workgroup's chunk i
+    {
+        const uint32_t left = n - i * kChunk;
+        return left < (uint32_t)kChunk ? left : (uint32_t)kChunk;
+    }
+};
+__device__ inline WRange w_range(const Layout &lay, uint32_t u, uint32_t b, uint32_t cpw)
+{
+    const bool small = cpw * kWWaves == kWgChunksSmall;
+    uint32_t lo = 0, hi = lay.nseg;   // last layer whose first workgroup is <= b (layers without chunks have none)
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if ((small ? lay.segs[mid].wg_small_start : lay.segs[mid].wg_start) <= b) lo = mid; else hi = mid;
+    }
+    const SegDev sd = lay.segs[lo];
+    WRange r;
+    r.first = sd.chunk_start + (uint64_t)(b - (small ? sd.wg_small_start : sd.wg_start)) * (kWWaves * cpw);
+    r.e0 = sd.offset + (r.first - sd.chunk_start) * kChunk;
+    const uint64_t left = sd.offset + sd.length - r.e0;   // > 0: layer lo has this workgroup
+    r.n = left < (uint64_t)(kWWaves * cpw * kChunk) ? (uint32_t)left : kWWaves * cpw * kChunk;
+    r.nck = (r.n + kChunk - 1) / kChunk;
+    r.book = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
+    return r;
+}
 constexpr uint32_t kWFastCodeBits = 25;   // s_fast entry: length << 25 | codeword, for lengths up to 25
 constexpr int kWSymLoads = (kChunk / 2 + 1 + 63) / 64;    // dword loads per lane to cover a chunk at any 2-byte offset (33)
 constexpr uint32_t kWSymMask2 = (uint32_t)(kWideMaxA - 1) * 0x10001u;
@@ -671,46 +711,53 @@ __device__ inline void w_rows_to_window(uint32_t *region, uint32_t lane, uint32_
 
 __global__ __launch_bounds__(kWThreads) void k_chunk_bits_wide(Layout lay, const uint16_t *__restrict__ sym,
                                                               uint64_t sym_stride, const BookWide *__restrict__ books,
-                                                              uint32_t *__restrict__ chunk_bits)
+                                                              uint32_t *__restrict__ chunk_bits, uint32_t cpw)
 {
     __shared__ uint8_t s_len[kWideMaxA];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t c_base = (uint64_t)blockIdx.x * kWChunksPerWg;   // < nchunks by the grid
     const uint32_t u = blockIdx.y;
-    const uint32_t wg_book = w_chunk(lay, c_base, u).book;
+    const WRange wg = w_range(lay, u, blockIdx.x, cpw);
     for (uint32_t i = threadIdx.x; i < (uint32_t)kWideMaxA; i += kWThreads)
-        s_len[i] = i < lay.A ? books[wg_book].len[i] : (uint8_t)0;
+        s_len[i] = i < lay.A ? books[wg.book].len[i] : (uint8_t)0;
     __syncthreads();
-    for (int it = 0; it < kWChunksPerWave; ++it) {
-        const uint64_t c = c_base + (uint64_t)it * kWWaves + wave;
-        if (c >= lay.nchunks) break;   // whole wavefront; no workgroup barriers below
-        const WChunk k = w_chunk(lay, c, u);
-        const uint16_t *src = sym + (uint64_t)u * sym_stride + k.e0;
+    for (uint32_t i_ck = wave; i_ck < wg.nck; i_ck += kWWaves) {   // whole wavefronts; no workgroup barriers below
+        const uint64_t c = wg.first + i_ck;
+        const uint32_t n = wg.count(i_ck);
+        const uint16_t *src = sym + (uint64_t)u * sym_stride + wg.e0 + i_ck * (uint32_t)kChunk;
         uint32_t total = 0;
-        if (k.book == wg_book) {
-            uint32_t done = 0;
-            if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) {   // eight symbols per load
-                const uint4 *src8 = reinterpret_cast<const uint4 *>(src);
-                uint4 v[kChunk / 8 / 64];   // a whole chunk is eight loads per lane, all requested before the first is used
+        if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) {   // eight symbols per load
+            const uint4 *src8 = reinterpret_cast<const uint4 *>(src);
+            uint4 v[kChunk / 8 / 64];   // a whole chunk is eight loads per lane, all requested before the first is used
 #pragma unroll
-                for (int r = 0; r < kChunk / 8 / 64; ++r) {
-                    const uint32_t i = lane + 64u * r;
-                    v[r] = i < (k.n >> 3) ? src8[i] : make_uint4(0u, 0u, 0u, 0u);
-                }
-#pragma unroll
-                for (int r = 0; r < kChunk / 8 / 64; ++r) {
-                    if (lane + 64u * r >= (k.n >> 3)) continue;
-                    const uint32_t w[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        total += (uint32_t)s_len[w[q] & (kWideMaxA - 1)] + (uint32_t)s_len[(w[q] >> 16) & (kWideMaxA - 1)];
-                }
-                done = k.n & ~7u;
+            for (int r = 0; r < kChunk / 8 / 64; ++r) {
+                const uint32_t i = lane + 64u * r;
+                v[r] = i < (n >> 3) ? src8[i] : make_uint4(0u, 0u, 0u, 0u);
             }
-            for (uint32_t e = done + lane; e < k.n; e += 64) total += s_len[src[e] & (kWideMaxA - 1)];
-        } else {
-            const uint8_t *len = books[k.book].len;
-            for (uint32_t e = lane; e < k.n; e += 64) total += len[src[e] & (kWideMaxA - 1)];
+#pragma unroll
+            for (int r = 0; r < kChunk / 8 / 64; ++r) {
+                if (lane + 64u * r >= (n >> 3)) continue;
+                const uint32_t w[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    total += (uint32_t)s_len[w[q] & (kWideMaxA - 1)] + (uint32_t)s_len[(w[q] >> 16) & (kWideMaxA - 1)];
+            }
+            for (uint32_t e = (n & ~7u) + lane; e < n; e += 64) total += s_len[src[e] & (kWideMaxA - 1)];
+        } else {   // any element offset: dwords from the 4-byte boundary below the chunk, requested together
+            const uint32_t shift = (uint32_t)(reinterpret_cast<uintptr_t>(src) >> 1) & 1u;
+            const uint32_t *src32 = reinterpret_cast<const uint32_t *>(src - shift);
+            const uint32_t end = shift + n;          // symbols from the boundary
+            uint32_t v[kWSymLoads];
+#pragma unroll
+            for (int r = 0; r < kWSymLoads; ++r) {
+                const uint32_t i = lane + 64u * r;
+                v[r] = i < ((end + 1u) >> 1) ? src32[i] : 0u;
+            }
+#pragma unroll
+            for (int r = 0; r < kWSymLoads; ++r) {
+                const uint32_t p = 2u * (lane + 64u * r);   // position of the low half
+                const uint32_t l0 = s_len[v[r] & (kWideMaxA - 1)], l1 = s_len[(v[r] >> 16) & (kWideMaxA - 1)];
+                total += (p >= shift && p < end ? l0 : 0u) + (p + 1u < end ? l1 : 0u);
+            }
         }
         total = w_wave_sum(total);
         if (lane == 0) chunk_bits[(uint64_t)u * lay.nchunks + c] = total;
@@ -721,17 +768,16 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
                                                         const BookWide *__restrict__ books,
                                                         const uint64_t *__restrict__ chunk_offset,
                                                         uint16_t *__restrict__ sub_bits, uint32_t *__restrict__ words,
-                                                        uint64_t words_stride, uint64_t *__restrict__ status)
+                                                        uint64_t words_stride, uint64_t *__restrict__ status, uint32_t cpw)
 {
     extern __shared__ uint32_t wp_smem[];   // kWPackLds bytes
     uint32_t *s_fast = wp_smem;                      // [kWideMaxA]
     uint32_t *s_wave_all = s_fast + kWideMaxA;       // [kWWaves][kWPackWaveWords]
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t c_base = (uint64_t)blockIdx.x * kWChunksPerWg;   // < nchunks by the grid
     const uint32_t u = blockIdx.y;
-    const uint32_t wg_book = w_chunk(lay, c_base, u).book;
+    const WRange wg = w_range(lay, u, blockIdx.x, cpw);
     {
-        const BookWide &tb = books[wg_book];
+        const BookWide &tb = books[wg.book];
         uint32_t tl[kWideMaxA / kWThreads], tc[kWideMaxA / kWThreads];   // the loads are issued together
 #pragma unroll
         for (int r = 0; r < kWideMaxA / kWThreads; ++r) {
@@ -747,19 +793,18 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
         }
     }
     __syncthreads();
+    const BookWide &book = books[wg.book];
     uint32_t *region = s_wave_all + wave * kWPackWaveWords;
-    for (int it = 0; it < kWChunksPerWave; ++it) {
-        const uint64_t c = c_base + (uint64_t)it * kWWaves + wave;
-        if (c >= lay.nchunks) break;   // whole wavefront; wavefront-level synchronisation only below
-        const WChunk k = w_chunk(lay, c, u);
-        const BookWide &book = books[k.book];
-        const uint16_t *src = sym + (uint64_t)u * sym_stride + k.e0;
+    for (uint32_t i_ck = wave; i_ck < wg.nck; i_ck += kWWaves) {   // whole wavefronts; wavefront-level synchronisation only below
+        const uint64_t c = wg.first + i_ck;
+        const uint32_t n = wg.count(i_ck);
+        const uint16_t *src = sym + (uint64_t)u * sym_stride + wg.e0 + i_ck * (uint32_t)kChunk;
         // The chunk's symbols, at any 2-byte offset and of any length: coalesced dwords from the 4-byte boundary
         // below the chunk go to LDS rows of 32 + 1 words (word i of the chunk at i + i / 32), from which lane l
         // funnels its 64 symbols (words 32 l .. 32 l + 32) into registers, two per word.
         const uint32_t shift = (uint32_t)(reinterpret_cast<uintptr_t>(src) >> 1) & 1u;
         const uint32_t *src32 = reinterpret_cast<const uint32_t *>(src - shift);
-        const uint32_t ndw = (shift + k.n + 1u) >> 1;      // <= kChunk / 2 + 1
+        const uint32_t ndw = (shift + n + 1u) >> 1;      // <= kChunk / 2 + 1
         uint32_t tmp[kWSymLoads];
 #pragma unroll
         for (int r = 0; r < kWSymLoads; ++r) {
@@ -775,7 +820,7 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
         }
         w_wave_sync_lds();
         const int first = (int)lane * kSub;
-        const int cnt = (int)k.n - first < 0 ? 0 : ((int)k.n - first > kSub ? kSub : (int)k.n - first);
+        const int cnt = (int)n - first < 0 ? 0 : ((int)n - first > kSub ? kSub : (int)n - first);
         uint32_t *row32 = region + lane * kWRowStride;
         uint32_t symw[kSub / 2];
         {
@@ -790,28 +835,24 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
         w_wave_sync_lds();   // every lane holds its symbols: the rows are free
 
         uint32_t bits = 0;
-        const bool in_lds = k.book == wg_book;   // whole wavefront: the table in LDS is this chunk's
-        int rows = kRowsSlow;
-        if (in_lds) {
-            uint32_t nocode = 0;
-            rows = k.n == (uint32_t)kChunk
-                       ? w_pack_rows<true>(symw, cnt, s_fast, book, region, region + kWRegion, lane, bits, nocode)
-                       : w_pack_rows<false>(symw, cnt, s_fast, book, region, region + kWRegion, lane, bits, nocode);
-            if (rows != kRowsSlow && nocode)   // (the plain loops below count them themselves)
-                atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
-        }
+        uint32_t redo_nocode = 0;
+        const int rows = n == (uint32_t)kChunk
+                             ? w_pack_rows<true>(symw, cnt, s_fast, book, region, region + kWRegion, lane, bits, redo_nocode)
+                             : w_pack_rows<false>(symw, cnt, s_fast, book, region, region + kWRegion, lane, bits, redo_nocode);
+        if (rows != kRowsSlow && redo_nocode)   // (the plain loops below count them themselves)
+            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)redo_nocode);
         const bool fast_ok = rows == kRowsOk;
         const uint16_t *row = reinterpret_cast<const uint16_t *>(row32);
-        // what the plain loops know of a symbol: from the table in LDS where that is this chunk's and holds the
-        // symbol's code, else from device memory
+        // what the plain loops know of a symbol: from the table in LDS where that holds the symbol's code, else from
+        // device memory
         auto lookup = [&](uint32_t sj, uint32_t &L, uint64_t &code) {
-            const uint32_t e = in_lds ? s_fast[sj] : (kWFastSlow << kWFastCodeBits);
+            const uint32_t e = s_fast[sj];
             L = e >> kWFastCodeBits;
             code = e & ((1u << kWFastCodeBits) - 1u);
             if (L == kWFastSlow) { L = book.len[sj]; code = book.code[sj]; }
         };
         if (rows == kRowsSlow) {
-            // a long code, a symbol without one, or another table: the symbols go back to the rows, plain loops
+            // long codes or symbols without one in more than a few lanes: the symbols go back to the rows, plain loops
             w_wave_sync_lds();
 #pragma unroll
             for (int jj = 0; jj < kSub / 2; ++jj) row32[jj] = symw[jj];
@@ -1284,10 +1325,12 @@ hipError_t launch_encode_wide(const Layout &lay, const co3_encode_args &a, BookW
     }
     if (lay.d) {
         ProfScope prof(K_QUANTIZE, s);
-        const dim3 grid((uint32_t)((lay.d + (uint64_t)kWqTile * kWqTiles - 1) / ((uint64_t)kWqTile * kWqTiles)), lay.U);
+        const uint64_t ntiles = (lay.d + kWqTile - 1) / kWqTile, per = ntiles * lay.U / kWqGrid;
+        const uint32_t tiles = per < 1 ? 1u : per < kWqTiles ? (uint32_t)per : kWqTiles;
+        const dim3 grid((uint32_t)((ntiles + tiles - 1) / tiles), lay.U);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, dim3(kWqThreads), 0, s, lay, a.g, a.m, a.m_out, sym, sym_stride, a.row_stride,
-                               a.gamma, a.seed, hist_rep, static_cast<const BookWide *>(books), chunk_bits, a.status);
+                               a.gamma, a.seed, hist_rep, static_cast<const BookWide *>(books), chunk_bits, a.status, tiles);
         };
         if (a.rounding == CO3_ROUND_STOCHASTIC) {
             if (bits_in_sweep) launch(k_quantize_wide<true, true>);
@@ -1305,10 +1348,11 @@ hipError_t launch_encode_wide(const Layout &lay, const co3_encode_args &a, BookW
         hipError_t e = launch_build_books_wide(books, lay.nbooks, lay.A, hist, a.status, s);
         if (e != hipSuccess) return e;
     }
-    const uint32_t gx = (uint32_t)((lay.nchunks + kWChunksPerWg - 1) / kWChunksPerWg);
+    const uint32_t cpw = w_chunks_per_wave(lay);
+    const uint32_t gx = cpw * kWWaves == kWgChunksSmall ? lay.nwg_small : lay.nwg;
     if (lay.nchunks && !bits_in_sweep) {
         ProfScope prof(K_CHUNK_BITS, s);
-        hipLaunchKernelGGL(k_chunk_bits_wide, dim3(gx, lay.U), dim3(kWThreads), 0, s, lay, sym, sym_stride, books, chunk_bits);
+        hipLaunchKernelGGL(k_chunk_bits_wide, dim3(gx, lay.U), dim3(kWThreads), 0, s, lay, sym, sym_stride, books, chunk_bits, cpw);
     }
     hipError_t e = launch_scan_chunks(lay, chunk_bits, a.chunk_offset, a.payload_bits, s);   // the byte path's scan
     if (e != hipSuccess) return e;
@@ -1318,7 +1362,7 @@ hipError_t launch_encode_wide(const Layout &lay, const co3_encode_args &a, BookW
         if (e != hipSuccess) return e;
         ProfScope prof(K_PACK, s);
         hipLaunchKernelGGL(k_pack_wide, dim3(gx, lay.U), dim3(kWThreads), kWPackLds, s, lay, sym, sym_stride, books,
-                           a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status);
+                           a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status, cpw);
     }
     return hipGetLastError();
 }

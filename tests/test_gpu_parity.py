@@ -702,6 +702,25 @@ def test_wide_alphabets_both_encoders(E, M, d):
         gu.assert_bits_equal(buf.words[u, :wds.size].cpu().numpy().view(np.uint32), wds, f"bitstream of user {u}")
 
 
+@pytest.mark.parametrize("U,seg_len", [(2, [4096 * 4, 4096 * 4 + 1, 1, 0, 4096 * 16 + 5, 4096 * 17, 63, 4096 * 5]),
+                                       (128, [1, 4096 * 17 - 3, 2, 63, 0, 65, 1, 127, 5])])
+def test_wide_coder_layers_of_whole_and_partial_workgroups(U, seg_len):
+    # the chunk kernels' workgroups end with a layer: layers of exactly 4, 16 and one more chunks, of none and of one
+    # element, at odd element offsets, neighbours with different tables; few users (4 chunks per workgroup) and as
+    # many as give workgroups of 16
+    E, M = 4, 5
+    seg_book = [k % 3 for k in range(len(seg_len))]
+    d = sum(seg_len)
+    rng = np.random.default_rng(U)
+    bias = rng.integers(14, 17, (U, len(seg_len))).astype(np.int32)
+    g = (rng.laplace(size=(U, d)) * 2.0 ** -6).astype(np.float32)
+    m = (rng.laplace(size=(U, d)) * 2.0 ** -8).astype(np.float32)
+    kw = dict(E=E, M=M, U=U, d=d, bias=bias, seg_len=seg_len, seg_book=seg_book)
+    ref = gu.oracle_round(kw, g, m, 0.9)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_EMPIRICAL)
+    gu.compare_round(gpu, ref, d)
+
+
 @pytest.mark.parametrize("stochastic", [False, True])
 def test_wide_held_code_with_layers_on_the_tile_grid(stochastic):
     # layers that start at multiples of 2048 elements (the held code's chunk sizes are then summed in the first
