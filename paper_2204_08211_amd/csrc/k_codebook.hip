@@ -5,7 +5,12 @@
 // internal nodes in creation order, merge the two smallest with leaves first on equal weight.
 // The merge runs in rounds that each pair off every node the serial merge would take before any
 // node it has yet to create; a table of 256 symbols takes some twenty rounds.
+//
+// What bounds it is the chain of dependent LDS accesses in one workgroup, not the work, so whatever was a loop of one
+// thread over the lengths is a scan over the lanes, and the merge runs in one wavefront without barriers (one user of
+// 2^20 elements in [1,3,0] with the code rebuilt, the whole round: 64.9 -> 52.2 us; tables of 256 symbols save more).
 #include "co3_internal.h"
+#include "pack_core.h"
 
 namespace co3 {
 
@@ -29,14 +34,17 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     __shared__ uint32_t sorted[kMaxA];
     __shared__ uint64_t tmpw[kMaxA];      // a round's nodes in merged order: weight
     __shared__ int tmpid[kMaxA];          // and node index
+    __shared__ uint32_t wcnt[kCbThreads / 64][65];   // codes of every length per wavefront of symbols
+    __shared__ uint32_t end[kDecBits];
+    __shared__ uint32_t long0;
     __shared__ int err;
 
     const uint64_t myw = (t < (int)A) ? w[t] : 0;
-    lw[t] = myw;
     slen[t] = 0;
     parent[t] = -1;
     parent[t + kMaxA] = -1;
-    if (t < 65) { cnt[t] = 0; off[t] = 0; first[t] = 0; }
+    for (int i = t; i < (kCbThreads / 64) * 65; i += kCbThreads) (&wcnt[0][0])[i] = 0;
+    if (t == 0) { cnt[0] = 0; off[0] = 0; first[0] = 0; }
     if (t == 0) err = 0;
     __syncthreads();
     // 2^64 - 1 marks an exhausted queue in the merge below; as a weight it is refused, like the
@@ -44,16 +52,24 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     if (myw == ~0ull) err = 1;
     const int n = __syncthreads_count(myw > 0);
 
-    // rank of this leaf in (weight, symbol) order among the active symbols
-    if (myw > 0) {
+    // rank of this leaf in (weight, symbol) order among the active symbols; an inactive one counts as heavier than
+    // all.  Of equal weights the earlier symbol comes first, so a symbol of an earlier wavefront counts up to this
+    // weight and one of a later wavefront below it: only the thread's own wavefront compares the symbols as well.
+    lw[t] = myw ? myw : ~0ull;
+    __syncthreads();
+    {
+        const int w0 = t & ~63, a = (int)A;
         int rank = 0;
 #pragma unroll 8
-        for (int j = 0; j < (int)A; ++j) {
-            const uint64_t wj = lw[j];
-            rank += (int)((wj != 0) & ((wj < myw) | ((wj == myw) & (j < t))));
+        for (int j = 0; j < (w0 < a ? w0 : a); ++j) rank += lw[j] <= myw;
+#pragma unroll 8
+        for (int j = w0; j < (w0 + 64 < a ? w0 + 64 : a); ++j) rank += lw[j] < myw + (uint64_t)(j < t);
+#pragma unroll 8
+        for (int j = w0 + 64; j < a; ++j) rank += lw[j] < myw;
+        if (myw > 0 && myw != ~0ull) {
+            nw[rank] = myw;
+            leaf_sym[rank] = t;
         }
-        nw[rank] = myw;
-        leaf_sym[rank] = t;
     }
     __syncthreads();
 
@@ -62,9 +78,9 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     // weights a leaf goes before an internal node and an older internal node before a newer one).  So the merged
     // order of those nodes — a leaf's rank is its own index plus the number of lighter internal nodes, an internal
     // node's its own plus the number of leaves that are not heavier — pairs off two by two exactly as the serial
-    // merge would; an odd one out stays at the head of its queue.  Every thread keeps the queue positions itself;
-    // a round has at most A <= 256 nodes, one per thread.
-    {
+    // merge would; an odd one out stays at the head of its queue.  One wavefront runs the rounds, 64 nodes at a time:
+    // the rounds of a table average n / 10 nodes, and without the other wavefronts a round needs no barrier.
+    if (t < 64) {
         const uint64_t kNone = ~0ull;
         int li = 0, ii = n, made = n;   // next leaf, next internal node, next node to create
         auto lower_bound = [&](int lo, int hi, uint64_t x) {   // first index in [lo, hi) with nw[index] >= x
@@ -75,7 +91,8 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
             while (lo < hi) { const int mid = (lo + hi) >> 1; if (nw[mid] <= x) lo = mid + 1; else hi = mid; }
             return lo;
         };
-        while (n >= 2 && !err && (n - li) + (made - ii) > 1) {   // the same in every thread
+        bool over = err != 0;   // the weights of this table sum to 2^64 - 1 or more
+        while (n >= 2 && !over && (n - li) + (made - ii) > 1) {   // the same in every lane
             const uint64_t c0 = li < n ? nw[li] : kNone, c1 = li + 1 < n ? nw[li + 1] : kNone;
             const uint64_t c2 = ii < made ? nw[ii] : kNone, c3 = ii + 1 < made ? nw[ii + 1] : kNone;
             // the two lightest of two sorted pairs
@@ -83,37 +100,43 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
             const uint64_t r1 = c0 < c2 ? c1 : c0, r2 = c0 < c2 ? c2 : c3;
             const uint64_t m2 = r1 < r2 ? r1 : r2;
             const uint64_t T = m1 + m2;
-            if (T < m2 || T == kNone) {   // the weights of this table sum to 2^64 - 1 or more
-                if (t == 0) err = 1;
+            if (T < m2 || T == kNone) {
+                over = true;
                 break;
             }
-            // leaves of weight <= T: they are sorted, so counting them (thread t looks at leaf li + t) gives the end
-            const int bL = __syncthreads_count(li + t < n && nw[li + t] <= T);
-            const int lj = li + bL;
+            // leaves of weight <= T: they are sorted, so counting them (lane t looks at leaf lj + t) gives the end
+            int lj = li, c;
+            do {
+                c = __popcll(__ballot(lj + t < n && nw[lj + t] <= T));
+                lj += c;
+            } while (c == 64);
+            const int bL = lj - li;
             const int bI = made - ii, nb = bL + bI;   // 2 <= nb <= 256: the two lightest are among them
-            if (t < nb) {
+            for (int k = t; k < nb; k += 64) {
                 int node, r;
-                if (t < bL) {
-                    node = li + t;
-                    r = t + (lower_bound(ii, made, nw[node]) - ii);
+                if (k < bL) {
+                    node = li + k;
+                    r = k + (lower_bound(ii, made, nw[node]) - ii);
                 } else {
-                    node = ii + (t - bL);
-                    r = (t - bL) + (upper_bound(li, lj, nw[node]) - li);
+                    node = ii + (k - bL);
+                    r = (k - bL) + (upper_bound(li, lj, nw[node]) - li);
                 }
                 tmpw[r] = nw[node];
                 tmpid[r] = node;
             }
-            __syncthreads();
+            pc_wave_sync_lds();
             const int npair = nb >> 1;
-            if (t < npair) {
-                const uint64_t wa = tmpw[2 * t], wb = tmpw[2 * t + 1];
+            bool wrapped = false;
+            for (int k = t; k < npair; k += 64) {
+                const uint64_t wa = tmpw[2 * k], wb = tmpw[2 * k + 1];
                 const uint64_t sum = wa + wb;
-                if (sum < wb || sum == kNone) err = 1;
-                nw[made + t] = sum;
-                parent[tmpid[2 * t]] = made + t;
-                parent[tmpid[2 * t + 1]] = made + t;
+                wrapped |= sum < wb || sum == kNone;
+                nw[made + k] = sum;
+                parent[tmpid[2 * k]] = made + k;
+                parent[tmpid[2 * k + 1]] = made + k;
             }
-            __syncthreads();
+            over = __any(wrapped);
+            pc_wave_sync_lds();
             int next_li = lj, next_ii = made;
             if (nb & 1) {   // the heaviest of the batch stays: the last internal node unless a leaf is heavier
                 if (bI > 0 && (bL == 0 || nw[made - 1] >= nw[lj - 1])) next_ii = made - 1;
@@ -123,10 +146,11 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
             ii = next_ii;
             made += npair;
         }
+        if (over && t == 0) err = 1;
     }
     __syncthreads();
 
-    if (t < n) {
+    if (t < n && !err) {
         int depth = 0;
         if (n == 1) depth = 1;
         for (int p = parent[t]; p >= 0 && depth <= CO3_MAX_CODE_LEN; p = parent[p]) ++depth;
@@ -141,44 +165,74 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     }
     __syncthreads();
 
+    // rank of the symbol among those of its length: the lanes of its wavefront with the same length by one ballot per
+    // bit of it, the wavefronts before by their counts
     const uint32_t L = slen[t];
-    if (L) atomicAdd(&cnt[L], 1u);
+    const int wave = t >> 6, lane = t & 63;
+    uint64_t same = ~0ull;
+#pragma unroll
+    for (int b = 0; b < 7; ++b) {
+        const uint64_t ones = __ballot((L >> b) & 1u);
+        same &= ((L >> b) & 1u) ? ones : ~ones;
+    }
+    const uint64_t before = same & ((1ull << lane) - 1ull);
+    uint32_t rank = (uint32_t)__popcll(before);
+    if (L && !before) wcnt[wave][L] = (uint32_t)__popcll(same);
     __syncthreads();
-    if (t == 0) {
-        uint64_t code = 0;
-        uint32_t o = 0, mx = 0, nlong = 0;
-        for (int l = 1; l <= 64; ++l) {
-            code = (code + cnt[l - 1]) << 1;
-            first[l] = code;
-            off[l] = o;
-            if (cnt[l]) {
-                mx = l;
-                if (l > kDecBits) {  // search list for codes longer than the direct table
-                    const uint64_t end_code = code + cnt[l];
-                    const uint64_t end_la = (l == 64) ? end_code : (end_code << (64 - l));
-                    B.long_last[nlong] = end_la - 1;
-                    B.long_base[nlong] = o - (uint32_t)code;
-                    B.long_len[nlong] = (uint32_t)l;
-                    ++nlong;
-                }
+    for (int k = 0; k < wave; ++k) rank += wcnt[k][L];
+    if (t < 64) {
+        // lane l - 1 takes length l; first[l] = 2 (first[l - 1] + cnt[l - 1]) as a scan whose step over k lengths
+        // shifts by k
+        uint32_t cl = 0, cp = 0;   // codes of length l, of length l - 1
+#pragma unroll
+        for (int k = 0; k < kCbThreads / 64; ++k) {
+            cl += wcnt[k][t + 1];
+            cp += t ? wcnt[k][t] : 0u;
+        }
+        uint64_t sum = cp;
+        uint32_t o = cp;
+#pragma unroll
+        for (int k = 1; k < 64; k <<= 1) {
+            const uint64_t s_up = __shfl_up(sum, k, 64);
+            const uint32_t o_up = __shfl_up(o, k, 64);
+            if (t >= k) {
+                sum += s_up << k;
+                o += o_up;
             }
-            o += cnt[l];
         }
-        for (uint32_t k = nlong; k < (uint32_t)kLongSlots; ++k) {
-            B.long_last[k] = 0; B.long_base[k] = 0; B.long_len[k] = 0;
+        const int l = t + 1;
+        const uint64_t code = sum << 1;
+        cnt[l] = cl;
+        first[l] = code;
+        off[l] = o;
+        const uint64_t used = __ballot(cl != 0), used_long = used & (~0ull << kDecBits);
+        const uint32_t nlong = (uint32_t)__popcll(used_long);
+        if ((used_long >> t) & 1ull) {   // search list for codes longer than the direct table
+            const uint32_t k = (uint32_t)__popcll(used_long & ((1ull << t) - 1ull));
+            const uint64_t end_code = code + cl;
+            B.long_last[k] = (l == 64 ? end_code : (end_code << (64 - l))) - 1;
+            B.long_base[k] = o - (uint32_t)code;
+            B.long_len[k] = (uint32_t)l;
         }
-        B.maxlen = mx;
-        B.nactive = bad ? 0 : (uint32_t)n;
-        B.nlong = nlong;
+        if (t >= (int)nlong && t < kLongSlots) {
+            B.long_last[t] = 0; B.long_base[t] = 0; B.long_len[t] = 0;
+        }
+        // the direct table's prefixes below end[l - 1] have codes of up to l bits
+        if (l <= kDecBits) end[t] = ((uint32_t)code + cl) << (kDecBits - l);
+        // the first of its prefixes that holds only longer codes
+        if (used_long ? (uint32_t)t == (uint32_t)__ffsll((unsigned long long)used_long) - 1u : t == 0)
+            long0 = used_long ? (uint32_t)(code >> (l - kDecBits)) : (uint32_t)kDecEntries;
+        if (t == 0) {
+            B.maxlen = used ? 64u - (uint32_t)__clzll((long long)used) : 0u;
+            B.nactive = bad ? 0 : (uint32_t)n;
+            B.nlong = nlong;
+        }
     }
     __syncthreads();
 
     uint64_t code = 0;
     uint32_t fast = kFastSlow << 24;  // a longer code, or none: the coders' general path
     if (L) {
-        uint32_t rank = 0;
-#pragma unroll 8
-        for (int j = 0; j < (int)A; ++j) rank += (uint32_t)((j < t) & (slen[j] == L));
         code = first[L] + rank;
         sorted[off[L] + rank] = (uint32_t)t;
         if (L <= (uint32_t)kFastLen) fast = (L << 24) | (uint32_t)code;
@@ -193,22 +247,20 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     // direct decode table: every kDecBits-bit prefix whose code is at most kDecBits long; the first
     // kDec2Tables prefixes that hold only longer codes (the largest prefixes: canonical codes grow
     // with their length) point to a second-level table over the next kDec2Bits bits
-    uint32_t long_prefix0 = kDecEntries;
-    for (int l = kDecBits + 1; l <= 64; ++l) {
-        if (cnt[l]) { long_prefix0 = (uint32_t)(first[l] >> (l - kDecBits)); break; }
-    }
+    const uint32_t long_prefix0 = long0;
     if (t == 0) B.long_prefix0 = long_prefix0;
+    uint32_t ends[kDecBits];
+#pragma unroll
+    for (int l = 0; l < kDecBits; ++l) ends[l] = end[l];
+#pragma unroll 4
     for (int idx = t; idx < kDecEntries; idx += kCbThreads) {
+        uint32_t l = 1;   // canonical codes grow with their length, so the ends do
+#pragma unroll
+        for (int k = 0; k < kDecBits; ++k) l += (uint32_t)idx >= ends[k];
         uint16_t e = 0;
-        for (int l = 1; l <= kDecBits; ++l) {
-            const uint32_t c = (uint32_t)idx >> (kDecBits - l);
-            const uint32_t f = (uint32_t)first[l];
-            if (cnt[l] && c >= f && c - f < cnt[l]) {
-                e = (uint16_t)((l << 8) | sorted[off[l] + (c - f)]);
-                break;
-            }
-        }
-        if (e == 0 && (uint32_t)idx >= long_prefix0 && (uint32_t)idx - long_prefix0 < (uint32_t)kDec2Tables)
+        if (l <= (uint32_t)kDecBits)
+            e = (uint16_t)((l << 8) | sorted[off[l] + (((uint32_t)idx >> (kDecBits - l)) - (uint32_t)first[l])]);
+        else if ((uint32_t)idx >= long_prefix0 && (uint32_t)idx - long_prefix0 < (uint32_t)kDec2Tables)
             e = (uint16_t)((uint32_t)idx - long_prefix0 + 1);
         B.dec[idx] = e;
     }

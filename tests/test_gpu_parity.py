@@ -1185,3 +1185,49 @@ def test_extreme_biases_through_the_many_user_average():
         kw = dict(E=E, M=M, U=U, d=d, bias=bias)
         gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_EMPIRICAL)
         gu.compare_round(gpu, gu.oracle_round(kw, g, m, 0.9), d)
+
+
+@pytest.mark.parametrize("K", [0, 2, 3, 4, 6, 7, 40])
+def test_device_built_decode_tables(K):
+    # a code built on the device with lengths of up to K + 8 bits: the direct table alone, the second-level tables and
+    # the search list have to lead back to the symbols that were coded
+    import torch
+    from paper_2204_08211_amd import binding as B
+    E, M, d, bias = 4, 3, 4096 * 3 + 5, 12
+    rng = np.random.default_rng(1700 + K)
+    g = torch.zeros((1, d + 3), dtype=torch.float32, device="cuda:0")
+    g[0, :d] = torch.from_numpy((rng.standard_normal(d) * 10.0 ** rng.uniform(-3, 1, d)).astype(np.float32))
+    m = torch.zeros_like(g)
+    w = np.ones(256, np.uint64)
+    w[rng.choice(256, K, replace=False)] = np.uint64(1) << np.arange(8, 8 + K, dtype=np.uint64)
+    plan = B.Plan(E, M, 1, d, [[bias]])
+    books = B.co3_build_codebook(E, M, 1, None)
+    buf = B.RoundBuffers(plan, torch.device("cuda:0"), max_code_len=64)
+    B.co3_build_codebook_device(books, torch.from_numpy(w.view(np.int64)[None, :]).to("cuda:0"), buf.status)
+    lens, _ = books.export(0)
+    assert lens.max() == K + 8
+    for single in (False, True):
+        B.co3_encode(plan, books, g, m, m.clone(), 0.0, buf, mode=B.BOOK_FIXED, single_sweep=single)
+        got = torch.zeros_like(buf.symbols)
+        B.co3_decode(plan, books, buf, symbols=got)
+        torch.cuda.synchronize()
+        assert not any(int(buf.status[k].item()) for k in (B.STAT_NOCODE, B.STAT_CODELEN, B.STAT_CORRUPT, B.STAT_CAPACITY))
+        gu.assert_bits_equal(got.cpu().numpy()[:d], buf.symbols.cpu().numpy()[:d], f"symbols, single sweep {single}")
+
+
+@pytest.mark.parametrize("seg_len", [[511], [512], [513], [2048 + 511], [4095], [4097], [3, 4096 * 2 + 513, 1, 2047, 4096 * 3]])
+@pytest.mark.parametrize("seed", [None, 11])
+def test_single_sweep_team_of_wavefronts(seg_len, seed):
+    # few chunks: four wavefronts share a chunk; ends of a chunk at and beside a wavefront's share, layers at odd
+    # elements, with and without the symbol counts and the dither
+    E, M, U = 4, 3, 3
+    d = sum(seg_len)
+    rng = np.random.default_rng(1800 + d)
+    g = np.stack([syn.gennorm_numpy(rng, d, 1.0, 1e-3) for _ in range(U)])
+    m = np.stack([syn.gennorm_numpy(rng, d, 1.0, 3e-4) for _ in range(U)])
+    bias = syn.bias_for_max(np.abs(g + np.float32(0.9) * m).max(), E)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias] * len(seg_len)] * U, seg_len=seg_len, seg_book=[0] * len(seg_len))
+    ref = gu.oracle_round(kw, g, m, 0.9, stochastic_seed=seed)
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=ref["hist"], stochastic_seed=seed)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, 0, weights=ref["hist"], single_sweep=True, stochastic_seed=seed)
+    gu.compare_round(gpu, ref, d, single_sweep=True)
