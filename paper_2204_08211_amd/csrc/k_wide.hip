@@ -320,7 +320,8 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
     __shared__ uint64_t first[65];
     __shared__ uint32_t wcnt[kWbWaves][65];   // symbols of each length in a wavefront's range; then running ranks
     __shared__ int err, s_n;
-    __shared__ uint32_t s_maxlen;
+    __shared__ uint32_t s_maxlen, long0;
+    __shared__ uint32_t end[kWideDecBits];
 
     BookWide &B = books[blockIdx.x];
     const uint64_t *w = weights + (uint64_t)blockIdx.x * A;
@@ -346,7 +347,9 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
     __syncthreads();
     const int nact = s_n;            // number of symbols with a weight
 
-    // ascending (weight, symbol); the keys are distinct, so the order does not depend on the network
+    // ascending (weight, symbol); the keys are distinct, so the order does not depend on the network.  A step over
+    // fewer than 64 entries stays inside a wavefront's own entries: the workgroup meets only where a step or the one
+    // after it reaches further (14 of the 55 steps of 1024 symbols).
     for (uint32_t k = 2; k <= A; k <<= 1) {
         for (uint32_t j = k >> 1; j > 0; j >>= 1) {
             for (uint32_t i = t; i < A; i += kWbThreads) {
@@ -358,7 +361,9 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
                     if (gt == ((i & k) == 0)) { nw[i] = wp; nw[p] = wi; leaf_sym[i] = sp; leaf_sym[p] = si; }
                 }
             }
-            __syncthreads();
+            const uint32_t next = j > 1 ? j >> 1 : k;
+            if (j >= 64u || next >= 64u || (j == 1 && k == A)) __syncthreads();
+            else w_wave_sync_lds();
         }
     }
 
@@ -469,15 +474,28 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
         if (run && t) atomicMax(&s_maxlen, t);
     }
     __syncthreads();
-    if (t == 0) {
-        uint64_t code = 0;
-        uint32_t o = 0;
-        for (int l = 1; l <= 64; ++l) {
-            code = (code + cnt[l - 1]) << 1;
-            first[l] = code;
-            off[l] = o;
-            o += cnt[l];
+    if (t < 64) {
+        // lane l - 1 takes length l: first[l] = 2 (first[l - 1] + cnt[l - 1]) as a scan whose step over k lengths
+        // shifts by k
+        uint64_t sum = t ? cnt[t] : 0u;
+        uint32_t o = t ? cnt[t] : 0u;
+#pragma unroll
+        for (int k = 1; k < 64; k <<= 1) {
+            const uint64_t s_up = __shfl_up(sum, k, 64);
+            const uint32_t o_up = __shfl_up(o, k, 64);
+            if ((int)t >= k) {
+                sum += s_up << k;
+                o += o_up;
+            }
         }
+        first[t + 1] = sum << 1;
+        off[t + 1] = o;
+        // the direct table's prefixes below end[l - 1] have codes of up to l bits
+        if (t < (uint32_t)kWideDecBits) end[t] = ((uint32_t)(sum << 1) + cnt[t + 1]) << ((uint32_t)kWideDecBits - 1u - t);
+        // the first of its prefixes that holds only longer codes
+        const uint64_t used_long = __ballot(cnt[t + 1] != 0u) & (~0ull << kWideDecBits);
+        if (used_long ? t == (uint32_t)__ffsll((unsigned long long)used_long) - 1u : t == 0)
+            long0 = used_long ? (uint32_t)((sum << 1) >> (t + 1u - (uint32_t)kWideDecBits)) : 1u << kWideDecBits;
     }
     __syncthreads();
     // canonical order: rank among the symbols of the same length, ascending symbol
@@ -501,23 +519,21 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
     if (t < 65) { B.first[t] = first[t]; B.count[t] = cnt[t]; B.offset[t] = off[t]; }
     if (t == 0) { B.maxlen = s_maxlen; B.nactive = bad ? 0u : (uint32_t)nact; }
     __syncthreads();
+    uint32_t ends[kWideDecBits];
+#pragma unroll
+    for (int l = 0; l < kWideDecBits; ++l) ends[l] = end[l];
+#pragma unroll
     for (uint32_t idx = t; idx < (1u << kWideDecBits); idx += kWbThreads) {
+        uint32_t l = 1;   // canonical codes grow with their length, so the ends do
+#pragma unroll
+        for (int k = 0; k < kWideDecBits; ++k) l += idx >= ends[k];
         uint32_t e = 0;
-        for (int l = 1; l <= kWideDecBits; ++l) {
-            const uint32_t c = idx >> (kWideDecBits - l);
-            const uint32_t f = (uint32_t)first[l];
-            if (cnt[l] && c >= f && c - f < cnt[l]) {
-                e = ((uint32_t)l << 12) | B.sorted[off[l] + (c - f)];
-                break;
-            }
-        }
+        if (l <= (uint32_t)kWideDecBits)
+            e = (l << 12) | B.sorted[off[l] + ((idx >> ((uint32_t)kWideDecBits - l)) - (uint32_t)first[l])];
         B.dec[idx] = (uint16_t)e;
     }
     // second-level tables under the first prefixes that hold only longer codes
-    uint32_t long_prefix0 = 1u << kWideDecBits;
-    for (int l = kWideDecBits + 1; l <= 64; ++l) {
-        if (cnt[l]) { long_prefix0 = (uint32_t)(first[l] >> (l - kWideDecBits)); break; }
-    }
+    const uint32_t long_prefix0 = long0;
     if (t == 0) B.long_prefix0 = long_prefix0;
     for (uint32_t idx = t; idx < (uint32_t)(kWideDec2Tables << kWideDec2Bits); idx += kWbThreads) {
         const uint32_t prefix = long_prefix0 + (idx >> kWideDec2Bits);
