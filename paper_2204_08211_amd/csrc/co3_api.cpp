@@ -319,7 +319,7 @@ int co3_build_codebook_device(co3_codebook *books, const uint64_t *weights, uint
     hipError_t e = books->d_wide
                        ? launch_build_books_wide(books->d_wide, books->nbooks, books->A, weights, status,
                                                  static_cast<hipStream_t>(stream))
-                       : launch_build_books(books->d_books, books->nbooks, books->A, weights, status,
+                       : launch_build_books(books->d_books, books->nbooks, books->A, weights, nullptr, status,
                                             static_cast<hipStream_t>(stream));
     return e == hipSuccess ? CO3_OK : CO3_ERR_HIP;
 }
@@ -414,9 +414,11 @@ static int encode_with_workspace(const co3_plan *plan, const co3_encode_args *a,
 
     if (launch_zero_u64(ws.hist_rep, hist_rep_n, s) != hipSuccess) return CO3_ERR_HIP;
     if (launch_quantize(lay, args, ws, s) != hipSuccess) return CO3_ERR_HIP;
-    if (a->mode == CO3_BOOK_EMPIRICAL &&
-        launch_build_books(a->books->d_books, lay.nbooks, lay.A, a->hist, a->status, s) != hipSuccess)
-        return CO3_ERR_HIP;
+    // this round's counts: folded by the code's builder, or on their own where the code is held
+    const hipError_t e = a->mode == CO3_BOOK_EMPIRICAL
+                             ? launch_build_books(a->books->d_books, lay.nbooks, lay.A, ws.hist_rep, a->hist, a->status, s)
+                             : launch_reduce_hist(ws.hist_rep, a->hist, (uint64_t)lay.nbooks * lay.A, s);
+    if (e != hipSuccess) return CO3_ERR_HIP;
     if (launch_pack(lay, args, a->books->d_books, ws, s) != hipSuccess) return CO3_ERR_HIP;
     return CO3_OK;
 }

@@ -16,8 +16,11 @@ namespace co3 {
 
 constexpr int kCbThreads = 256;
 
+// counts: `weights` are the sweep's kHistGlobalRep partial tables of symbol counts, one table of all codes after the
+// other; their sum is the weight and is left in `counts` (a kernel of its own for it was another 3.4 to 5 us).
 __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict__ books, uint32_t A,
                                                            const uint64_t *__restrict__ weights,
+                                                           uint64_t *__restrict__ counts,
                                                            uint64_t *__restrict__ status)
 {
     BookDev &B = books[blockIdx.x];
@@ -39,7 +42,17 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     __shared__ uint32_t long0;
     __shared__ int err;
 
-    const uint64_t myw = (t < (int)A) ? w[t] : 0;
+    uint64_t myw = 0;
+    if (t < (int)A) {
+        if (counts) {
+            const uint64_t n = (uint64_t)gridDim.x * A;
+#pragma unroll 16
+            for (int r = 0; r < kHistGlobalRep; ++r) myw += w[(uint64_t)r * n + t];
+            counts[(uint64_t)blockIdx.x * A + t] = myw;
+        } else {
+            myw = w[t];
+        }
+    }
     slen[t] = 0;
     parent[t] = -1;
     parent[t + kMaxA] = -1;
@@ -281,12 +294,12 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     }
 }
 
-hipError_t launch_build_books(BookDev *books, uint32_t nbooks, uint32_t A, const uint64_t *weights,
+hipError_t launch_build_books(BookDev *books, uint32_t nbooks, uint32_t A, const uint64_t *weights, uint64_t *counts,
                               uint64_t *status, hipStream_t s)
 {
     if (nbooks == 0) return hipSuccess;
     ProfScope prof(K_BUILD_BOOKS, s);
-    hipLaunchKernelGGL(k_build_books, dim3(nbooks), dim3(kCbThreads), 0, s, books, A, weights, status);
+    hipLaunchKernelGGL(k_build_books, dim3(nbooks), dim3(kCbThreads), 0, s, books, A, weights, counts, status);
     return hipGetLastError();
 }
 

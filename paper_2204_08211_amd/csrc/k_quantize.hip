@@ -10,7 +10,7 @@
 // the nontemporal hint.  Symbol counts go to lane-replicated LDS bins (the peaked symbol
 // distribution would otherwise serialise the atomics), are summed per workgroup and added to
 // one of kHistGlobalRep copies of the global table, so that no address sees every workgroup;
-// k_reduce_hist folds the copies.
+// k_reduce_hist, or the builder of this round's code, folds the copies.
 #include "co3_internal.h"
 #include "quantize_math.h"
 
@@ -193,7 +193,7 @@ hipError_t launch_quantize(const Layout &lay, const co3_encode_args &a, const En
     const uint64_t ntiles = (lay.d + kQTile - 1) / kQTile;
     const uint64_t sym_stride = symbol_row_stride(lay.d);
     const size_t lds = (size_t)lay.A * kHistRep * sizeof(uint32_t);
-    if (lay.d) {  // a vector without elements still gets its (all-zero) symbol counts from the fold below
+    if (lay.d) {  // a vector without elements still gets its (all-zero) symbol counts from the fold that follows
         ProfScope prof(K_QUANTIZE, s);
         if (a.rounding == CO3_ROUND_STOCHASTIC)
             hipLaunchKernelGGL(k_quantize<true>, dim3((uint32_t)ntiles, lay.U), dim3(kQThreads), lds, s, lay, a.g, a.m,
@@ -202,7 +202,7 @@ hipError_t launch_quantize(const Layout &lay, const co3_encode_args &a, const En
             hipLaunchKernelGGL(k_quantize<false>, dim3((uint32_t)ntiles, lay.U), dim3(kQThreads), lds, s, lay, a.g, a.m,
                                a.m_out, a.symbols, sym_stride, a.row_stride, a.gamma, a.seed, ws.hist_rep, ws.chunk_hist, a.status);
     }
-    return launch_reduce_hist(ws.hist_rep, a.hist, (uint64_t)lay.nbooks * lay.A, s);
+    return hipGetLastError();
 }
 
 }  // namespace co3
