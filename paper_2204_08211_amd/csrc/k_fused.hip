@@ -125,8 +125,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     const uint32_t wv = t >> 6;
     const uint32_t u = blockIdx.y;
 
-    const uint64_t ticket_slot = kTeam > 1 ? (uint64_t)u * (nblk + 1ull) : u;   // of 64 bits, the low 32 are the counter
-    if (t == 0) s_ticket = atomicAdd(&tickets[2 * ticket_slot], 1u);
+    if (t == 0) s_ticket = atomicAdd(&tickets[kTeam > 1 ? 2 * (uint64_t)u * (nblk + 1ull) : u], 1u);
     fu_lds_barrier();
     const uint32_t b = s_ticket;  // position among the user's workgroups, < nblk = gridDim.x
     const uint64_t c0 = (uint64_t)b * kCpb;
