@@ -391,7 +391,9 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
         pay += cbits;
     }
     uint64_t *state = lb_state + (uint64_t)u * (kTeam > 1 ? nblk + 1ull : nblk);
-    if (t == 0)
+    // By the lane that replaces the entry with the running total (or the stalled mark) below: the two stores are
+    // relaxed, only one lane's program order keeps the size from landing last.
+    if (t == 64u * kLbWave)
         __hip_atomic_store(&state[b], (b == 0 ? kLbPrefix : kLbAgg) | own, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     // the nearest 64 predecessor entries, requested now and looked at after the coding below

@@ -1231,3 +1231,40 @@ def test_single_sweep_team_of_wavefronts(seg_len, seed):
     ref = gu.oracle_round(kw, g, m, 0.9, weights=ref["hist"], stochastic_seed=seed)
     gpu, _ = gu.gpu_round(kw, g, m, 0.9, 0, weights=ref["hist"], single_sweep=True, stochastic_seed=seed)
     gu.compare_round(gpu, ref, d, single_sweep=True)
+
+
+@pytest.mark.parametrize("polls", [None, 0])
+def test_single_sweep_small_form_leaves_final_entries(polls):
+    # a chunk per workgroup: when the launch has drained, every look-back entry holds its workgroup's final mark -
+    # the running total up to and including its chunk, or "stalled" exactly where the chunk was not written (a bound
+    # of zero polls makes some give up) - never the chunk's own size, which is published first
+    from paper_2204_08211_amd import binding as B
+    E, M, U = 4, 3, 6
+    d = 4096 * 70 + 33
+    rng = np.random.default_rng(1900)
+    g = np.stack([syn.gennorm_numpy(rng, d, 1.0, 1e-3) for _ in range(U)])
+    m = np.stack([syn.gennorm_numpy(rng, d, 1.0, 3e-4) for _ in range(U)])
+    bias = syn.bias_for_max(np.abs(g + np.float32(0.9) * m).max(), E)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias]] * U)
+    weights = gu.oracle_round(kw, g, m, 0.9)["hist"]
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=weights)
+    if polls is not None:
+        B.set_lookback_polls(polls)
+    try:
+        gpu, (plan, books, buf, gt, mt) = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=weights, single_sweep=True,
+                                                       want_decode=False)
+    finally:
+        B.set_lookback_polls(B.LOOKBACK_POLLS_DEFAULT)
+    n = plan.num_chunks
+    ws = buf.workspace.cpu().numpy()
+    skip = (-buf.workspace.data_ptr()) % 256
+    e = ws[skip:skip + 8 * U * (n + 1)].view(np.uint64).reshape(U, n + 1)
+    assert np.all(e[:, 0] == n)                        # the user's ticket counter, then its entries
+    flag, value = e[:, 1:] >> np.uint64(62), e[:, 1:] & np.uint64((1 << 62) - 1)
+    written = gpu["chunk_offset"][:, :n] != np.uint64(0xFFFFFFFFFFFFFFFF)
+    assert np.array_equal(flag, np.where(written, np.uint64(2), np.uint64(3)))
+    total = np.asarray(ref["chunk_offset"], np.uint64)[:, 1:]
+    assert np.array_equal(value[written], total[written])
+    assert int(gpu["status_encode"][B.STAT_STALLED]) == int((~written).sum())
+    if polls is None:
+        gu.compare_round(gpu, ref, d, decode=False, single_sweep=True)
