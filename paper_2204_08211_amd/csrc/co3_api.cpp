@@ -119,13 +119,15 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     if (!segments) { segments = &whole; nseg = 1; }
     if (nseg == 0 || nseg > (1u << 20)) return CO3_ERR_ARG;
     std::vector<SegDev> segs(nseg + 1);
+    std::vector<SegWgDev> seg_wg(nseg);
     uint64_t off = 0, chunks = 0, wg = 0, wg_small = 0;
     int32_t max_book = 0;
     for (uint32_t k = 0; k < nseg; ++k) {
         if (segments[k].offset != off || segments[k].codebook < 0 || segments[k].codebook >= (1 << 16))
             return CO3_ERR_ARG;
         if (off + segments[k].length < off) return CO3_ERR_ARG;
-        segs[k] = {off, segments[k].length, chunks, segments[k].codebook, (uint32_t)wg, (uint32_t)wg_small, 0};
+        segs[k] = {off, segments[k].length, chunks, segments[k].codebook, 0};
+        seg_wg[k] = {(uint32_t)wg, (uint32_t)wg_small};
         const uint64_t n = (segments[k].length + kChunk - 1) / kChunk;
         off += segments[k].length;
         chunks += n;
@@ -135,7 +137,7 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     }
     if (off != d) return CO3_ERR_ARG;
     if (chunks >= (1ull << 31)) return CO3_ERR_ARG;  // one workgroup per chunk in grid.x
-    segs[nseg] = {d, 0, chunks, 0, (uint32_t)wg, (uint32_t)wg_small, 0};
+    segs[nseg] = {d, 0, chunks, 0, 0};
     int rc = check_bias_table(format, bias, (size_t)U * nseg);
     if (rc != CO3_OK) return rc;
 
@@ -161,10 +163,15 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     }
     Layout &l = p->lay;
     l.U = U; l.nseg = nseg; l.d = d; l.nchunks = chunks;
-    l.nwg = (uint32_t)wg; l.nwg_small = (uint32_t)wg_small;
     l.E = format.exp_bits; l.M = format.mant_bits;
     l.A = 1u << (1 + format.exp_bits + format.mant_bits);
     l.wide = l.A > (uint32_t)kMaxA ? 1u : 0u;
+    if (l.wide && (hipMalloc(&p->d_seg_wg, sizeof(SegWgDev) * nseg) != hipSuccess ||
+                   hipMemcpy(p->d_seg_wg, seg_wg.data(), sizeof(SegWgDev) * nseg, hipMemcpyHostToDevice) != hipSuccess)) {
+        co3_plan_destroy(p);
+        return CO3_ERR_HIP;
+    }
+    p->wide = {p->d_seg_wg, (uint32_t)wg, (uint32_t)wg_small};
     l.vec_aligned = 1u;
     l.tile_aligned = 1u;
     for (uint32_t k = 0; k < nseg; ++k) {
@@ -224,6 +231,7 @@ void co3_plan_destroy(co3_plan *plan)
     if (!plan) return;
     DeviceGuard guard(plan->device);
     if (plan->d_segs) (void)hipFree(plan->d_segs);
+    if (plan->d_seg_wg) (void)hipFree(plan->d_seg_wg);
     if (plan->d_bias) (void)hipFree(plan->d_bias);
     if (plan->d_gain) (void)hipFree(plan->d_gain);
     delete plan;
@@ -405,7 +413,7 @@ static int encode_with_workspace(const co3_plan *plan, const co3_encode_args *a,
     args.workspace_bytes = workspace_bytes;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (lay.wide) {   // alphabets above 8 bits: a fixed code without a symbol buffer keeps its symbols in the workspace
-        return launch_encode_wide(lay, args, a->books->d_wide, workspace, s) == hipSuccess ? CO3_OK : CO3_ERR_HIP;
+        return launch_encode_wide(lay, plan->wide, args, a->books->d_wide, workspace, s) == hipSuccess ? CO3_OK : CO3_ERR_HIP;
     }
     if (single_sweep)
         return launch_encode_fused(lay, args, a->books->d_books, s) == hipSuccess ? CO3_OK : CO3_ERR_HIP;

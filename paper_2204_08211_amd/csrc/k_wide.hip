@@ -563,9 +563,9 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
 // workgroups, and one otherwise.
 static_assert(kWgChunksSmall == kWWaves && kWgChunks == 4 * kWWaves, "the plan's workgroup counts");
 constexpr uint64_t kWSmallGrid = 1024;   // workgroups of kWgChunks chunks below which they take kWgChunksSmall
-inline uint32_t w_chunks_per_wave(const Layout &lay)
+inline uint32_t w_chunks_per_wave(const Layout &lay, const WideCut &cut)
 {
-    return (uint64_t)lay.nwg * lay.U < kWSmallGrid ? kWgChunksSmall / kWWaves : kWgChunks / kWWaves;
+    return (uint64_t)cut.nwg * lay.U < kWSmallGrid ? kWgChunksSmall / kWWaves : kWgChunks / kWWaves;
 }
 // first chunk of workgroup b and its first element, chunks and elements of the workgroup, the layer's code table
 struct WRange {
@@ -577,17 +577,17 @@ struct WRange {
         return left < (uint32_t)kChunk ? left : (uint32_t)kChunk;
     }
 };
-__device__ inline WRange w_range(const Layout &lay, uint32_t u, uint32_t b, uint32_t cpw)
+__device__ inline WRange w_range(const Layout &lay, const SegWgDev *seg_wg, uint32_t u, uint32_t b, uint32_t cpw)
 {
     const bool small = cpw * kWWaves == kWgChunksSmall;
     uint32_t lo = 0, hi = lay.nseg;   // last layer whose first workgroup is <= b (layers without chunks have none)
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if ((small ? lay.segs[mid].wg_small_start : lay.segs[mid].wg_start) <= b) lo = mid; else hi = mid;
+        if ((small ? seg_wg[mid].small_start : seg_wg[mid].start) <= b) lo = mid; else hi = mid;
     }
     const SegDev sd = lay.segs[lo];
     WRange r;
-    r.first = sd.chunk_start + (uint64_t)(b - (small ? sd.wg_small_start : sd.wg_start)) * (kWWaves * cpw);
+    r.first = sd.chunk_start + (uint64_t)(b - (small ? seg_wg[lo].small_start : seg_wg[lo].start)) * (kWWaves * cpw);
     r.e0 = sd.offset + (r.first - sd.chunk_start) * kChunk;
     const uint64_t left = sd.offset + sd.length - r.e0;   // > 0: layer lo has this workgroup
     r.n = left < (uint64_t)(kWWaves * cpw * kChunk) ? (uint32_t)left : kWWaves * cpw * kChunk;
@@ -727,12 +727,13 @@ __device__ inline void w_rows_to_window(uint32_t *region, uint32_t lane, uint32_
 
 __global__ __launch_bounds__(kWThreads) void k_chunk_bits_wide(Layout lay, const uint16_t *__restrict__ sym,
                                                               uint64_t sym_stride, const BookWide *__restrict__ books,
-                                                              uint32_t *__restrict__ chunk_bits, uint32_t cpw)
+                                                              uint32_t *__restrict__ chunk_bits, const SegWgDev *__restrict__ seg_wg,
+                                                              uint32_t cpw)
 {
     __shared__ uint8_t s_len[kWideMaxA];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t u = blockIdx.y;
-    const WRange wg = w_range(lay, u, blockIdx.x, cpw);
+    const WRange wg = w_range(lay, seg_wg, u, blockIdx.x, cpw);
     for (uint32_t i = threadIdx.x; i < (uint32_t)kWideMaxA; i += kWThreads)
         s_len[i] = i < lay.A ? books[wg.book].len[i] : (uint8_t)0;
     __syncthreads();
@@ -784,14 +785,15 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
                                                         const BookWide *__restrict__ books,
                                                         const uint64_t *__restrict__ chunk_offset,
                                                         uint16_t *__restrict__ sub_bits, uint32_t *__restrict__ words,
-                                                        uint64_t words_stride, uint64_t *__restrict__ status, uint32_t cpw)
+                                                        uint64_t words_stride, uint64_t *__restrict__ status,
+                                                        const SegWgDev *__restrict__ seg_wg, uint32_t cpw)
 {
     extern __shared__ uint32_t wp_smem[];   // kWPackLds bytes
     uint32_t *s_fast = wp_smem;                      // [kWideMaxA]
     uint32_t *s_wave_all = s_fast + kWideMaxA;       // [kWWaves][kWPackWaveWords]
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t u = blockIdx.y;
-    const WRange wg = w_range(lay, u, blockIdx.x, cpw);
+    const WRange wg = w_range(lay, seg_wg, u, blockIdx.x, cpw);
     {
         const BookWide &tb = books[wg.book];
         uint32_t tl[kWideMaxA / kWThreads], tc[kWideMaxA / kWThreads];   // the loads are issued together
@@ -1313,7 +1315,7 @@ hipError_t launch_build_books_wide(BookWide *books, uint32_t nbooks, uint32_t A,
     return hipGetLastError();
 }
 
-hipError_t launch_encode_wide(const Layout &lay, const co3_encode_args &a, BookWide *books, void *workspace,
+hipError_t launch_encode_wide(const Layout &lay, const WideCut &cut, const co3_encode_args &a, BookWide *books, void *workspace,
                               hipStream_t s)
 {
     if (lay.U == 0) return hipSuccess;
@@ -1364,11 +1366,12 @@ hipError_t launch_encode_wide(const Layout &lay, const co3_encode_args &a, BookW
         hipError_t e = launch_build_books_wide(books, lay.nbooks, lay.A, hist, a.status, s);
         if (e != hipSuccess) return e;
     }
-    const uint32_t cpw = w_chunks_per_wave(lay);
-    const uint32_t gx = cpw * kWWaves == kWgChunksSmall ? lay.nwg_small : lay.nwg;
+    const uint32_t cpw = w_chunks_per_wave(lay, cut);
+    const uint32_t gx = cpw * kWWaves == kWgChunksSmall ? cut.nwg_small : cut.nwg;
     if (lay.nchunks && !bits_in_sweep) {
         ProfScope prof(K_CHUNK_BITS, s);
-        hipLaunchKernelGGL(k_chunk_bits_wide, dim3(gx, lay.U), dim3(kWThreads), 0, s, lay, sym, sym_stride, books, chunk_bits, cpw);
+        hipLaunchKernelGGL(k_chunk_bits_wide, dim3(gx, lay.U), dim3(kWThreads), 0, s, lay, sym, sym_stride, books, chunk_bits,
+                           cut.seg, cpw);
     }
     hipError_t e = launch_scan_chunks(lay, chunk_bits, a.chunk_offset, a.payload_bits, s);   // the byte path's scan
     if (e != hipSuccess) return e;
@@ -1378,7 +1381,7 @@ hipError_t launch_encode_wide(const Layout &lay, const co3_encode_args &a, BookW
         if (e != hipSuccess) return e;
         ProfScope prof(K_PACK, s);
         hipLaunchKernelGGL(k_pack_wide, dim3(gx, lay.U), dim3(kWThreads), kWPackLds, s, lay, sym, sym_stride, books,
-                           a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status, cpw);
+                           a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status, cut.seg, cpw);
     }
     return hipGetLastError();
 }
