@@ -119,20 +119,15 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     if (!segments) { segments = &whole; nseg = 1; }
     if (nseg == 0 || nseg > (1u << 20)) return CO3_ERR_ARG;
     std::vector<SegDev> segs(nseg + 1);
-    std::vector<SegWgDev> seg_wg(nseg);
-    uint64_t off = 0, chunks = 0, wg = 0, wg_small = 0;
+    uint64_t off = 0, chunks = 0;
     int32_t max_book = 0;
     for (uint32_t k = 0; k < nseg; ++k) {
         if (segments[k].offset != off || segments[k].codebook < 0 || segments[k].codebook >= (1 << 16))
             return CO3_ERR_ARG;
         if (off + segments[k].length < off) return CO3_ERR_ARG;
         segs[k] = {off, segments[k].length, chunks, segments[k].codebook, 0};
-        seg_wg[k] = {(uint32_t)wg, (uint32_t)wg_small};
-        const uint64_t n = (segments[k].length + kChunk - 1) / kChunk;
         off += segments[k].length;
-        chunks += n;
-        wg += (n + kWgChunks - 1) / kWgChunks;   // never more than chunks, which is checked below
-        wg_small += (n + kWgChunksSmall - 1) / kWgChunksSmall;
+        chunks += (segments[k].length + kChunk - 1) / kChunk;
         if (segments[k].codebook > max_book) max_book = segments[k].codebook;
     }
     if (off != d) return CO3_ERR_ARG;
@@ -166,12 +161,26 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     l.E = format.exp_bits; l.M = format.mant_bits;
     l.A = 1u << (1 + format.exp_bits + format.mant_bits);
     l.wide = l.A > (uint32_t)kMaxA ? 1u : 0u;
-    if (l.wide && (hipMalloc(&p->d_seg_wg, sizeof(SegWgDev) * nseg) != hipSuccess ||
-                   hipMemcpy(p->d_seg_wg, seg_wg.data(), sizeof(SegWgDev) * nseg, hipMemcpyHostToDevice) != hipSuccess)) {
-        co3_plan_destroy(p);
-        return CO3_ERR_HIP;
+    if (l.wide) {
+        std::vector<RunDev> runs;
+        for (uint32_t k = 0; k < nseg; ++k) {   // layers without elements have no chunks and end no run
+            if (segs[k].length && (runs.empty() || runs.back().book != segs[k].book))
+                runs.push_back({segs[k].chunk_start, 0, 0, segs[k].book, k});
+        }
+        const uint32_t nrun = (uint32_t)runs.size();
+        runs.push_back({chunks, 0, 0, 0, nseg});
+        for (uint32_t r = 0; r < nrun; ++r) {   // the sums stay below the number of chunks
+            const uint64_t n = runs[r + 1].chunk_start - runs[r].chunk_start;
+            runs[r + 1].wg_start = runs[r].wg_start + (uint32_t)((n + kWgChunks - 1) / kWgChunks);
+            runs[r + 1].wg_small_start = runs[r].wg_small_start + (uint32_t)((n + kWgChunksSmall - 1) / kWgChunksSmall);
+        }
+        if (hipMalloc(&p->d_runs, sizeof(RunDev) * runs.size()) != hipSuccess ||
+            hipMemcpy(p->d_runs, runs.data(), sizeof(RunDev) * runs.size(), hipMemcpyHostToDevice) != hipSuccess) {
+            co3_plan_destroy(p);
+            return CO3_ERR_HIP;
+        }
+        p->wide = {p->d_runs, nrun, runs[nrun].wg_start, runs[nrun].wg_small_start};
     }
-    p->wide = {p->d_seg_wg, (uint32_t)wg, (uint32_t)wg_small};
     l.vec_aligned = 1u;
     l.tile_aligned = 1u;
     for (uint32_t k = 0; k < nseg; ++k) {
@@ -231,7 +240,7 @@ void co3_plan_destroy(co3_plan *plan)
     if (!plan) return;
     DeviceGuard guard(plan->device);
     if (plan->d_segs) (void)hipFree(plan->d_segs);
-    if (plan->d_seg_wg) (void)hipFree(plan->d_seg_wg);
+    if (plan->d_runs) (void)hipFree(plan->d_runs);
     if (plan->d_bias) (void)hipFree(plan->d_bias);
     if (plan->d_gain) (void)hipFree(plan->d_gain);
     delete plan;

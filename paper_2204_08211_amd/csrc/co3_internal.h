@@ -82,12 +82,18 @@ struct SegDev {
     int32_t pad;
 };
 
-// How the wide coder (k_wide.hip) cuts a user's chunks into workgroups: per layer the first of its workgroups of up
-// to kWgChunks chunks, and of up to kWgChunksSmall, and their numbers per user.
-struct SegWgDev { uint32_t start, small_start; };
+// How the wide coder (k_wide.hip) cuts a user's chunks into workgroups: at every change of the code table, and after
+// kWgChunks (or kWgChunksSmall) chunks.  A run is a longest stretch of chunks under one table.
+struct RunDev {
+    uint64_t chunk_start;             // its first chunk
+    uint32_t wg_start, wg_small_start;   // its first workgroup of up to kWgChunks, of up to kWgChunksSmall chunks
+    int32_t book;                     // code table id within a user's (or the shared) set
+    uint32_t seg;                     // its first layer
+};
 struct WideCut {
-    const SegWgDev *seg;       // device [nseg]
-    uint32_t nwg, nwg_small;
+    const RunDev *runs;               // device [nrun + 1] (last entry: chunk_start = nchunks, seg = nseg)
+    uint32_t nrun;
+    uint32_t nwg, nwg_small;          // workgroups per user
 };
 constexpr uint32_t kWgChunks = 16, kWgChunksSmall = 4;
 
@@ -119,7 +125,7 @@ static_assert(sizeof(SegDev) == 32 && sizeof(Layout) == 88, "read by every kerne
 struct co3_plan {
     co3::Layout lay;
     co3::SegDev *d_segs = nullptr;
-    co3::SegWgDev *d_seg_wg = nullptr;   // wide alphabets only: wide.seg
+    co3::RunDev *d_runs = nullptr;   // wide alphabets only: wide.runs
     co3::WideCut wide = {};
     int32_t *d_bias = nullptr;
     float *d_gain = nullptr;

@@ -3,9 +3,9 @@
 // The steps are those of the byte path (Algorithm 1 lines 8-10 and 13-14; Sec. IV-A (i)-(iii), Sec. II-B (iv))
 // and the container is the same; symbols are 16-bit words and a code table has up to 4096 entries, too many
 // for the per-wavefront LDS tables the byte kernels are built around: here a workgroup shares one copy of the
-// table of the layer it works on, and loads the next one where its range of the vector crosses into a layer with
-// another table.  A fixed code without a symbol buffer ("single sweep" in the byte path) runs the same three steps
-// here with the symbols kept in the workspace.
+// table in use.  The coder's workgroups end where the table changes, the quantizer's go on with the next one, the
+// PS kernels' have a chunk each.  A fixed code without a symbol buffer ("single sweep" in the byte path) runs the
+// same three steps here with the symbols kept in the workspace.
 //
 //   k_quantize_wide      v = g + gamma m, Q_fp, m' = v - ghat, symbol; symbol counts in an LDS table per workgroup
 //                        (and, for a held code on layers that start on its tile grid, the chunks' coded sizes)
@@ -555,44 +555,68 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
 
 // ---- user side, steps 2 and 3 -------------------------------------------------------------------------------
 
-// Both chunk kernels give a workgroup up to kWWaves * cpw consecutive chunks of one layer of one user, wavefront w
-// chunks w, w + kWWaves, ..., with the layer's code table in LDS; a layer's last workgroup has fewer.  (Workgroups
-// cut from the chunks of all layers kept the first layer's table only and coded another layer's chunks by rolled
-// loops from device memory: three users of 2 M elements in five layers, k_pack_wide 383 us, this way 16 us.)
-// A table is up to 36 KB to read, so a wavefront takes four chunks where that still leaves every CU several
-// workgroups, and one otherwise.
+// Both chunk kernels give a workgroup up to kWWaves * cpw consecutive chunks of one user, wavefront w chunks w,
+// w + kWWaves, ..., with their code table in LDS; where the next chunk has another table a workgroup ends early.
+// (Workgroups that went on kept the first table only and coded the other chunks by rolled loops from device memory:
+// three users of 2 M elements in five layers with a table each, k_pack_wide 370 us, this way 16 us.  Workgroups that
+// end with every layer read up to 36 KB of table for each and leave wavefronts without a chunk: sixteen users of
+// 1000 layers of 1000 elements under one table in [1,4,5], both kernels 226 and 48 us, this way 79 and 23.)
+// A wavefront takes four chunks where that still leaves every CU several workgroups, and one otherwise.
 static_assert(kWgChunksSmall == kWWaves && kWgChunks == 4 * kWWaves, "the plan's workgroup counts");
 constexpr uint64_t kWSmallGrid = 1024;   // workgroups of kWgChunks chunks below which they take kWgChunksSmall
 inline uint32_t w_chunks_per_wave(const Layout &lay, const WideCut &cut)
 {
     return (uint64_t)cut.nwg * lay.U < kWSmallGrid ? kWgChunksSmall / kWWaves : kWgChunks / kWWaves;
 }
-// first chunk of workgroup b and its first element, chunks and elements of the workgroup, the layer's code table
+// First chunk of workgroup b, the number of its chunks, their code table, the layers [seg, seg_end) they lie in.  Where
+// that is one layer, as in any large one, a chunk's place follows from the first's: no search per chunk.  i is the same
+// in the whole wavefront and said to be (readfirstlane), so that places are kept in scalar registers: sixteen users of
+// 25.6 M elements, k_pack_wide 530 us without that, 488 us with it.
 struct WRange {
-    uint64_t first, e0;
-    uint32_t nck, n, book;
-    __device__ inline uint32_t count(uint32_t i) const   // elements of the workgroup's chunk i
+    uint64_t first, e0, left;   // left: elements of the first chunk's layer from e0 on
+    uint32_t nck, book, seg, seg_end;
+    __device__ inline void place(const SegDev *segs, uint32_t i, uint64_t &e, uint32_t &n) const   // of the workgroup's chunk i
     {
-        const uint32_t left = n - i * kChunk;
-        return left < (uint32_t)kChunk ? left : (uint32_t)kChunk;
+        e = e0 + i * (uint32_t)kChunk;
+        uint64_t rest = left - i * (uint32_t)kChunk;
+        if (seg_end - seg > 1) {
+            uint32_t lo = seg, hi = seg_end;   // last layer that starts at or before the chunk
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (segs[mid].chunk_start <= first + i) lo = mid; else hi = mid;
+            }
+            const SegDev sd = segs[lo];
+            e = sd.offset + (first + i - sd.chunk_start) * kChunk;
+            rest = sd.offset + sd.length - e;
+        }
+        n = rest < (uint64_t)kChunk ? (uint32_t)rest : (uint32_t)kChunk;
     }
 };
-__device__ inline WRange w_range(const Layout &lay, const SegWgDev *seg_wg, uint32_t u, uint32_t b, uint32_t cpw)
+__device__ inline WRange w_range(const Layout &lay, const RunDev *runs, uint32_t nrun, uint32_t u, uint32_t b, uint32_t cpw)
 {
     const bool small = cpw * kWWaves == kWgChunksSmall;
-    uint32_t lo = 0, hi = lay.nseg;   // last layer whose first workgroup is <= b (layers without chunks have none)
+    uint32_t lo = 0, hi = nrun;   // last run whose first workgroup is <= b: every run has one
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if ((small ? seg_wg[mid].small_start : seg_wg[mid].start) <= b) lo = mid; else hi = mid;
+        if ((small ? runs[mid].wg_small_start : runs[mid].wg_start) <= b) lo = mid; else hi = mid;
     }
-    const SegDev sd = lay.segs[lo];
+    const RunDev rd = runs[lo];
     WRange r;
-    r.first = sd.chunk_start + (uint64_t)(b - (small ? seg_wg[lo].small_start : seg_wg[lo].start)) * (kWWaves * cpw);
+    r.first = rd.chunk_start + (uint64_t)(b - (small ? rd.wg_small_start : rd.wg_start)) * (kWWaves * cpw);
+    const uint64_t chunks = runs[lo + 1].chunk_start - r.first;   // > 0: run lo has this workgroup
+    r.nck = chunks < (uint64_t)(kWWaves * cpw) ? (uint32_t)chunks : kWWaves * cpw;
+    r.book = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)rd.book;
+    r.seg = rd.seg;
+    r.seg_end = runs[lo + 1].seg;
+    uint32_t top = r.seg_end;     // last layer that starts at or before the first chunk
+    while (top - r.seg > 1) {
+        const uint32_t mid = (r.seg + top) >> 1;
+        if (lay.segs[mid].chunk_start <= r.first) r.seg = mid; else top = mid;
+    }
+    const SegDev sd = lay.segs[r.seg];
+    if (r.first + r.nck <= lay.segs[r.seg + 1].chunk_start) r.seg_end = r.seg + 1;
     r.e0 = sd.offset + (r.first - sd.chunk_start) * kChunk;
-    const uint64_t left = sd.offset + sd.length - r.e0;   // > 0: layer lo has this workgroup
-    r.n = left < (uint64_t)(kWWaves * cpw * kChunk) ? (uint32_t)left : kWWaves * cpw * kChunk;
-    r.nck = (r.n + kChunk - 1) / kChunk;
-    r.book = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
+    r.left = sd.offset + sd.length - r.e0;
     return r;
 }
 constexpr uint32_t kWFastCodeBits = 25;   // s_fast entry: length << 25 | codeword, for lengths up to 25
@@ -727,20 +751,22 @@ __device__ inline void w_rows_to_window(uint32_t *region, uint32_t lane, uint32_
 
 __global__ __launch_bounds__(kWThreads) void k_chunk_bits_wide(Layout lay, const uint16_t *__restrict__ sym,
                                                               uint64_t sym_stride, const BookWide *__restrict__ books,
-                                                              uint32_t *__restrict__ chunk_bits, const SegWgDev *__restrict__ seg_wg,
-                                                              uint32_t cpw)
+                                                              uint32_t *__restrict__ chunk_bits, const RunDev *__restrict__ runs,
+                                                              uint32_t nrun, uint32_t cpw)
 {
     __shared__ uint8_t s_len[kWideMaxA];
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t u = blockIdx.y;
-    const WRange wg = w_range(lay, seg_wg, u, blockIdx.x, cpw);
+    const WRange wg = w_range(lay, runs, nrun, u, blockIdx.x, cpw);
     for (uint32_t i = threadIdx.x; i < (uint32_t)kWideMaxA; i += kWThreads)
         s_len[i] = i < lay.A ? books[wg.book].len[i] : (uint8_t)0;
     __syncthreads();
     for (uint32_t i_ck = wave; i_ck < wg.nck; i_ck += kWWaves) {   // whole wavefronts; no workgroup barriers below
         const uint64_t c = wg.first + i_ck;
-        const uint32_t n = wg.count(i_ck);
-        const uint16_t *src = sym + (uint64_t)u * sym_stride + wg.e0 + i_ck * (uint32_t)kChunk;
+        uint64_t e0;
+        uint32_t n;
+        wg.place(lay.segs, i_ck, e0, n);
+        const uint16_t *src = sym + (uint64_t)u * sym_stride + e0;
         uint32_t total = 0;
         if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) {   // eight symbols per load
             const uint4 *src8 = reinterpret_cast<const uint4 *>(src);
@@ -786,14 +812,14 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
                                                         const uint64_t *__restrict__ chunk_offset,
                                                         uint16_t *__restrict__ sub_bits, uint32_t *__restrict__ words,
                                                         uint64_t words_stride, uint64_t *__restrict__ status,
-                                                        const SegWgDev *__restrict__ seg_wg, uint32_t cpw)
+                                                        const RunDev *__restrict__ runs, uint32_t nrun, uint32_t cpw)
 {
     extern __shared__ uint32_t wp_smem[];   // kWPackLds bytes
     uint32_t *s_fast = wp_smem;                      // [kWideMaxA]
     uint32_t *s_wave_all = s_fast + kWideMaxA;       // [kWWaves][kWPackWaveWords]
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t u = blockIdx.y;
-    const WRange wg = w_range(lay, seg_wg, u, blockIdx.x, cpw);
+    const WRange wg = w_range(lay, runs, nrun, u, blockIdx.x, cpw);
     {
         const BookWide &tb = books[wg.book];
         uint32_t tl[kWideMaxA / kWThreads], tc[kWideMaxA / kWThreads];   // the loads are issued together
@@ -815,8 +841,10 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
     uint32_t *region = s_wave_all + wave * kWPackWaveWords;
     for (uint32_t i_ck = wave; i_ck < wg.nck; i_ck += kWWaves) {   // whole wavefronts; wavefront-level synchronisation only below
         const uint64_t c = wg.first + i_ck;
-        const uint32_t n = wg.count(i_ck);
-        const uint16_t *src = sym + (uint64_t)u * sym_stride + wg.e0 + i_ck * (uint32_t)kChunk;
+        uint64_t e0;
+        uint32_t n;
+        wg.place(lay.segs, i_ck, e0, n);
+        const uint16_t *src = sym + (uint64_t)u * sym_stride + e0;
         // The chunk's symbols, at any 2-byte offset and of any length: coalesced dwords from the 4-byte boundary
         // below the chunk go to LDS rows of 32 + 1 words (word i of the chunk at i + i / 32), from which lane l
         // funnels its 64 symbols (words 32 l .. 32 l + 32) into registers, two per word.
@@ -1371,7 +1399,7 @@ hipError_t launch_encode_wide(const Layout &lay, const WideCut &cut, const co3_e
     if (lay.nchunks && !bits_in_sweep) {
         ProfScope prof(K_CHUNK_BITS, s);
         hipLaunchKernelGGL(k_chunk_bits_wide, dim3(gx, lay.U), dim3(kWThreads), 0, s, lay, sym, sym_stride, books, chunk_bits,
-                           cut.seg, cpw);
+                           cut.runs, cut.nrun, cpw);
     }
     hipError_t e = launch_scan_chunks(lay, chunk_bits, a.chunk_offset, a.payload_bits, s);   // the byte path's scan
     if (e != hipSuccess) return e;
@@ -1381,7 +1409,7 @@ hipError_t launch_encode_wide(const Layout &lay, const WideCut &cut, const co3_e
         if (e != hipSuccess) return e;
         ProfScope prof(K_PACK, s);
         hipLaunchKernelGGL(k_pack_wide, dim3(gx, lay.U), dim3(kWThreads), kWPackLds, s, lay, sym, sym_stride, books,
-                           a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status, cut.seg, cpw);
+                           a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status, cut.runs, cut.nrun, cpw);
     }
     return hipGetLastError();
 }

@@ -1268,3 +1268,24 @@ def test_single_sweep_small_form_leaves_final_entries(polls):
     assert int(gpu["status_encode"][B.STAT_STALLED]) == int((~written).sum())
     if polls is None:
         gu.compare_round(gpu, ref, d, decode=False, single_sweep=True)
+
+
+@pytest.mark.parametrize("U,per_user", [(2, False), (3, True), (128, False)])
+def test_wide_coder_runs_of_layers_under_one_table(U, per_user):
+    # the chunk kernels' workgroups end where the table changes, not with a layer: runs of many one-chunk layers, of 3,
+    # 4, 5, 16 and 17 chunks, layers without elements (with the same table and with another) inside a run and between
+    # runs, a run that ends inside a workgroup's budget after a layer of several chunks; workgroups of 4 and of 16
+    E, M = 4, 5
+    runs = [([7] * 3, 0), ([0, 1, 0, 4096, 4097, 0], 1), ([64, 65, 63, 1, 130], 0), ([0], 2), ([33] * 16, 0), ([9] * 17, 2),
+            ([4096 * 3 + 1, 5], 1), ([11, 4096 * 2 + 7, 2, 0], 0), ([0], 1)]
+    seg_len = [n for lens, _ in runs for n in lens]
+    seg_book = [b for lens, b in runs for _ in lens]
+    d = sum(seg_len)
+    rng = np.random.default_rng(100 + U)
+    bias = rng.integers(14, 17, (U, len(seg_len))).astype(np.int32)
+    g = (rng.laplace(size=(U, d)) * 2.0 ** -6).astype(np.float32)
+    m = (rng.laplace(size=(U, d)) * 2.0 ** -8).astype(np.float32)
+    kw = dict(E=E, M=M, U=U, d=d, bias=bias, seg_len=seg_len, seg_book=seg_book, per_user_books=per_user)
+    ref = gu.oracle_round(kw, g, m, 0.9)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_EMPIRICAL)
+    gu.compare_round(gpu, ref, d)
