@@ -259,8 +259,8 @@ __global__ __launch_bounds__(kMwThreads) void k_model_weights(Layout lay, const 
 
 // Exponent bias from the model, eq. (exp bias) with integer b.  The expected squared error of a candidate
 // bias is a sum of non-negative shares, one per symbol's cell, so any few shares bound it from below:
-//   k_model_bias_bounds  per (user, layer), kErrLanes threads per symbol: the shares of the zero cell and of the two
-//                        outermost cells (too coarse a set loses in the first, too narrow a one in the others)
+//   k_model_bias_bounds  per (user, layer), a workgroup per kBoundCands candidates: the shares of the zero cell and
+//                        of the two outermost cells (too coarse a set loses in the first, too narrow a one in the others)
 //   k_model_bias_ref     per (user, layer): the candidate with the smallest bound, evaluated in full; no
 //                        candidate whose bound exceeds that error can be the minimum or tie with it
 //   k_model_bias_errors  workgroup per (candidate bias, layer, user): the integral of (x - r)^2 f(x) over
@@ -270,16 +270,27 @@ __global__ __launch_bounds__(kMwThreads) void k_model_weights(Layout lay, const 
 //   k_model_bias_pick    wavefront per (user, layer): the smallest bias whose error is within kBiasTie of the
 //                        minimum (a format with many binades has a plateau of equally good biases;
 //                        the smallest has the most headroom).  No model (alpha = 0): the IEEE bias.
-// What bounds all of it is the length of one incomplete gamma function in fp64 (some microseconds each: a power, an
-// exponential, a series with a division per term), so the six that a cell needs - three moments at two ends - are
-// evaluated side by side by kErrLanes threads, and what they share, the log-gammas of the three shapes, once per
-// workgroup.  (Thread per symbol, the six one after the other, picks by one thread: 280 us for eight
-// users in [1,5,2]; this way 92 us.)
+// What bounds all of it is the incomplete gamma functions in fp64 (a power, an exponential, a series with a division
+// per term: some microseconds each, three moments at every place where two cells meet).  Each is evaluated once, by a
+// thread of its own, for both cells that meet there, the moments one after the other so that a wavefront's lanes run
+// the same shape at neighbouring places; what they share, the log-gammas of the three shapes, once per workgroup.
+// For few pairs that is a chain, so a workgroup has a thread for each place and moment of 256 symbols; many pairs fill
+// the device and take four wavefronts (and nearly all workgroups of the search only find that their candidate is
+// ruled out).  us, a thread per symbol with its six integrals one after the other / eight threads per symbol, 1024 to
+// a workgroup, every place twice / this way: the bias search of 8 pairs in [1,5,2] 324 / 109 / 75, 384 pairs in
+// [1,4,3] 862 / 990 / 347, 2400 pairs 4180 / 5740 / 1650, 384 pairs in [1,5,6] 8050 / 9800 / 3620; the scale search of 8 pairs in
+// [1,4,3] 6190 / 3630 / 2160, 2400 pairs 33 900 / 41 500 / 15 300.
 constexpr int kBiasSlots = 256;  // error slots per (user, layer); candidates: at most 226
 constexpr double kBiasPrune = 1e-6;  // margin of the bound test, far above the rounding of the sums and the tie width
-constexpr int kErrLanes = 8;     // threads per symbol: moment (0, 1, 2) x end of the cell; two idle
-constexpr int kErrThreads = 1024;
-constexpr int kErrSyms = kErrThreads / kErrLanes;   // symbols a workgroup evaluates at a time
+constexpr int kErrPlaces = kMaxA + 1;               // where the cells of a block of 256 symbols meet, and the next one's
+constexpr int kErrThreads = 768;                    // 3 x 252 places for the largest alphabet of up to 8 bits
+constexpr int kErrThreadsMany = kMaxA;
+// Pairs from which a workgroup takes kErrThreadsMany: the candidates' search, some six of whose 226 workgroups a pair
+// evaluate (40 pairs: 118 us with kErrThreads, 120 with kErrThreadsMany; 96 pairs: 196 and 154), and the kernels with
+// one workgroup a pair, which from then on are one on every CU (the scale search of 192 pairs: 2340 and 3170 us; of
+// 384: 4390 and 4070).
+constexpr uint64_t kErrManySearch = 40, kErrManyOne = 256;
+inline uint32_t err_threads(const Layout &lay, uint64_t many) { return (uint64_t)lay.U * lay.nseg < many ? kErrThreads : kErrThreadsMany; }
 
 // What the cells of one (mu, alpha, beta) share: per moment the log-gamma of its shape and the moment's factor.
 struct ErrModel { double lg[3], ck[3]; };
@@ -294,49 +305,90 @@ __device__ inline void err_factors(ErrModel *em, uint32_t t, double alpha)   // 
     __syncthreads();
 }
 
-// sq_error_of_symbol() by kErrLanes neighbouring threads, part = threadIdx.x % kErrLanes; all of them call it with the
-// same symbol.  The share is returned in the thread of part 0.
-__device__ inline double err_of_symbol(uint32_t s, int E, int M, int bias, double mu, double alpha, double beta,
-                                       const ErrModel *em, uint32_t part)
+// P and Q of a moment at a place |x - mu|, place by place
+template <int kN> struct ErrPlaces { double P[3][kN], Q[3][kN]; };
+
+// The place where the cells of magnitude codes k and k + 1 meet, on the negative axis if neg (what symbol_cell returns)
+__device__ inline double err_place(bool neg, int k, int M, int bias)
 {
-    const uint32_t k = part >> 1, end = part & 1u;
-    double lo, hi, j = 0.0, c = 0.0;
-    const bool cell = symbol_cell(s, E, M, bias, &lo, &hi);
-    if (cell) {
-        const int code = (int)(s & ((1u << (E + M)) - 1u));
-        const double r = ((s >> (E + M)) & 1u) ? -magnitude_of_code(code, M, bias) : magnitude_of_code(code, M, bias);
-        c = r - mu;
-        const double a = lo - mu, b = hi - mu;
-        double side[2] = {0.0, 0.0};   // the part on the positive axis, the mirrored part on the negative one
-#pragma unroll 1
-        for (int n = 0; n < 2; ++n) {
-            const double x0 = n ? -b : a, x1 = n ? -a : b;
-            const double p0 = x0 > 0.0 ? x0 : 0.0, p1 = x1 > 0.0 ? x1 : 0.0;
-            if (!(p1 > p0)) continue;  // the same for all threads of a symbol
-            double P = 0.0, Q = 0.0;
-            if (k < 3u) inc_gamma(((double)k + 1.0) / beta, pow((end ? p1 : p0) / alpha, beta), em->lg[k], &P, &Q);
-            const double Pb = __shfl_xor(P, 1, 64), Qb = __shfl_xor(Q, 1, 64);
-            if (k < 3u) side[n] = moment_between(em->ck[k], P, Q, Pb, Qb);   // right in the thread of end 0
-        }
-        j = (k & 1u) ? side[0] - side[1] : side[0] + side[1];
-    }
-    const double j1 = __shfl_down(j, 2, 64), j2 = __shfl_down(j, 4, 64);
-    return cell ? sq_error_of_moments(c, j, j1, j2) : 0.0;
+    const double x = 0.5 * (magnitude_of_code(k, M, bias) + magnitude_of_code(k + 1, M, bias));
+    return neg ? -x : x;
+}
+template <int kN>
+__device__ inline void err_eval(ErrPlaces<kN> *pl, uint32_t place, uint32_t k, double x, double mu, double alpha, double beta, const ErrModel *em)
+{
+    double P, Q;
+    inc_gamma(((double)k + 1.0) / beta, pow(fabs(x - mu) / alpha, beta), em->lg[k], &P, &Q);
+    pl->P[k][place] = P;
+    pl->Q[k][place] = Q;
 }
 
-// Expected squared error of one candidate by a workgroup of kErrThreads: the shares of symbols i, i + 256, ... are
-// added in this order (one symbol for alphabets of up to 8 bits), then the 256 sums in a fixed tree.
-__device__ inline double err_total(double *s_red, uint32_t t, uint32_t A, int E, int M, int bias, double mu, double alpha,
-                                   double beta, const ErrModel *em)
+// sq_error_of_symbol() from the places its cell (lo, hi] ends at; at +-infinity P = 1, and where the cell reaches over
+// the location its two sides start there, P = 0.
+template <int kN>
+__device__ inline double err_of_symbol(uint32_t s, int E, int M, int bias, double mu, const ErrPlaces<kN> *pl, uint32_t place_lo,
+                                       uint32_t place_hi, const ErrModel *em)
 {
-    static_assert(kMaxA == 2 * kErrSyms, "two symbols of a block of 256 per thread group");
-    const uint32_t part = t % kErrLanes, sl = t / kErrLanes;
-    double e0 = 0.0, e1 = 0.0;
-    for (uint32_t s0 = 0; s0 < A; s0 += kMaxA) {
-        if (s0 + sl < A) e0 += err_of_symbol(s0 + sl, E, M, bias, mu, alpha, beta, em, part);
-        if (s0 + kErrSyms + sl < A) e1 += err_of_symbol(s0 + kErrSyms + sl, E, M, bias, mu, alpha, beta, em, part);
+    double lo, hi;
+    if (!symbol_cell(s, E, M, bias, &lo, &hi)) return 0.0;
+    const int code = (int)(s & ((1u << (E + M)) - 1u));
+    const double r = ((s >> (E + M)) & 1u) ? -magnitude_of_code(code, M, bias) : magnitude_of_code(code, M, bias);
+    const double c = r - mu, a = lo - mu, b = hi - mu;
+    double j[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        double pos = 0.0, neg = 0.0;
+        const double Pl = isinf(lo) ? 1.0 : pl->P[k][place_lo], Ql = isinf(lo) ? 0.0 : pl->Q[k][place_lo];
+        const double Ph = isinf(hi) ? 1.0 : pl->P[k][place_hi], Qh = isinf(hi) ? 0.0 : pl->Q[k][place_hi];
+        if ((b > 0.0 ? b : 0.0) > (a > 0.0 ? a : 0.0)) pos = moment_between(em->ck[k], a > 0.0 ? Pl : 0.0, a > 0.0 ? Ql : 1.0, Ph, Qh);
+        if ((-a > 0.0 ? -a : 0.0) > (-b > 0.0 ? -b : 0.0)) neg = moment_between(em->ck[k], -b > 0.0 ? Ph : 0.0, -b > 0.0 ? Qh : 1.0, Pl, Ql);
+        j[k] = (k & 1) ? pos - neg : pos + neg;
     }
-    if (part == 0) { s_red[sl] = e0; s_red[kErrSyms + sl] = e1; }
+    return sq_error_of_moments(c, j[0], j[1], j[2]);
+}
+
+// Expected squared error of one candidate by a workgroup of nt >= 256 threads: the shares of symbols i, i + 256, ...
+// are added in this order (one symbol for alphabets of up to 8 bits), then the 256 sums in a fixed tree.
+__device__ inline double err_total(double *s_red, ErrPlaces<kErrPlaces> *pl, uint32_t t, uint32_t nt, uint32_t A, int E, int M, int bias,
+                                   double mu, double alpha, double beta, const ErrModel *em)
+{
+    const uint32_t half = 1u << (E + M);
+    const int nmag = ((1 << E) - 1) << M;      // magnitude codes Q_fp can produce: they meet at nmag - 1 places
+    const bool byte = A <= (uint32_t)kMaxA;    // both signs in one block, else blocks of one sign
+    double e = 0.0;
+    for (uint32_t s0 = 0; s0 < A; s0 += kMaxA) {
+        const bool neg0 = s0 >= half;
+        const int k0 = (int)(s0 & (half - 1u));
+        if (!byte && k0 >= nmag) continue;     // the same in every thread
+        // byte: places 0 .. nmag - 2 on the positive axis, then the negative one's; else place i is that between
+        // k0 - 1 + i and the next code, and before code 0 the zero cell's lower end
+        const uint32_t n = byte ? 2u * (uint32_t)(nmag - 1) : (uint32_t)kErrPlaces;
+#pragma unroll 1
+        for (uint32_t i = t; i < 3u * n; i += nt) {
+            const uint32_t k = (i >= n ? 1u : 0u) + (i >= 2u * n ? 1u : 0u), place = i - k * n;
+            bool neg = neg0;
+            int code = k0 - 1 + (int)place;
+            if (byte) {
+                neg = place >= (uint32_t)(nmag - 1);
+                code = (int)place - (neg ? nmag - 1 : 0);
+            } else if (code < 0) {
+                neg = true;
+                code = 0;
+            }
+            if (code < nmag - 1) err_eval(pl, place, k, err_place(neg, code, M, bias), mu, alpha, beta, em);
+        }
+        __syncthreads();
+        if (t < (uint32_t)kMaxA && s0 + t < A) {
+            const bool neg = byte ? t >= half : neg0;
+            const int code = (int)((s0 + t) & (half - 1u));
+            const uint32_t base = byte ? (neg ? (uint32_t)(nmag - 1) : 0u) : 1u;   // the place beyond code k0
+            const uint32_t outer = base + (uint32_t)(code - k0);
+            const uint32_t inner = byte && code == 0 ? (uint32_t)(nmag - 1) : outer - 1u;   // the zero cell's: below zero
+            e += err_of_symbol(s0 + t, E, M, bias, mu, pl, neg ? outer : inner, neg ? inner : outer, em);
+        }
+        __syncthreads();
+    }
+    if (t < (uint32_t)kMaxA) s_red[t] = e;
     __syncthreads();
     for (int o = kMaxA / 2; o > 0; o >>= 1) {
         if (t < (uint32_t)o) s_red[t] += s_red[t + o];
@@ -347,39 +399,47 @@ __device__ inline double err_total(double *s_red, uint32_t t, uint32_t A, int E,
     return r;
 }
 
-constexpr int kBoundLanes = 4 * kErrLanes;   // threads per candidate: three symbols, kErrLanes threads idle
-constexpr int kBoundCands = 8;               // candidates per workgroup
-__global__ __launch_bounds__(kBoundLanes *kBoundCands) void k_model_bias_bounds(
+constexpr int kBoundCands = 16;               // candidates per workgroup, four places each ...
+constexpr int kBoundPlaces = 4 * kBoundCands; // ... and a wavefront per moment
+static_assert(kBoundPlaces == 64, "a wavefront per moment");
+__global__ __launch_bounds__(3 * kBoundPlaces) void k_model_bias_bounds(
     Layout lay, const co3_gennorm_params *__restrict__ params, double *__restrict__ bounds)
 {
     __shared__ ErrModel s_em;
+    __shared__ ErrPlaces<kBoundPlaces> s_pl;
     __shared__ double s_share[kBoundCands][3];
     const uint32_t seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x;
-    const uint32_t cl = t / kBoundLanes, which = t % kBoundLanes / kErrLanes, part = t % kErrLanes;
-    const uint32_t cand = blockIdx.x * kBoundCands + cl;
+    const uint32_t cand0 = blockIdx.x * kBoundCands;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
     const co3_gennorm_params p = params[pair];
     const uint32_t ncand = (uint32_t)(kBiasMax - bias_min_supported(lay.E) + 1);
+    const int bias0 = bias_min_supported(lay.E) + (int)cand0;
     const bool model = p.alpha > 0.0 && p.beta > 0.0;   // the same in every thread
     if (model) {
         err_log_gammas(&s_em, t, p.beta);
         err_factors(&s_em, t, p.alpha);
         const uint32_t top = (((1u << lay.E) - 1u) << lay.M) - 1u;        // largest magnitude code
-        if (cand < ncand && which < 3u) {
-            const uint32_t sy = which == 0u ? 0u : which == 1u ? top : (1u << (lay.E + lay.M)) | top;
-            const double e = err_of_symbol(sy, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em, part);
-            if (part == 0) s_share[cl][which] = e;
+        const uint32_t place = t % kBoundPlaces, which = place & 3u;      // above and below zero, before the outermost cells
+        if (cand0 + (place >> 2) < ncand)
+            err_eval(&s_pl, place, t / kBoundPlaces, err_place((which & 1u) != 0u, (which & 2u) ? (int)top - 1 : 0, lay.M, bias0 + (int)(place >> 2)),
+                     p.mu, p.alpha, p.beta, &s_em);
+        __syncthreads();
+        if (t < 3u * kBoundCands && cand0 + t / 3u < ncand) {
+            const uint32_t cl = t / 3u, w = t % 3u, pc = 4u * cl;
+            const uint32_t sy = w == 0u ? 0u : w == 1u ? top : (1u << (lay.E + lay.M)) | top;
+            s_share[cl][w] = err_of_symbol(sy, lay.E, lay.M, bias0 + (int)cl, p.mu, &s_pl, w == 0u ? pc + 1u : pc + 2u, w == 0u ? pc : pc + 3u, &s_em);
         }
         __syncthreads();
     }
-    if (cand < ncand && t % kBoundLanes == 0)
-        bounds[pair * kBiasSlots + cand] = model ? s_share[cl][0] + s_share[cl][1] + s_share[cl][2] : INFINITY;
+    if (t < (uint32_t)kBoundCands && cand0 + t < ncand)
+        bounds[pair * kBiasSlots + cand0 + t] = model ? s_share[t][0] + s_share[t][1] + s_share[t][2] : INFINITY;
 }
 
 __global__ __launch_bounds__(kErrThreads) void k_model_bias_ref(Layout lay, const co3_gennorm_params *__restrict__ params,
                                                                 const double *__restrict__ bounds, double *__restrict__ ref)
 {
     __shared__ double s_red[kMaxA];
+    __shared__ ErrPlaces<kErrPlaces> s_pl;
     __shared__ ErrModel s_em;
     __shared__ int s_c0;
     const uint32_t seg = blockIdx.x, u = blockIdx.y, t = threadIdx.x;
@@ -406,7 +466,7 @@ __global__ __launch_bounds__(kErrThreads) void k_model_bias_ref(Layout lay, cons
     }
     err_log_gammas(&s_em, t, p.beta);
     err_factors(&s_em, t, p.alpha);
-    const double total = err_total(s_red, t, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + s_c0, p.mu, p.alpha, p.beta, &s_em);
+    const double total = err_total(s_red, &s_pl, t, blockDim.x, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + s_c0, p.mu, p.alpha, p.beta, &s_em);
     if (t == 0) ref[pair] = total;
 }
 
@@ -415,6 +475,7 @@ __global__ __launch_bounds__(kErrThreads) void k_model_bias_errors(Layout lay, c
                                                                    const double *__restrict__ ref, double *__restrict__ errors)
 {
     __shared__ double s_red[kMaxA];
+    __shared__ ErrPlaces<kErrPlaces> s_pl;
     __shared__ ErrModel s_em;
     const uint32_t cand = blockIdx.x, seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
@@ -427,7 +488,7 @@ __global__ __launch_bounds__(kErrThreads) void k_model_bias_errors(Layout lay, c
     }
     err_log_gammas(&s_em, t, p.beta);
     err_factors(&s_em, t, p.alpha);
-    const double total = err_total(s_red, t, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em);
+    const double total = err_total(s_red, &s_pl, t, blockDim.x, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em);
     if (t == 0) errors[pair * kBiasSlots + cand] = total;
 }
 
@@ -489,9 +550,9 @@ hipError_t launch_model_bias(const Layout &lay, const co3_gennorm_params *params
     const uint64_t pairs = (uint64_t)lay.U * lay.nseg;
     double *bounds = errors_ws + pairs * kBiasSlots, *ref = bounds + pairs * kBiasSlots;
     hipLaunchKernelGGL(k_model_bias_bounds, dim3((uint32_t)(ncand + kBoundCands - 1) / kBoundCands, lay.nseg, lay.U),
-                       dim3(kBoundLanes * kBoundCands), 0, s, lay, params, bounds);
-    hipLaunchKernelGGL(k_model_bias_ref, dim3(lay.nseg, lay.U), dim3(kErrThreads), 0, s, lay, params, bounds, ref);
-    hipLaunchKernelGGL(k_model_bias_errors, dim3((uint32_t)ncand, lay.nseg, lay.U), dim3(kErrThreads), 0, s, lay, params,
+                       dim3(3 * kBoundPlaces), 0, s, lay, params, bounds);
+    hipLaunchKernelGGL(k_model_bias_ref, dim3(lay.nseg, lay.U), dim3(err_threads(lay, kErrManyOne)), 0, s, lay, params, bounds, ref);
+    hipLaunchKernelGGL(k_model_bias_errors, dim3((uint32_t)ncand, lay.nseg, lay.U), dim3(err_threads(lay, kErrManySearch)), 0, s, lay, params,
                        bounds, ref, errors_ws);
     hipLaunchKernelGGL(k_model_bias_pick, dim3((uint32_t)pairs), dim3(64), 0, s, lay, errors_ws, bias,
                        error);
@@ -511,6 +572,7 @@ __global__ __launch_bounds__(kErrThreads) void k_model_scale(Layout lay, const c
                                                        float *__restrict__ gain_pairs, double *error_out)
 {
     __shared__ double s_red[kMaxA];
+    __shared__ ErrPlaces<kErrPlaces> s_pl;
     __shared__ ErrModel s_em;
     const uint32_t seg = blockIdx.x, u = blockIdx.y, t = threadIdx.x;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
@@ -524,49 +586,56 @@ __global__ __launch_bounds__(kErrThreads) void k_model_scale(Layout lay, const c
     if (p.alpha > 0.0 && p.beta > 0.0) {   // the same in every thread
         const int bmin = bias_min_supported(lay.E), bmax = kBiasMax;
         err_log_gammas(&s_em, t, p.beta);
-        auto split = [&](double sc, int &b, double &tt) {
-            b = (int)lround(-sc);
-            b = b < bmin ? bmin : (b > bmax ? bmax : b);
-            tt = sc + (double)b;
-        };
-        auto err_at = [&](int b, double tt) {
+        // Evaluation i of the expected error: 0 .. 2 kHalf the scan, from kGold on the golden-section search (two points,
+        // kSteps more, the middle of what is left), kLast that of the fp32 pair that is returned.  One loop, so that
+        // the evaluation is in the code once (called from eight places it spilt 356 bytes a thread).
+        constexpr int kHalf = 24, kSteps = 60, kGold = 2 * kHalf + 1, kMid = kGold + 2 + kSteps, kLast = kMid + 1;
+        const double r = 0.6180339887498949, s0 = -(double)b_int;
+        double best_s = s0, best_f = e_int, a = 0.0, b = 0.0, x1 = 0.0, x2 = 0.0, f1 = 0.0, f2 = 0.0;
+        int best_k = 0;
+#pragma unroll 1
+        for (int i = 0; i <= kLast; ++i) {
+            double sc;
+            bool first = true;          // golden section: whether x1 is evaluated, or x2
+            if (i == kGold) {
+                if (best_k == -kHalf || best_k == kHalf) i = kLast;
+                a = best_s - 1.0 / 16.0; b = best_s + 1.0 / 16.0;
+                x1 = b - r * (b - a); x2 = a + r * (b - a);
+            }
+            if (i < kGold) {
+                sc = s0 + (double)(i - kHalf) / 16.0;
+            } else if (i < kMid) {
+                first = i == kGold || (i > kGold + 1 && f1 < f2);
+                if (i > kGold + 1) {
+                    if (first) { b = x2; x2 = x1; f2 = f1; x1 = b - r * (b - a); }
+                    else { a = x1; x1 = x2; f1 = f2; x2 = a + r * (b - a); }
+                }
+                sc = first ? x1 : x2;
+            } else {
+                sc = i == kMid ? 0.5 * (a + b) : best_s;
+            }
+            int eb = (int)lround(-sc);
+            eb = eb < bmin ? bmin : (eb > bmax ? bmax : eb);
+            double tt = sc + (double)eb;
+            if (i == kLast) {
+                if (!(best_f < e_int * (1.0 - kBiasTie))) break;
+                ig = (float)exp2(tt);
+                gn = 1.0f / ig;
+                b_out = eb;
+                tt = log2((double)ig);
+            }
             const double c = exp2(tt);
             err_factors(&s_em, t, p.alpha / c);
-            return c * c * err_total(s_red, t, lay.A, lay.E, lay.M, b, p.mu / c, p.alpha / c, p.beta, &s_em);
-        };
-        auto f = [&](double sc) {
-            int b;
-            double tt;
-            split(sc, b, tt);
-            return err_at(b, tt);
-        };
-        const double s0 = -(double)b_int;
-        const int kHalf = 24;
-        double best_s = s0, best_f = e_int;
-        int best_k = 0;
-        for (int k = -kHalf; k <= kHalf; ++k) {
-            const double sc = s0 + (double)k / 16.0, v = f(sc);
-            if (v < best_f) { best_f = v; best_s = sc; best_k = k; }
-        }
-        if (best_k > -kHalf && best_k < kHalf) {
-            const double r = 0.6180339887498949;
-            double a = best_s - 1.0 / 16.0, b = best_s + 1.0 / 16.0;
-            double x1 = b - r * (b - a), x2 = a + r * (b - a), f1 = f(x1), f2 = f(x2);
-            for (int it = 0; it < 60; ++it) {
-                if (f1 < f2) { b = x2; x2 = x1; f2 = f1; x1 = b - r * (b - a); f1 = f(x1); }
-                else { a = x1; x1 = x2; f1 = f2; x2 = a + r * (b - a); f2 = f(x2); }
+            const double v = c * c * err_total(s_red, &s_pl, t, blockDim.x, lay.A, lay.E, lay.M, eb, p.mu / c, p.alpha / c, p.beta, &s_em);
+            if (i < kGold) {
+                if (v < best_f) { best_f = v; best_s = sc; best_k = i - kHalf; }
+            } else if (i < kMid) {
+                if (first) f1 = v; else f2 = v;
+            } else if (i == kMid) {
+                if (v < best_f) { best_f = v; best_s = sc; }
+            } else {
+                e_out = v;
             }
-            const double xm = 0.5 * (a + b), fm = f(xm);
-            if (fm < best_f) { best_f = fm; best_s = xm; }
-        }
-        if (best_f < e_int * (1.0 - kBiasTie)) {
-            int b;
-            double tt;
-            split(best_s, b, tt);
-            ig = (float)exp2(tt);
-            gn = 1.0f / ig;
-            b_out = b;
-            e_out = err_at(b, log2((double)ig));   // of the fp32 pair that is returned
         }
     }
     if (t == 0) {
@@ -590,7 +659,7 @@ hipError_t launch_model_scale(const Layout &lay, const co3_gennorm_params *param
     hipError_t e = launch_model_bias(lay, params, bias, err_int, ws_int, s);
     if (e != hipSuccess) return e;
     ProfScope prof(K_MODEL_BIAS, s);
-    hipLaunchKernelGGL(k_model_scale, dim3(lay.nseg, lay.U), dim3(kErrThreads), 0, s, lay, params, bias, err_int, gain_pairs,
+    hipLaunchKernelGGL(k_model_scale, dim3(lay.nseg, lay.U), dim3(err_threads(lay, kErrManyOne)), 0, s, lay, params, bias, err_int, gain_pairs,
                        error);
     return hipGetLastError();
 }

@@ -345,3 +345,41 @@ def test_real_valued_scale_on_the_device_and_a_round_with_it(E, M):
     plan.set_gain(None, None)
     B.co3_encode(plan, books, gt, mt, mt, 0.9, buf, mode=B.BOOK_EMPIRICAL, stochastic_seed=3)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("E,M,U,nseg", [(2, 0, 3, 13), (2, 0, 2, 20), (7, 0, 8, 5), (6, 1, 1, 7), (4, 3, 16, 17), (4, 4, 4, 11), (5, 6, 2, 3),
+                                        (3, 8, 8, 33)])
+def test_bias_and_scale_search_of_few_and_many_pairs(E, M, U, nseg):
+    # the searches' workgroups shrink with the number of (user, layer) pairs (39 and 40; below and above 256): every pair's
+    # result is, bit for bit, that of a plan with this pair alone, and the host routine's; the smallest alphabet, those
+    # with the most cells in one block of 256 symbols, and those of several blocks; means on either side, in a cell's
+    # middle and where two cells meet, and pairs without a model
+    import torch
+    from paper_2204_08211_amd import binding as B
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(1000 * E + 10 * M + nseg)
+    par = np.zeros((U, nseg, 4))
+    par[..., 1] = 10.0 ** rng.uniform(-4, 1, (U, nseg))
+    par[..., 2] = rng.uniform(0.4, 3.0, (U, nseg))
+    par[..., 0] = rng.choice([0.0, -0.3, 0.3, 0.01], (U, nseg)) * par[..., 1]
+    par[rng.random((U, nseg)) < 0.1] = 0.0
+    par[0, 0] = [2.0 ** -3, 2.0 ** -4, 1.0, 6.0]
+
+    def search(params):
+        u, n = params.shape[:2]
+        plan = B.Plan(E, M, u, 8 * n, [[2 ** (E - 1) - 1] * n] * u, seg_len=[8] * n, seg_book=[0] * n)
+        p = torch.from_numpy(np.ascontiguousarray(params)).to(dev)
+        bias, err = B.co3_model_bias_device(plan, p)
+        sb, gains, serr = B.co3_model_scale_device(plan, p)
+        return [x.cpu().numpy() for x in (bias, err, sb, gains, serr)]
+
+    every = search(par)
+    for idx in [(0, 0)] + [tuple(rng.integers(0, (U, nseg))) for _ in range(5)]:
+        alone = search(par[idx][None, None])
+        for a, b in zip(every, alone):
+            assert np.array_equal(a[idx], b[0, 0]), (idx, a[idx], b[0, 0])
+        if par[idx][1] > 0.0:
+            hb, he = B.co3_bias_from_model(E, M, *par[idx][:3])
+            assert hb == every[0][idx] and abs(every[1][idx] / he - 1.0) < 1e-8
+        else:
+            assert every[0][idx] == (1 << (E - 1)) - 1 and every[1][idx] == 0.0
