@@ -549,13 +549,23 @@ static void launch_fused_waves(const Layout &lay, const co3_encode_args &a, cons
                        a.chunk_offset, a.sub_bits, a.payload_bits, a.words, a.words_stride, a.status, hist_rep);
 }
 
+// Wavefronts per SIMD the kernel is cut for: five only for the conversion to the nearest representative without symbol
+// counts, and in the large form only where no chunk needs shifted vectors (k_encode_fused's comment).  The team's
+// wavefronts hold a quarter of a chunk each: 85 registers either way, so there is no second cut of it.
 template <bool kSR, int kCpb, int kTeam>
 static void launch_fused_variant(const Layout &lay, const co3_encode_args &a, const BookDev *books, uint32_t *tickets,
-                               uint64_t *lb_state, uint32_t nblk, uint64_t *hist_rep, hipStream_t s)
+                                 uint64_t *lb_state, uint32_t nblk, uint64_t *hist_rep, hipStream_t s)
 {
-    if (a.hist) launch_fused_waves<kSR, kCpb, kTeam, 4, true>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-    else if (lay.vec_aligned && !kSR) launch_fused_waves<kSR, kCpb, kTeam, 5, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-    else launch_fused_waves<kSR, kCpb, kTeam, 4, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    if (a.hist) {
+        launch_fused_waves<kSR, kCpb, kTeam, 4, true>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    } else if constexpr (kSR) {
+        launch_fused_waves<kSR, kCpb, kTeam, 4, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    } else if constexpr (kTeam > 1) {
+        launch_fused_waves<kSR, kCpb, kTeam, 5, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    } else {
+        if (lay.vec_aligned) launch_fused_waves<kSR, kCpb, kTeam, 5, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+        else launch_fused_waves<kSR, kCpb, kTeam, 4, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    }
 }
 
 hipError_t launch_encode_fused(const Layout &lay, const co3_encode_args &a, const BookDev *books, hipStream_t s)
