@@ -116,9 +116,28 @@ struct Layout {
     const float *gain;         // device [U][nseg][2]: (gain, inv_gain) of the real-valued scale; (1, 1) when unused
 };
 // Every kernel takes a Layout and looks its layers up, so what one kernel needs alone stays out of both: at 40 and 96
-// bytes, with the wide coder's cut in them, the decode of sixteen users' 122 404 elements took 26.5 instead of 25.7 us,
-// the wide average of sixteen users' 25.6 M elements 941 instead of 909 us.
+// bytes, with the wide coder's cut in them, sixteen users' round of 25.6 M elements took 1347 instead of 1336 us, the
+// wide average of the same size 941 instead of 909 us.
 static_assert(sizeof(SegDev) == 32 && sizeof(Layout) == 88, "read by every kernel");
+
+// A layer's entry.  kOneLoad: requested as a whole; left to itself the compiler requests its parts where they are used.
+// Which is better was measured kernel by kernel: as a whole in the decoders (two users of 29.5 M elements with their own
+// tables, k_decode: 598 -> 566 us; three users of 11.3 M in eleven layers in [1,5,6], k_decode_wide: 187 -> 182 us), in
+// parts in the averages (sixteen users of 25.6 M in [1,5,6], k_aggregate_wide: 906 against 922 us; three users in seven
+// layers, k_aggregate_staged<4>: 27.1 against 27.8 us).
+template <bool kOneLoad>
+__device__ inline SegDev load_segment(const SegDev *p)
+{
+    if constexpr (!kOneLoad) return *p;
+    typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
+    const u64x4 e = *reinterpret_cast<const u64x4 *>(p);   // entries of 32 bytes from a 256-byte boundary on
+    SegDev sd;
+    sd.offset = e[0];
+    sd.length = e[1];
+    sd.chunk_start = e[2];
+    sd.book = (int32_t)(uint32_t)e[3];
+    return sd;
+}
 
 }  // namespace co3
 

@@ -357,11 +357,12 @@ struct ChunkGeom {
     int32_t book;     // table id within a user's set
 };
 
+template <bool kOneLoad>
 __device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
 {
     ChunkGeom g;
     g.seg = find_chunk_segment_d(lay.segs, lay.nseg, c);
-    const SegDev sd = lay.segs[g.seg];
+    const SegDev sd = load_segment<kOneLoad>(lay.segs + g.seg);
     g.e0 = sd.offset + (c - sd.chunk_start) * kChunk;
     const uint64_t left = sd.offset + sd.length - g.e0;
     g.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
     const uint64_t c = blockIdx.x;
     const uint32_t u = blockIdx.y * kDecWaves + wave;
     const bool active = u < lay.U;
-    const ChunkGeom g = chunk_geom(lay, c);
+    const ChunkGeom g = chunk_geom<true>(lay, c);
     ChunkIndex ix;
     if (active) ix = read_index(lay, c, u, words, words_stride, chunk_offset, sub_bits);
     const DecLds *my_tab = s_tab;
@@ -537,7 +538,7 @@ __global__ __launch_bounds__(64 * W) void k_aggregate_staged(Layout lay, const u
     constexpr int G = (kChunk / 4) / T;  // 4-element groups per thread
     const uint32_t t = threadIdx.x, wave = t >> 6;
     const uint64_t c = blockIdx.x;
-    const ChunkGeom g = chunk_geom(lay, c);
+    const ChunkGeom g = chunk_geom<false>(lay, c);
     const uint32_t sign_shift = (uint32_t)(lay.E + lay.M);
     const uint32_t mag_mask = (1u << sign_shift) - 1u;
     const uint32_t sign_up = 31u - sign_shift;
@@ -648,7 +649,7 @@ __global__ __launch_bounds__(64 * W) void k_aggregate(Layout lay, const uint32_t
     constexpr int T = 64 * W;
     const uint32_t t = threadIdx.x, wave = t >> 6, lane = t & 63u;
     const uint64_t c = blockIdx.x;
-    const ChunkGeom g = chunk_geom(lay, c);
+    const ChunkGeom g = chunk_geom<false>(lay, c);
 
     for (uint32_t i = t; i < (uint32_t)kAccWords; i += T) s_acc[i] = 0.0;
     if constexpr (kPerUser) {

@@ -83,11 +83,12 @@ struct WChunk {
     uint32_t book;
 };
 
+template <bool kOneLoad>
 __device__ inline WChunk w_chunk(const Layout &lay, uint64_t c, uint32_t u)
 {
     WChunk k;
     k.seg = w_find_chunk_segment(lay.segs, lay.nseg, c);
-    const SegDev sd = lay.segs[k.seg];
+    const SegDev sd = load_segment<kOneLoad>(lay.segs + k.seg);
     k.e0 = sd.offset + (c - sd.chunk_start) * kChunk;
     const uint64_t left = sd.offset + sd.length - k.e0;
     k.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
@@ -1184,11 +1185,11 @@ __global__ __launch_bounds__(64 * kWDecWaves) void k_decode_wide(Layout lay, con
     const uint64_t c = blockIdx.x;
     const uint32_t u = blockIdx.y * nwaves + wave;
     if (!kPerUser) {
-        w_load_tabs<true>(reinterpret_cast<WideTabs *>(s_tabs), books[w_chunk(lay, c, 0).book], threadIdx.x, nthreads);
+        w_load_tabs<true>(reinterpret_cast<WideTabs *>(s_tabs), books[w_chunk<true>(lay, c, 0).book], threadIdx.x, nthreads);
         __syncthreads();
     }
     if (u >= lay.U) return;  // whole wavefront; wavefront-level synchronisation only below
-    const WChunk k = w_chunk(lay, c, u);
+    const WChunk k = w_chunk<true>(lay, c, u);
     const BookWide &book = books[k.book];
     WideTabs *T = reinterpret_cast<WideTabs *>(s_tabs + (kPerUser ? wave * kWTabsShort : 0u));
     uint16_t *rows = s_rows + wave * kWDecRowsWave;
@@ -1257,7 +1258,7 @@ __global__ __launch_bounds__(kWAggThreads, kPerUser ? 2 : 6) void k_aggregate_wi
     unsigned char *s_tabs = reinterpret_cast<unsigned char *>(s_acc + kWAccWords);   // one table, or a short one per wavefront
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const uint64_t c = blockIdx.x;
-    const WChunk k0 = w_chunk(lay, c, 0);
+    const WChunk k0 = w_chunk<false>(lay, c, 0);
     const uint32_t nthreads = blockDim.x, nwaves = blockDim.x >> 6;
     for (uint32_t i = t; i < (uint32_t)kWAccWords; i += nthreads) s_acc[i] = 0.0;
     if (!kPerUser) w_load_tabs<true>(reinterpret_cast<WideTabs *>(s_tabs), books[k0.book], t, nthreads);
@@ -1267,7 +1268,7 @@ __global__ __launch_bounds__(kWAggThreads, kPerUser ? 2 : 6) void k_aggregate_wi
     WUpper32 U32;
     if (!kPerUser) U32.load(T);
     for (uint32_t u = wave; u < lay.U; u += nwaves) {
-        const WChunk k = w_chunk(lay, c, u);
+        const WChunk k = w_chunk<false>(lay, c, u);
         const BookWide &book = books[k.book];
         const WIndex ix = w_read_index(lay, c, u, words, words_stride, chunk_offset, sub_bits, lane);
         if (kPerUser) {
