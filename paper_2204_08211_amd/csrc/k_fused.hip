@@ -40,7 +40,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int kFuCpb = 4;                            // chunks (= wavefronts) per workgroup ...
 constexpr int kFuCpbSmall = 1;                       // ... and for inputs too small to fill the device that way,
 constexpr int kFuTeamSmall = 4;                      // where as many wavefronts quantize a chunk together
-constexpr uint64_t kFuSmallGrid = 2048;              // workgroups of kFuCpb chunks below which the small form is used
 constexpr int kFuRow = kPcSymRow;                    // 16 words of symbols + 1 pad
 constexpr int kFuStage = kPcSymWords;                // 1088 words hold a chunk's symbols
 constexpr int kFuBatch = 4;                          // 16-byte vectors of g (and of m) a lane requests at a time
@@ -95,7 +94,7 @@ __device__ inline void fu_lds_barrier()
 // kTeam: wavefronts per chunk.  More than one only with kCpb = 1, for inputs whose chunks are too few to fill the
 // device with a wavefront each: such a launch is a wavefront's chain of loads, quantizing and packing, so its batches
 // are spread over a team; then wavefront 0 packs while wavefront 1 looks back, and all of them copy out.  Four
-// users of 20 011 elements: 24 -> 12 us; one of 2 * 10^7, the whole round: 227 -> 175 us.
+// users of 20 011 elements: 24 -> 12 us.
 template <bool kSR, int kCpb, int kTeam, int kWaves, bool kHist>
 __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     Layout lay, const float *__restrict__ g, const float *m, float *m_out, uint64_t row_stride, float gamma,
@@ -523,16 +522,25 @@ __global__ void k_zero_fused(uint64_t *p, uint64_t n, uint64_t *q, uint64_t nq)
     if (i < nq) q[i] = 0;
 }
 
-// Chunks per workgroup for this layout: fewer when there would be too few workgroups to fill the device.
-static int fused_chunks_per_workgroup(const Layout &lay)
+// Chunks per workgroup.  The small form wins while a launch is one workgroup's latency: it quantizes a chunk in a
+// quarter of the time.  It loses once the chunks are many, for three of its four wavefronts wait while one packs, and
+// once a user's are, for a user has one ticket counter and one chain of look-back entries, here one a chunk.  In
+// groups of kFuCpb chunks the two meet, for the conversion to the nearest representative, near 185 of one user, 320 of
+// four, 400 of eight, 450 of 24 (encode of one user, small and large form: 160 groups 27 and 28 us, 256 groups 38 and
+// 31; of eight users: 320 groups 31 and 38, 496 groups 46 and 44; of five users: 1895 groups 197 and 105): a line in
+// groups and groups per user.  The stochastic conversion is the longer part of its sweep and keeps the small form for
+// longer (eight users, 600 groups: 56 and 66 us, 720 groups: 68 and 69; one user, 320 groups: 55 and 52).
+constexpr uint64_t kFuSmallLine = 960, kFuSmallLineStochastic = 1650;
+static int fused_chunks_per_workgroup(const Layout &lay, bool stochastic)
 {
-    const uint64_t groups = (uint64_t)lay.U * ((lay.nchunks + kFuCpb - 1) / kFuCpb);
-    return groups < kFuSmallGrid ? kFuCpbSmall : kFuCpb;
+    const uint64_t per_user = (lay.nchunks + kFuCpb - 1) / kFuCpb, groups = (uint64_t)lay.U * per_user;
+    return 2 * groups + 3 * per_user < (stochastic ? kFuSmallLineStochastic : kFuSmallLine) ? kFuCpbSmall : kFuCpb;
 }
 
 size_t fused_workspace_bytes(const Layout &lay)
 {
-    const uint64_t cpb = (uint64_t)fused_chunks_per_workgroup(lay);
+    static_assert(kFuSmallLineStochastic >= kFuSmallLine, "a plan's workspace serves both conversions");
+    const uint64_t cpb = (uint64_t)fused_chunks_per_workgroup(lay, true);
     const uint64_t nblk = (lay.nchunks + cpb - 1) / cpb;
     // the look-back entries and a ticket counter (one 64-bit slot per user), the partial symbol-count tables of the
     // histogram option, plus alignment slack
@@ -571,14 +579,15 @@ static void launch_fused_variant(const Layout &lay, const co3_encode_args &a, co
 hipError_t launch_encode_fused(const Layout &lay, const co3_encode_args &a, const BookDev *books, hipStream_t s)
 {
     if (lay.U == 0) return hipSuccess;
-    const int cpb = fused_chunks_per_workgroup(lay);
+    const bool sr = a.rounding == CO3_ROUND_STOCHASTIC;
+    const int cpb = fused_chunks_per_workgroup(lay, sr);
     const uint64_t nblk = (lay.nchunks + (uint64_t)cpb - 1) / (uint64_t)cpb;
     uint64_t *base = reinterpret_cast<uint64_t *>((reinterpret_cast<uintptr_t>(a.workspace) + 255u) & ~(uintptr_t)255u);
     // A ticket counter per user and the look-back entries.  Atomics on one cache line take turns whichever word they
-    // add to.  In the small form the users' workgroups all start at once, so a user's counter lies in front of its
-    // entries, away from the others' (8 users of 10^6 elements: 63 -> 44 us, with the team; the whole round 87 -> 68 us
-    // by the counters alone); in the large form the workgroups resident at a time are one user's, and the counters lie
-    // side by side in front of all entries.
+    // add to.  In the small form all users' workgroups start together, so a user's counter lies in front of its own
+    // entries: on a line of its own from fifteen chunks a user on, beside few others below that (eight users of 10^6
+    // elements, a round: 87 -> 68 us).  In the large form they lie side by side in front of all entries; where a
+    // user's workgroups are fewer than fit the device, the users that run together share the line.
     uint64_t *lb_state = base + (cpb == kFuCpbSmall ? 1 : lay.U);
     uint64_t *hist_rep = base + (uint64_t)lay.U * (nblk + 1);   // [kHistGlobalRep][nbooks][A], with a.hist only
     const uint64_t hist_n = (uint64_t)lay.nbooks * lay.A;
@@ -602,7 +611,6 @@ hipError_t launch_encode_fused(const Layout &lay, const co3_encode_args &a, cons
     {
         ProfScope prof(K_FUSED, s);
         uint32_t *tickets = reinterpret_cast<uint32_t *>(base);
-        const bool sr = a.rounding == CO3_ROUND_STOCHASTIC;
         if (cpb == kFuCpb) {
             if (sr) launch_fused_variant<true, kFuCpb, 1>(lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
             else launch_fused_variant<false, kFuCpb, 1>(lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);

@@ -1289,3 +1289,27 @@ def test_wide_coder_runs_of_layers_under_one_table(U, per_user):
     ref = gu.oracle_round(kw, g, m, 0.9)
     gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_EMPIRICAL)
     gu.compare_round(gpu, ref, d)
+
+
+@pytest.mark.parametrize("U,groups,seed,hist,small", [(1, 191, None, False, True), (1, 192, None, True, False), (1, 329, 5, False, True),
+                                                      (1, 330, 5, False, False), (3, 106, None, True, True), (3, 107, None, False, False)])
+def test_single_sweep_on_both_sides_of_the_forms_line(U, groups, seed, hist, small):
+    # `groups` of four chunks a user: the last size of the small form and the first of the large one, for both
+    # conversions; a user's ticket counter says how many workgroups took it
+    E, M = 3, 2
+    d = groups * 4 * 4096 - 4096 - 37          # the last group has three chunks, the last chunk is ragged
+    rng = np.random.default_rng(2000 + groups)
+    g = rng.laplace(size=(U, d)).astype(np.float32) * np.float32(1e-3)
+    m = rng.laplace(size=(U, d)).astype(np.float32) * np.float32(3e-4)
+    bias = syn.bias_for_max(np.abs(g + np.float32(0.9) * m).max(), E)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias]] * U)
+    weights = np.maximum(gu.oracle_round(kw, g[:, :4096], m[:, :4096], 0.9)["hist"], 1)
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=weights, stochastic_seed=seed)
+    gpu, (plan, books, buf, gt, mt) = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=weights, single_sweep=True,
+                                                   stochastic_seed=seed, single_sweep_hist=hist)
+    gu.compare_round(gpu, ref, d, single_sweep=True)
+    if hist:
+        gu.assert_bits_equal(gpu["hist"], ref["hist"], "histogram")
+    skip = (-buf.workspace.data_ptr()) % 256
+    ticket = int(buf.workspace[skip:skip + 4].cpu().numpy().view(np.uint32)[0])
+    assert ticket == (plan.num_chunks if small else groups)
