@@ -1217,7 +1217,8 @@ def test_device_built_decode_tables(K):
 
 @pytest.mark.parametrize("seg_len", [[511], [512], [513], [2048 + 511], [4095], [4097], [3, 4096 * 2 + 513, 1, 2047, 4096 * 3]])
 @pytest.mark.parametrize("seed", [None, 11])
-def test_single_sweep_team_of_wavefronts(seg_len, seed):
+@pytest.mark.parametrize("hist", [False, True])
+def test_single_sweep_team_of_wavefronts(seg_len, seed, hist):
     # few chunks: four wavefronts share a chunk; ends of a chunk at and beside a wavefront's share, layers at odd
     # elements, with and without the symbol counts and the dither
     E, M, U = 4, 3, 3
@@ -1229,8 +1230,10 @@ def test_single_sweep_team_of_wavefronts(seg_len, seed):
     kw = dict(E=E, M=M, U=U, d=d, bias=[[bias] * len(seg_len)] * U, seg_len=seg_len, seg_book=[0] * len(seg_len))
     ref = gu.oracle_round(kw, g, m, 0.9, stochastic_seed=seed)
     ref = gu.oracle_round(kw, g, m, 0.9, weights=ref["hist"], stochastic_seed=seed)
-    gpu, _ = gu.gpu_round(kw, g, m, 0.9, 0, weights=ref["hist"], single_sweep=True, stochastic_seed=seed)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, 0, weights=ref["hist"], single_sweep=True, stochastic_seed=seed, single_sweep_hist=hist)
     gu.compare_round(gpu, ref, d, single_sweep=True)
+    if hist:
+        gu.assert_bits_equal(gpu["hist"], ref["hist"], "histogram")
 
 
 @pytest.mark.parametrize("polls", [None, 0])
