@@ -342,8 +342,9 @@ int co3_profile_end(co3_kernel_time *out, uint32_t capacity, uint32_t *count);
 /* The single-sweep encoder waits for the sizes of the chunks ahead of a workgroup by polling; the
  * wait is bounded by `polls` re-reads per predecessor entry (default CO3_LOOKBACK_POLLS_DEFAULT,
  * far more than any wait that ends).  A workgroup whose bound runs out writes no stream words,
- * leaves its chunk_offset entries untouched and is counted in status[CO3_STAT_STALLED]; so are all
- * later workgroups of that user.  m_out, sub_bits and payload_bits are complete all the same.
+ * leaves its chunk_offset entries untouched and is counted in status[CO3_STAT_STALLED]; so are the
+ * later workgroups of that user that meet its mark before a running total.  m_out, sub_bits and
+ * payload_bits are complete all the same.
  * polls = 0 gives up at the first entry that is not there yet (a way to exercise that path from
  * the host).  Process-wide; applies to calls of co3_encode made afterwards.                    */
 #define CO3_LOOKBACK_POLLS_DEFAULT (1u << 20)

@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
 
     // ascending (weight, symbol); the keys are distinct, so the order does not depend on the network.  A step over
     // fewer than 64 entries stays inside a wavefront's own entries: the workgroup meets only where a step or the one
-    // after it reaches further (14 of the 55 steps of 1024 symbols).
+    // after it reaches further (after 15 of the 55 steps of 1024 symbols).
     for (uint32_t k = 2; k <= A; k <<= 1) {
         for (uint32_t j = k >> 1; j > 0; j >>= 1) {
             for (uint32_t i = t; i < A; i += kWbThreads) {
