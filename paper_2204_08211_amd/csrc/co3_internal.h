@@ -122,9 +122,9 @@ static_assert(sizeof(SegDev) == 32 && sizeof(Layout) == 88, "read by every kerne
 
 // A layer's entry.  kOneLoad: requested as a whole; left to itself the compiler requests its parts where they are used.
 // Which is better was measured kernel by kernel: as a whole in the decoders (two users of 29.5 M elements with their own
-// tables, k_decode: 598 -> 566 us; three users of 11.3 M in eleven layers in [1,5,6], k_decode_wide: 187 -> 182 us), in
-// parts in the averages (sixteen users of 25.6 M in [1,5,6], k_aggregate_wide: 906 against 922 us; three users in seven
-// layers, k_aggregate_staged<4>: 27.1 against 27.8 us).
+// tables, k_decode: 598 -> 566 us; three users of 11.3 M in eleven layers in [1,5,6], k_decode_wide: 187 -> 183 us) and
+// in the average of few users (four users of 20 011 elements, k_aggregate_staged<4>: 25.6 -> 25.3 us), in parts in the
+// averages of many (sixteen users of 25.6 M in [1,5,6], k_aggregate_wide: 906 against 922 us).
 template <bool kOneLoad>
 __device__ inline SegDev load_segment(const SegDev *p)
 {

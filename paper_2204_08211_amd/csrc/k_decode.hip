@@ -538,7 +538,7 @@ __global__ __launch_bounds__(64 * W) void k_aggregate_staged(Layout lay, const u
     constexpr int G = (kChunk / 4) / T;  // 4-element groups per thread
     const uint32_t t = threadIdx.x, wave = t >> 6;
     const uint64_t c = blockIdx.x;
-    const ChunkGeom g = chunk_geom<false>(lay, c);
+    const ChunkGeom g = chunk_geom<true>(lay, c);
     const uint32_t sign_shift = (uint32_t)(lay.E + lay.M);
     const uint32_t mag_mask = (1u << sign_shift) - 1u;
     const uint32_t sign_up = 31u - sign_shift;
@@ -552,8 +552,8 @@ __global__ __launch_bounds__(64 * W) void k_aggregate_staged(Layout lay, const u
     for (uint32_t u0 = 0; u0 < lay.U; u0 += W) {
         const uint32_t u = u0 + wave;
         const bool active = u < lay.U;
-        ChunkIndex ix;
-        if (active) ix = read_index(lay, c, u, words, words_stride, chunk_offset, sub_bits);
+        // (a wavefront without a user requests the first one's: no branch between this and the tables)
+        const ChunkIndex ix = read_index(lay, c, active ? u : 0u, words, words_stride, chunk_offset, sub_bits);
         const DecLds *my_tab = s_tab;
         if (lay.per_user_books) {
             my_tab = s_tab + wave;
