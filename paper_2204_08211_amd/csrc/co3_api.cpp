@@ -59,6 +59,21 @@ int check_bias_table(const co3_format &f, const int32_t *bias, size_t n)
     return CO3_OK;
 }
 
+int32_t bias_spread(const int32_t *bias, uint32_t U, uint32_t nseg)
+{
+    int32_t spread = 0;
+    for (uint32_t k = 0; k < nseg; ++k) {
+        int32_t lo = bias[k], hi = bias[k];
+        for (uint32_t u = 1; u < U; ++u) {
+            const int32_t b = bias[(size_t)u * nseg + k];
+            lo = b < lo ? b : lo;
+            hi = b > hi ? b : hi;
+        }
+        spread = hi - lo > spread ? hi - lo : spread;
+    }
+    return spread;
+}
+
 }  // namespace
 
 namespace co3 {
@@ -193,6 +208,7 @@ int co3_plan_create(co3_format format, uint32_t U, uint64_t d, uint32_t nseg, co
     l.segs = p->d_segs;
     l.bias = p->d_bias;
     l.gain = p->d_gain;
+    p->facts.bias_spread = bias_spread(bias, U, nseg);
     *out = p;
     return CO3_OK;
 }
@@ -209,6 +225,7 @@ int co3_plan_set_bias(co3_plan *plan, const int32_t *bias, void *stream)
     if (hipMemcpyAsync(plan->d_bias, bias, sizeof(int32_t) * n, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return CO3_ERR_HIP;
+    plan->facts.bias_spread = bias_spread(bias, plan->lay.U, plan->lay.nseg);
     return CO3_OK;
 }
 
@@ -231,7 +248,7 @@ int co3_plan_set_gain(co3_plan *plan, const float *gain, const float *inv_gain, 
     if (hipMemcpyAsync(plan->d_gain, pairs.data(), sizeof(float) * pairs.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return CO3_ERR_HIP;
-    plan->has_gain = any;
+    plan->facts.has_gain = any;
     return CO3_OK;
 }
 
@@ -302,10 +319,13 @@ int co3_build_codebook(co3_format format, uint32_t nbooks, const uint64_t *weigh
         }
     } else {
         std::memset(host.data(), 0, sizeof(BookDev) * nbooks);
-        for (auto &b : host)   // a table not built yet has no codes at all
+        for (auto &b : host) {   // a table not built yet has no codes at all
+            if (weights) break;
             for (uint32_t s = 0; s < (uint32_t)kMaxA; ++s) b.fast[s] = kFastSlow << 24;
+            for (uint32_t i = 0; i < kDecTableMax; ++i) b.dsym[i] = b.dval[i] = kLenSlow;
+        }
         for (uint32_t b = 0; weights && b < nbooks; ++b) {
-            int rc = build_book_host(weights + (size_t)b * A, A, &host[b]);
+            int rc = build_book_host(weights + (size_t)b * A, A, format.exp_bits, format.mant_bits, &host[b]);
             if (rc != CO3_OK) return rc;
         }
     }
@@ -336,7 +356,7 @@ int co3_build_codebook_device(co3_codebook *books, const uint64_t *weights, uint
     hipError_t e = books->d_wide
                        ? launch_build_books_wide(books->d_wide, books->nbooks, books->A, weights, status,
                                                  static_cast<hipStream_t>(stream))
-                       : launch_build_books(books->d_books, books->nbooks, books->A, weights, nullptr, status,
+                       : launch_build_books(books->d_books, books->nbooks, books->format.exp_bits, books->format.mant_bits, weights, nullptr, status,
                                             static_cast<hipStream_t>(stream));
     return e == hipSuccess ? CO3_OK : CO3_ERR_HIP;
 }
@@ -403,7 +423,7 @@ static int encode_with_workspace(const co3_plan *plan, const co3_encode_args *a,
         return CO3_ERR_ARG;
     if (a->mode != CO3_BOOK_FIXED && a->mode != CO3_BOOK_EMPIRICAL) return CO3_ERR_ARG;
     if (a->rounding != CO3_ROUND_NEAREST && a->rounding != CO3_ROUND_STOCHASTIC) return CO3_ERR_ARG;
-    if (a->rounding == CO3_ROUND_STOCHASTIC && plan->has_gain) return CO3_ERR_ARG;  // defined for the closest representative only
+    if (a->rounding == CO3_ROUND_STOCHASTIC && plan->facts.has_gain) return CO3_ERR_ARG;  // defined for the closest representative only
     // symbols and hist come as a pair; without them a fixed code is encoded in a single sweep
     // without a symbol buffer a fixed code is encoded in a single sweep (with or without the symbol counts);
     // everything else needs both buffers
@@ -433,7 +453,7 @@ static int encode_with_workspace(const co3_plan *plan, const co3_encode_args *a,
     if (launch_quantize(lay, args, ws, s) != hipSuccess) return CO3_ERR_HIP;
     // this round's counts: folded by the code's builder, or on their own where the code is held
     const hipError_t e = a->mode == CO3_BOOK_EMPIRICAL
-                             ? launch_build_books(a->books->d_books, lay.nbooks, lay.A, ws.hist_rep, a->hist, a->status, s)
+                             ? launch_build_books(a->books->d_books, lay.nbooks, lay.E, lay.M, ws.hist_rep, a->hist, a->status, s)
                              : launch_reduce_hist(ws.hist_rep, a->hist, (uint64_t)lay.nbooks * lay.A, s);
     if (e != hipSuccess) return CO3_ERR_HIP;
     if (launch_pack(lay, args, a->books->d_books, ws, s) != hipSuccess) return CO3_ERR_HIP;
@@ -505,10 +525,11 @@ int co3_plan_set_bias_device(co3_plan *plan, const int32_t *bias, void *stream)
     if (!plan || !bias) return CO3_ERR_ARG;
     DeviceGuard guard(plan->device);
     const size_t n = (size_t)plan->lay.U * plan->lay.nseg;
-    return hipMemcpyAsync(plan->d_bias, bias, sizeof(int32_t) * n, hipMemcpyDeviceToDevice,
-                          static_cast<hipStream_t>(stream)) == hipSuccess
-               ? CO3_OK
-               : CO3_ERR_HIP;
+    if (hipMemcpyAsync(plan->d_bias, bias, sizeof(int32_t) * n, hipMemcpyDeviceToDevice,
+                       static_cast<hipStream_t>(stream)) != hipSuccess)
+        return CO3_ERR_HIP;
+    plan->facts.bias_spread = 0;   // not read back: the kernels look for themselves
+    return CO3_OK;
 }
 
 size_t co3_plan_scale_workspace_bytes(const co3_plan *plan) { return plan ? scale_workspace_bytes(plan->lay) : 0; }
@@ -534,7 +555,7 @@ int co3_plan_set_gain_device(co3_plan *plan, const float *gain_pairs, void *stre
     if (hipMemcpyAsync(plan->d_gain, gain_pairs, sizeof(float) * 2 * n, hipMemcpyDeviceToDevice,
                        static_cast<hipStream_t>(stream)) != hipSuccess)
         return CO3_ERR_HIP;
-    plan->has_gain = true;   // the values are not read back: a scale is taken to be there until the host setter says otherwise
+    plan->facts.has_gain = true;   // the values are not read back: a scale is taken to be there until the host setter says otherwise
     return CO3_OK;
 }
 
@@ -564,7 +585,7 @@ int co3_ps_aggregate(const co3_plan *plan, const co3_aggregate_args *a, void *st
     if (rc != CO3_OK) return rc;
     DeviceGuard guard(plan->device);
     const hipError_t e = lay.wide ? launch_aggregate_wide(lay, *a, a->books->d_wide, static_cast<hipStream_t>(stream))
-                                  : launch_aggregate(lay, *a, a->books->d_books, static_cast<hipStream_t>(stream));
+                                  : launch_aggregate(lay, plan->facts, *a, a->books->d_books, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? CO3_OK : CO3_ERR_HIP;
 }
 

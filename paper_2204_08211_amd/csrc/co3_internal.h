@@ -17,11 +17,11 @@ constexpr int kWideMaxA = 4096;     // alphabets of 9 to 12 bits: symbols are 16
 constexpr int kWideDecBits = 12;    // prefix width of the wide path's direct decode table
 constexpr int kWideDec2Bits = 5;    // its second-level tables are indexed by the next bits
 constexpr int kWideDec2Tables = 128;   // number of second-level tables
-constexpr int kDecBits = 11;        // prefix width of the direct decode table
-constexpr int kDecEntries = 1 << kDecBits;
-constexpr int kLongSlots = 64 - kDecBits;  // lengths kDecBits+1 .. 64
-constexpr int kDec2Bits = 3;        // second-level tables resolve codes of up to kDecBits + kDec2Bits bits
-constexpr int kDec2Tables = 40;     // for the first prefixes that hold only longer codes (they are the largest ones)
+// Decode tables of byte alphabets (decode_core.h): 32 binades of A / 2 entries.
+constexpr uint32_t kDecTableMax = 16 * kMaxA;
+__host__ __device__ constexpr uint32_t dec_table_entries(uint32_t A) { return 16u * A; }
+__host__ __device__ constexpr uint32_t dec_format(int E, int M) { return ((uint32_t)E << 8) | (uint32_t)M; }
+constexpr uint32_t kLenSlow = 32;   // an entry's length field: none of the codes of up to 31 bits
 // Symbols between two users' rows of a symbol buffer: the row length rounded up to 128 symbols, so that rows
 // start on 128-byte lines (of a 256-byte-aligned buffer).
 inline uint64_t symbol_row_stride(uint64_t d) { return (d + 127) & ~(uint64_t)127; }
@@ -37,22 +37,16 @@ struct BookDev {
     uint32_t fast[kMaxA];        // (len << 24) | code for len <= 24; len field 0xFF: a longer code, or none
     uint32_t count[65];          // count[L]: symbols with length L
     uint32_t offset[65];         // offset[L]: index of the first length-L symbol in sorted[]
-    uint16_t dec[kDecEntries];   // prefix -> (len << 8) | symbol for len <= 11; else 1 + its second-level table, or 0
-    uint16_t dec2[kDec2Tables << kDec2Bits];  // [table][next kDec2Bits bits] -> (len << 8) | symbol, 0: longer code;
-                                 // directly behind dec[]: the decoders index both as one array
     uint8_t len[kMaxA];          // codeword length, 0 = no code
     uint8_t sorted[kMaxA];       // symbols ordered by (length, symbol)
     uint32_t maxlen;
     uint32_t nactive;
-    // Lengths above kDecBits that occur, ascending.  A 64-bit left-aligned window w whose code is
-    // longer than kDecBits has the first listed length with w <= long_last[k]; its symbol is
-    // sorted[(uint32_t)(w >> (64 - len)) + long_base[k]].
-    uint32_t nlong;
-    uint32_t long_prefix0;       // first kDecBits-bit prefix under which only longer codes live (kDecEntries: none);
-                                 // prefix long_prefix0 + j, j < kDec2Tables, has second-level table j
-    uint64_t long_last[kLongSlots];   // left-aligned last code of the length, low bits all ones
-    uint32_t long_base[kLongSlots];   // offset[len] - first[len] (mod 2^32)
-    uint32_t long_len[kLongSlots];
+    uint32_t format;             // (E << 8) | M that dval[] was filled for
+    // Decode tables over the complement u of the next 32 bits: entry i serves the u whose leading bits, as a floating
+    // point number of log2(A) - 1 mantissa bits, are i = (exponent mod 32) * A / 2 + mantissa.
+    // (symbol << 8) | length, and (what the PS sums (dec_value_bits) | length); kLenSlow: no code of up to 31 bits
+    alignas(16) uint16_t dsym[kDecTableMax];
+    alignas(16) uint32_t dval[kDecTableMax];
 };
 
 // One Huffman code table of a wide alphabet (9 to 12 symbol bits) as the wide kernels read it.
@@ -121,10 +115,9 @@ struct Layout {
 static_assert(sizeof(SegDev) == 32 && sizeof(Layout) == 88, "read by every kernel");
 
 // A layer's entry.  kOneLoad: requested as a whole; left to itself the compiler requests its parts where they are used.
-// Which is better was measured kernel by kernel: as a whole in the decoders (two users of 29.5 M elements with their own
-// tables, k_decode: 598 -> 566 us; three users of 11.3 M in eleven layers in [1,5,6], k_decode_wide: 187 -> 183 us) and
-// in the average of few users (four users of 20 011 elements, k_aggregate_staged<4>: 25.6 -> 25.3 us), in parts in the
-// averages of many (sixteen users of 25.6 M in [1,5,6], k_aggregate_wide: 906 against 922 us).
+// Which is better was measured kernel by kernel: as a whole in the decoders (three users of 11.3 M elements in eleven
+// layers in [1,5,6], k_decode_wide: 187 -> 183 us), in parts in the wide average (sixteen users of 25.6 M in [1,5,6],
+// k_aggregate_wide: 906 against 922 us).
 template <bool kOneLoad>
 __device__ inline SegDev load_segment(const SegDev *p)
 {
@@ -141,6 +134,14 @@ __device__ inline SegDev load_segment(const SegDev *p)
 
 }  // namespace co3
 
+namespace co3 {
+// What the host knows of a plan beside its layout.
+struct PlanFacts {
+    bool has_gain = false;     // a gain other than (1, 1) was installed
+    int32_t bias_spread = 0;   // how far the users' biases of a layer lie apart at most; 0 where they came from device memory
+};
+}  // namespace co3
+
 struct co3_plan {
     co3::Layout lay;
     co3::SegDev *d_segs = nullptr;
@@ -148,7 +149,7 @@ struct co3_plan {
     co3::WideCut wide = {};
     int32_t *d_bias = nullptr;
     float *d_gain = nullptr;
-    bool has_gain = false;     // a gain other than (1, 1) was installed
+    co3::PlanFacts facts;
     int device = 0;
 };
 
@@ -178,7 +179,7 @@ private:
 };
 
 // Host Huffman builder (host_codebook.cpp): fills one table; returns a co3_status.
-int build_book_host(const uint64_t *weights, uint32_t A, BookDev *out);
+int build_book_host(const uint64_t *weights, uint32_t A, int E, int M, BookDev *out);
 int build_wide_host(const uint64_t *weights, uint32_t A, BookWide *out);
 
 // Kernel launchers (one per .hip file).  All return a hipError_t from hipGetLastError().
@@ -196,7 +197,7 @@ EncodeWs three_step_workspace(const Layout &lay, void *workspace, size_t bytes);
 hipError_t launch_zero_u64(uint64_t *p, uint64_t n, hipStream_t s);
 hipError_t launch_reduce_hist(const uint64_t *hist_rep, uint64_t *hist, uint64_t n, hipStream_t s);   // hist[i] = sum of the partial tables
 hipError_t launch_quantize(const Layout &lay, const co3_encode_args &a, const EncodeWs &ws, hipStream_t s);
-hipError_t launch_build_books(BookDev *books, uint32_t nbooks, uint32_t A, const uint64_t *weights, uint64_t *counts,
+hipError_t launch_build_books(BookDev *books, uint32_t nbooks, int E, int M, const uint64_t *weights, uint64_t *counts,
                               uint64_t *status, hipStream_t s);
 hipError_t launch_pack(const Layout &lay, const co3_encode_args &a, const BookDev *books,
                        const EncodeWs &ws, hipStream_t s);
@@ -219,7 +220,7 @@ size_t scale_workspace_bytes(const Layout &lay);
 hipError_t launch_model_scale(const Layout &lay, const co3_gennorm_params *params, int32_t *bias, float *gain_pairs,
                               double *error, double *workspace, hipStream_t s);
 hipError_t launch_decode(const Layout &lay, const co3_decode_args &a, const BookDev *books, hipStream_t s);
-hipError_t launch_aggregate(const Layout &lay, const co3_aggregate_args &a, const BookDev *books,
+hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3_aggregate_args &a, const BookDev *books,
                             hipStream_t s);
 // wide alphabets (k_wide.hip): the same steps with 16-bit symbols and tables in device memory
 size_t wide_workspace_bytes(const Layout &lay);

@@ -1,0 +1,377 @@
+// Wavefront-level core of the decoder (Sec. II-B (iv)): lane j of a wavefront decodes sub-chunk j (64 symbols) of a
+// chunk, eight symbols at a time, shared by co3_decode and the PS average (k_decode.hip).
+//
+// Table.  Canonical codes grow with their length, so the long codes are the largest prefixes.  With u the complement of
+// the next 32 bits and k the number of its leading zeros, the codeword at the front has at most k + log2(A) bits: it is
+// all ones (and not longer than k), or its first zero is at bit k; in the latter case the prefix of k + 1 ones behind it
+// has to hold codes as long or longer, a share of 2^-(k+1) of the code space, at least 2^(len - k - 1) of them, and there
+// are fewer than A.  So u's exponent and log2(A) - 1 bits behind its leading one - the top bits of u as a floating point
+// number - index a table that resolves every code of up to 31 bits in one look-up: 32 binades of A / 2 entries, 16 KB
+// for 256 symbols, 1 KB for 16.  (The binade of u < 4 holds no codes; longer codes, streams that are not one and the
+// absent second codeword of a code of one symbol take the slow path.)
+//
+// Reader.  A lane's words lie complemented and in reverse order in its column of LDS, so that the stream is one large
+// number read from its top: 32 bits at any bit address N are two LDS words and one v_alignbit, with nothing carried from
+// symbol to symbol but N.  A window serves two symbols (together 31 bits at most: otherwise the group's lanes concerned
+// take the slow path, one window per symbol).
+//
+// What bounds it: vector instructions (some nine per symbol of a wavefront, 27 in the form this replaced: two words and an
+// offset in registers, an 11-bit table and second-level tables), the LDS look-ups of 64 lanes at unrelated addresses, and
+// the chain of three LDS reads per pair.  Sixteen users of 25.6 M elements in [1,4,3] (6.9 bit/element): decoded to
+// symbols 365 -> 172 us, averaged 380 -> 228 us; with the words of a chunk in order in LDS, where two of the lanes'
+// reads in three met in a bank, 200 us.
+#pragma once
+
+#include "co3_internal.h"
+#include "quantize_math.h"
+
+namespace co3 {
+
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) uint16_t lds_u16;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A wavefront's window: rows of 64 words, the word of lane j in column j, so that the lanes' reads never meet in a bank.
+// Word k behind the one with the lane's position when the window was loaded lies k rows below the top row.
+constexpr uint32_t kRowBytes = 256;
+// Bits that a group reads at most, on the slow path too: eight of the longest codes an alphabet can have, and a window.
+__host__ __device__ constexpr uint32_t group_bits(uint32_t A) { return 8u * (A > 64u ? 64u : A - 1u) + 64u; }
+// Rows, a multiple of four: room for a sub-chunk of the bits its symbols have and an eighth more, and for a group.  A lane
+// whose sub-chunk is longer loads again on the way.
+__host__ __device__ constexpr uint32_t window_rows(uint32_t A)
+{
+    const uint32_t nbits = (uint32_t)(31 - __builtin_clz(A));
+    return nbits >= 6u ? 20u : (2u * nbits + 5u) & ~3u;
+}
+__host__ __device__ constexpr bool holds_group(uint32_t A) { return 32u * (window_rows(A) - 1u) - 31u >= group_bits(A); }
+static_assert(holds_group(8) && holds_group(16) && holds_group(32) && holds_group(64) && holds_group(128) && holds_group(256),
+              "wherever a window starts in its first word, it holds a group");
+constexpr uint32_t kMaxRows = 20;   // and 8 at least: formats have three bits or more
+__host__ __device__ constexpr uint32_t window_words(uint32_t A) { return window_rows(A) * 64u; }
+// In front of the windows lies at least this much (tables): a group of a damaged stream reads up to eight rows below its
+// window before it is found out.
+constexpr uint32_t kFrontWords = 8 * kRowBytes / 4;
+__host__ __device__ constexpr uint32_t front_words(uint32_t table_words) { return table_words < kFrontWords ? kFrontWords : table_words; }
+constexpr uint32_t kBehindWords = 64;   // and a row behind them: the reader takes a word from the row above its place
+constexpr int kGroup = 8;                           // symbols decoded between two checks
+constexpr int kGroups = kSub / kGroup;
+
+__device__ inline uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
+}
+__device__ inline uint32_t lds_word(uint32_t byte) { return *(const lds_u32 *)byte; }
+
+__device__ inline void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ inline uint32_t wave_inclusive_scan_dpp(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// Between the two, conversions to fp32 round toward zero, so that u's leading bits survive; nothing else there rounds in
+// fp32.  (Register MODE, its two bits for fp32.)  The conversions take words read from LDS behind a fence and feed
+// addresses of reads before one, so they stay where they are written.
+__device__ inline void round_toward_zero() { __builtin_amdgcn_s_setreg(1 | (1 << 11), 3); }
+__device__ inline void round_to_nearest() { __builtin_amdgcn_s_setreg(1 | (1 << 11), 0); }
+
+// A value made here and not earlier (what depends on the lane alone would be computed once per kernel) or not later (a
+// group's entries would wait for their use at the end): both would hold registers over the decoding.
+template <class T>
+__device__ inline T here(T x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// Where the entries of a code lie in LDS.  Entry: code length in bits 0..7 (kLenSlow: slow path), above it what the sink
+// asks for.  kBytes 4 or 2 per entry.  The table lies at a multiple of its size.
+template <int kBytes>
+struct DecTable {
+    uint32_t base;    // LDS address
+    uint32_t shift, mask;
+    __device__ inline void init(uint32_t address, uint32_t A)
+    {
+        const uint32_t nbits = 31u - (uint32_t)__builtin_clz(A);
+        base = address;
+        shift = 24u - nbits - (kBytes == 4 ? 2u : 1u);
+        mask = here(dec_table_entries(A) * (uint32_t)kBytes - (uint32_t)kBytes);   // (v_and_or_b32 takes one scalar operand)
+    }
+    // u is a window's complement.  kTrunc: the rounding mode is not set, the conversion has to be exact
+    template <bool kTrunc>
+    __device__ inline uint32_t operator()(uint32_t u) const
+    {
+        const float f = (float)(kTrunc ? u & 0xffffff00u : u);   // (kTrunc: u < 256 takes the slow path)
+        const uint32_t a = ((__float_as_uint(f) >> shift) & mask) | base;
+        if constexpr (kBytes == 4) return *(const lds_u32 *)a;
+        else return *(const lds_u16 *)a;
+    }
+};
+
+// Loads that return zeros beyond `bytes`, without a branch.
+__device__ inline __amdgpu_buffer_rsrc_t bounded(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+__device__ inline u32x4 load16(__amdgpu_buffer_rsrc_t r, uint32_t byte) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte, 0, 0); }
+
+// A table of `bytes` (a multiple of 16) from device memory to LDS.
+__device__ inline void load_table(uint32_t *dst, const void *src, uint32_t bytes, uint32_t thread, uint32_t nthreads)
+{
+    const __amdgpu_buffer_rsrc_t r = bounded(src, bytes);
+    char *d = reinterpret_cast<char *>(dst);
+    const uint32_t t = here(thread) * 16u, step = nthreads * 16u;
+#pragma unroll 1
+    for (uint32_t i = 0; i < bytes; i += 4u * step) {
+        u32x4 v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) v[k] = load16(r, t + i + k * step);
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (t + i + k * step < bytes) *reinterpret_cast<u32x4 *>(d + t + i + k * step) = v[k];
+    }
+}
+
+struct ChunkGeom {
+    uint32_t seg;
+    uint32_t n;       // elements in the chunk
+    uint64_t e0;      // first element
+    int32_t book;     // table id within a user's set
+};
+
+__device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
+{
+    uint32_t lo = 0, hi = lay.nseg;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (lay.segs[mid].chunk_start <= c) lo = mid; else hi = mid;
+    }
+    ChunkGeom g;
+    g.seg = lo;
+    const SegDev sd = load_segment<true>(lay.segs + lo);
+    g.e0 = sd.offset + (c - sd.chunk_start) * kChunk;
+    const uint64_t left = sd.offset + sd.length - g.e0;
+    g.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
+    g.book = sd.book;
+    return g;
+}
+
+__device__ inline uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ inline uint64_t uniform(uint64_t x) { return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x); }
+
+// What a wavefront needs to know about chunk c of user u before it can decode it.
+struct ChunkIndex {
+    const uint32_t *w;   // chunk's first word
+    uint32_t nw;         // its words (0 if the index is malformed)
+    uint32_t sb;         // this lane's sub-chunk bit count
+    bool ok;             // 32-bit aligned, ordered, inside the buffer
+};
+
+__device__ inline ChunkIndex read_index(const Layout &lay, uint64_t c, uint32_t u, const uint32_t *__restrict__ words,
+                                        uint64_t words_stride, const uint64_t *__restrict__ chunk_offset,
+                                        const uint16_t *__restrict__ sub_bits)
+{
+    ChunkIndex ix;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t *at = chunk_offset + (uint64_t)u * (lay.nchunks + 1) + c;
+    ix.sb = sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + lane];
+    const uint64_t off = uniform(at[0]), end = uniform(at[1]);
+    ix.ok = !(off & 31u) && end >= off && (end >> 5) <= words_stride &&
+            ((end - off) >> 5) <= (uint64_t)kChunk * CO3_MAX_CODE_LEN / 32;
+    ix.nw = ix.ok ? (uint32_t)((end - off) >> 5) : 0u;
+    ix.w = words + (uint64_t)u * words_stride + (ix.ok ? (off >> 5) : 0);
+    return ix;
+}
+
+// A lane's place in its stream.
+struct Stream {
+    uint32_t N;       // bit address of the low end of the next 32 bits, counted in rows: LDS row N / 32, bit N % 32
+    uint32_t first;   // word of the chunk that lies in the top row
+    uint32_t end;     // bit of the chunk where the lane's sub-chunk ends
+    uint32_t column;  // LDS address of the lane's column
+    uint32_t row0, rows;   // the window's rows (the same in all lanes)
+    int cnt;          // symbols to decode
+    bool bad;         // a prefix matched no codeword
+    __device__ inline uint32_t top() const { return 32u * (row0 + rows - 1u); }
+    __device__ inline uint32_t bit() const { return 32u * first + (top() - N); }
+    __device__ inline uint32_t word(uint32_t row) const { return lds_word(column + row * kRowBytes); }
+    // the complements of 32 bits and of the 32 bits behind them
+    __device__ inline uint32_t window(uint32_t n) const
+    {
+        const uint32_t r = n >> 5;
+        return __builtin_amdgcn_alignbit(word(r + 1u), word(r), n);
+    }
+};
+
+// Loads every lane's window from the word with its position on, 16 bytes a lane at a time (the lanes' pieces overlap or
+// follow each other: the first request of a line serves the others from the cache), nothing beyond the chunk.
+__device__ inline void load_window(Stream &st, const ChunkIndex &ix, uint32_t bit)
+{
+    constexpr int n = (int)kMaxRows / 4;
+    st.first = bit >> 5;
+    st.N = st.top() - (bit & 31u);
+    const __amdgpu_buffer_rsrc_t r = bounded(ix.w, 4u * ix.nw);
+    const uint32_t at = 4u * (st.first < ix.nw ? st.first : ix.nw);
+    // pieces of four words: what the longest sub-chunk needs
+    uint32_t pieces = 2;
+#pragma unroll
+    for (int k = 2; k < n; ++k) pieces += __any((st.first + 4u * (uint32_t)k) * 32u < st.end) ? 1u : 0u;
+    pieces = pieces < st.rows / 4u ? pieces : st.rows / 4u;
+    u32x4 v[n];
+#pragma unroll
+    for (int k = 0; k < n; ++k)
+        if (k < 2 || (uint32_t)k < pieces) v[k] = load16(r, at + 16u * (uint32_t)k);
+    // word 4 k + 3 - i lies i rows above the lowest of its piece
+    const uint32_t low = st.column + (st.row0 + st.rows - 16u) * kRowBytes;
+#pragma unroll
+    for (int k = 0; k < n; ++k)
+        if (k < 2 || (uint32_t)k < pieces) {
+            const uint32_t at_row = k < 4 ? low + (uint32_t)(12 - 4 * k) * kRowBytes : low - 4u * kRowBytes;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(lds_u32 *)(at_row + (uint32_t)i * kRowBytes) = ~v[k][3 - i];
+        }
+    wave_lds_fence();
+}
+
+// Where some lane's sub-chunk does not fit its window: the windows are loaded anew unless every lane has the `bits` bits
+// that a group reads at most, or all there is.
+__device__ inline void refill(Stream &st, const ChunkIndex &ix, uint32_t bits)
+{
+    const bool low = st.N < 32u * st.row0 + bits && 32u * (st.first + st.rows) < st.end;
+    if (!__any(low)) return;
+    wave_lds_fence();
+    load_window(st, ix, st.bit());
+}
+
+// Symbols j0 .. j0 + 7, of which those from cnt on give the entry 0 and take no bits (full: cnt is kSub in every lane).
+// Where bit 5, 6 or 7 of the result is set the lane's entries are not to be used: two symbols of 32 bits or more
+// together, or a code the table does not hold.  n0: where the group started.
+template <bool kTrunc, class Table>
+__device__ inline uint32_t fast_group(Stream &st, uint32_t (&e)[kGroup], uint32_t &n0, int j0, const Table &tab, bool full)
+{
+    const uint32_t least = 32u * (st.row0 - 1u);   // (a damaged stream only)
+    n0 = st.N > least ? st.N : least;
+    uint32_t N = n0, over = 0;
+#pragma unroll
+    for (int b = 0; b < kGroup; b += 2) {
+        const uint32_t u = st.window(N);
+        const uint32_t x = tab.template operator()<kTrunc>(u);
+        const uint32_t y = tab.template operator()<kTrunc>(u << (x & 31u));
+        e[b] = x;
+        e[b + 1] = y;
+        const uint32_t both = x + y;   // bits 0..7: the two lengths, up to 64
+        over |= both;
+        N -= both & 0xffu;
+    }
+    if (!full) {
+        N = n0;
+#pragma unroll
+        for (int b = 0; b < kGroup; ++b) {
+            e[b] = j0 + b < st.cnt ? e[b] : 0u;
+            N -= e[b] & 0xffu;
+        }
+        over = j0 < st.cnt ? over : 0u;
+    }
+    st.N = N;
+    return over;
+}
+
+// The exact decoder, for the lanes `redo` of a group that started at n0: one window per symbol; a code the table does
+// not hold is searched by all lanes together, lane l comparing the window with the codes of l + 1 bits.
+template <bool kTrunc, class Table, class Value>
+__device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0, bool redo, int j0, const Table &tab,
+                                  const BookDev *__restrict__ book, Value value)
+{
+    const uint32_t lane = here(threadIdx.x & 63);
+    st.N = redo ? n0 : st.N;
+#pragma unroll 1
+    for (int i = 0; i < kGroup; ++i) {
+        const bool on = redo && j0 + i < st.cnt;
+        const uint32_t least = 32u * (st.row0 - 1u);
+        const uint32_t n = st.N > least ? st.N : least;
+        const uint32_t u0 = st.window(n), u1 = st.window(n - 32u);
+        uint32_t x = tab.template operator()<kTrunc>(u0);
+        uint64_t todo = __ballot(on && (x & 0xffu) == kLenSlow);
+        while (todo) {
+            const int src = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const uint64_t win = ~(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)u0, src) << 32) |
+                                   (uint32_t)__builtin_amdgcn_readlane((int)u1, src));
+            const uint64_t c = win >> (63u - lane), first = book->first[lane + 1u];
+            const uint64_t hits = __ballot(c >= first && c - first < book->count[lane + 1u]);
+            uint32_t y = 1u;   // nothing matches: one bit is passed over, as symbol 0
+            if (hits) {
+                const uint32_t L = (uint32_t)__ffsll((unsigned long long)hits);
+                y = value(book->sorted[(book->offset[L] + (uint32_t)(win >> (64u - L)) - (uint32_t)book->first[L]) & (kMaxA - 1)]) | L;
+            }
+            if ((int)lane == src) {
+                x = y;
+                st.bad = st.bad || !hits;
+            }
+        }
+        x = on ? x : 0u;
+        st.N = on ? n - (x & 0xffu) : st.N;
+        if (redo) {
+#pragma unroll
+            for (int b = 0; b + 1 < kGroup; ++b) e[b] = e[b + 1];
+            e[kGroup - 1] = x;
+        }
+    }
+}
+
+// Where a wavefront decodes chunk (g, ix): `window` is the LDS address of its `rows` rows.
+__device__ inline void start_chunk(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t window, uint32_t rows)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    st.end = wave_inclusive_scan_dpp(ix.sb);
+    st.row0 = window / kRowBytes;
+    st.rows = rows;
+    st.column = 4u * lane;
+    const int left = (int)g.n - (int)lane * kSub;
+    st.cnt = (int)here((uint32_t)(left < 0 ? 0 : (left > kSub ? kSub : left)));
+    st.bad = false;
+    load_window(st, ix, st.end - ix.sb);
+}
+__device__ inline void finish_chunk(const Stream &st, const ChunkIndex &ix, uint64_t *__restrict__ status)
+{
+    if (!ix.ok || st.bad || st.bit() != st.end || (st.cnt > 0 && st.end > 32u * ix.nw))
+        atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CORRUPT), 1ull);
+    wave_lds_fence();   // the next chunk's words overwrite these
+}
+
+// on_group(gr, e) gets the entries of symbols 8 gr .. 8 gr + 7 of every lane, gr = 0 .. 7.  kUnroll: gr is a constant
+// there (sums in registers), at eight times the code, which a launch of few workgroups waits for.
+template <bool kTrunc, bool kUnroll, class Table, class Value, class OnGroup>
+__device__ inline void decode_started(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t A, const Table &tab,
+                                      const BookDev *__restrict__ book, Value value, OnGroup on_group)
+{
+    const bool part = __any(32u * (st.first + st.rows) < st.end), full = g.n == (uint32_t)kChunk;
+    auto group = [&](int gr) {
+        uint32_t e[kGroup], n0;
+        if (__builtin_expect(part, 0)) refill(st, ix, group_bits(A));
+        const uint32_t over = fast_group<kTrunc>(st, e, n0, gr * kGroup, tab, full);
+        const bool redo = (over & 0xe0u) != 0u;
+        if (__builtin_expect(__any(redo), 0)) slow_group<kTrunc>(st, e, n0, redo, gr * kGroup, tab, book, value);
+        on_group(gr, e);
+    };
+    if constexpr (kUnroll) {
+#pragma unroll
+        for (int gr = 0; gr < kGroups; ++gr) group(gr);
+    } else {
+#pragma unroll 1
+        for (int gr = 0; gr < kGroups; ++gr) group(gr);
+    }
+}
+
+}  // namespace co3

@@ -11,19 +11,18 @@
 #include <vector>
 
 #include "co3_internal.h"
+#include "quantize_math.h"
 
 namespace co3 {
 
 // Fill every derived table of `b` from b->len[] (lengths) for alphabet size A.
-static void finish_tables(BookDev *b, uint32_t A)
+static void finish_tables(BookDev *b, uint32_t A, int E, int M)
 {
     std::memset(b->count, 0, sizeof(b->count));
     std::memset(b->first, 0, sizeof(b->first));
     std::memset(b->offset, 0, sizeof(b->offset));
     std::memset(b->code, 0, sizeof(b->code));
     for (uint32_t s = 0; s < (uint32_t)kMaxA; ++s) b->fast[s] = kFastSlow << 24;  // no code: the coders' general path counts it
-    std::memset(b->dec, 0, sizeof(b->dec));
-    std::memset(b->dec2, 0, sizeof(b->dec2));
     std::memset(b->sorted, 0, sizeof(b->sorted));
     b->maxlen = 0;
     b->nactive = 0;
@@ -42,33 +41,6 @@ static void finish_tables(BookDev *b, uint32_t A)
         b->offset[L] = off;
         off += b->count[L];
     }
-    // search list for codes longer than the direct table
-    b->nlong = 0;
-    b->long_prefix0 = kDecEntries;
-    std::memset(b->long_last, 0, sizeof(b->long_last));
-    std::memset(b->long_base, 0, sizeof(b->long_base));
-    std::memset(b->long_len, 0, sizeof(b->long_len));
-    for (int L = kDecBits + 1; L <= 64; ++L) {
-        if (!b->count[L]) continue;
-        const uint32_t k = b->nlong++;
-        const uint64_t end_code = b->first[L] + b->count[L];                  // 2^L when the code is complete
-        const uint64_t end_la = (L == 64) ? end_code : (end_code << (64 - L));  // wraps to 0 then
-        b->long_last[k] = end_la - 1;
-        b->long_base[k] = b->offset[L] - (uint32_t)b->first[L];
-        b->long_len[k] = (uint32_t)L;
-    }
-    // Prefixes of kDecBits bits under which only longer codes live are the largest ones (canonical
-    // codes grow with their length); the first kDec2Tables of them get a second-level table over
-    // the next kDec2Bits bits.
-    uint32_t long_prefix0 = kDecEntries;
-    for (int L = kDecBits + 1; L <= 64; ++L) {
-        if (!b->count[L]) continue;
-        long_prefix0 = (uint32_t)(b->first[L] >> (L - kDecBits));
-        break;
-    }
-    b->long_prefix0 = long_prefix0;
-    for (uint32_t p = long_prefix0; p < (uint32_t)kDecEntries && p - long_prefix0 < (uint32_t)kDec2Tables; ++p)
-        b->dec[p] = (uint16_t)(p - long_prefix0 + 1);  // entries of the second-level tables follow with the symbols
     uint32_t next[65];
     std::memset(next, 0, sizeof(next));
     for (uint32_t s = 0; s < A; ++s) {  // ascending symbol within each length
@@ -79,18 +51,28 @@ static void finish_tables(BookDev *b, uint32_t A)
         b->sorted[b->offset[L] + rank] = (uint8_t)s;
         if (L <= kFastLen) b->fast[s] = ((uint32_t)L << 24) | (uint32_t)b->code[s];
         else b->fast[s] = kFastSlow << 24;
-        if (L <= kDecBits) {
-            const uint32_t lo = (uint32_t)b->code[s] << (kDecBits - L);
-            const uint32_t n = 1u << (kDecBits - L);
-            for (uint32_t i = 0; i < n; ++i) b->dec[lo + i] = (uint16_t)((L << 8) | s);
-        } else if (L <= kDecBits + kDec2Bits) {
-            const uint32_t lo = (uint32_t)b->code[s] << (kDecBits + kDec2Bits - L);
-            const uint32_t n = 1u << (kDecBits + kDec2Bits - L);
-            for (uint32_t i = 0; i < n; ++i) {
-                const uint32_t j = ((lo + i) >> kDec2Bits) - long_prefix0;
-                if (j < (uint32_t)kDec2Tables) b->dec2[(j << kDec2Bits) | ((lo + i) & ((1u << kDec2Bits) - 1u))] = (uint16_t)((L << 8) | s);
-            }
+    }
+    // decode tables: entry i belongs to the windows whose complement u has exponent i / (A / 2) mod 32 and, behind its
+    // leading one, the bits i mod (A / 2); a code of up to 31 bits covers whole entries
+    const uint32_t half = A / 2;
+    int nm = 0;
+    while ((1u << nm) < half) ++nm;
+    b->format = dec_format(E, M);
+    for (uint32_t i = 0; i < dec_table_entries(A); ++i) {
+        const uint32_t binade = i / half;
+        const int ex = binade == 31 ? 0 : (int)binade + 1;   // exponent of u
+        const uint64_t lead = (uint64_t)(half + i % half);   // leading one and mantissa
+        const uint32_t x = ~(uint32_t)(ex >= nm ? lead << (ex - nm) : lead >> (nm - ex));
+        uint32_t len = kLenSlow, sym = 0;
+        for (int L = 1; binade != 0 && L <= 31; ++L) {
+            const uint64_t c = x >> (32 - L);
+            if (c < b->first[L] || c - b->first[L] >= b->count[L]) continue;
+            len = (uint32_t)L;
+            sym = b->sorted[b->offset[L] + (uint32_t)(c - b->first[L])];
+            break;
         }
+        b->dsym[i] = (uint16_t)((sym << 8) | len);
+        b->dval[i] = dec_value_bits(sym, E, M) | len;
     }
 }
 
@@ -187,7 +169,7 @@ int build_wide_host(const uint64_t *w, uint32_t A, BookWide *b)
     return CO3_OK;
 }
 
-int build_book_host(const uint64_t *w, uint32_t A, BookDev *b)
+int build_book_host(const uint64_t *w, uint32_t A, int E, int M, BookDev *b)
 {
     std::memset(b, 0, sizeof(*b));
     struct Leaf { uint64_t w; uint32_t s; };
@@ -200,8 +182,8 @@ int build_book_host(const uint64_t *w, uint32_t A, BookDev *b)
         leaves.push_back({w[s], s});
     }
     const int n = (int)leaves.size();
-    if (n == 0) { finish_tables(b, A); return CO3_OK; }
-    if (n == 1) { b->len[leaves[0].s] = 1; finish_tables(b, A); return CO3_OK; }
+    if (n == 0) { finish_tables(b, A, E, M); return CO3_OK; }
+    if (n == 1) { b->len[leaves[0].s] = 1; finish_tables(b, A, E, M); return CO3_OK; }
     std::sort(leaves.begin(), leaves.end(),
               [](const Leaf &x, const Leaf &y) { return x.w != y.w ? x.w < y.w : x.s < y.s; });
     // nodes 0..n-1: sorted leaves; n..2n-2: internal nodes in creation order
@@ -227,7 +209,7 @@ int build_book_host(const uint64_t *w, uint32_t A, BookDev *b)
         if (depth > CO3_MAX_CODE_LEN) return CO3_ERR_CODELEN;
         b->len[leaves[i].s] = (uint8_t)depth;
     }
-    finish_tables(b, A);
+    finish_tables(b, A, E, M);
     return CO3_OK;
 }
 

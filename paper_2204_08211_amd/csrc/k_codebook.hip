@@ -11,6 +11,7 @@
 // 2^20 elements in [1,3,0] with the code rebuilt, the whole round: 64.9 -> 52.2 us; tables of 256 symbols save more).
 #include "co3_internal.h"
 #include "pack_core.h"
+#include "quantize_math.h"
 
 namespace co3 {
 
@@ -18,12 +19,13 @@ constexpr int kCbThreads = 256;
 
 // counts: `weights` are the sweep's kHistGlobalRep partial tables of symbol counts, one table of all codes after the
 // other; their sum is the weight and is left in `counts` (a kernel of its own for it was another 3.4 to 5 us).
-__global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict__ books, uint32_t A,
+__global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict__ books, int E, int M,
                                                            const uint64_t *__restrict__ weights,
                                                            uint64_t *__restrict__ counts,
                                                            uint64_t *__restrict__ status)
 {
     BookDev &B = books[blockIdx.x];
+    const uint32_t A = 1u << (1 + E + M);
     const uint64_t *w = weights + (uint64_t)blockIdx.x * A;
     const int t = threadIdx.x;
 
@@ -38,8 +40,8 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     __shared__ uint64_t tmpw[kMaxA];      // a round's nodes in merged order: weight
     __shared__ int tmpid[kMaxA];          // and node index
     __shared__ uint32_t wcnt[kCbThreads / 64][65];   // codes of every length per wavefront of symbols
-    __shared__ uint32_t end[kDecBits];
-    __shared__ uint32_t long0;
+    __shared__ uint64_t end32[33];        // codes of up to l bits lie below end32[l], left-aligned in 32 bits
+    __shared__ uint32_t entry_sym[kMaxA], entry_val[kMaxA];   // what a decode table's entry carries, by rank
     __shared__ int err;
 
     uint64_t myw = 0;
@@ -218,27 +220,13 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
         cnt[l] = cl;
         first[l] = code;
         off[l] = o;
-        const uint64_t used = __ballot(cl != 0), used_long = used & (~0ull << kDecBits);
-        const uint32_t nlong = (uint32_t)__popcll(used_long);
-        if ((used_long >> t) & 1ull) {   // search list for codes longer than the direct table
-            const uint32_t k = (uint32_t)__popcll(used_long & ((1ull << t) - 1ull));
-            const uint64_t end_code = code + cl;
-            B.long_last[k] = (l == 64 ? end_code : (end_code << (64 - l))) - 1;
-            B.long_base[k] = o - (uint32_t)code;
-            B.long_len[k] = (uint32_t)l;
-        }
-        if (t >= (int)nlong && t < kLongSlots) {
-            B.long_last[t] = 0; B.long_base[t] = 0; B.long_len[t] = 0;
-        }
-        // the direct table's prefixes below end[l - 1] have codes of up to l bits
-        if (l <= kDecBits) end[t] = ((uint32_t)code + cl) << (kDecBits - l);
-        // the first of its prefixes that holds only longer codes
-        if (used_long ? (uint32_t)t == (uint32_t)__ffsll((unsigned long long)used_long) - 1u : t == 0)
-            long0 = used_long ? (uint32_t)(code >> (l - kDecBits)) : (uint32_t)kDecEntries;
+        const uint64_t used = __ballot(cl != 0);
+        if (l <= 32) end32[l] = (code + cl) << (32 - l);
+        if (t == 0) end32[0] = 0;
         if (t == 0) {
             B.maxlen = used ? 64u - (uint32_t)__clzll((long long)used) : 0u;
             B.nactive = bad ? 0 : (uint32_t)n;
-            B.nlong = nlong;
+            B.format = dec_format(E, M);
         }
     }
     __syncthreads();
@@ -248,6 +236,8 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     if (L) {
         code = first[L] + rank;
         sorted[off[L] + rank] = (uint32_t)t;
+        entry_sym[off[L] + rank] = ((uint32_t)t << 8) | L;
+        entry_val[off[L] + rank] = dec_value_bits((uint32_t)t, E, M) | L;
         if (L <= (uint32_t)kFastLen) fast = (L << 24) | (uint32_t)code;
     }
     B.code[t] = code;
@@ -257,49 +247,41 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     __syncthreads();
     B.sorted[t] = (t < n && !bad) ? (uint8_t)sorted[t] : 0;
 
-    // direct decode table: every kDecBits-bit prefix whose code is at most kDecBits long; the first
-    // kDec2Tables prefixes that hold only longer codes (the largest prefixes: canonical codes grow
-    // with their length) point to a second-level table over the next kDec2Bits bits
-    const uint32_t long_prefix0 = long0;
-    if (t == 0) B.long_prefix0 = long_prefix0;
-    uint32_t ends[kDecBits];
-#pragma unroll
-    for (int l = 0; l < kDecBits; ++l) ends[l] = end[l];
+    // decode tables (decode_core.h), two entries at a time: the window's complement at the entry's low end, its code's
+    // length by a binary search of the ends (they grow with the length), the rest from the code's rank
+    const uint32_t nm = (uint32_t)(E + M);
 #pragma unroll 4
-    for (int idx = t; idx < kDecEntries; idx += kCbThreads) {
-        uint32_t l = 1;   // canonical codes grow with their length, so the ends do
+    for (uint32_t i2 = t; i2 < dec_table_entries(A) / 2; i2 += kCbThreads) {
+        uint32_t es[2], ev[2];
 #pragma unroll
-        for (int k = 0; k < kDecBits; ++k) l += (uint32_t)idx >= ends[k];
-        uint16_t e = 0;
-        if (l <= (uint32_t)kDecBits)
-            e = (uint16_t)((l << 8) | sorted[off[l] + (((uint32_t)idx >> (kDecBits - l)) - (uint32_t)first[l])]);
-        else if ((uint32_t)idx >= long_prefix0 && (uint32_t)idx - long_prefix0 < (uint32_t)kDec2Tables)
-            e = (uint16_t)((uint32_t)idx - long_prefix0 + 1);
-        B.dec[idx] = e;
-    }
-    for (int idx = t; idx < (kDec2Tables << kDec2Bits); idx += kCbThreads) {
-        const uint32_t wide = ((long_prefix0 + ((uint32_t)idx >> kDec2Bits)) << kDec2Bits) |
-                              ((uint32_t)idx & ((1u << kDec2Bits) - 1u));  // kDecBits + kDec2Bits bits
-        uint16_t e = 0;
-        if ((wide >> kDec2Bits) < (uint32_t)kDecEntries) {
-            for (int l = kDecBits + 1; l <= kDecBits + kDec2Bits; ++l) {
-                const uint64_t c = wide >> (kDecBits + kDec2Bits - l);
-                if (cnt[l] && c >= first[l] && c - first[l] < cnt[l]) {
-                    e = (uint16_t)((l << 8) | sorted[off[l] + (uint32_t)(c - first[l])]);
-                    break;
-                }
+        for (uint32_t b = 0; b < 2; ++b) {
+            const uint32_t i = 2 * i2 + b, binade = i >> nm;
+            const uint32_t ex = binade == 31u ? 0u : binade + 1u;            // exponent of u
+            const uint32_t lead = (1u << nm) | (i & ((1u << nm) - 1u));
+            const uint32_t x = ~(ex >= nm ? (uint32_t)((uint64_t)lead << (ex - nm)) : lead >> (nm - ex));
+            uint32_t l = 0;   // the largest l with x >= end32[l]: the code has l + 1 bits
+#pragma unroll
+            for (uint32_t k = 16; k; k >>= 1) l = (uint64_t)x >= end32[l + k] ? l + k : l;
+            es[b] = kLenSlow;
+            ev[b] = kLenSlow;
+            const uint32_t L = l + 1;
+            if (binade != 0 && L < 32u) {   // (below the end of every code of up to 31 bits)
+                const uint32_t r = off[L] + ((x >> (32 - L)) - (uint32_t)first[L]);
+                es[b] = entry_sym[r & (kMaxA - 1)];
+                ev[b] = entry_val[r & (kMaxA - 1)];
             }
         }
-        B.dec2[idx] = e;
+        reinterpret_cast<uint32_t *>(B.dsym)[i2] = es[0] | (es[1] << 16);
+        reinterpret_cast<uint2 *>(B.dval)[i2] = make_uint2(ev[0], ev[1]);
     }
 }
 
-hipError_t launch_build_books(BookDev *books, uint32_t nbooks, uint32_t A, const uint64_t *weights, uint64_t *counts,
+hipError_t launch_build_books(BookDev *books, uint32_t nbooks, int E, int M, const uint64_t *weights, uint64_t *counts,
                               uint64_t *status, hipStream_t s)
 {
     if (nbooks == 0) return hipSuccess;
     ProfScope prof(K_BUILD_BOOKS, s);
-    hipLaunchKernelGGL(k_build_books, dim3(nbooks), dim3(kCbThreads), 0, s, books, A, weights, counts, status);
+    hipLaunchKernelGGL(k_build_books, dim3(nbooks), dim3(kCbThreads), 0, s, books, E, M, weights, counts, status);
     return hipGetLastError();
 }
 

@@ -1,0 +1,120 @@
+"""The decoder's windows and tables and the averages' sums at the places where they change, against the oracle."""
+import numpy as np
+import pytest
+
+import gpu_util as gu
+from oracle import co3_oracle as orc
+
+pytestmark = pytest.mark.gpu
+BOOK_FIXED, BOOK_EMPIRICAL = 0, 1
+
+
+def on_grid(rng, E, M, bias, d, p=None):
+    """Gradients that are representatives of the users' grids, magnitudes drawn with probabilities p."""
+    g = np.empty((len(bias), d), np.float32)
+    for u, b in enumerate(bias):
+        grid = orc.grid(E, M, int(b))
+        g[u] = (grid[rng.choice(grid.size, d, p=p)] * rng.choice([-1.0, 1.0], d)).astype(np.float32)
+    return g
+
+
+@pytest.mark.parametrize("E,M", [(2, 0), (2, 1), (3, 1), (3, 2), (3, 3), (4, 3), (5, 2)])
+@pytest.mark.parametrize("U", [1, 3])
+def test_sub_chunks_longer_than_a_window(E, M, U):
+    # a held code that gives the frequent symbols its long words: a sub-chunk takes up to several windows, some lanes'
+    # do and others' do not, in whole chunks and in a ragged one
+    rng = np.random.default_rng(100 * E + M)
+    d = 2 * 4096 + 1000
+    bias = np.full((U, 1), 2 ** (E - 1) - 1 + 6, np.int32)
+    nm = orc.num_magnitudes(E, M)
+    p = 0.55 ** np.arange(nm)[::-1]
+    g = on_grid(rng, E, M, bias[:, 0], d, p / p.sum())
+    g[:, 4096:4096 + 64 * 20] = 0.0             # twenty lanes with the shortest word only
+    m = np.zeros_like(g)
+    A = 1 << (1 + E + M)
+    w = np.zeros(A, np.uint64)
+    emit = [0] + [s for s in range(A) if 0 < (s & (A // 2 - 1)) < nm]
+    order = sorted(emit, key=lambda s: s & (A // 2 - 1))
+    w[order] = [max(1, int(2.0 ** (45 - 45.0 * i / len(order)))) for i in range(len(order))]
+    kw = dict(E=E, M=M, U=U, d=d, bias=bias)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w[None, :], max_code_len=64)
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=w[None, :])
+    rows = {3: 8, 4: 12, 5: 12}.get(1 + E + M, 20)
+    if (E, M) != (2, 0):
+        assert ref["sub_bits"].max() > 32 * rows
+    assert ref["sub_bits"].min() < 32 * rows
+    gu.compare_round(gpu, ref, d)
+
+
+@pytest.mark.parametrize("U", [2, 4, 5, 8, 11, 34])
+@pytest.mark.parametrize("spread", [0, 9, 12, 13, 60])
+@pytest.mark.parametrize("own", [False, True])
+def test_average_over_users_whose_biases_lie_apart(U, spread, own):
+    # integer sums per wavefront and workgroup, fp64 sums where they would not fit, more users than one turn holds;
+    # with a few chunks (a wavefront per user) and a plan that learns its biases on the device
+    import torch
+    from paper_2204_08211_amd import binding as B
+    E, M, d = 4, 3, 4096 + 333
+    rng = np.random.default_rng(1000 * U + spread)
+    bias = (10 + rng.integers(0, spread + 1, (U, 1))).astype(np.int32)
+    bias[0], bias[-1] = 10, 10 + spread
+    g = np.concatenate([rng.standard_normal((1, d)) * orc.grid(E, M, int(b))[-1] / 3 for b in bias[:, 0]]).astype(np.float32)
+    m = np.zeros_like(g)
+    kw = dict(E=E, M=M, U=U, d=d, bias=bias, per_user_books=own)
+    gpu, (plan, books, buf, _, _) = gu.gpu_round(kw, g, m, 0.9, BOOK_EMPIRICAL)
+    ref = gu.oracle_round(kw, g, m, 0.9)
+    # beyond 53 bits the last one may depend on the order of the users
+    gu.compare_round(gpu, ref, d, avg_exact=spread < 30)
+    same = torch.from_numpy(bias).to("cuda:0")
+    plan_near = B.Plan(E, M, U, d, np.full((U, 1), 10, np.int32), per_user_books=own)   # as the host knows it: no spread
+    B._check("co3_plan_set_bias_device", B.lib().co3_plan_set_bias_device(plan_near.handle, same.data_ptr(), B._stream()))
+    again = torch.zeros(d, dtype=torch.float32, device="cuda:0")
+    B.co3_ps_aggregate(plan_near, books, buf, again)
+    torch.cuda.synchronize()
+    if spread < 30:
+        gu.assert_bits_equal(again.cpu().numpy(), ref["avg"], "average, biases set on the device")
+    else:
+        scale = np.maximum(np.abs(ref["avg"]), np.abs(ref["dec_q"]).mean(axis=0))
+        assert np.all(np.abs(again.cpu().numpy().astype(np.float64) - ref["avg"]) <= 1e-6 * scale)
+
+
+@pytest.mark.parametrize("chunks", [520, 1100])
+@pytest.mark.parametrize("U,E,M", [(3, 4, 3), (4, 5, 2), (7, 3, 2), (13, 2, 1)])
+def test_average_on_both_sides_of_the_wavefronts_rule(chunks, U, E, M):
+    # a wavefront per user, several users a wavefront, a wavefront per chunk; layers of different tables that start and
+    # end inside a workgroup's chunks, the average at any element
+    rng = np.random.default_rng(chunks + U)
+    seg_len = [4096 * 3 + 17, 0, 5, 4096 * (chunks - 9), 4096 * 4 + 1]
+    d = sum(seg_len)
+    bias = rng.integers(14, 18, (U, len(seg_len))).astype(np.int32)
+    sym_top = np.float32(orc.grid(E, M, 16)[-1])
+    g = (rng.standard_normal((U, d)) * sym_top / 4).astype(np.float32)
+    m = np.zeros_like(g)
+    kw = dict(E=E, M=M, U=U, d=d, bias=bias, seg_len=seg_len, seg_book=[0, 1, 1, 2, 0])
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_EMPIRICAL)
+    vals = np.zeros(d)
+    off = 0
+    for k, n in enumerate(seg_len):                  # the oracle's average of the symbols the GPU coded
+        for u in range(U):
+            lut = np.array([orc.value(s, E, M, int(bias[u, k])) for s in range(1 << (1 + E + M))], np.float64)
+            vals[off:off + n] += lut[gpu["sym"][u, off:off + n]]
+        off += n
+    gu.assert_bits_equal(gpu["dec_sym"], gpu["sym"], "decoded symbols")
+    gu.assert_bits_equal(gpu["avg"], (vals * (1.0 / U)).astype(np.float32), "average")
+    assert int(gpu["status"][5]) == 0
+
+
+def test_table_set_of_another_format_of_the_same_alphabet():
+    # a code names symbols, not values: a set made for [1,5,2] serves a plan in [1,4,3]
+    import torch
+    from paper_2204_08211_amd import binding as B
+    E, M, U, d = 4, 3, 3, 9000
+    rng = np.random.default_rng(5)
+    bias = np.array([[12], [14], [13]], np.int32)
+    g = (rng.standard_normal((U, d)) * 2.0).astype(np.float32)
+    m = np.zeros_like(g)
+    kw = dict(E=E, M=M, U=U, d=d, bias=bias)
+    w = gu.oracle_round(kw, g, m, 0.9)["hist"]
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=w)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w, books=B.co3_build_codebook(5, 2, 1, w))
+    gu.compare_round(gpu, ref, d)
