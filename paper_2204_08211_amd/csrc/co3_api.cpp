@@ -1,6 +1,7 @@
 // Host side of the C ABI declared in include/co3.h: argument checks, plans, code-table sets and
 // the launch sequences.  No codec arithmetic happens here except the host Huffman builder that
 // co3_build_codebook exposes.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -313,6 +314,12 @@ int co3_build_codebook(co3_format format, uint32_t nbooks, const uint64_t *weigh
     std::vector<BookWide> host_wide(wide ? nbooks : 0);
     if (wide) {
         std::memset(host_wide.data(), 0, sizeof(BookWide) * nbooks);
+        for (auto &b : host_wide) {   // a table not built yet has no codes at all
+            if (weights) break;
+            std::fill(b.tab, b.tab + kWideTabMax, kLenSlow);
+            std::fill(b.limit, b.limit + 32, ~0u);
+            b.tab_bits = 2;
+        }
         for (uint32_t b = 0; weights && b < nbooks; ++b) {
             int rc = build_wide_host(weights + (size_t)b * A, A, &host_wide[b]);
             if (rc != CO3_OK) return rc;
@@ -322,7 +329,8 @@ int co3_build_codebook(co3_format format, uint32_t nbooks, const uint64_t *weigh
         for (auto &b : host) {   // a table not built yet has no codes at all
             if (weights) break;
             for (uint32_t s = 0; s < (uint32_t)kMaxA; ++s) b.fast[s] = kFastSlow << 24;
-            for (uint32_t i = 0; i < kDecTableMax; ++i) b.dsym[i] = b.dval[i] = kLenSlow;
+            std::fill(b.dsym, b.dsym + kDecTableMax, (uint16_t)kLenSlow);
+            std::fill(b.dval, b.dval + kDecTableMax, kLenSlow);
         }
         for (uint32_t b = 0; weights && b < nbooks; ++b) {
             int rc = build_book_host(weights + (size_t)b * A, A, format.exp_bits, format.mant_bits, &host[b]);

@@ -14,9 +14,13 @@ constexpr int kSub = CO3_SUB;
 constexpr int kSubsPerChunk = CO3_SUBS_PER_CHUNK;
 constexpr int kMaxA = 256;          // alphabets of up to 8 bits: symbols are bytes
 constexpr int kWideMaxA = 4096;     // alphabets of 9 to 12 bits: symbols are 16-bit words (k_wide.hip)
-constexpr int kWideDecBits = 12;    // prefix width of the wide path's direct decode table
-constexpr int kWideDec2Bits = 5;    // its second-level tables are indexed by the next bits
-constexpr int kWideDec2Tables = 128;   // number of second-level tables
+// Decode table of a wide alphabet (decode_core.h): binades 10 to 30 (binade 10 stands for all below and holds nothing) of
+// up to 2^9 entries, 42 KB of the 160 that a CU's wavefronts share.
+constexpr uint32_t kWideTabLow = 10, kWideTabBinades = 21;
+__host__ __device__ constexpr uint32_t wide_tab_bits_max(uint32_t A) { return A > 512u ? 9u : 8u; }
+constexpr uint32_t kWideTabMax = kWideTabBinades << 9;
+constexpr uint32_t kWidePrefixBits = 12;   // of a code for which a table by prefixes resolves more
+__host__ __device__ constexpr uint32_t wide_tab_entries(uint32_t bits) { return bits ? kWideTabBinades << bits : 1u << kWidePrefixBits; }
 // Decode tables of byte alphabets (decode_core.h): 32 binades of A / 2 entries.
 constexpr uint32_t kDecTableMax = 16 * kMaxA;
 __host__ __device__ constexpr uint32_t dec_table_entries(uint32_t A) { return 16u * A; }
@@ -55,16 +59,14 @@ struct BookWide {
     uint64_t first[65];                   // first[L]: first canonical code of length L
     uint32_t count[65];                   // symbols with length L
     uint32_t offset[65];                  // index of the first length-L symbol in sorted[]
-    uint16_t dec[1 << kWideDecBits];      // prefix -> (len << 12) | symbol for len <= kWideDecBits, else 0
-    // the first kWideDec2Tables prefixes that hold only longer codes (the largest prefixes: canonical codes grow
-    // with their length) each have a table over the next kWideDec2Bits bits:
-    // ((len - kWideDecBits) << 12) | symbol for len <= kWideDecBits + kWideDec2Bits, else 0
-    uint16_t dec2[kWideDec2Tables << kWideDec2Bits];
-    uint32_t long_prefix0;                // first prefix that holds only longer codes (1 << kWideDecBits: none)
     uint16_t sorted[kWideMaxA];           // symbols ordered by (length, symbol)
     uint8_t len[kWideMaxA];               // codeword length, 0 = no code
     uint32_t maxlen;
     uint32_t nactive;
+    uint32_t tab_bits;                    // mantissa bits of the decode table's index; 0: indexed by the complement's top 12 bits
+    uint32_t limit[32];                   // a window's complement <= limit[l] (and not 0): its code has more than l bits
+    // (symbol << 8) | length, kLenSlow: a code the table does not resolve; entry i belongs to binade kWideTabLow + i >> tab_bits
+    alignas(16) uint32_t tab[kWideTabMax];
 };
 
 // One layer of the flat vector as the kernels read it.
@@ -114,14 +116,10 @@ struct Layout {
 // wide average of the same size 941 instead of 909 us.
 static_assert(sizeof(SegDev) == 32 && sizeof(Layout) == 88, "read by every kernel");
 
-// A layer's entry.  kOneLoad: requested as a whole; left to itself the compiler requests its parts where they are used.
-// Which is better was measured kernel by kernel: as a whole in the decoders (three users of 11.3 M elements in eleven
-// layers in [1,5,6], k_decode_wide: 187 -> 183 us), in parts in the wide average (sixteen users of 25.6 M in [1,5,6],
-// k_aggregate_wide: 906 against 922 us).
-template <bool kOneLoad>
+// A layer's entry, requested as a whole; left to itself the compiler requests its parts where they are used (three users of
+// 11.3 M elements in eleven layers in [1,5,6], the former wide decoder: 187 -> 183 us).
 __device__ inline SegDev load_segment(const SegDev *p)
 {
-    if constexpr (!kOneLoad) return *p;
     typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
     const u64x4 e = *reinterpret_cast<const u64x4 *>(p);   // entries of 32 bytes from a 256-byte boundary on
     SegDev sd;
@@ -181,6 +179,7 @@ private:
 // Host Huffman builder (host_codebook.cpp): fills one table; returns a co3_status.
 int build_book_host(const uint64_t *weights, uint32_t A, int E, int M, BookDev *out);
 int build_wide_host(const uint64_t *weights, uint32_t A, BookWide *out);
+
 
 // Kernel launchers (one per .hip file).  All return a hipError_t from hipGetLastError().
 struct EncodeWs {

@@ -41,12 +41,12 @@ __host__ __device__ constexpr uint32_t group_bits(uint32_t A) { return 8u * (A >
 __host__ __device__ constexpr uint32_t window_rows(uint32_t A)
 {
     const uint32_t nbits = (uint32_t)(31 - __builtin_clz(A));
-    return nbits >= 6u ? 20u : (2u * nbits + 5u) & ~3u;
+    return nbits > 8u ? 24u : (nbits >= 6u ? 20u : (2u * nbits + 5u) & ~3u);
 }
 __host__ __device__ constexpr bool holds_group(uint32_t A) { return 32u * (window_rows(A) - 1u) - 31u >= group_bits(A); }
-static_assert(holds_group(8) && holds_group(16) && holds_group(32) && holds_group(64) && holds_group(128) && holds_group(256),
+static_assert(holds_group(8) && holds_group(16) && holds_group(32) && holds_group(64) && holds_group(128) && holds_group(256) && holds_group(4096),
               "wherever a window starts in its first word, it holds a group");
-constexpr uint32_t kMaxRows = 20;   // and 8 at least: formats have three bits or more
+constexpr int kRowsByte = 20, kRowsWide = 24;   // at most; 8 at least: formats have three bits or more
 __host__ __device__ constexpr uint32_t window_words(uint32_t A) { return window_rows(A) * 64u; }
 // In front of the windows lies at least this much (tables): a group of a damaged stream reads up to eight rows below its
 // window before it is found out.
@@ -99,6 +99,7 @@ __device__ inline T here(T x)
 // asks for.  kBytes 4 or 2 per entry.  The table lies at a multiple of its size.
 template <int kBytes>
 struct DecTable {
+    static constexpr int kMaxRows = kRowsByte;
     uint32_t base;    // LDS address
     uint32_t shift, mask;
     __device__ inline void init(uint32_t address, uint32_t A)
@@ -116,6 +117,53 @@ struct DecTable {
         const uint32_t a = ((__float_as_uint(f) >> shift) & mask) | base;
         if constexpr (kBytes == 4) return *(const lds_u32 *)a;
         else return *(const lds_u16 *)a;
+    }
+    // entry of a code of up to 31 bits that the table does not resolve: there is none
+    __device__ inline uint32_t search(uint32_t, const BookDev *) const { return kLenSlow; }
+};
+
+// The same for alphabets of 9 to 12 bits, entries of four bytes with the symbol.  The full table would take 32 binades of
+// up to 2048 entries, more than LDS has.  A code built from gradients needs fewer mantissa bits than the worst one (two to
+// four fewer: its symbols come in groups of like weight), so the builder chooses them (BookWide::tab_bits, at most nine),
+// and the binades below 2^12 are left out (one window in 2^20).  What the table does not resolve is found by a search of
+// the lengths' limits, as costly as the former decoder was for every symbol.  A code whose symbols are all about as likely
+// would need eleven bits; where a table by the first twelve bits of the window resolves more, it is that
+// (prefixes; sixteen users of 4 M elements in [1,2,9], symbols all alike: averaged 231 us by the search, 75 by that table).
+struct WideDecTable {
+    static constexpr int kMaxRows = kRowsWide;
+    uint32_t base, off, width;
+    uint32_t limits;          // LDS address of the lengths' limits, 32 words
+    bool prefixes;
+    __device__ inline void init(uint32_t address, uint32_t bits, uint32_t limits_address)
+    {
+        limits = limits_address;
+        prefixes = bits == 0;
+        if (prefixes) {
+            base = address;
+            off = 32u - kWidePrefixBits;
+            width = here(kWidePrefixBits);
+            return;
+        }
+        base = address - (kWideTabLow << bits) * 4u;
+        off = 23u - bits;
+        width = here(bits + 5u);   // (v_bfe_u32 takes one scalar operand)
+    }
+    template <bool kTrunc>
+    __device__ inline uint32_t operator()(uint32_t u) const
+    {
+        const float f = (float)(u > (2u << kWideTabLow) ? u : 2u << kWideTabLow);   // the lowest binade holds nothing
+        const uint32_t key = prefixes ? u : __float_as_uint(f);
+        return *(const lds_u32 *)(__builtin_amdgcn_ubfe(key, off, width) * 4u + base);
+    }
+    __device__ inline uint32_t search(uint32_t u, const BookWide *__restrict__ book) const
+    {
+        uint32_t l = 0;   // the largest l whose codes, and shorter ones, lie below the window
+#pragma unroll
+        for (uint32_t k = 16; k; k >>= 1) l = u <= lds_word(limits + 4u * (l + k)) ? l + k : l;
+        const uint32_t L = l + 1u;
+        if (L > 31u) return kLenSlow;
+        const uint32_t r = book->offset[L] + ((~u >> (32u - L)) - (uint32_t)book->first[L]);
+        return ((uint32_t)book->sorted[r & (kWideMaxA - 1)] << 8) | L;
     }
 };
 
@@ -159,7 +207,7 @@ __device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
     }
     ChunkGeom g;
     g.seg = lo;
-    const SegDev sd = load_segment<true>(lay.segs + lo);
+    const SegDev sd = load_segment(lay.segs + lo);
     g.e0 = sd.offset + (c - sd.chunk_start) * kChunk;
     const uint64_t left = sd.offset + sd.length - g.e0;
     g.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
@@ -216,9 +264,10 @@ struct Stream {
 
 // Loads every lane's window from the word with its position on, 16 bytes a lane at a time (the lanes' pieces overlap or
 // follow each other: the first request of a line serves the others from the cache), nothing beyond the chunk.
+template <int kMaxRows>
 __device__ inline void load_window(Stream &st, const ChunkIndex &ix, uint32_t bit)
 {
-    constexpr int n = (int)kMaxRows / 4;
+    constexpr int n = kMaxRows / 4;
     st.first = bit >> 5;
     st.N = st.top() - (bit & 31u);
     const __amdgpu_buffer_rsrc_t r = bounded(ix.w, 4u * ix.nw);
@@ -237,7 +286,7 @@ __device__ inline void load_window(Stream &st, const ChunkIndex &ix, uint32_t bi
 #pragma unroll
     for (int k = 0; k < n; ++k)
         if (k < 2 || (uint32_t)k < pieces) {
-            const uint32_t at_row = k < 4 ? low + (uint32_t)(12 - 4 * k) * kRowBytes : low - 4u * kRowBytes;
+            const uint32_t at_row = k < 4 ? low + (uint32_t)(12 - 4 * k) * kRowBytes : low - (uint32_t)(4 * k - 12) * kRowBytes;
 #pragma unroll
             for (int i = 0; i < 4; ++i) *(lds_u32 *)(at_row + (uint32_t)i * kRowBytes) = ~v[k][3 - i];
         }
@@ -246,12 +295,13 @@ __device__ inline void load_window(Stream &st, const ChunkIndex &ix, uint32_t bi
 
 // Where some lane's sub-chunk does not fit its window: the windows are loaded anew unless every lane has the `bits` bits
 // that a group reads at most, or all there is.
+template <int kMaxRows>
 __device__ inline void refill(Stream &st, const ChunkIndex &ix, uint32_t bits)
 {
     const bool low = st.N < 32u * st.row0 + bits && 32u * (st.first + st.rows) < st.end;
     if (!__any(low)) return;
     wave_lds_fence();
-    load_window(st, ix, st.bit());
+    load_window<kMaxRows>(st, ix, st.bit());
 }
 
 // Symbols j0 .. j0 + 7, of which those from cnt on give the entry 0 and take no bits (full: cnt is kSub in every lane).
@@ -289,9 +339,9 @@ __device__ inline uint32_t fast_group(Stream &st, uint32_t (&e)[kGroup], uint32_
 
 // The exact decoder, for the lanes `redo` of a group that started at n0: one window per symbol; a code the table does
 // not hold is searched by all lanes together, lane l comparing the window with the codes of l + 1 bits.
-template <bool kTrunc, class Table, class Value>
+template <bool kTrunc, class Table, class Book, class Value>
 __device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0, bool redo, int j0, const Table &tab,
-                                  const BookDev *__restrict__ book, Value value)
+                                  const Book *__restrict__ book, Value value)
 {
     const uint32_t lane = here(threadIdx.x & 63);
     st.N = redo ? n0 : st.N;
@@ -302,6 +352,7 @@ __device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0
         const uint32_t n = st.N > least ? st.N : least;
         const uint32_t u0 = st.window(n), u1 = st.window(n - 32u);
         uint32_t x = tab.template operator()<kTrunc>(u0);
+        if (on && (x & 0xffu) == kLenSlow) x = tab.search(u0, book);
         uint64_t todo = __ballot(on && (x & 0xffu) == kLenSlow);
         while (todo) {
             const int src = __ffsll((unsigned long long)todo) - 1;
@@ -313,7 +364,7 @@ __device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0
             uint32_t y = 1u;   // nothing matches: one bit is passed over, as symbol 0
             if (hits) {
                 const uint32_t L = (uint32_t)__ffsll((unsigned long long)hits);
-                y = value(book->sorted[(book->offset[L] + (uint32_t)(win >> (64u - L)) - (uint32_t)book->first[L]) & (kMaxA - 1)]) | L;
+                y = value(book->sorted[(book->offset[L] + (uint32_t)(win >> (64u - L)) - (uint32_t)book->first[L]) & ((uint32_t)(sizeof(book->sorted) / sizeof(book->sorted[0])) - 1u)]) | L;
             }
             if ((int)lane == src) {
                 x = y;
@@ -331,6 +382,7 @@ __device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0
 }
 
 // Where a wavefront decodes chunk (g, ix): `window` is the LDS address of its `rows` rows.
+template <int kMaxRows>
 __device__ inline void start_chunk(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t window, uint32_t rows)
 {
     const uint32_t lane = threadIdx.x & 63;
@@ -341,7 +393,7 @@ __device__ inline void start_chunk(Stream &st, const ChunkGeom &g, const ChunkIn
     const int left = (int)g.n - (int)lane * kSub;
     st.cnt = (int)here((uint32_t)(left < 0 ? 0 : (left > kSub ? kSub : left)));
     st.bad = false;
-    load_window(st, ix, st.end - ix.sb);
+    load_window<kMaxRows>(st, ix, st.end - ix.sb);
 }
 __device__ inline void finish_chunk(const Stream &st, const ChunkIndex &ix, uint64_t *__restrict__ status)
 {
@@ -352,14 +404,14 @@ __device__ inline void finish_chunk(const Stream &st, const ChunkIndex &ix, uint
 
 // on_group(gr, e) gets the entries of symbols 8 gr .. 8 gr + 7 of every lane, gr = 0 .. 7.  kUnroll: gr is a constant
 // there (sums in registers), at eight times the code, which a launch of few workgroups waits for.
-template <bool kTrunc, bool kUnroll, class Table, class Value, class OnGroup>
+template <bool kTrunc, bool kUnroll, class Table, class Book, class Value, class OnGroup>
 __device__ inline void decode_started(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t A, const Table &tab,
-                                      const BookDev *__restrict__ book, Value value, OnGroup on_group)
+                                      const Book *__restrict__ book, Value value, OnGroup on_group)
 {
     const bool part = __any(32u * (st.first + st.rows) < st.end), full = g.n == (uint32_t)kChunk;
     auto group = [&](int gr) {
         uint32_t e[kGroup], n0;
-        if (__builtin_expect(part, 0)) refill(st, ix, group_bits(A));
+        if (__builtin_expect(part, 0)) refill<Table::kMaxRows>(st, ix, group_bits(A));
         const uint32_t over = fast_group<kTrunc>(st, e, n0, gr * kGroup, tab, full);
         const bool redo = (over & 0xe0u) != 0u;
         if (__builtin_expect(__any(redo), 0)) slow_group<kTrunc>(st, e, n0, redo, gr * kGroup, tab, book, value);
@@ -371,6 +423,69 @@ __device__ inline void decode_started(Stream &st, const ChunkGeom &g, const Chun
     } else {
 #pragma unroll 1
         for (int gr = 0; gr < kGroups; ++gr) group(gr);
+    }
+}
+
+// ---- what becomes of the symbols ----
+
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+
+// A symbol's value at exponent bias 127: its bits at their places in an fp32 pattern, so that the format's subnormals
+// come out as fp32 ones, at their value.  Times 2^(127 - bias) it is the user's, exactly.
+struct SymbolValue {
+    uint32_t pattern, up, down;
+    __device__ inline SymbolValue(int E, int M)
+    {
+        const uint32_t sign_shift = (uint32_t)(E + M);
+        pattern = 0x80000000u | (((1u << sign_shift) - 1u) << (23 - M));
+        up = 31u - sign_shift;
+        down = 8u - (uint32_t)E;
+    }
+    // the symbol that lies `bit` bits up in a word (0, 8, 16, 24; of more than 8 bits: 0, 16)
+    __device__ inline float operator()(uint32_t word, uint32_t bit) const
+    {
+        return __uint_as_float((uint32_t)((int32_t)(word << (up - bit)) >> down) & pattern);
+    }
+};
+
+template <class Book>
+struct AggArgsT {
+    const uint32_t *words;
+    uint64_t words_stride;
+    const uint64_t *chunk_offset;
+    const uint16_t *sub_bits;
+    const Book *books;
+    float *out;
+    float *model;
+    double eta;
+    uint64_t *status;
+};
+
+// Four averages from sums, and with `model` the PS update w - eta * average (eq. (aggregate hat), Algorithm 1 line 14):
+// products and difference in fp64, one rounding.  e: first of the four elements within the chunk; whole: so is the chunk.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));   // layers start anywhere: 16 bytes at any element
+typedef u32x4 u32x4_u16 __attribute__((aligned(2)));
+typedef u32x4 u32x4_u8 __attribute__((aligned(1)));
+template <class Args>
+__device__ inline void write_four(const ChunkGeom &g, const Args &a, uint32_t e, const double (&avg)[4], bool whole)
+{
+    if (whole) {
+        if (a.out)
+            *reinterpret_cast<f32x4_any *>(a.out + g.e0 + e) = f32x4{(float)avg[0], (float)avg[1], (float)avg[2], (float)avg[3]};
+        if (a.model) {
+            f32x4 w = *reinterpret_cast<const f32x4_any *>(a.model + g.e0 + e);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) w[b] = (float)((double)w[b] - a.eta * avg[b]);
+            *reinterpret_cast<f32x4_any *>(a.model + g.e0 + e) = w;
+        }
+    } else {
+#pragma unroll
+        for (uint32_t b = 0; b < 4; ++b) {
+            if (e + b >= g.n) continue;
+            if (a.out) a.out[g.e0 + e + b] = (float)avg[b];
+            if (a.model) a.model[g.e0 + e + b] = (float)((double)a.model[g.e0 + e + b] - a.eta * avg[b]);
+        }
     }
 }
 

@@ -119,6 +119,44 @@ static int huffman_lengths_host(const uint64_t *w, uint32_t A, uint8_t *len)
     return CO3_OK;
 }
 
+// The decode table of `b` from its lengths, codes and order.
+static void finish_wide_table(BookWide *b, uint32_t A)
+{
+    // mantissa bits: what the codes with up to ten leading ones need
+    uint32_t nm = 2;
+    for (uint32_t s = 0; s < A; ++s) {
+        const uint32_t L = b->len[s];
+        if (!L) continue;
+        uint32_t k = 0;
+        while (k < L && ((b->code[s] >> (L - 1 - k)) & 1u)) ++k;
+        if (k <= 10 && k < L && L - k - 1 > nm) nm = L - k - 1;
+    }
+    if (nm > wide_tab_bits_max(A)) nm = wide_tab_bits_max(A);
+    uint64_t end[33];   // codes of up to l bits lie below end[l], left-aligned in 32 bits
+    end[0] = 0;
+    for (int l = 1; l <= 32; ++l) end[l] = (b->first[l] + b->count[l]) << (32 - l);
+    for (int l = 0; l < 32; ++l) b->limit[l] = end[l] >> 32 ? 0u : 0xffffffffu - (uint32_t)end[l];
+    uint64_t missing = 0;   // share of the code space the table leaves to the search, in 2^-32
+    auto entry = [&](uint32_t x, uint32_t longest) {   // window, longest code that covers the entry
+        uint32_t L = 1;
+        while (L < 32 && (uint64_t)x >= end[L]) ++L;
+        if (L > 31 || L > longest) return kLenSlow;
+        return ((uint32_t)b->sorted[b->offset[L] + ((x >> (32 - L)) - (uint32_t)b->first[L])] << 8) | L;
+    };
+    b->tab_bits = nm;
+    std::fill(b->tab, b->tab + kWideTabMax, kLenSlow);
+    for (uint32_t i = 1u << nm; i < wide_tab_entries(nm); ++i) {
+        const uint32_t ex = kWideTabLow + (i >> nm) + 1;   // exponent of the window's complement
+        b->tab[i] = entry(~(uint32_t)((uint64_t)((1u << nm) | (i & ((1u << nm) - 1u))) << (ex - nm)), 32 - ex + nm);
+        if (b->tab[i] == kLenSlow) missing += 1ull << (ex - nm);
+    }
+    if (missing > (1ull << 32) - end[kWidePrefixBits]) {
+        b->tab_bits = 0;
+        std::fill(b->tab, b->tab + kWideTabMax, kLenSlow);
+        for (uint32_t i = 0; i < wide_tab_entries(0); ++i) b->tab[i] = entry(~(i << (32 - kWidePrefixBits)), kWidePrefixBits);
+    }
+}
+
 int build_wide_host(const uint64_t *w, uint32_t A, BookWide *b)
 {
     std::memset(b, 0, sizeof(*b));
@@ -146,26 +184,8 @@ int build_wide_host(const uint64_t *w, uint32_t A, BookWide *b)
         const uint32_t rank = next[L]++;
         b->code[s] = b->first[L] + rank;
         b->sorted[b->offset[L] + rank] = (uint16_t)s;
-        if (L <= kWideDecBits) {
-            const uint32_t lo = (uint32_t)b->code[s] << (kWideDecBits - L);
-            for (uint32_t i = 0; i < (1u << (kWideDecBits - L)); ++i) b->dec[lo + i] = (uint16_t)((L << 12) | s);
-        }
     }
-    // second-level tables under the first prefixes that hold only longer codes
-    b->long_prefix0 = 1u << kWideDecBits;
-    for (int L = kWideDecBits + 1; L <= 64; ++L)
-        if (b->count[L]) { b->long_prefix0 = (uint32_t)(b->first[L] >> (L - kWideDecBits)); break; }
-    for (uint32_t s = 0; s < A; ++s) {
-        const int L = b->len[s];
-        if (L <= kWideDecBits || L > kWideDecBits + kWideDec2Bits) continue;
-        const uint32_t span = kWideDecBits + kWideDec2Bits;
-        const uint32_t lo = (uint32_t)b->code[s] << (span - L);   // the code followed by zeros, span bits
-        const uint32_t tab = (lo >> kWideDec2Bits) - b->long_prefix0;
-        if (tab >= (uint32_t)kWideDec2Tables) continue;
-        for (uint32_t i = 0; i < (1u << (span - L)); ++i)
-            b->dec2[(tab << kWideDec2Bits) | ((lo + i) & ((1u << kWideDec2Bits) - 1u))] =
-                (uint16_t)(((L - kWideDecBits) << 12) | s);
-    }
+    finish_wide_table(b, A);
     return CO3_OK;
 }
 

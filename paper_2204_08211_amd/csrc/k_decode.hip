@@ -10,7 +10,7 @@
 
 namespace co3 {
 
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));   // a sub-chunk's symbols, four to a word
+typedef AggArgsT<BookDev> AggArgs;
 
 // Symbols 8 gr .. 8 gr + 7 of a sub-chunk: byte 1 of their entries.
 __device__ inline void pack_group(u32x16 &packed, int gr, const uint32_t (&e)[kGroup])
@@ -21,25 +21,9 @@ __device__ inline void pack_group(u32x16 &packed, int gr, const uint32_t (&e)[kG
                              __builtin_amdgcn_perm(e[4 * h + 3], e[4 * h + 2], 0x05010c0cu);
 }
 
-// A symbol's value at exponent bias 127: its bits at their places in an fp32 pattern, so that the format's subnormals
-// come out as fp32 ones, at their value.  Times 2^(127 - bias) it is the user's, exactly.
-struct SymbolValue {
-    uint32_t pattern, up, down;
-    __device__ inline SymbolValue(int E, int M)
-    {
-        const uint32_t sign_shift = (uint32_t)(E + M);
-        pattern = 0x80000000u | (((1u << sign_shift) - 1u) << (23 - M));
-        up = 31u - sign_shift;
-        down = 8u - (uint32_t)E;
-    }
-    __device__ inline float operator()(uint32_t word, uint32_t byte) const
-    {
-        return __uint_as_float((uint32_t)((int32_t)(word << (up - 8u * byte)) >> down) & pattern);
-    }
-};
-
 // co3_decode: a workgroup takes kDecWaves consecutive chunks of one user, a wavefront per chunk, so that one copy of the
 // table serves them; where the code table changes among them (layers) the workgroup takes one stretch after the other.
+// by_chunk: the users' chunks 0, then their chunks 1, ...
 constexpr int kDecWaves = 8;
 constexpr int kStageStride = 20;   // words per staged sub-chunk row (16, and 4 that keep 16-byte accesses apart)
 // Words of a wavefront's window where something is staged in it afterwards: a chunk's symbols, pieces of its sums.
@@ -52,7 +36,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
                                                            const uint16_t *__restrict__ sub_bits,
                                                            const BookDev *__restrict__ books, uint8_t *__restrict__ sym,
                                                            uint64_t sym_stride, float *__restrict__ q, uint64_t q_stride,
-                                                           uint64_t *__restrict__ status)
+                                                           uint64_t *__restrict__ status, uint32_t by_chunk)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const uint32_t tab_words = dec_table_entries(lay.A) / 2;
@@ -62,9 +46,15 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
     int32_t *s_book = reinterpret_cast<int32_t *>(s_win + kDecWaves * win_words);   // [kDecWaves], part of the row behind
     const uint32_t t = threadIdx.x, lane = t & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
-    const uint64_t c = (uint64_t)blockIdx.x * kDecWaves + wave;
-    const uint32_t u = blockIdx.y;
+    uint64_t c = (uint64_t)blockIdx.x * kDecWaves + wave;
+    uint32_t u = blockIdx.y;
+    if (by_chunk) {
+        const uint64_t item = c;
+        c = item / lay.U;
+        u = (uint32_t)(item - c * lay.U);
+    }
     const bool active = c < lay.nchunks;
+    const bool several = lay.books_per_user > 1;
     const ChunkGeom g = chunk_geom(lay, active ? c : lay.nchunks - 1);
     const ChunkIndex ix = read_index(lay, active ? c : lay.nchunks - 1, u, words, words_stride, chunk_offset, sub_bits);
     uint32_t *win = s_win + wave * win_words;
@@ -74,7 +64,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
     tab.init(lds_address(s_tab), lay.A);
     round_toward_zero();
     bool todo = true;
-    if (lay.books_per_user > 1) {
+    if (several) {
         if (lane == 0) s_book[wave] = g.book;
         __syncthreads();
     }
@@ -82,7 +72,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
     do {
         int32_t b = g.book;
         uint32_t w1 = kDecWaves;
-        if (lay.books_per_user > 1) {
+        if (several) {
             b = __builtin_amdgcn_readfirstlane(s_book[w0]);
             for (w1 = w0 + 1; w1 < kDecWaves && __builtin_amdgcn_readfirstlane(s_book[w1]) == b;) ++w1;
             if (w0) __syncthreads();   // the stretch before is decoded
@@ -93,7 +83,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
         if (active && todo && wave >= w0 && wave < w1) {
             todo = false;
             Stream st;
-            start_chunk(st, g, ix, lds_address(win), window_rows(lay.A));
+            start_chunk<kRowsByte>(st, g, ix, lds_address(win), window_rows(lay.A));
             decode_started<false, false>(st, g, ix, lay.A, tab, book, [](uint32_t s) { return s << 8; },
                                   [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(packed, gr, e); });
             finish_chunk(st, ix, status);
@@ -113,17 +103,11 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
     const bool full = g.n == (uint32_t)kChunk;
     if (sym) {
         uint8_t *dst = sym + (uint64_t)u * sym_stride + g.e0;
-        if (full && (reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
+        if (full) {   // layers start anywhere
 #pragma unroll
             for (int k = 0; k < kChunk / 1024; ++k)
-                *reinterpret_cast<u32x4 *>(dst + 1024 * k + 16 * lane) =
+                *reinterpret_cast<u32x4_u8 *>(dst + 1024 * k + 16 * lane) =
                     *reinterpret_cast<const u32x4 *>(s_stage + (16 * k + (lane >> 2)) * kStageStride + 4 * (lane & 3u));
-        } else if ((reinterpret_cast<uintptr_t>(dst) & 3u) == 0) {
-            for (uint32_t e = 4 * lane; e < g.n; e += 256) {
-                const uint32_t wv = s_stage[(e >> 6) * kStageStride + ((e & 63u) >> 2)];
-                if (e + 3 < g.n) *reinterpret_cast<uint32_t *>(dst + e) = wv;
-                else for (uint32_t b = 0; e + b < g.n; ++b) dst[e + b] = (uint8_t)(wv >> (8 * b));
-            }
         } else {
             for (uint32_t e = lane; e < g.n; e += 64)
                 dst[e] = stage_b[(e >> 6) * (kStageStride * 4) + (e & 63u)];
@@ -135,57 +119,18 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
         const int up = 127 - (int)uniform((uint32_t)lay.bias[pair]);
         const float inv_gain = lay.gain[2 * pair + 1];   // 1 unless the plan carries a scale
         float *dst = q + (uint64_t)u * q_stride + g.e0;
-        if (full && (reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
+        if (full) {
 #pragma unroll 4
             for (uint32_t e = 4 * lane; e < (uint32_t)kChunk; e += 256) {
                 const uint32_t w = s_stage[(e >> 6) * kStageStride + ((e & 63u) >> 2)];
-                float4 v;
-                v.x = __fmul_rn(ldexpf(val(w, 0), up), inv_gain);
-                v.y = __fmul_rn(ldexpf(val(w, 1), up), inv_gain);
-                v.z = __fmul_rn(ldexpf(val(w, 2), up), inv_gain);
-                v.w = __fmul_rn(ldexpf(val(w, 3), up), inv_gain);
-                *reinterpret_cast<float4 *>(dst + e) = v;
+                f32x4 v;
+#pragma unroll
+                for (uint32_t b = 0; b < 4; ++b) v[b] = __fmul_rn(ldexpf(val(w, 8u * b), up), inv_gain);
+                *reinterpret_cast<f32x4_any *>(dst + e) = v;
             }
         } else {
             for (uint32_t e = lane; e < g.n; e += 64)
                 dst[e] = __fmul_rn(ldexpf(val(stage_b[(e >> 6) * (kStageStride * 4) + (e & 63u)], 0), up), inv_gain);
-        }
-    }
-}
-
-struct AggArgs {
-    const uint32_t *words;
-    uint64_t words_stride;
-    const uint64_t *chunk_offset;
-    const uint16_t *sub_bits;
-    const BookDev *books;
-    float *out;
-    float *model;
-    double eta;
-    uint64_t *status;
-};
-
-// Four averages from sums, and with `model` the PS update w - eta * average (eq. (aggregate hat), Algorithm 1 line 14):
-// products and difference in fp64, one rounding.  e: first of the four elements within the chunk; whole: so is the chunk.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef f32x4 f32x4_any __attribute__((aligned(4)));   // layers start anywhere: 16 bytes at any element
-__device__ inline void write_four(const ChunkGeom &g, const AggArgs &a, uint32_t e, const double (&avg)[4], bool whole)
-{
-    if (whole) {
-        if (a.out)
-            *reinterpret_cast<f32x4_any *>(a.out + g.e0 + e) = f32x4{(float)avg[0], (float)avg[1], (float)avg[2], (float)avg[3]};
-        if (a.model) {
-            f32x4 w = *reinterpret_cast<const f32x4_any *>(a.model + g.e0 + e);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) w[b] = (float)((double)w[b] - a.eta * avg[b]);
-            *reinterpret_cast<f32x4_any *>(a.model + g.e0 + e) = w;
-        }
-    } else {
-#pragma unroll
-        for (uint32_t b = 0; b < 4; ++b) {
-            if (e + b >= g.n) continue;
-            if (a.out) a.out[g.e0 + e + b] = (float)avg[b];
-            if (a.model) a.model[g.e0 + e + b] = (float)((double)a.model[g.e0 + e + b] - a.eta * avg[b]);
         }
     }
 }
@@ -275,7 +220,7 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
     };
     auto decode = [&](uint32_t i, uint32_t u, const ChunkIndex &ix, uint32_t *win, const DecTable<kBytes> &tab, const BookDev *book) {
         Stream st;
-        start_chunk(st, p.g, ix, lds_address(win), window_rows(lay.A));
+        start_chunk<kRowsByte>(st, p.g, ix, lds_address(win), window_rows(lay.A));
         on_user(i, u, ix, st, tab, book);
         finish_chunk(st, ix, p.a.status);
     };
@@ -472,7 +417,7 @@ __device__ inline void aggregate_spread(const AggPart &p)
 #pragma unroll
                 for (int i = 0; i < kSub / 2; ++i) {
                     const uint32_t w = half ? packed[(kSub / 2 + i) >> 2] : packed[i >> 2];
-                    sum[i] = here(__builtin_fma((double)val(w, (uint32_t)(i & 3)), scale, sum[i]));
+                    sum[i] = here(__builtin_fma((double)val(w, 8u * (uint32_t)(i & 3)), scale, sum[i]));
                 }
             });
         round_to_nearest();
@@ -514,7 +459,7 @@ __device__ inline void aggregate_packed(const AggPart &p)
             double sum = 0.0;
 #pragma unroll
             for (int s = 0; s < kUsers; ++s) {
-                const double v = (double)val(pk[s][j >> 2], (uint32_t)(j & 3));
+                const double v = (double)val(pk[s][j >> 2], 8u * (uint32_t)(j & 3));
                 if constexpr (kGain) sum += (double)__fmul_rn((float)(v * scale[s]), inv_gain[s]);   // fl32(value * inv_gain)
                 else sum = __builtin_fma(v, scale[s], sum);   // the product is exact
             }
@@ -595,9 +540,13 @@ hipError_t launch_decode(const Layout &lay, const co3_decode_args &a, const Book
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ProfScope prof(K_DECODE, s);
-    hipLaunchKernelGGL(k_decode, dim3((uint32_t)((lay.nchunks + kDecWaves - 1) / kDecWaves), lay.U), dim3(64 * kDecWaves),
-                       lds, s, lay, a.words, a.words_stride, a.chunk_offset, a.sub_bits, books, a.symbols, sym_stride,
-                       a.q, a.q_stride, a.status);
+    // Where layers under tables of their own are short, the users' parts of a chunk go to one workgroup: it meets few tables,
+    // which it takes one after the other (24 users of 353 444 elements in twelve layers, [1,5,2]: by user 28, by chunk 14 us).
+    const bool by_chunk = lay.books_per_user > 1 && !lay.per_user_books;
+    const uint64_t chunks = by_chunk ? lay.nchunks * lay.U : lay.nchunks;
+    const dim3 grid((uint32_t)((chunks + kDecWaves - 1) / kDecWaves), by_chunk ? 1u : lay.U);
+    hipLaunchKernelGGL(k_decode, grid, dim3(64 * kDecWaves), lds, s, lay, a.words, a.words_stride, a.chunk_offset, a.sub_bits,
+                       books, a.symbols, sym_stride, a.q, a.q_stride, a.status, by_chunk ? 1u : 0u);
     return hipGetLastError();
 }
 

@@ -3,8 +3,7 @@
 // The steps are those of the byte path (Algorithm 1 lines 8-10 and 13-14; Sec. IV-A (i)-(iii), Sec. II-B (iv))
 // and the container is the same; symbols are 16-bit words and a code table has up to 4096 entries, too many
 // for the per-wavefront LDS tables the byte kernels are built around: here a workgroup shares one copy of the
-// table in use.  The coder's workgroups end where the table changes, the quantizer's go on with the next one, the
-// PS kernels' have a chunk each.  A fixed code without a symbol buffer ("single sweep" in the byte path) runs the
+// table in use.  The coder's workgroups end where the table changes, the quantizer's go on with the next one.  A fixed code without a symbol buffer ("single sweep" in the byte path) runs the
 // same three steps here with the symbols kept in the workspace.
 //
 //   k_quantize_wide      v = g + gamma m, Q_fp, m' = v - ghat, symbol; symbol counts in an LDS table per workgroup
@@ -15,10 +14,7 @@
 //   (k_scan_chunks of k_pack.hip gives the chunk offsets)
 //   k_pack_wide          wavefront per chunk, lane per sub-chunk with its 64 symbols in registers: lengths, wave
 //                        prefix sum, codewords ORed into an LDS window at their bit offsets, window copied out
-//   k_decode_wide        wavefront per (chunk, user), lane per sub-chunk: prefix table for codes of up to 12 bits,
-//                        second-level tables over the next 5 bits under the first 128 prefixes of longer codes,
-//                        the rest by their value among the per-length bounds of the canonical code
-//   k_aggregate_wide     the same decoder; values added to per-element fp64 sums in LDS, then averaged
+// (the PS side is in k_decode_wide.hip)
 #include "co3_internal.h"
 #include "quantize_math.h"
 
@@ -38,16 +34,6 @@ __device__ inline uint32_t w_find_segment(const SegDev *segs, uint32_t nseg, uin
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
         if (segs[mid].offset <= elem) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-__device__ inline uint32_t w_find_chunk_segment(const SegDev *segs, uint32_t nseg, uint64_t chunk)
-{
-    uint32_t lo = 0, hi = nseg;  // segs[nseg].chunk_start = nchunks > chunk
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (segs[mid].chunk_start <= chunk) lo = mid; else hi = mid;
     }
     return lo;
 }
@@ -74,26 +60,6 @@ __device__ inline uint32_t w_wave_inclusive_scan(uint32_t x, uint32_t lane)
         if ((int)lane >= o) x += y;
     }
     return x;
-}
-
-// Where chunk c lies: layer, first element, element count, code table within a user's set.
-struct WChunk {
-    uint32_t seg, n;
-    uint64_t e0;
-    uint32_t book;
-};
-
-template <bool kOneLoad>
-__device__ inline WChunk w_chunk(const Layout &lay, uint64_t c, uint32_t u)
-{
-    WChunk k;
-    k.seg = w_find_chunk_segment(lay.segs, lay.nseg, c);
-    const SegDev sd = load_segment<kOneLoad>(lay.segs + k.seg);
-    k.e0 = sd.offset + (c - sd.chunk_start) * kChunk;
-    const uint64_t left = sd.offset + sd.length - k.e0;
-    k.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
-    k.book = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
-    return k;
 }
 
 // ---- user side, step 1 ------------------------------------------------------------------------------------
@@ -321,8 +287,9 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
     __shared__ uint64_t first[65];
     __shared__ uint32_t wcnt[kWbWaves][65];   // symbols of each length in a wavefront's range; then running ranks
     __shared__ int err, s_n;
-    __shared__ uint32_t s_maxlen, long0;
-    __shared__ uint32_t end[kWideDecBits];
+    __shared__ uint32_t s_maxlen, s_bits;
+    __shared__ unsigned long long s_missing;
+    __shared__ uint64_t end32[33];   // codes of up to l bits lie below end32[l], left-aligned in 32 bits
 
     BookWide &B = books[blockIdx.x];
     const uint64_t *w = weights + (uint64_t)blockIdx.x * A;
@@ -331,7 +298,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
 
     if (t < 65) { cnt[t] = 0; off[t] = 0; first[t] = 0; }
     for (uint32_t i = t; i < (uint32_t)kWbWaves * 65u; i += kWbThreads) wcnt[i / 65u][i % 65u] = 0;
-    if (t == 0) { err = 0; s_maxlen = 0; s_n = 0; }
+    if (t == 0) { err = 0; s_maxlen = 0; s_n = 0; s_bits = 2; s_missing = 0; end32[0] = 0; }
     for (uint32_t i = t; i < 2 * A; i += kWbThreads) parent[i] = -1;
     __syncthreads();
     int active = 0;
@@ -491,15 +458,11 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
         }
         first[t + 1] = sum << 1;
         off[t + 1] = o;
-        // the direct table's prefixes below end[l - 1] have codes of up to l bits
-        if (t < (uint32_t)kWideDecBits) end[t] = ((uint32_t)(sum << 1) + cnt[t + 1]) << ((uint32_t)kWideDecBits - 1u - t);
-        // the first of its prefixes that holds only longer codes
-        const uint64_t used_long = __ballot(cnt[t + 1] != 0u) & (~0ull << kWideDecBits);
-        if (used_long ? t == (uint32_t)__ffsll((unsigned long long)used_long) - 1u : t == 0)
-            long0 = used_long ? (uint32_t)((sum << 1) >> (t + 1u - (uint32_t)kWideDecBits)) : 1u << kWideDecBits;
+        if (t < 32) end32[t + 1] = ((sum << 1) + cnt[t + 1]) << (31u - t);
     }
     __syncthreads();
-    // canonical order: rank among the symbols of the same length, ascending symbol
+    // canonical order: rank among the symbols of the same length, ascending symbol (and, in tmpid, for the table below)
+    uint32_t bits = 0;
     for (uint32_t sb = 0; sb < per_wave; sb += 64) {
         const uint32_t i = sb + lane;
         const uint32_t s_i = wave * per_wave + i;
@@ -508,8 +471,13 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
             const uint32_t base = wcnt[wave][L0];
             if (myL == L0) {
                 const uint32_t rank = base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-                B.code[s_i] = first[L0] + rank;
+                const uint64_t code = first[L0] + rank;
+                B.code[s_i] = code;
                 B.sorted[off[L0] + rank] = (uint16_t)s_i;
+                tmpid[off[L0] + rank] = (uint16_t)s_i;
+                // mantissa bits that a code with up to ten leading ones asks of the decode table
+                const uint32_t ones = (uint32_t)__clzll((long long)~(code << (64u - L0)));   // (a 64-bit code: code itself)
+                if (ones <= 10u && ones < L0 && L0 - ones - 1u > bits) bits = L0 - ones - 1u;
             }
             w_wave_sync_lds();   // every lane has read the base
             if (lane == 0) wcnt[wave][L0] = base + (uint32_t)__popcll(mask);
@@ -517,41 +485,41 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
         });
     }
     for (uint32_t i = (bad ? 0u : (uint32_t)nact) + t; i < A; i += kWbThreads) B.sorted[i] = 0;
+    if (bits > 2u) atomicMax(&s_bits, bits);
     if (t < 65) { B.first[t] = first[t]; B.count[t] = cnt[t]; B.offset[t] = off[t]; }
     if (t == 0) { B.maxlen = s_maxlen; B.nactive = bad ? 0u : (uint32_t)nact; }
     __syncthreads();
-    uint32_t ends[kWideDecBits];
+    // the decode table (decode_core.h): an entry's window by its low end, the length by a binary search of the ends (they
+    // grow with it), the symbol by its rank
+    const uint32_t nm = s_bits < wide_tab_bits_max(A) ? s_bits : wide_tab_bits_max(A);
+    if (t < 32) B.limit[t] = end32[t] >> 32 ? 0u : 0xffffffffu - (uint32_t)end32[t];
+    auto entry = [&](uint32_t x, uint32_t longest) {   // window, longest code that covers the entry
+        uint32_t l = 0;   // the largest l with x >= end32[l]: the code has l + 1 bits
 #pragma unroll
-    for (int l = 0; l < kWideDecBits; ++l) ends[l] = end[l];
-#pragma unroll
-    for (uint32_t idx = t; idx < (1u << kWideDecBits); idx += kWbThreads) {
-        uint32_t l = 1;   // canonical codes grow with their length, so the ends do
-#pragma unroll
-        for (int k = 0; k < kWideDecBits; ++k) l += idx >= ends[k];
-        uint32_t e = 0;
-        if (l <= (uint32_t)kWideDecBits)
-            e = (l << 12) | B.sorted[off[l] + ((idx >> ((uint32_t)kWideDecBits - l)) - (uint32_t)first[l])];
-        B.dec[idx] = (uint16_t)e;
+        for (uint32_t k = 16; k; k >>= 1) l = (uint64_t)x >= end32[l + k] ? l + k : l;
+        const uint32_t L = l + 1u;
+        uint32_t e = kLenSlow;
+        if (L < 32u && L <= longest)
+            e = ((uint32_t)tmpid[(off[L] + ((x >> (32u - L)) - (uint32_t)first[L])) & (A - 1u)] << 8) | L;
+        return e;
+    };
+    uint64_t missing = 0;   // share of the code space the table leaves to the search, in 2^-32
+#pragma unroll 2
+    for (uint32_t i = t; i < wide_tab_entries(nm); i += kWbThreads) {
+        const uint32_t ex = kWideTabLow + (i >> nm) + 1u;
+        const uint32_t e = i >> nm ? entry(~(uint32_t)((uint64_t)((1u << nm) | (i & ((1u << nm) - 1u))) << (ex - nm)), 32u - ex + nm) : kLenSlow;
+        if (e == kLenSlow && i >> nm) missing += 1ull << (ex - nm);
+        B.tab[i] = e;
     }
-    // second-level tables under the first prefixes that hold only longer codes
-    const uint32_t long_prefix0 = long0;
-    if (t == 0) B.long_prefix0 = long_prefix0;
-    for (uint32_t idx = t; idx < (uint32_t)(kWideDec2Tables << kWideDec2Bits); idx += kWbThreads) {
-        const uint32_t prefix = long_prefix0 + (idx >> kWideDec2Bits);
-        const uint32_t wide = (prefix << kWideDec2Bits) | (idx & ((1u << kWideDec2Bits) - 1u));   // 17 bits
-        uint32_t e = 0;
-        if (prefix < (1u << kWideDecBits)) {
-            for (int l = kWideDecBits + 1; l <= kWideDecBits + kWideDec2Bits; ++l) {
-                const uint32_t c = wide >> (kWideDecBits + kWideDec2Bits - l);
-                const uint32_t f = (uint32_t)first[l];   // first[l] <= 2^l: in 32 bits
-                if (cnt[l] && c >= f && c - f < cnt[l]) {
-                    e = ((uint32_t)(l - kWideDecBits) << 12) | B.sorted[off[l] + (c - f)];
-                    break;
-                }
-            }
-        }
-        B.dec2[idx] = (uint16_t)e;
+    bool prefixes = false;
+    if (nm == wide_tab_bits_max(A)) {   // (with fewer bits it leaves next to nothing)
+        if (missing) atomicAdd(&s_missing, (unsigned long long)missing);
+        __syncthreads();
+        prefixes = s_missing > (1ull << 32) - end32[kWidePrefixBits];
+        if (prefixes)
+            for (uint32_t i = t; i < wide_tab_entries(0); i += kWbThreads) B.tab[i] = entry(~(i << (32u - kWidePrefixBits)), kWidePrefixBits);
     }
+    if (t == 0) B.tab_bits = prefixes ? 0u : nm;
 }
 
 // ---- user side, steps 2 and 3 -------------------------------------------------------------------------------
@@ -984,340 +952,6 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
     }
 }
 
-// ---- PS side ----------------------------------------------------------------------------------------------
-
-// What the decoder keeps in LDS of one table; the symbols in canonical order, which only the search for a code
-// that neither table holds needs, stay in device memory.  The second-level tables come last: a wavefront that
-// keeps a table of its own (a set of tables per user) leaves them out - kWTabsShort bytes per table, so that
-// twice as many wavefronts fit a CU - and finds every code of more than kWideDecBits bits by value.
-struct WideTabs {
-    uint16_t dec[1 << kWideDecBits];
-    uint64_t first[65];
-    uint64_t upper[65];    // (first[L] + count[L]) left-aligned in 64 bits: every code of L or fewer bits lies below
-    uint32_t count[65];
-    uint32_t offset[65];
-    uint32_t maxlen;
-    uint32_t long_prefix0;
-    uint16_t dec2[kWideDec2Tables << kWideDec2Bits];
-};
-constexpr size_t kWTabsShort = offsetof(WideTabs, dec2);
-static_assert(kWTabsShort % 8 == 0 && sizeof(WideTabs) % 8 == 0, "tables follow each other in LDS");
-
-template <bool kDec2>
-__device__ inline void w_load_tabs(WideTabs *T, const BookWide &book, uint32_t t, uint32_t nthreads)
-{
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(book.dec);   // two entries per word
-    uint32_t *dst = reinterpret_cast<uint32_t *>(T->dec);
-#pragma unroll 8
-    for (uint32_t i = t; i < (1u << kWideDecBits) / 2; i += nthreads) dst[i] = src[i];
-    if constexpr (kDec2) {
-        src = reinterpret_cast<const uint32_t *>(book.dec2);
-        dst = reinterpret_cast<uint32_t *>(T->dec2);
-#pragma unroll 8
-        for (uint32_t i = t; i < (uint32_t)(kWideDec2Tables << kWideDec2Bits) / 2; i += nthreads) dst[i] = src[i];
-    }
-#pragma unroll 1
-    for (uint32_t i = t; i < 65u; i += nthreads) {
-        const uint64_t f = book.first[i];
-        const uint32_t c = book.count[i];
-        T->first[i] = f;
-        T->count[i] = c;
-        T->offset[i] = book.offset[i];
-        uint64_t up = ~0ull;   // lengths 0 and 64, and sums that leave L bits, bound nothing
-        if (i >= 1u && i < 64u && ((f + c) >> i) == 0) up = (f + c) << (64u - i);
-        T->upper[i] = up;
-    }
-    if (t == 0) { T->maxlen = book.maxlen > 64u ? 64u : book.maxlen; T->long_prefix0 = book.long_prefix0; }
-}
-
-// A chunk's payload words in global memory; reads nothing outside w[0 .. nw).
-struct WGlobalWords {
-    const uint32_t *w;
-    uint32_t nw;
-    __device__ inline uint32_t word(uint32_t i) const { return i < nw ? w[i] : 0u; }
-};
-
-// The three words of a chunk's payload at the read position, and the one after them, which is requested when the
-// position enters a new word and first used when it enters the next one: the load has the symbols in between
-// to complete.
-template <class Src>
-struct WReader {
-    Src src;
-    uint32_t i0, w0, w1, w2, w3;
-    __device__ inline void seek(uint32_t pos)
-    {
-        i0 = pos >> 5;
-        w0 = src.word(i0);
-        w1 = src.word(i0 + 1u);
-        w2 = src.word(i0 + 2u);
-        w3 = src.word(i0 + 3u);
-    }
-    // the 32 bits from bit `pos` on; pos never decreases between calls
-    __device__ inline uint32_t window32(uint32_t pos)
-    {
-        const uint32_t i = pos >> 5, s0 = pos & 31u;
-        if (i == i0 + 1u) { w0 = w1; w1 = w2; w2 = w3; w3 = src.word(i + 3u); i0 = i; }
-        else if (i != i0) seek(pos);
-        return s0 ? __builtin_amdgcn_alignbit(w0, w1, 32u - s0) : w0;   // ({w0, w1} >> (32 - s0)), low word
-    }
-    // the 32 bits after those, for the same pos
-    __device__ inline uint32_t next32(uint32_t pos) const
-    {
-        const uint32_t s0 = pos & 31u;
-        return s0 ? __builtin_amdgcn_alignbit(w1, w2, 32u - s0) : w1;
-    }
-};
-
-constexpr int kWUpRegs = 12;   // lengths kWideDecBits + 1 .. kWideDecBits + 12 have their bound in a register
-
-// The bounds of lengths kWideDecBits + 1 .. kWideDecBits + kWUpRegs, top 32 bits (exact: a bound of length
-// l <= 32 has no lower bits); lengths from maxlen on bound nothing.
-struct WUpper32 {
-    uint32_t up[kWUpRegs];
-    __device__ inline void load(const WideTabs *T)
-    {
-#pragma unroll
-        for (int t = 0; t < kWUpRegs; ++t) {
-            const uint32_t l = kWideDecBits + 1 + t;
-            up[t] = l < T->maxlen ? (uint32_t)(T->upper[l] >> 32) : 0xffffffffu;
-        }
-    }
-};
-
-template <bool kDec2, class Src>
-__device__ inline uint32_t w_decode_one(WReader<Src> &r, uint32_t pos, const WideTabs *T, const uint16_t *__restrict__ sorted,
-                                        const WUpper32 &U32, uint32_t &len)
-{
-    const uint32_t hi = r.window32(pos);
-    const uint32_t prefix = hi >> (32 - kWideDecBits);
-    const uint32_t e = T->dec[prefix];
-    if (e) { len = e >> 12; return e & 0xfffu; }
-    if constexpr (kDec2) {
-        const uint32_t tab = prefix - T->long_prefix0;   // wraps below it: no table
-        if (tab < (uint32_t)kWideDec2Tables) {
-            const uint32_t e2 = T->dec2[(tab << kWideDec2Bits) | ((hi >> (32 - kWideDecBits - kWideDec2Bits)) & ((1u << kWideDec2Bits) - 1u))];
-            if (e2) { len = kWideDecBits + (e2 >> 12); return e2 & 0xfffu; }
-        }
-    }
-    const uint32_t maxlen = T->maxlen;   // <= 64
-    len = 0;
-    if (maxlen <= (uint32_t)kWideDecBits) return 0u;   // every code is in the prefix table
-    // the bounds in two halves: few codes reach the second
-    uint32_t L = kWideDecBits + 1;
-#pragma unroll
-    for (int t = 0; t < kWUpRegs / 2; ++t) L += hi >= U32.up[t] ? 1u : 0u;
-    if (L == kWideDecBits + 1 + kWUpRegs / 2) {
-#pragma unroll
-        for (int t = kWUpRegs / 2; t < kWUpRegs; ++t) L += hi >= U32.up[t] ? 1u : 0u;
-    }
-    uint64_t full = 0;
-    if (L == kWideDecBits + 1 + kWUpRegs) {   // longer than the registers cover
-        full = ((uint64_t)hi << 32) | r.next32(pos);
-        for (uint32_t l = L; l < maxlen; ++l) L += full >= T->upper[l] ? 1u : 0u;
-    }
-    L = min(L, maxlen);   // a window of ones passes the bounds that bound nothing, too
-    uint32_t rank;
-    if (L <= 32u) {       // first[L] < 2^L: its low word is all of it
-        const uint32_t cde = hi >> (32u - L);
-        const uint32_t f = (uint32_t)T->first[L];
-        if (cde < f) return 0u;
-        rank = cde - f;
-    } else {
-        if (!full) full = ((uint64_t)hi << 32) | r.next32(pos);
-        const uint64_t cde = full >> (64u - L);
-        const uint64_t f = T->first[L];
-        if (cde < f || cde - f >= (uint64_t)kWideMaxA) return 0u;
-        rank = (uint32_t)(cde - f);
-    }
-    if (rank >= T->count[L]) return 0u;
-    len = L;
-    return sorted[(T->offset[L] + rank) & (kWideMaxA - 1)];
-}
-
-// Index entries of chunk c of user u, checked as in the byte decoder.
-struct WIndex {
-    const uint32_t *w;
-    uint32_t nw, sb;
-    bool ok;
-};
-
-__device__ inline WIndex w_read_index(const Layout &lay, uint64_t c, uint32_t u, const uint32_t *__restrict__ words,
-                                      uint64_t words_stride, const uint64_t *__restrict__ chunk_offset,
-                                      const uint16_t *__restrict__ sub_bits, uint32_t lane)
-{
-    WIndex ix;
-    const uint64_t off = chunk_offset[(uint64_t)u * (lay.nchunks + 1) + c];
-    const uint64_t end = chunk_offset[(uint64_t)u * (lay.nchunks + 1) + c + 1];
-    ix.sb = sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + lane];
-    ix.ok = !(off & 31u) && end >= off && (end >> 5) <= words_stride &&
-            ((end - off) >> 5) <= (uint64_t)kChunk * CO3_MAX_CODE_LEN / 32;
-    ix.nw = ix.ok ? (uint32_t)((end - off) >> 5) : 0u;
-    ix.w = words + (uint64_t)u * words_stride + (ix.ok ? (off >> 5) : 0);
-    return ix;
-}
-
-constexpr int kWDecWaves = 8;          // wavefronts of a decode workgroup with one set of code tables for all users
-constexpr int kWDecWavesPerUser = 4;   // and with a set per user (a table per wavefront in LDS)
-constexpr int kWDecBlock = 32;         // symbols a lane decodes between two copies to device memory
-constexpr int kWDecRow = kWDecBlock + 2;                  // 16-bit units of a lane's row: 17 words, odd
-constexpr int kWDecRowsWave = kSubsPerChunk * kWDecRow;   // 16-bit units of a wavefront's 64 rows
-static_assert(kSub % kWDecBlock == 0 && (kWDecRowsWave * sizeof(uint16_t)) % 8 == 0, "blocks per sub-chunk, table alignment");
-
-template <bool kPerUser>
-__global__ __launch_bounds__(64 * kWDecWaves) void k_decode_wide(Layout lay, const uint32_t *__restrict__ words,
-                                                                uint64_t words_stride,
-                                                                const uint64_t *__restrict__ chunk_offset,
-                                                                const uint16_t *__restrict__ sub_bits,
-                                                                const BookWide *__restrict__ books, uint16_t *__restrict__ sym,
-                                                                uint64_t sym_stride, float *__restrict__ q, uint64_t q_stride,
-                                                                uint64_t *__restrict__ status)
-{
-    // The wavefronts of a workgroup decode the same chunk of as many users: with one set of code tables for all
-    // users they share one copy of the chunk's table, else each keeps its own.  A lane decodes its sub-chunk
-    // kWDecBlock symbols at a time into a row of LDS (rows for all 64 symbols would leave room for 12 wavefronts
-    // per CU; blocks of 16 for 32, but store 32 bytes at a time); after each block the rows go out in element
-    // order, 32 consecutive elements per row and 2 rows per store.
-    extern __shared__ uint64_t wd_smem[];
-    const uint32_t nthreads = blockDim.x, nwaves = blockDim.x >> 6;
-    uint16_t *s_rows = reinterpret_cast<uint16_t *>(wd_smem);                                // [nwaves][64 rows]
-    unsigned char *s_tabs = reinterpret_cast<unsigned char *>(s_rows + nwaves * kWDecRowsWave);   // one table, or nwaves short ones
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t c = blockIdx.x;
-    const uint32_t u = blockIdx.y * nwaves + wave;
-    if (!kPerUser) {
-        w_load_tabs<true>(reinterpret_cast<WideTabs *>(s_tabs), books[w_chunk<true>(lay, c, 0).book], threadIdx.x, nthreads);
-        __syncthreads();
-    }
-    if (u >= lay.U) return;  // whole wavefront; wavefront-level synchronisation only below
-    const WChunk k = w_chunk<true>(lay, c, u);
-    const BookWide &book = books[k.book];
-    WideTabs *T = reinterpret_cast<WideTabs *>(s_tabs + (kPerUser ? wave * kWTabsShort : 0u));
-    uint16_t *rows = s_rows + wave * kWDecRowsWave;
-    const WIndex ix = w_read_index(lay, c, u, words, words_stride, chunk_offset, sub_bits, lane);
-    if (kPerUser) w_load_tabs<false>(T, book, lane, 64);
-    w_wave_sync_lds();
-    WUpper32 U32;
-    U32.load(T);
-    const uint32_t p0 = w_wave_inclusive_scan(ix.sb, lane) - ix.sb;
-    const int first = (int)lane * kSub;
-    const int cnt = (int)k.n - first < 0 ? 0 : ((int)k.n - first > kSub ? kSub : (int)k.n - first);
-    const uint64_t pair = (uint64_t)u * lay.nseg + k.seg;
-    const int bias = lay.bias[pair];
-    const float inv_gain = lay.gain[2 * pair + 1];
-    uint32_t pos = p0;
-    bool bad = false;
-    WReader<WGlobalWords> rd{WGlobalWords{ix.w, ix.nw}, 0u, 0u, 0u, 0u, 0u};
-    rd.seek(p0);
-    const uint32_t col = lane & (uint32_t)(kWDecBlock - 1), rsub = lane / (uint32_t)kWDecBlock;   // of the copy
-    for (int blk = 0; blk < kSub / kWDecBlock; ++blk) {
-        if ((uint32_t)(blk * kWDecBlock) >= k.n) break;   // wavefront-uniform: no lane has a symbol left
-        for (int jj = 0; jj < kWDecBlock; ++jj) {
-            if (blk * kWDecBlock + jj < cnt) {
-                uint32_t len;
-                const uint32_t s = w_decode_one<!kPerUser>(rd, pos, T, book.sorted, U32, len);
-                if (len == 0u) { bad = true; len = 1u; }
-                pos += len;
-                rows[lane * kWDecRow + jj] = (uint16_t)s;
-            }
-        }
-        w_wave_sync_lds();
-        for (uint32_t r = rsub; r < (uint32_t)kSubsPerChunk; r += 64u / (uint32_t)kWDecBlock) {
-            const uint32_t e = 64u * r + (uint32_t)(blk * kWDecBlock) + col;   // element of the chunk
-            if (e < k.n) {
-                const uint32_t s = rows[r * kWDecRow + col];
-                if (sym) sym[(uint64_t)u * sym_stride + k.e0 + e] = (uint16_t)s;
-                if (q) q[(uint64_t)u * q_stride + k.e0 + e] = __fmul_rn(__uint_as_float(symbol_value_bits(s, lay.E, lay.M, bias)), inv_gain);
-            }
-        }
-        w_wave_sync_lds();   // the rows are free again
-    }
-    if (bad || pos - p0 != ix.sb || !ix.ok)
-        atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CORRUPT), 1ull);
-}
-
-constexpr int kWAccStride = kSub + 1;
-constexpr int kWAccWords = kSubsPerChunk * kWAccStride;
-constexpr int kWAggWaves = 8;          // wavefronts of a workgroup with one set of code tables for all users
-constexpr int kWAggWavesPerUser = 4;   // and with a set per user (a table per wavefront in LDS)
-constexpr int kWAggThreads = 64 * kWAggWaves;
-
-// One workgroup per chunk; wavefront w of n decodes users w, w + n, ... and adds their values to the chunk's fp64
-// sums in LDS.  With one set of code tables for all users the workgroup keeps a single copy of the chunk's table,
-// else one per wavefront.
-template <bool kPerUser>
-__global__ __launch_bounds__(kWAggThreads, kPerUser ? 2 : 6) void k_aggregate_wide(Layout lay, const uint32_t *__restrict__ words,
-                                                                uint64_t words_stride,
-                                                                const uint64_t *__restrict__ chunk_offset,
-                                                                const uint16_t *__restrict__ sub_bits,
-                                                                const BookWide *__restrict__ books, float *__restrict__ out,
-                                                                float *__restrict__ model, float eta,
-                                                                uint64_t *__restrict__ status)
-{
-    extern __shared__ uint64_t wa_smem[];
-    double *s_acc = reinterpret_cast<double *>(wa_smem);                      // [64][kWAccStride]
-    unsigned char *s_tabs = reinterpret_cast<unsigned char *>(s_acc + kWAccWords);   // one table, or a short one per wavefront
-    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const uint64_t c = blockIdx.x;
-    const WChunk k0 = w_chunk<false>(lay, c, 0);
-    const uint32_t nthreads = blockDim.x, nwaves = blockDim.x >> 6;
-    for (uint32_t i = t; i < (uint32_t)kWAccWords; i += nthreads) s_acc[i] = 0.0;
-    if (!kPerUser) w_load_tabs<true>(reinterpret_cast<WideTabs *>(s_tabs), books[k0.book], t, nthreads);
-    __syncthreads();
-    WideTabs *T = reinterpret_cast<WideTabs *>(s_tabs + (kPerUser ? wave * kWTabsShort : 0u));
-    const uint32_t sign_shift = (uint32_t)(lay.E + lay.M), kmask = (1u << sign_shift) - 1u, mshift = 23u - (uint32_t)lay.M;
-    WUpper32 U32;
-    if (!kPerUser) U32.load(T);
-    for (uint32_t u = wave; u < lay.U; u += nwaves) {
-        const WChunk k = w_chunk<false>(lay, c, u);
-        const BookWide &book = books[k.book];
-        const WIndex ix = w_read_index(lay, c, u, words, words_stride, chunk_offset, sub_bits, lane);
-        if (kPerUser) {
-            w_wave_sync_lds();   // the previous user's table has been read
-            w_load_tabs<false>(T, book, lane, 64);
-            w_wave_sync_lds();
-            U32.load(T);
-        }
-        const uint32_t p0 = w_wave_inclusive_scan(ix.sb, lane) - ix.sb;
-        const int first = (int)lane * kSub;
-        const int cnt = (int)k.n - first < 0 ? 0 : ((int)k.n - first > kSub ? kSub : (int)k.n - first);
-        const uint64_t pair = (uint64_t)u * lay.nseg + k.seg;
-        const int bias = lay.bias[pair];
-        const float inv_gain = lay.gain[2 * pair + 1];
-        const bool scaled = inv_gain != 1.0f;
-        const uint32_t ebias = (uint32_t)(127 - bias) << 23;
-        double *acc = s_acc + lane * kWAccStride;
-        uint32_t pos = p0;
-        bool bad = false;
-        WReader<WGlobalWords> rd{WGlobalWords{ix.w, ix.nw}, 0u, 0u, 0u, 0u, 0u};
-        rd.seek(p0);
-        for (int j = 0; j < cnt; ++j) {
-            uint32_t len;
-            const uint32_t s = w_decode_one<!kPerUser>(rd, pos, T, book.sorted, U32, len);
-            if (len == 0u) { bad = true; len = 1u; }
-            pos += len;
-            // a representative of a normal binade is the symbol's exponent and mantissa fields moved to their fp32
-            // places plus the difference of the biases
-            const uint32_t k = s & kmask;
-            uint32_t vb = (k << mshift) + ebias;
-            if (k < (1u << lay.M)) vb = symbol_value_bits(k, lay.E, lay.M, bias);   // zero and the subnormal row
-            vb |= (s >> sign_shift) << 31;
-            float val = __uint_as_float(vb);
-            if (scaled) val = __fmul_rn(val, inv_gain);   // (the same in every lane)
-            __hip_atomic_fetch_add(&acc[j], (double)val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        if (bad || pos - p0 != ix.sb || !ix.ok)
-            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CORRUPT), 1ull);
-    }
-    __syncthreads();
-    const double inv_u = 1.0 / (double)lay.U;
-    const double eta64 = (double)eta;
-    for (uint32_t e = t; e < k0.n; e += nthreads) {
-        const double avg = s_acc[(e >> 6) * kWAccStride + (e & 63u)] * inv_u;
-        if (out) out[k0.e0 + e] = (float)avg;
-        if (model) model[k0.e0 + e] = (float)((double)model[k0.e0 + e] - eta64 * avg);
-    }
-}
-
 // ---- launchers ----------------------------------------------------------------------------------------------
 
 static inline size_t w_up256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1412,47 +1046,6 @@ hipError_t launch_encode_wide(const Layout &lay, const WideCut &cut, const co3_e
         hipLaunchKernelGGL(k_pack_wide, dim3(gx, lay.U), dim3(kWThreads), kWPackLds, s, lay, sym, sym_stride, books,
                            a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status, cut.runs, cut.nrun, cpw);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_decode_wide(const Layout &lay, const co3_decode_args &a, const BookWide *books, hipStream_t s)
-{
-    if (lay.U == 0 || lay.nchunks == 0) return hipSuccess;
-    const uint64_t sym_stride = symbol_row_stride(lay.d);
-    const uint32_t nwaves = lay.per_user_books ? kWDecWavesPerUser : kWDecWaves;
-    const size_t lds = (size_t)nwaves * kWDecRowsWave * sizeof(uint16_t) +
-                       (lay.per_user_books ? (size_t)nwaves * kWTabsShort : sizeof(WideTabs));   // 52 KB, or 55 KB with a set per user
-    const void *fn = lay.per_user_books ? reinterpret_cast<const void *>(&k_decode_wide<true>)
-                                        : reinterpret_cast<const void *>(&k_decode_wide<false>);
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    ProfScope prof(K_DECODE, s);
-    const dim3 grid((uint32_t)lay.nchunks, (lay.U + nwaves - 1) / nwaves);
-    if (lay.per_user_books)
-        hipLaunchKernelGGL(k_decode_wide<true>, grid, dim3(64 * nwaves), lds, s, lay, a.words, a.words_stride, a.chunk_offset,
-                           a.sub_bits, books, reinterpret_cast<uint16_t *>(a.symbols), sym_stride, a.q, a.q_stride, a.status);
-    else
-        hipLaunchKernelGGL(k_decode_wide<false>, grid, dim3(64 * nwaves), lds, s, lay, a.words, a.words_stride, a.chunk_offset,
-                           a.sub_bits, books, reinterpret_cast<uint16_t *>(a.symbols), sym_stride, a.q, a.q_stride, a.status);
-    return hipGetLastError();
-}
-
-hipError_t launch_aggregate_wide(const Layout &lay, const co3_aggregate_args &a, const BookWide *books, hipStream_t s)
-{
-    if (lay.U == 0 || lay.nchunks == 0) return hipSuccess;
-    const uint32_t nwaves = lay.per_user_books ? kWAggWavesPerUser : kWAggWaves;
-    const size_t lds = (size_t)kWAccWords * sizeof(double) + (lay.per_user_books ? (size_t)nwaves * kWTabsShort : sizeof(WideTabs));
-    const void *fn = lay.per_user_books ? reinterpret_cast<const void *>(&k_aggregate_wide<true>)
-                                        : reinterpret_cast<const void *>(&k_aggregate_wide<false>);
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);   // 71 KB or 50 KB
-    if (e != hipSuccess) return e;
-    ProfScope prof(K_AGGREGATE, s);
-    if (lay.per_user_books)
-        hipLaunchKernelGGL(k_aggregate_wide<true>, dim3((uint32_t)lay.nchunks), dim3(64 * nwaves), lds, s, lay, a.words,
-                           a.words_stride, a.chunk_offset, a.sub_bits, books, a.out, a.model, a.eta, a.status);
-    else
-        hipLaunchKernelGGL(k_aggregate_wide<false>, dim3((uint32_t)lay.nchunks), dim3(64 * nwaves), lds, s, lay, a.words,
-                           a.words_stride, a.chunk_offset, a.sub_bits, books, a.out, a.model, a.eta, a.status);
     return hipGetLastError();
 }
 
