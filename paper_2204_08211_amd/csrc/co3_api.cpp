@@ -316,6 +316,7 @@ int co3_build_codebook(co3_format format, uint32_t nbooks, const uint64_t *weigh
         std::memset(host_wide.data(), 0, sizeof(BookWide) * nbooks);
         for (auto &b : host_wide) {   // a table not built yet has no codes at all
             if (weights) break;
+            std::fill(b.fast, b.fast + kWideMaxA, kWFastSlow << kWFastCodeBits);
             std::fill(b.tab, b.tab + kWideTabMax, kLenSlow);
             std::fill(b.limit, b.limit + 32, ~0u);
             b.tab_bits = 2;
@@ -449,7 +450,7 @@ static int encode_with_workspace(const co3_plan *plan, const co3_encode_args *a,
     args.workspace = workspace;
     args.workspace_bytes = workspace_bytes;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (lay.wide) {   // alphabets above 8 bits: a fixed code without a symbol buffer keeps its symbols in the workspace
+    if (lay.wide) {   // alphabets above 8 bits (a fixed code without a symbol buffer: see there)
         return launch_encode_wide(lay, plan->wide, args, a->books->d_wide, workspace, s) == hipSuccess ? CO3_OK : CO3_ERR_HIP;
     }
     if (single_sweep)

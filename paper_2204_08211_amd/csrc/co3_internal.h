@@ -34,6 +34,9 @@ constexpr int kHistGlobalRep = 64;   // copies of the global symbol-count table 
 constexpr int kFastLen = 24;        // longest code held in the 32-bit encode entry
 constexpr uint32_t kFastSlow = 0xFFu;  // length field marking "use the 64-bit table"
 
+constexpr uint32_t kWFastCodeBits = 25;   // longest code held in a wide alphabet's encode entry ...
+constexpr uint32_t kWFastSlow = 127;      // ... and the length field of the others
+
 // One Huffman code table as the kernels read it.
 struct BookDev {
     uint64_t code[kMaxA];        // right-aligned codeword of each symbol
@@ -61,6 +64,7 @@ struct BookWide {
     uint32_t offset[65];                  // index of the first length-L symbol in sorted[]
     uint16_t sorted[kWideMaxA];           // symbols ordered by (length, symbol)
     uint8_t len[kWideMaxA];               // codeword length, 0 = no code
+    alignas(16) uint32_t fast[kWideMaxA]; // (len << kWFastCodeBits) | code; length field kWFastSlow: a longer code, or none
     uint32_t maxlen;
     uint32_t nactive;
     uint32_t tab_bits;                    // mantissa bits of the decode table's index; 0: indexed by the complement's top 12 bits

@@ -160,6 +160,7 @@ static void finish_wide_table(BookWide *b, uint32_t A)
 int build_wide_host(const uint64_t *w, uint32_t A, BookWide *b)
 {
     std::memset(b, 0, sizeof(*b));
+    std::fill(b->fast, b->fast + kWideMaxA, kWFastSlow << kWFastCodeBits);
     int rc = huffman_lengths_host(w, A, b->len);
     if (rc != CO3_OK) { std::memset(b, 0, sizeof(*b)); return rc; }
     for (uint32_t s = 0; s < A; ++s) {
@@ -183,6 +184,7 @@ int build_wide_host(const uint64_t *w, uint32_t A, BookWide *b)
         if (!L) continue;
         const uint32_t rank = next[L]++;
         b->code[s] = b->first[L] + rank;
+        if ((uint32_t)L <= kWFastCodeBits) b->fast[s] = ((uint32_t)L << kWFastCodeBits) | (uint32_t)b->code[s];
         b->sorted[b->offset[L] + rank] = (uint16_t)s;
     }
     finish_wide_table(b, A);

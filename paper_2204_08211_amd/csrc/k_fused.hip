@@ -30,6 +30,7 @@
 #include <atomic>
 
 #include "co3_internal.h"
+#include "lookback.h"
 #include "pack_core.h"
 #include "quantize_math.h"
 
@@ -46,12 +47,7 @@ constexpr int kFuBatch = 4;                          // 16-byte vectors of g (an
 constexpr int kFuBatches = kChunk / 4 / 64 / kFuBatch; // batches per chunk
 constexpr int kFuScalar = 8;                         // element rounds a lane requests together on the element path
 static std::atomic<uint32_t> g_spin_limit{CO3_LOOKBACK_POLLS_DEFAULT};  // polls of one predecessor entry before giving up
-
-// look-back entry: flag in the top two bits, size in bits below
-constexpr uint64_t kLbAgg = 1ull << 62;      // size of this workgroup alone
-constexpr uint64_t kLbPrefix = 2ull << 62;   // size of this workgroup and all before it
-constexpr uint64_t kLbStalled = 3ull << 62;
-constexpr uint64_t kLbValue = (1ull << 62) - 1;
+uint32_t lookback_polls() { return g_spin_limit.load(); }
 
 static_assert(kChunk % (4 * 64 * kFuBatch) == 0, "whole batches per chunk");
 static_assert(kChunk % (64 * kFuScalar) == 0, "whole element rounds per chunk");
@@ -553,7 +549,7 @@ static void launch_fused_waves(const Layout &lay, const co3_encode_args &a, cons
                                uint64_t *lb_state, uint32_t nblk, uint64_t *hist_rep, hipStream_t s)
 {
     hipLaunchKernelGGL((k_encode_fused<kSR, kCpb, kTeam, kWaves, kHist>), dim3(nblk, lay.U), dim3(64 * kCpb * kTeam), 0, s, lay, a.g, a.m,
-                       a.m_out, a.row_stride, a.gamma, a.seed, books, tickets, lb_state, nblk, g_spin_limit.load(),
+                       a.m_out, a.row_stride, a.gamma, a.seed, books, tickets, lb_state, nblk, lookback_polls(),
                        a.chunk_offset, a.sub_bits, a.payload_bits, a.words, a.words_stride, a.status, hist_rep);
 }
 

@@ -3,8 +3,7 @@
 // The steps are those of the byte path (Algorithm 1 lines 8-10 and 13-14; Sec. IV-A (i)-(iii), Sec. II-B (iv))
 // and the container is the same; symbols are 16-bit words and a code table has up to 4096 entries, too many
 // for the per-wavefront LDS tables the byte kernels are built around: here a workgroup shares one copy of the
-// table in use.  The coder's workgroups end where the table changes, the quantizer's go on with the next one.  A fixed code without a symbol buffer ("single sweep" in the byte path) runs the
-// same three steps here with the symbols kept in the workspace.
+// table in use.  The coder's workgroups end where the table changes, the quantizer's go on with the next one.
 //
 //   k_quantize_wide      v = g + gamma m, Q_fp, m' = v - ghat, symbol; symbol counts in an LDS table per workgroup
 //                        (and, for a held code on layers that start on its tile grid, the chunks' coded sizes)
@@ -14,8 +13,10 @@
 //   (k_scan_chunks of k_pack.hip gives the chunk offsets)
 //   k_pack_wide          wavefront per chunk, lane per sub-chunk with its 64 symbols in registers: lengths, wave
 //                        prefix sum, codewords ORed into an LDS window at their bit offsets, window copied out
+//   k_encode_wide        the three steps in one sweep, for a held code whose symbols and counts nobody asks for
 // (the PS side is in k_decode_wide.hip)
 #include "co3_internal.h"
+#include "lookback.h"
 #include "quantize_math.h"
 
 namespace co3 {
@@ -259,10 +260,11 @@ __global__ __launch_bounds__(256) void k_reduce_hist_wide(const uint64_t *__rest
     hist[i] = s;
 }
 
-__global__ void k_zero_wide(uint64_t *p, uint64_t n)
+__global__ void k_zero_wide(uint64_t *p, uint64_t n, uint64_t *q, uint32_t nq)   // nq <= n
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
+    if (i < nq) q[i] = 0;
 }
 
 // ---- code tables ------------------------------------------------------------------------------------------
@@ -310,6 +312,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
         leaf_sym[s] = (uint16_t)s;
         B.len[s] = 0;
         B.code[s] = 0;
+        B.fast[s] = kWFastSlow << kWFastCodeBits;
     }
     if (active) atomicAdd(&s_n, active);
     __syncthreads();
@@ -473,6 +476,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
                 const uint32_t rank = base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
                 const uint64_t code = first[L0] + rank;
                 B.code[s_i] = code;
+                if (L0 <= kWFastCodeBits) B.fast[s_i] = (L0 << kWFastCodeBits) | (uint32_t)code;
                 B.sorted[off[L0] + rank] = (uint16_t)s_i;
                 tmpid[off[L0] + rank] = (uint16_t)s_i;
                 // mantissa bits that a code with up to ten leading ones asks of the decode table
@@ -588,7 +592,6 @@ __device__ inline WRange w_range(const Layout &lay, const RunDev *runs, uint32_t
     r.left = sd.offset + sd.length - r.e0;
     return r;
 }
-constexpr uint32_t kWFastCodeBits = 25;   // s_fast entry: length << 25 | codeword, for lengths up to 25
 constexpr int kWSymLoads = (kChunk / 2 + 1 + 63) / 64;    // dword loads per lane to cover a chunk at any 2-byte offset (33)
 constexpr uint32_t kWSymMask2 = (uint32_t)(kWideMaxA - 1) * 0x10001u;
 // A wavefront's LDS words in the coder: 64 rows of 32 + 1 words and one word more.  They hold the staged symbols,
@@ -600,7 +603,6 @@ constexpr int kWRegion = kSubsPerChunk * kWRowStride + 1;         // 2113
 constexpr int kWWinSlow = 128;
 constexpr int kWWinMedium = 2048;                                // the rows' storage as a window
 constexpr int kWPackWaveWords = kWRegion + kWWinSlow + 1;
-constexpr uint32_t kWFastSlow = 127;                              // length field of a symbol the unrolled coder cannot take
 constexpr size_t kWPackLds = sizeof(uint32_t) * (kWideMaxA + kWWaves * kWPackWaveWords);   // 52 KB: three workgroups per CU
 
 // Step 1 of the coder: every lane concatenates the codewords of its 64 symbols (two per word of sym) from bit 0
@@ -776,6 +778,118 @@ __global__ __launch_bounds__(kWThreads) void k_chunk_bits_wide(Layout lay, const
     }
 }
 
+// A chunk's coded sub-chunks: `rows` says where the codewords are (w_pack_rows), bits and excl are the lane's own and
+// those of the lanes before it, nwords the words of the whole chunk.
+struct WCoded {
+    uint32_t bits, excl, nwords;
+    int rows;
+};
+
+// What the plain loops know of a symbol: from the table in LDS where that holds the symbol's code, else from device memory.
+__device__ inline void w_lookup(const uint32_t *fast, const BookWide &book, uint32_t s, uint32_t &L, uint64_t &code)
+{
+    const uint32_t e = fast[s];
+    L = e >> kWFastCodeBits;
+    code = e & ((1u << kWFastCodeBits) - 1u);
+    if (L == kWFastSlow) { L = book.len[s]; code = book.code[s]; }
+}
+
+// Codes a wavefront's chunk, lane l its sub-chunk of cnt symbols in sym (two per word); whole: every lane has kSub.
+// Where rows says kRowsOk, w_rows_to_window makes the chunk's words of the rows.
+__device__ inline WCoded w_code_chunk(const uint32_t (&sym)[kSub / 2], int cnt, bool whole, const uint32_t *fast,
+                                      const BookWide &book, uint32_t *region, uint32_t lane, uint64_t *status)
+{
+    WCoded r;
+    r.bits = 0;
+    uint32_t nocode = 0;
+    r.rows = whole ? w_pack_rows<true>(sym, cnt, fast, book, region, region + kWRegion, lane, r.bits, nocode)
+                   : w_pack_rows<false>(sym, cnt, fast, book, region, region + kWRegion, lane, r.bits, nocode);
+    if (r.rows == kRowsSlow) {
+        // long codes or symbols without one in more than a few lanes: the symbols go back to the rows, plain loops
+        uint32_t *row32 = region + lane * kWRowStride;
+        w_wave_sync_lds();
+#pragma unroll
+        for (int jj = 0; jj < kSub / 2; ++jj) row32[jj] = sym[jj];
+        w_wave_sync_lds();
+        const uint16_t *row = reinterpret_cast<const uint16_t *>(row32);
+        nocode = 0;      // (the rows' redone lanes are counted here again)
+        r.bits = 0;
+        for (int j = 0; j < cnt; ++j) {
+            uint32_t L;
+            uint64_t code;
+            w_lookup(fast, book, row[j], L, code);
+            nocode += L == 0u ? 1u : 0u;
+            r.bits += L;
+        }
+    }
+    if (nocode)
+        atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
+    const uint32_t incl = w_wave_inclusive_scan(r.bits, lane);
+    r.excl = incl - r.bits;
+    r.nwords = ((uint32_t)__shfl(incl, 63, 64) + 31u) >> 5;
+    return r;
+}
+
+// Writes the words of a coded chunk to dst: the window, where there is one.
+__device__ inline void w_store_chunk(const WCoded &r, const uint32_t (&sym)[kSub / 2], int cnt, const uint32_t *fast,
+                                     const BookWide &book, uint32_t *region, uint32_t lane, uint32_t *dst)
+{
+    if (r.rows == kRowsOk) {
+        for (uint32_t i = lane; i < r.nwords; i += 64) __builtin_nontemporal_store(region[i], dst + i);
+        return;
+    }
+    // Rows too short for some lane (more than 16 bits per symbol on average): the codewords are appended at
+    // their final bit offsets instead, entries from the table in LDS, the rows' storage as the window.  After
+    // the plain loops above: the same from the rows' symbols, a small window behind them.
+    const bool medium = r.rows == kRowsOverflow;
+    const uint16_t *row = reinterpret_cast<const uint16_t *>(region + lane * kWRowStride);
+    uint32_t *win = medium ? region : region + kWRegion;
+    const uint32_t wcap = medium ? (uint32_t)kWWinMedium : (uint32_t)kWWinSlow;
+    for (uint32_t wbase = 0; wbase < r.nwords; wbase += wcap) {
+        const uint32_t wn = r.nwords - wbase < wcap ? r.nwords - wbase : wcap;
+        w_wave_sync_lds();
+        for (uint32_t i = lane; i <= wn; i += 64) win[i] = 0u;
+        w_wave_sync_lds();
+        uint32_t wi = (r.excl >> 5) - wbase;  // window word receiving the next completed 32 bits (may start below the window)
+        uint32_t np = r.excl & 31u;           // bits pending in acc (the leading np bits belong to earlier lanes)
+        uint64_t acc = 0;
+        auto append = [&](uint64_t code, uint32_t L) {  // L <= 32, np < 32
+            acc = (acc << L) | code;
+            np += L;
+            if (np >= 32u) {
+                np -= 32u;
+                if (wi < wn) atomicOr(&win[wi], (uint32_t)(acc >> np));  // unsigned: false below the window
+                ++wi;
+            }
+        };
+        // a lane whose bits all lie outside this window has nothing to add
+        const bool overlaps = r.excl + r.bits > wbase * 32u && r.excl < (wbase + wn) * 32u;
+        if (medium) {   // whole wavefront; every existing symbol has a code of at most kWFastCodeBits bits
+#pragma unroll
+            for (int j = 0; j < kSub; ++j) {
+                const uint32_t e = fast[(j & 1) ? sym[j >> 1] >> 16 : sym[j >> 1] & 0xffffu];
+                if (overlaps && j < cnt) append(e & ((1u << kWFastCodeBits) - 1u), e >> kWFastCodeBits);
+            }
+        }
+        for (int j = 0; !medium && overlaps && j < cnt; ++j) {
+            uint32_t L;
+            uint64_t code;
+            w_lookup(fast, book, row[j], L, code);
+            if (!L) continue;
+            if (L > 32u) {
+                append(code >> 32, L - 32u);
+                code &= 0xffffffffull;
+                L = 32u;
+            }
+            append(code, L);
+        }
+        if (overlaps && np && wi < wn) atomicOr(&win[wi], (uint32_t)(acc << (32u - np)));
+        w_wave_sync_lds();
+        for (uint32_t i = lane; i < wn; i += 64) dst[wbase + i] = win[i];
+        w_wave_sync_lds();
+    }
+}
+
 __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const uint16_t *__restrict__ sym, uint64_t sym_stride,
                                                         const BookWide *__restrict__ books,
                                                         const uint64_t *__restrict__ chunk_offset,
@@ -791,19 +905,11 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
     const WRange wg = w_range(lay, runs, nrun, u, blockIdx.x, cpw);
     {
         const BookWide &tb = books[wg.book];
-        uint32_t tl[kWideMaxA / kWThreads], tc[kWideMaxA / kWThreads];   // the loads are issued together
+        uint32_t tab[kWideMaxA / kWThreads];   // the loads are issued together
 #pragma unroll
-        for (int r = 0; r < kWideMaxA / kWThreads; ++r) {
-            const uint32_t i = threadIdx.x + (uint32_t)r * kWThreads;
-            tl[r] = i < lay.A ? (uint32_t)tb.len[i] : 0u;
-            tc[r] = i < lay.A ? (uint32_t)tb.code[i] : 0u;
-        }
+        for (int r = 0; r < kWideMaxA / kWThreads; ++r) tab[r] = tb.fast[threadIdx.x + (uint32_t)r * kWThreads];
 #pragma unroll
-        for (int r = 0; r < kWideMaxA / kWThreads; ++r) {
-            const uint32_t i = threadIdx.x + (uint32_t)r * kWThreads;
-            // no code, or a longer one than an entry holds: kWFastSlow
-            s_fast[i] = (tl[r] >= 1u && tl[r] <= kWFastCodeBits) ? ((tl[r] << kWFastCodeBits) | tc[r]) : (kWFastSlow << kWFastCodeBits);
-        }
+        for (int r = 0; r < kWideMaxA / kWThreads; ++r) s_fast[threadIdx.x + (uint32_t)r * kWThreads] = tab[r];
     }
     __syncthreads();
     const BookWide &book = books[wg.book];
@@ -849,107 +955,258 @@ __global__ __launch_bounds__(kWThreads, 3) void k_pack_wide(Layout lay, const ui
         }
         w_wave_sync_lds();   // every lane holds its symbols: the rows are free
 
-        uint32_t bits = 0;
-        uint32_t redo_nocode = 0;
-        const int rows = n == (uint32_t)kChunk
-                             ? w_pack_rows<true>(symw, cnt, s_fast, book, region, region + kWRegion, lane, bits, redo_nocode)
-                             : w_pack_rows<false>(symw, cnt, s_fast, book, region, region + kWRegion, lane, bits, redo_nocode);
-        if (rows != kRowsSlow && redo_nocode)   // (the plain loops below count them themselves)
-            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)redo_nocode);
-        const bool fast_ok = rows == kRowsOk;
-        const uint16_t *row = reinterpret_cast<const uint16_t *>(row32);
-        // what the plain loops know of a symbol: from the table in LDS where that holds the symbol's code, else from
-        // device memory
-        auto lookup = [&](uint32_t sj, uint32_t &L, uint64_t &code) {
-            const uint32_t e = s_fast[sj];
-            L = e >> kWFastCodeBits;
-            code = e & ((1u << kWFastCodeBits) - 1u);
-            if (L == kWFastSlow) { L = book.len[sj]; code = book.code[sj]; }
-        };
-        if (rows == kRowsSlow) {
-            // long codes or symbols without one in more than a few lanes: the symbols go back to the rows, plain loops
-            w_wave_sync_lds();
-#pragma unroll
-            for (int jj = 0; jj < kSub / 2; ++jj) row32[jj] = symw[jj];
-            w_wave_sync_lds();
-            uint32_t nocode = 0;
-            bits = 0;
-            for (int j = 0; j < cnt; ++j) {
-                uint32_t L;
-                uint64_t code;
-                lookup(row[j], L, code);
-                nocode += L == 0u ? 1u : 0u;
-                bits += L;
-            }
-            if (nocode)
-                atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
-        }
-        sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + lane] = (uint16_t)bits;
-        const uint32_t incl = w_wave_inclusive_scan(bits, lane);
-        const uint32_t excl = incl - bits;
-        const uint32_t chunk_total = __shfl(incl, 63, 64);
-        const uint32_t nwords = (chunk_total + 31u) >> 5;
+        const WCoded coded = w_code_chunk(symw, cnt, n == (uint32_t)kChunk, s_fast, book, region, lane, status);
+        sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + lane] = (uint16_t)coded.bits;
         const uint64_t off_words = off >> 5;
-        if (off_words + nwords > words_stride) {   // whole wavefront
+        if (off_words + coded.nwords > words_stride) {   // whole wavefront
             if (lane == 0) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CAPACITY), 1ull);
             continue;
         }
         uint32_t *dst = words + (uint64_t)u * words_stride + off_words;
-        if (fast_ok) {
-            w_rows_to_window(region, lane, bits, excl, nwords);
-            for (uint32_t i = lane; i < nwords; i += 64) __builtin_nontemporal_store(region[i], dst + i);
+        if (coded.rows == kRowsOk) {
+            w_rows_to_window(region, lane, coded.bits, coded.excl, coded.nwords);
+            for (uint32_t i = lane; i < coded.nwords; i += 64) __builtin_nontemporal_store(region[i], dst + i);
             continue;
         }
-        // Rows too short for some lane (more than 16 bits per symbol on average): the codewords are appended at
-        // their final bit offsets instead, entries from the table in LDS, the rows' storage as the window.  After
-        // the plain loops above: the same from the rows' symbols, a small window behind them.
-        const bool medium = rows == kRowsOverflow;
-        uint32_t *win = medium ? region : region + kWRegion;
-        const uint32_t wcap = medium ? (uint32_t)kWWinMedium : (uint32_t)kWWinSlow;
-        for (uint32_t wbase = 0; wbase < nwords; wbase += wcap) {
-            const uint32_t wn = nwords - wbase < wcap ? nwords - wbase : wcap;
-            w_wave_sync_lds();
-            for (uint32_t i = lane; i <= wn; i += 64) win[i] = 0u;
-            w_wave_sync_lds();
-            uint32_t wi = (excl >> 5) - wbase;  // window word receiving the next completed 32 bits (may start below the window)
-            uint32_t np = excl & 31u;           // bits pending in acc (the leading np bits belong to earlier lanes)
-            uint64_t acc = 0;
-            auto append = [&](uint64_t code, uint32_t L) {  // L <= 32, np < 32
-                acc = (acc << L) | code;
-                np += L;
-                if (np >= 32u) {
-                    np -= 32u;
-                    if (wi < wn) atomicOr(&win[wi], (uint32_t)(acc >> np));  // unsigned: false below the window
-                    ++wi;
-                }
-            };
-            // a lane whose bits all lie outside this window has nothing to add
-            const bool overlaps = excl + bits > wbase * 32u && excl < (wbase + wn) * 32u;
-            if (medium) {   // whole wavefront; every existing symbol has a code of at most kWFastCodeBits bits
+        w_store_chunk(coded, symw, cnt, s_fast, book, region, lane, dst);
+    }
+}
+
+// ---- user side for a held code, in one sweep ------------------------------------------------------------------
+
+// The same steps without the symbols ever reaching memory, as the byte path's k_encode_fused does it: a workgroup takes
+// the next four chunks under one code table (its place from a ticket counter), a wavefront quantizes a chunk into LDS
+// rows while it sums the code lengths, the size is published, and while the predecessors' sizes are looked up every
+// wavefront codes its chunk.  The look-back and its bound are k_encode_fused's.
+// Bound by the streams of g, m and m' (12 bytes an element; the three steps move 4 more for the symbols, and wait for
+// one another): sixteen users of 25.6 M elements in [1,5,6], 1.64 ms in three steps, 1.04 in this, 5.2 TB/s.
+// 52 KB of LDS (the table 16, a wavefront's rows 9) let three workgroups share a CU, so the registers are cut for that.
+// A chunk starts at any element: its vectors are read and written at 4-byte alignment, which a vector access to device
+// memory may have, so there is one path for whole chunks and one, element by element, for a layer's ragged last one.
+// kSR: the stochastic conversion.  A vector's four random words are one Philox block, so layers have to start at
+// multiples of four elements (lay.vec_aligned).
+typedef float wf4u __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kWfBatch = 4;                                   // vectors of g (and of m) a lane requests at a time
+constexpr int kWfBatches = kChunk / 4 / 64 / kWfBatch;
+constexpr int kWfScalar = 8;                                  // element rounds a lane requests together
+static_assert(kChunk % (4 * 64 * kWfBatch) == 0 && kChunk % (64 * kWfScalar) == 0, "whole batches per chunk");
+
+__device__ inline void w_lds_barrier()   // orders LDS accesses only: nobody here reads the stores to memory that are under way
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <bool kSR>
+__global__ __launch_bounds__(kWThreads, 3) void k_encode_wide(
+    Layout lay, const float *__restrict__ g, const float *m, float *m_out, uint64_t row_stride, float gamma, uint64_t seed,
+    const BookWide *__restrict__ books, uint64_t *lookback, uint32_t nwg, uint32_t spin_limit,
+    uint64_t *__restrict__ chunk_offset, uint16_t *__restrict__ sub_bits, uint64_t *__restrict__ payload_bits,
+    uint32_t *__restrict__ words, uint64_t words_stride, uint64_t *__restrict__ status, const RunDev *__restrict__ runs,
+    uint32_t nrun)
+{
+    __shared__ uint32_t s_fast[kWideMaxA];
+    __shared__ uint32_t s_wave_all[kWWaves * kWPackWaveWords];
+    __shared__ uint32_t s_cbits[kWWaves];
+    __shared__ uint64_t s_prefix;
+    __shared__ uint32_t s_ticket, s_stalled;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    const uint32_t u = blockIdx.y;
+    uint64_t *state = lookback + (uint64_t)u * (nwg + 1ull) + 1;   // a user's ticket counter lies in front of its entries
+
+    if (t == 0) s_ticket = atomicAdd(reinterpret_cast<uint32_t *>(state - 1), 1u);
+    w_lds_barrier();
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_ticket);   // < nwg = gridDim.x
+    const WRange wg = w_range(lay, runs, nrun, u, b, 1u);
+    const bool active = wave < wg.nck;
+    const BookWide &book = books[wg.book];
+    uint32_t *region = s_wave_all + wave * kWPackWaveWords;
+    uint64_t e0 = 0;
+    uint32_t n = 0;
+    if (active) wg.place(lay.segs, wave, e0, n);
+    const float *gu = g + (uint64_t)u * row_stride + e0;
+    const float *mu = m + (uint64_t)u * row_stride + e0;
+    float *mo = m_out + (uint64_t)u * row_stride + e0;
+    const bool whole = n == (uint32_t)kChunk;
+
+    // The code's table is requested first and stored to LDS when the first vectors are under way.
+    uint32_t tab[kWideMaxA / kWThreads];
 #pragma unroll
-                for (int j = 0; j < kSub; ++j) {
-                    const uint32_t e = s_fast[(j & 1) ? symw[j >> 1] >> 16 : symw[j >> 1] & 0xffffu];
-                    if (overlaps && j < cnt) append(e & ((1u << kWFastCodeBits) - 1u), e >> kWFastCodeBits);
-                }
-            }
-            for (int j = 0; !medium && overlaps && j < cnt; ++j) {
-                uint32_t L;
-                uint64_t code;
-                lookup(row[j], L, code);
-                if (!L) continue;
-                if (L > 32u) {
-                    append(code >> 32, L - 32u);
-                    code &= 0xffffffffull;
-                    L = 32u;
-                }
-                append(code, L);
-            }
-            if (overlaps && np && wi < wn) atomicOr(&win[wi], (uint32_t)(acc << (32u - np)));
-            w_wave_sync_lds();
-            for (uint32_t i = lane; i < wn; i += 64) dst[wbase + i] = win[i];
-            w_wave_sync_lds();
+    for (int r = 0; r < kWideMaxA / kWThreads; ++r) tab[r] = book.fast[t + (uint32_t)r * kWThreads];
+    wf4u gn[kWfBatch], mn[kWfBatch];
+    if (whole) {
+#pragma unroll
+        for (int r = 0; r < kWfBatch; ++r) {
+            const uint32_t i = 4u * (lane + 64u * (uint32_t)r);
+            gn[r] = __builtin_nontemporal_load(reinterpret_cast<const wf4u *>(gu + i));
+            mn[r] = __builtin_nontemporal_load(reinterpret_cast<const wf4u *>(mu + i));
         }
     }
+#pragma unroll
+    for (int r = 0; r < kWideMaxA / kWThreads; ++r) s_fast[t + (uint32_t)r * kWThreads] = tab[r];
+    w_lds_barrier();
+
+    // ---- 1. wavefront w quantizes chunk w: two symbols a word, word i at i + i / 32 of its rows ---------------------
+    const uint32_t sign_shift = lay.E + lay.M;
+    uint32_t len_sum = 0, n_nonfinite = 0, n_clamped = 0;
+    if (active) {
+        // the chunk's layer: last one that starts at or before the chunk
+        uint32_t seg = wg.seg, seg_end = wg.seg_end;
+        while (seg_end - seg > 1) {
+            const uint32_t mid = (seg + seg_end) >> 1;
+            if (lay.segs[mid].chunk_start <= wg.first + wave) seg = mid; else seg_end = mid;
+        }
+        const uint64_t pair = (uint64_t)u * lay.nseg + seg;
+        const int bias = lay.bias[pair];
+        const QConst qc = make_qconst(lay.E, lay.M, bias);
+        const float gain = lay.gain[2 * pair], inv_gain = lay.gain[2 * pair + 1];
+        // an entry of the table holds the length of a code of up to kWFastCodeBits bits
+        auto code_len = [&](uint32_t s, uint32_t e) { return e >> kWFastCodeBits == kWFastSlow ? (uint32_t)book.len[s] : e >> kWFastCodeBits; };
+        if (whole) {
+#pragma unroll 1
+            for (int bt = 0; bt < kWfBatches; ++bt) {
+                wf4u gc[kWfBatch], mc[kWfBatch];
+#pragma unroll
+                for (int r = 0; r < kWfBatch; ++r) { gc[r] = gn[r]; mc[r] = mn[r]; }
+                if (bt + 1 < kWfBatches) {
+#pragma unroll
+                    for (int r = 0; r < kWfBatch; ++r) {
+                        const uint32_t i = 4u * (lane + 64u * (uint32_t)((bt + 1) * kWfBatch + r));
+                        gn[r] = __builtin_nontemporal_load(reinterpret_cast<const wf4u *>(gu + i));
+                        mn[r] = __builtin_nontemporal_load(reinterpret_cast<const wf4u *>(mu + i));
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < kWfBatch; ++r) {
+                    const uint32_t k = lane + 64u * (uint32_t)(bt * kWfBatch + r);   // vector of the chunk
+                    wf4u eo;
+                    uint32_t sp[4], en[4];
+                    Philox4 rw;
+                    if constexpr (kSR) rw = element_random_words(e0 + 4u * k, u, seed);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float v = __fadd_rn(gc[r][j], __fmul_rn(gamma, mc[r][j]));
+                        const float y = __fmul_rn(v, gain);
+                        uint32_t s, flags;
+                        float q;
+                        if constexpr (kSR) quantize_stochastic(y, qc, lay.E, lay.M, bias, sign_shift, rw.w[j], s, q, flags);
+                        else quantize(y, qc, sign_shift, s, q, flags);
+                        q = __fmul_rn(q, inv_gain);
+                        eo[j] = (flags & 1u) ? 0.0f : __fsub_rn(v, q);
+                        n_nonfinite += flags & 1u;
+                        n_clamped += (flags >> 1) & 1u;
+                        sp[j] = s & (uint32_t)(kWideMaxA - 1);
+                        en[j] = s_fast[sp[j]];
+                    }
+                    __builtin_nontemporal_store(eo, reinterpret_cast<wf4u *>(mo + 4u * k));
+                    const uint32_t at = 2u * k + ((2u * k) >> 5);   // both words lie in one row
+                    region[at] = sp[0] | (sp[1] << 16);
+                    region[at + 1u] = sp[2] | (sp[3] << 16);
+                    const uint32_t top = max(max(en[0], en[1]), max(en[2], en[3]));
+                    if (__any(top >= (kWFastSlow << kWFastCodeBits))) {   // a long code, or a symbol without one
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) len_sum += code_len(sp[j], en[j]);
+                    } else {
+                        len_sum += (en[0] >> kWFastCodeBits) + (en[1] >> kWFastCodeBits) + (en[2] >> kWFastCodeBits) +
+                                   (en[3] >> kWFastCodeBits);
+                    }
+                }
+            }
+        } else {
+            uint16_t *half = reinterpret_cast<uint16_t *>(region);
+            for (uint32_t base = 0; base < n; base += 64u * kWfScalar) {
+                float gs[kWfScalar], ms[kWfScalar];
+#pragma unroll
+                for (int r = 0; r < kWfScalar; ++r) {
+                    const uint32_t j = base + lane + 64u * (uint32_t)r;
+                    gs[r] = j < n ? gu[j] : 0.0f;
+                    ms[r] = j < n ? mu[j] : 0.0f;
+                }
+#pragma unroll
+                for (int r = 0; r < kWfScalar; ++r) {
+                    const uint32_t j = base + lane + 64u * (uint32_t)r;   // < kChunk: base is a multiple of 64 kWfScalar
+                    if (j < n) {
+                        const float v = __fadd_rn(gs[r], __fmul_rn(gamma, ms[r]));
+                        const float y = __fmul_rn(v, gain);
+                        uint32_t s, flags;
+                        float q;
+                        if constexpr (kSR)
+                            quantize_stochastic(y, qc, lay.E, lay.M, bias, sign_shift,
+                                                element_random_words(e0 + j, u, seed).w[(e0 + j) & 3u], s, q, flags);
+                        else quantize(y, qc, sign_shift, s, q, flags);
+                        q = __fmul_rn(q, inv_gain);
+                        mo[j] = (flags & 1u) ? 0.0f : __fsub_rn(v, q);
+                        n_nonfinite += flags & 1u;
+                        n_clamped += (flags >> 1) & 1u;
+                        s &= (uint32_t)(kWideMaxA - 1);
+                        len_sum += code_len(s, s_fast[s]);
+                        half[j + 2u * (j >> 6)] = (uint16_t)s;
+                    }
+                }
+            }
+        }
+        if (n_nonfinite)
+            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NONFINITE), (unsigned long long)n_nonfinite);
+        if (n_clamped)
+            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CLAMPED), (unsigned long long)n_clamped);
+    }
+    len_sum = w_wave_sum(len_sum);
+    if (lane == 0) s_cbits[wave] = len_sum;      // 0 for a wavefront without a chunk
+    w_lds_barrier();
+
+    // ---- 2. the workgroup's size is published, its predecessors' are requested ---------------------------------------
+    uint32_t before = 0, own = 0, pay = 0;       // 32-bit-rounded sizes of the chunks ahead of this one, of all; exact size
+#pragma unroll
+    for (int k = 0; k < kWWaves; ++k) {
+        const uint32_t cbits = s_cbits[k], a = (cbits + 31u) & ~31u;
+        if ((uint32_t)k < wave) before += a;
+        own += a;
+        pay += cbits;
+    }
+    if (t == 0) lookback_publish(state, b, own);   // by the lane that looks back: an entry has one writer
+    const uint64_t lb_first = wave == 0 ? lookback_first(state, b, lane) : 0ull;
+
+    // ---- 3. wavefront = chunk, lane = sub-chunk: the chunk's words, from a word boundary on ----------------------
+    const int first = (int)lane * kSub;
+    const int cnt = (int)n - first < 0 ? 0 : ((int)n - first > kSub ? kSub : (int)n - first);
+    uint32_t symw[kSub / 2];
+    WCoded coded = {0u, 0u, 0u, kRowsOk};
+    if (active) {
+        const uint32_t *row32 = region + lane * kWRowStride;
+#pragma unroll
+        for (int jj = 0; jj < kSub / 2; ++jj) symw[jj] = row32[jj] & kWSymMask2;   // (beyond a ragged chunk's end: stale words)
+        w_wave_sync_lds();   // every lane holds its symbols: the rows are free
+        coded = w_code_chunk(symw, cnt, whole, s_fast, book, region, lane, status);
+        sub_bits[((uint64_t)u * lay.nchunks + wg.first + wave) * kSubsPerChunk + lane] = (uint16_t)coded.bits;
+        if (coded.rows == kRowsOk) w_rows_to_window(region, lane, coded.bits, coded.excl, coded.nwords);
+    }
+    if (wave == 0) {
+        uint64_t prefix;
+        const bool ok = lookback_collect(state, b, lb_first, lane, spin_limit, prefix);
+        if (lane == 0) {
+            lookback_finish(state, b, ok, prefix, own, status);
+            s_prefix = prefix;
+            s_stalled = ok ? 0u : 1u;
+            atomicAdd(reinterpret_cast<unsigned long long *>(payload_bits + u), (unsigned long long)pay);
+        }
+    }
+    w_lds_barrier();
+    if (!active || s_stalled) return;   // whole wavefronts; no workgroup barrier below
+
+    // ---- 4. the chunk's words go to their place in the stream -------------------------------------------------------
+    const uint64_t off = s_prefix + before, c = wg.first + wave;
+    if (lane == 0) {
+        uint64_t *co = chunk_offset + (uint64_t)u * (lay.nchunks + 1);
+        co[c] = off;
+        if (c + 1 == lay.nchunks) co[lay.nchunks] = off + ((uint64_t)coded.nwords << 5);
+    }
+    const uint64_t off_words = off >> 5;
+    if (off_words + coded.nwords > words_stride) {
+        if (lane == 0) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CAPACITY), 1ull);
+        return;
+    }
+    w_store_chunk(coded, symw, cnt, s_fast, book, region, lane, words + (uint64_t)u * words_stride + off_words);
 }
 
 // ---- launchers ----------------------------------------------------------------------------------------------
@@ -978,10 +1235,43 @@ hipError_t launch_build_books_wide(BookWide *books, uint32_t nbooks, uint32_t A,
     return hipGetLastError();
 }
 
+// The single sweep's look-back entries, a ticket counter in front of every user's.
+static uint64_t sweep_entries(const Layout &lay, const WideCut &cut) { return (uint64_t)lay.U * (cut.nwg_small + 1ull); }
+
+// A held code whose symbols and counts nobody asks for is coded in one sweep: it moves 12 bytes an element beside the
+// streams, the three steps 16.  They keep the stochastic conversion of layers off the four-element grid (a vector's four
+// random words are one block of the generator), and a plan whose workgroups are so many, with tables that change every
+// few elements, that their entries do not fit the workspace laid out for the three steps.
+static bool sweep_fits(const Layout &lay, const WideCut &cut, const co3_encode_args &a)
+{
+    return a.mode == CO3_BOOK_FIXED && !a.symbols && !a.hist && lay.nchunks &&
+           (a.rounding != CO3_ROUND_STOCHASTIC || lay.vec_aligned) &&
+           sweep_entries(lay, cut) * sizeof(uint64_t) + 256 <= wide_workspace_bytes(lay);
+}
+
 hipError_t launch_encode_wide(const Layout &lay, const WideCut &cut, const co3_encode_args &a, BookWide *books, void *workspace,
                               hipStream_t s)
 {
     if (lay.U == 0) return hipSuccess;
+    if (sweep_fits(lay, cut, a)) {
+        uint64_t *lookback = reinterpret_cast<uint64_t *>((reinterpret_cast<uintptr_t>(workspace) + 255u) & ~(uintptr_t)255u);
+        const uint64_t nlb = sweep_entries(lay, cut);
+        {
+            ProfScope prof(K_ZERO, s);
+            hipLaunchKernelGGL(k_zero_wide, dim3((uint32_t)((nlb + 255) / 256)), dim3(256), 0, s, lookback, nlb, a.payload_bits,
+                               lay.U);
+        }
+        ProfScope prof(K_FUSED, s);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(cut.nwg_small, lay.U), dim3(kWThreads), 0, s, lay, a.g, a.m, a.m_out, a.row_stride,
+                               a.gamma, a.seed, static_cast<const BookWide *>(books), lookback, cut.nwg_small,
+                               lookback_polls(), a.chunk_offset, a.sub_bits, a.payload_bits, a.words, a.words_stride,
+                               a.status, cut.runs, cut.nrun);
+        };
+        if (a.rounding == CO3_ROUND_STOCHASTIC) launch(k_encode_wide<true>);
+        else launch(k_encode_wide<false>);
+        return hipGetLastError();
+    }
     const uint64_t sym_stride = symbol_row_stride(lay.d);
     const uint64_t hist_n = (uint64_t)lay.nbooks * lay.A, hist_rep_n = (uint64_t)kHistGlobalRep * hist_n;
     uintptr_t p = (reinterpret_cast<uintptr_t>(workspace) + 255u) & ~(uintptr_t)255u;
@@ -1002,7 +1292,7 @@ hipError_t launch_encode_wide(const Layout &lay, const WideCut &cut, const co3_e
         const uint64_t zero_n = bits_in_sweep ? (w_up256(hist_rep_n * sizeof(uint64_t)) + w_up256((size_t)lay.U * lay.nchunks * sizeof(uint32_t))) / sizeof(uint64_t)
                                               : hist_rep_n;
         ProfScope prof(K_ZERO, s);
-        hipLaunchKernelGGL(k_zero_wide, dim3((uint32_t)((zero_n + 255) / 256)), dim3(256), 0, s, hist_rep, zero_n);
+        hipLaunchKernelGGL(k_zero_wide, dim3((uint32_t)((zero_n + 255) / 256)), dim3(256), 0, s, hist_rep, zero_n, a.payload_bits, 0u);
     }
     if (lay.d) {
         ProfScope prof(K_QUANTIZE, s);

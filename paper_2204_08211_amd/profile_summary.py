@@ -30,7 +30,8 @@ TIMING_NAME = {"k_pack_chunk": "k_pack", "k_chunk_bits_hist": "k_chunk_bits", "k
                # the kernels for 16-bit symbols are timed under the names of the steps they take
                "k_quantize_wide": "k_quantize", "k_reduce_hist_wide": "k_reduce_hist", "k_build_books_wide": "k_build_books",
                "k_chunk_bits_wide": "k_chunk_bits", "k_pack_wide": "k_pack", "k_aggregate_wide": "k_aggregate",
-               "k_decode_wide": "k_decode", "k_zero_wide": "k_zero_u64"}
+               "k_aggregate_wide_own": "k_aggregate", "k_decode_wide": "k_decode", "k_zero_wide": "k_zero_u64",
+               "k_encode_wide": "k_encode_fused"}
 
 
 def short_name(kernel):

@@ -1316,3 +1316,46 @@ def test_single_sweep_on_both_sides_of_the_forms_line(U, groups, seed, hist, sma
     skip = (-buf.workspace.data_ptr()) % 256
     ticket = int(buf.workspace[skip:skip + 4].cpu().numpy().view(np.uint32)[0])
     assert ticket == (plan.num_chunks if small else groups)
+
+
+@pytest.mark.parametrize("U,per_user,seed,grid,code", [(1, False, None, 1, "near"), (3, True, None, 1, "near"), (2, False, 9, 4, "near"),
+                                                       (2, True, 9, 1, "near"), (2, False, None, 1, "long"), (40, False, None, 4, "long")])
+def test_wide_single_sweep(U, per_user, seed, grid, code):
+    # the wide alphabets' single sweep: whole, shifted and ragged chunks, runs of layers under one table that end inside
+    # a workgroup, an empty layer; codes of more than 25 bits (their lengths come from device memory, rows overflow); the
+    # stochastic conversion on the four-element grid, and off it (which keeps the three steps)
+    from paper_2204_08211_amd import binding as B
+    E, M, A = 4, 5, 1024
+    seg_len = [4096 * 5 + 4 * 3, 0, 4096 * 2, 8, 4096 + 4092, 4096 * 3 + 20, 4]
+    seg_book = [0, 1, 1, 1, 0, 0, 2]
+    if grid == 1:
+        seg_len = [n + (k % 3) for k, n in enumerate(seg_len)]
+    d = sum(seg_len)
+    rng = np.random.default_rng(3000 + U)
+    bias = rng.integers(14, 17, (U, len(seg_len))).astype(np.int32)
+    g = (rng.laplace(size=(U, d)) * 2.0 ** -6).astype(np.float32)
+    m = (rng.laplace(size=(U, d)) * 2.0 ** -8).astype(np.float32)
+    g[0, 2:6] = [np.nan, np.inf, -1e30, 0.0]
+    kw = dict(E=E, M=M, U=U, d=d, bias=bias, seg_len=seg_len, seg_book=seg_book, per_user_books=per_user)
+    weights = gu.oracle_round(kw, g, m, 0.9)["hist"] + 1          # a held code that is not this round's
+    if code == "long":      # the lightest symbols get codes of up to 40 bits, among them one that is met often
+        order = np.argsort(weights[0], kind="stable")
+        weights[0, order] = np.sort(rng.integers(1 << 40, 1 << 41, A).astype(np.uint64))
+        weights[0, order[:40]] = np.uint64(1) << np.arange(40, dtype=np.uint64)
+        weights[0, [order[7], order[-1]]] = weights[0, [order[-1], order[7]]]
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=weights, stochastic_seed=seed)
+    gpu, (plan, books, buf, gt, mt) = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=weights, single_sweep=True, stochastic_seed=seed)
+    gu.compare_round(gpu, ref, d, single_sweep=True)
+    if seed is None:
+        victim = int(np.argsort(ref["hist"][0])[-2])              # a symbol without a code; too short a stream buffer
+        w = weights.copy()
+        w[0, victim] = 0
+        short = min(x.size for x in ref["words"]) - 1500
+        gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w, want_decode=False, single_sweep=True)
+        assert int(gpu["status_encode"][B.STAT_NOCODE]) == int(ref["hist"][0][victim])
+        gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=weights, want_decode=False, single_sweep=True, words_stride=short)
+        assert int(gpu["status_encode"][B.STAT_CAPACITY]) >= U
+        gu.assert_bits_equal(gpu["chunk_offset"], ref["chunk_offset"], "offsets still exact")
+        gu.assert_bits_equal(gpu["m_new"], ref["m_new"], "memory")
+        for u in range(U):
+            gu.assert_bits_equal(gpu["words"][u, :short - 2000], ref["words"][u][:short - 2000], "what fits is written")
