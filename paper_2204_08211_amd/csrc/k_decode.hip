@@ -474,7 +474,79 @@ __device__ inline void aggregate_packed(const AggPart &p)
     }
 }
 
-// Shared by the two kernels below: the wavefront's chunk.  kAcross: the wavefronts of a workgroup share a chunk and split
+// Users whose symbols meet in LDS at most: two a wavefront, 5 KB each, so that sixteen wavefronts still fit a CU.  (Four a
+// wavefront leave room for eight: sixteen users of 12 M elements in [1,5,2], a round 600 us from the sums, 794 this way.)
+constexpr uint32_t kStageUsers = 2 * kAggWaves;
+// The same sums where the workgroup's wavefronts decode all users in one turn: the symbols meet in LDS, an eighth of what
+// the fp64 sums would be, and every thread adds up its elements in the users' order, where the sums would be added up by
+// one wavefront after the other (the others at barriers).  A small launch is one workgroup's way: a round of three users of
+// 63 112 elements in [1,4,1] with a scale 29.5 -> 23.2 us, of four of 600 001 in [1,5,2] with a table each 47 -> 40, of ten
+// of 10^6 in [1,4,3] with a scale 86 -> 70, of sixteen of 300 001 in [1,5,2] 66 -> 60.
+template <int kUsers, bool kGain>
+__device__ inline void aggregate_staged(const AggPart &p)
+{
+    const Layout &lay = p.lay;
+    double *s_scale = reinterpret_cast<double *>(p.smem + lay.U * kStageWords);   // [kStageUsers], behind the symbols
+    float *s_inv_gain = reinterpret_cast<float *>(s_scale + kStageUsers);         // [kStageUsers]
+    const uint32_t t = threadIdx.x, lane = t & 63u;
+    u32x16 pk[kUsers];
+#pragma unroll
+    for (int s = 0; s < kUsers; ++s) pk[s] = 0u;
+    each_user<true, 2, kUsers>(
+        p, 0, kUsers,
+        [&](uint32_t i, uint32_t, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
+            decode_started<kGain, false>(st, p.g, ix, lay.A, tab, book, SymbolEntry{},
+                                         [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(pk[i], gr, e); });
+        });
+    if constexpr (!kGain) round_to_nearest();
+    int bias = 0;
+    float inv_gain = 1.0f;
+    if (t < lay.U) {   // a workgroup has as many threads
+        const uint64_t pair = (uint64_t)t * lay.nseg + p.g.seg;
+        bias = lay.bias[pair];
+        if (kGain) inv_gain = lay.gain[2 * pair + 1];
+    }
+    __syncthreads();   // tables and windows are done with
+    if (t < lay.U) {
+        s_scale[t] = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
+        s_inv_gain[t] = inv_gain;
+    }
+#pragma unroll
+    for (int s = 0; s < kUsers; ++s) {
+        const uint32_t u = p.wave + (uint32_t)s * p.waves;
+        if (u >= lay.U) break;
+        uint32_t *row = p.smem + u * kStageWords + lane * kStageStride;
+#pragma unroll
+        for (int i = 0; i < kSub / 16; ++i)
+            *reinterpret_cast<u32x4 *>(row + 4 * i) = u32x4{pk[s][4 * i], pk[s][4 * i + 1], pk[s][4 * i + 2], pk[s][4 * i + 3]};
+    }
+    __syncthreads();
+    const SymbolValue val(lay.E, lay.M);
+    const double inv_u = 1.0 / (double)lay.U;
+    const bool whole = p.g.n == (uint32_t)kChunk;
+    for (uint32_t k = t; k < (uint32_t)kChunk / 4; k += 64 * p.waves) {   // elements 4 k .. 4 k + 3
+        const uint32_t *at = p.smem + (k >> 4) * kStageStride + (k & 15u);
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (uint32_t u = 0; u < lay.U; ++u) {
+            const uint32_t w = at[u * kStageWords];
+            const double scale = s_scale[u];
+            const float inv = s_inv_gain[u];
+#pragma unroll
+            for (uint32_t b = 0; b < 4; ++b) {
+                const double v = (double)val(w, 8u * b);
+                if constexpr (kGain) sum[b] += (double)__fmul_rn((float)(v * scale), inv);   // fl32(value * inv_gain)
+                else sum[b] = __builtin_fma(v, scale, sum[b]);   // the product is exact
+            }
+        }
+        double avg[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) avg[b] = sum[b] * inv_u;
+        write_four(p.g, p.a, 4 * k, avg, whole);
+    }
+}
+
+// Shared by the kernels below: the wavefront's chunk.  kAcross: the wavefronts of a workgroup share a chunk and split
 // the users, else each has a chunk.
 template <bool kAcross>
 __device__ inline AggPart agg_part(const Layout &lay, const AggArgs &a, uint32_t *smem, uint32_t all_at)
@@ -530,6 +602,16 @@ __global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggrega
     aggregate_packed<kUsers, kGain, kAcross>(p);
 }
 
+// The same where a workgroup's wavefronts take all users of a chunk in one turn, one or two each.
+template <int kUsers, bool kGain>
+__global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggregate_staged(Layout lay, AggArgs a)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    const AggPart p = agg_part<true>(lay, a, smem, 0);
+    if constexpr (!kGain) round_toward_zero();
+    aggregate_staged<kUsers, kGain>(p);
+}
+
 hipError_t launch_decode(const Layout &lay, const co3_decode_args &a, const BookDev *books, hipStream_t s)
 {
     if (lay.U == 0 || lay.nchunks == 0) return hipSuccess;
@@ -579,7 +661,12 @@ static hipError_t launch_aggregate_packed(const Layout &lay, const AggArgs &a, u
         return launch_aggregate_k(k_aggregate<kPackUsers, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u);
     }
     size_t lds = aggregate_lds(lay, false, waves, true);
-    if (lay.U <= waves) return launch_aggregate_k(k_aggregate<1, kGain, true>, lay, waves, true, lds, s, a, 0u);
+    if (lay.U <= 2 * waves) {
+        const size_t stage = 4 * (size_t)lay.U * kStageWords + kStageUsers * (sizeof(double) + sizeof(float));
+        if (stage > lds) lds = stage;
+        if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1, kGain>, lay, waves, true, lds, s, a);
+        return launch_aggregate_k(k_aggregate_staged<2, kGain>, lay, waves, true, lds, s, a);
+    }
     uint32_t all_at = 0;
     if (lay.U > waves * kPackUsers) {   // several turns: the sums need a place of their own
         all_at = (uint32_t)((lds + 15) / 16 * 4);

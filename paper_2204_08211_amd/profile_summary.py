@@ -27,6 +27,7 @@ from paper_2204_08211_amd import build as hip_build
 
 # kernels whose name in the library's event timing (co3_profile_end) differs from the function's
 TIMING_NAME = {"k_pack_chunk": "k_pack", "k_chunk_bits_hist": "k_chunk_bits", "k_aggregate_int": "k_aggregate",
+               "k_aggregate_staged": "k_aggregate",
                # the kernels for 16-bit symbols are timed under the names of the steps they take
                "k_quantize_wide": "k_quantize", "k_reduce_hist_wide": "k_reduce_hist", "k_build_books_wide": "k_build_books",
                "k_chunk_bits_wide": "k_chunk_bits", "k_pack_wide": "k_pack", "k_aggregate_wide": "k_aggregate",

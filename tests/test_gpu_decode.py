@@ -180,3 +180,48 @@ def test_wide_codes_the_table_does_not_resolve(E, M, kind):
     for made in (None, books):
         gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w[None, :], max_code_len=64, books=made)
         gu.compare_round(gpu, ref, d)
+
+
+@pytest.mark.parametrize("U", [2, 3, 8, 9, 16, 17])
+@pytest.mark.parametrize("gain", [False, True])
+@pytest.mark.parametrize("own", [False, True])
+def test_average_whose_users_meet_in_lds(U, gain, own):
+    # formats without integer sums, and plans with a scale: a user per wavefront, two, and one more than meet in LDS; whole,
+    # shifted and ragged chunks.  The fp64 sums in the users' order of the values that co3_decode gives, rounded once.
+    import torch
+    from paper_2204_08211_amd import binding as B
+    E, M, seg_len = 5, 2, [4096 + 77, 5, 2 * 4096]
+    d, nseg = sum(seg_len), len(seg_len)
+    rng = np.random.default_rng(7000 + U)
+    bias = rng.integers(20, 29, (U, nseg)).astype(np.int32)
+    plan = B.Plan(E=E, M=M, U=U, d=d, bias=bias, seg_len=seg_len, seg_book=[0, 1, 0], per_user_books=own)
+    if gain:
+        inv = (2.0 ** rng.uniform(-0.5, 0.5, (U, nseg))).astype(np.float32)
+        plan.set_gain((np.float32(1.0) / inv).astype(np.float32), inv)
+    dev = torch.device("cuda:0")
+    stride = (d + 3) // 4 * 4
+    g = torch.zeros((U, stride), dtype=torch.float32, device=dev)
+    g[:, :d] = torch.from_numpy((rng.laplace(size=(U, d)) * 1e-3).astype(np.float32)).to(dev)
+    m = torch.zeros_like(g)
+    books = B.co3_build_codebook(E, M, plan.num_books, None)
+    buf = B.RoundBuffers(plan, dev, max_code_len=32)
+    buf.status.zero_()
+    B.co3_encode(plan, books, g, m, m, 0.9, buf, mode=BOOK_EMPIRICAL)
+    q = torch.zeros((U, stride), dtype=torch.float32, device=dev)
+    B.co3_decode(plan, books, buf, q=q)
+    out = torch.full((d,), float("nan"), dtype=torch.float32, device=dev)
+    model = torch.from_numpy(rng.standard_normal(d).astype(np.float32)).to(dev)
+    before = model.cpu().numpy().astype(np.float64)
+    B.co3_ps_aggregate(plan, books, buf, out, model=model, eta=0.25)
+    torch.cuda.synchronize()
+    assert not buf.status.cpu().numpy().any()
+    total = np.zeros(d)
+    for row in q[:, :d].cpu().numpy().astype(np.float64):
+        total += row
+    mean = total * (1.0 / U)
+    if U <= 16 or not gain:      # (scaled values are no exact sums; beyond 16 users their order is not defined)
+        gu.assert_bits_equal(out.cpu().numpy(), mean.astype(np.float32), "average")
+        gu.assert_bits_equal(model.cpu().numpy(), (before - 0.25 * mean).astype(np.float32), "model")
+    else:
+        size = np.abs(q[:, :d].cpu().numpy()).mean(axis=0)
+        assert np.all(np.abs(out.cpu().numpy() - mean) <= 2.0 ** -23 * np.maximum(np.abs(mean), 2.0 ** -20 * size))
