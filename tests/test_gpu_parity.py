@@ -1359,3 +1359,29 @@ def test_wide_single_sweep(U, per_user, seed, grid, code):
         gu.assert_bits_equal(gpu["m_new"], ref["m_new"], "memory")
         for u in range(U):
             gu.assert_bits_equal(gpu["words"][u, :short - 2000], ref["words"][u][:short - 2000], "what fits is written")
+
+
+def test_wide_single_sweep_bounded_wait_gives_up():
+    # the wait's bound set to zero: a workgroup that gives up writes no stream words and no offsets and is counted;
+    # memory, sub-chunk bits and payload are complete, and the offsets that are written are the oracle's
+    from paper_2204_08211_amd import binding as B
+    E, M, U, d = 4, 5, 2, 4096 * 4 * 300 + 17
+    rng = np.random.default_rng(78)
+    g = (rng.laplace(size=(U, d)) * 1e-3).astype(np.float32)
+    m = np.zeros_like(g)
+    bias = syn.bias_for_max(np.abs(g).max(), E)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias]] * U)
+    weights = gu.oracle_round(kw, g, m, 0.9)["hist"]
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=weights)
+    B.set_lookback_polls(0)
+    try:
+        gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=weights, single_sweep=True, want_decode=False)
+    finally:
+        B.set_lookback_polls(B.LOOKBACK_POLLS_DEFAULT)
+    assert int(gpu["status_encode"][B.STAT_STALLED]) > 0
+    gu.assert_bits_equal(gpu["m_new"], ref["m_new"], "memory m'")
+    gu.assert_bits_equal(gpu["sub_bits"], ref["sub_bits"], "sub-chunk bits")
+    gu.assert_bits_equal(gpu["payload_bits"], ref["payload_bits"], "payload bits")
+    written = gpu["chunk_offset"] != np.uint64(0xFFFFFFFFFFFFFFFF)
+    assert written.any() and not written.all()
+    assert np.array_equal(gpu["chunk_offset"][written], ref["chunk_offset"][written])
