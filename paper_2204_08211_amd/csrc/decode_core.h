@@ -94,6 +94,14 @@ __device__ inline T here(T x)
     asm volatile("" : "+v"(x));
     return x;
 }
+// The same for sixteen words, one by one: they need not lie side by side.  fp32 arithmetic on decoded symbols in registers
+// stays behind round_to_nearest() by taking them from here: the compiler knows no order between MODE and arithmetic.
+template <class Words>
+__device__ inline void words_here(Words &w)
+{
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = here(w[i]);
+}
 
 // Where the entries of a code lie in LDS.  Entry: code length in bits 0..7 (kLenSlow: slow path), above it what the sink
 // asks for.  kBytes 4 or 2 per entry.  The table lies at a multiple of its size.
@@ -109,11 +117,10 @@ struct DecTable {
         shift = 24u - nbits - (kBytes == 4 ? 2u : 1u);
         mask = here(dec_table_entries(A) * (uint32_t)kBytes - (uint32_t)kBytes);   // (v_and_or_b32 takes one scalar operand)
     }
-    // u is a window's complement.  kTrunc: the rounding mode is not set, the conversion has to be exact
-    template <bool kTrunc>
+    // u is a window's complement, whole: an entry of a code of 25 bits or more depends on its low byte too
     __device__ inline uint32_t operator()(uint32_t u) const
     {
-        const float f = (float)(kTrunc ? u & 0xffffff00u : u);   // (kTrunc: u < 256 takes the slow path)
+        const float f = (float)u;
         const uint32_t a = ((__float_as_uint(f) >> shift) & mask) | base;
         if constexpr (kBytes == 4) return *(const lds_u32 *)a;
         else return *(const lds_u16 *)a;
@@ -148,7 +155,6 @@ struct WideDecTable {
         off = 23u - bits;
         width = here(bits + 5u);   // (v_bfe_u32 takes one scalar operand)
     }
-    template <bool kTrunc>
     __device__ inline uint32_t operator()(uint32_t u) const
     {
         const float f = (float)(u > (2u << kWideTabLow) ? u : 2u << kWideTabLow);   // the lowest binade holds nothing
@@ -307,7 +313,7 @@ __device__ inline void refill(Stream &st, const ChunkIndex &ix, uint32_t bits)
 // Symbols j0 .. j0 + 7, of which those from cnt on give the entry 0 and take no bits (full: cnt is kSub in every lane).
 // Where bit 5, 6 or 7 of the result is set the lane's entries are not to be used: two symbols of 32 bits or more
 // together, or a code the table does not hold.  n0: where the group started.
-template <bool kTrunc, class Table>
+template <class Table>
 __device__ inline uint32_t fast_group(Stream &st, uint32_t (&e)[kGroup], uint32_t &n0, int j0, const Table &tab, bool full)
 {
     const uint32_t least = 32u * (st.row0 - 1u);   // (a damaged stream only)
@@ -316,8 +322,8 @@ __device__ inline uint32_t fast_group(Stream &st, uint32_t (&e)[kGroup], uint32_
 #pragma unroll
     for (int b = 0; b < kGroup; b += 2) {
         const uint32_t u = st.window(N);
-        const uint32_t x = tab.template operator()<kTrunc>(u);
-        const uint32_t y = tab.template operator()<kTrunc>(u << (x & 31u));
+        const uint32_t x = tab(u);
+        const uint32_t y = tab(u << (x & 31u));
         e[b] = x;
         e[b + 1] = y;
         const uint32_t both = x + y;   // bits 0..7: the two lengths, up to 64
@@ -339,7 +345,7 @@ __device__ inline uint32_t fast_group(Stream &st, uint32_t (&e)[kGroup], uint32_
 
 // The exact decoder, for the lanes `redo` of a group that started at n0: one window per symbol; a code the table does
 // not hold is searched by all lanes together, lane l comparing the window with the codes of l + 1 bits.
-template <bool kTrunc, class Table, class Book, class Value>
+template <class Table, class Book, class Value>
 __device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0, bool redo, int j0, const Table &tab,
                                   const Book *__restrict__ book, Value value)
 {
@@ -351,7 +357,7 @@ __device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0
         const uint32_t least = 32u * (st.row0 - 1u);
         const uint32_t n = st.N > least ? st.N : least;
         const uint32_t u0 = st.window(n), u1 = st.window(n - 32u);
-        uint32_t x = tab.template operator()<kTrunc>(u0);
+        uint32_t x = tab(u0);
         if (on && (x & 0xffu) == kLenSlow) x = tab.search(u0, book);
         uint64_t todo = __ballot(on && (x & 0xffu) == kLenSlow);
         while (todo) {
@@ -404,7 +410,7 @@ __device__ inline void finish_chunk(const Stream &st, const ChunkIndex &ix, uint
 
 // on_group(gr, e) gets the entries of symbols 8 gr .. 8 gr + 7 of every lane, gr = 0 .. 7.  kUnroll: gr is a constant
 // there (sums in registers), at eight times the code, which a launch of few workgroups waits for.
-template <bool kTrunc, bool kUnroll, class Table, class Book, class Value, class OnGroup>
+template <bool kUnroll, class Table, class Book, class Value, class OnGroup>
 __device__ inline void decode_started(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t A, const Table &tab,
                                       const Book *__restrict__ book, Value value, OnGroup on_group)
 {
@@ -412,9 +418,9 @@ __device__ inline void decode_started(Stream &st, const ChunkGeom &g, const Chun
     auto group = [&](int gr) {
         uint32_t e[kGroup], n0;
         if (__builtin_expect(part, 0)) refill<Table::kMaxRows>(st, ix, group_bits(A));
-        const uint32_t over = fast_group<kTrunc>(st, e, n0, gr * kGroup, tab, full);
+        const uint32_t over = fast_group(st, e, n0, gr * kGroup, tab, full);
         const bool redo = (over & 0xe0u) != 0u;
-        if (__builtin_expect(__any(redo), 0)) slow_group<kTrunc>(st, e, n0, redo, gr * kGroup, tab, book, value);
+        if (__builtin_expect(__any(redo), 0)) slow_group(st, e, n0, redo, gr * kGroup, tab, book, value);
         on_group(gr, e);
     };
     if constexpr (kUnroll) {

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
             todo = false;
             Stream st;
             start_chunk<kRowsByte>(st, g, ix, lds_address(win), window_rows(lay.A));
-            decode_started<false, false>(st, g, ix, lay.A, tab, book, [](uint32_t s) { return s << 8; },
+            decode_started<false>(st, g, ix, lay.A, tab, book, [](uint32_t s) { return s << 8; },
                                   [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(packed, gr, e); });
             finish_chunk(st, ix, status);
         }
@@ -384,7 +384,7 @@ __device__ inline void aggregate_int(const AggPart &p, int bias_hi, bool wide)
         [&](uint32_t, uint32_t u, const ChunkIndex &ix, Stream &st, const DecTable<4> &tab, const BookDev *book) {
             const int shift = bias_hi - (int)uniform((uint32_t)p.lay.bias[(uint64_t)u * p.lay.nseg + p.g.seg]);
             auto value = [E, M](uint32_t s) { return dec_value_bits(s, E, M); };
-            decode_started<false, true>(st, p.g, ix, p.lay.A, tab, book, value, [&](int gr, const uint32_t (&e)[kGroup]) {
+            decode_started<true>(st, p.g, ix, p.lay.A, tab, book, value, [&](int gr, const uint32_t (&e)[kGroup]) {
 #pragma unroll
                 for (int b = 0; b < kGroup; ++b)
                     sum[gr * kGroup + b] = here(sum[gr * kGroup + b] + (((int32_t)e[b] >> 8) << shift));
@@ -410,7 +410,7 @@ __device__ inline void aggregate_spread(const AggPart &p)
             p, 0, users_each(p, kAcross),
             [&](uint32_t, uint32_t u, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
                 u32x16 packed = 0u;
-                decode_started<false, false>(st, p.g, ix, p.lay.A, tab, book, SymbolEntry{},
+                decode_started<false>(st, p.g, ix, p.lay.A, tab, book, SymbolEntry{},
                                       [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(packed, gr, e); });
                 const int bias = (int)uniform((uint32_t)p.lay.bias[(uint64_t)u * p.lay.nseg + p.g.seg]);
                 const double scale = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
@@ -441,10 +441,14 @@ __device__ inline void aggregate_packed(const AggPart &p)
         each_user<kAcross, 2, kUsers>(
             p, u0, kUsers,
             [&](uint32_t i, uint32_t, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
-                decode_started<kGain, false>(st, p.g, ix, p.lay.A, tab, book, SymbolEntry{},
+                decode_started<false>(st, p.g, ix, p.lay.A, tab, book, SymbolEntry{},
                                              [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(pk[i], gr, e); });
             });
-        if constexpr (!kGain) round_to_nearest();
+        round_to_nearest();
+        if constexpr (kGain) {   // (the products below round)
+#pragma unroll
+            for (int s = 0; s < kUsers; ++s) words_here(pk[s]);
+        }
         double scale[kUsers];
         float inv_gain[kUsers];
 #pragma unroll
@@ -468,7 +472,7 @@ __device__ inline void aggregate_packed(const AggPart &p)
         const bool last = u0 + step * kUsers >= lay.U;
         write_sums<kAcross, double, 0, kSub>(p, 1.0, sum_of, u0 == 0, last);
         if (kAcross && !last) {
-            if constexpr (!kGain) round_toward_zero();
+            round_toward_zero();
             __syncthreads();
         }
     }
@@ -495,10 +499,10 @@ __device__ inline void aggregate_staged(const AggPart &p)
     each_user<true, 2, kUsers>(
         p, 0, kUsers,
         [&](uint32_t i, uint32_t, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
-            decode_started<kGain, false>(st, p.g, ix, lay.A, tab, book, SymbolEntry{},
+            decode_started<false>(st, p.g, ix, lay.A, tab, book, SymbolEntry{},
                                          [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(pk[i], gr, e); });
         });
-    if constexpr (!kGain) round_to_nearest();
+    round_to_nearest();
     int bias = 0;
     float inv_gain = 1.0f;
     if (t < lay.U) {   // a workgroup has as many threads
@@ -594,7 +598,7 @@ __global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggrega
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<kAcross>(lay, a, smem, all_at);
-    if constexpr (!kGain) round_toward_zero();
+    round_toward_zero();
     if constexpr (!kAcross) {
         if ((threadIdx.x & 63) == 0) p.s_book[p.wave] = p.g.book;
         __syncthreads();
@@ -608,7 +612,7 @@ __global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggrega
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<true>(lay, a, smem, 0);
-    if constexpr (!kGain) round_toward_zero();
+    round_toward_zero();
     aggregate_staged<kUsers, kGain>(p);
 }
 

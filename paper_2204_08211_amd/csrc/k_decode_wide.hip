@@ -35,7 +35,7 @@ __device__ inline void decode_wide(Stream &st, const ChunkGeom &g, const ChunkIn
 {
     WideDecTable tab;
     tab.init(lds_address(table), bits, lds_address(limits));
-    decode_started<false, false>(st, g, ix, A, tab, book, WideEntry{},
+    decode_started<false>(st, g, ix, A, tab, book, WideEntry{},
                                  [&](int gr, const uint32_t (&e)[kGroup]) { packed.group(gr, e); });
 }
 

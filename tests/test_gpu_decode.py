@@ -225,3 +225,55 @@ def test_average_whose_users_meet_in_lds(U, gain, own):
     else:
         size = np.abs(q[:, :d].cpu().numpy()).mean(axis=0)
         assert np.all(np.abs(out.cpu().numpy() - mean) <= 2.0 ** -23 * np.maximum(np.abs(mean), 2.0 ** -20 * size))
+
+
+@pytest.mark.parametrize("E,M", [(5, 2), (5, 1), (4, 3)])
+@pytest.mark.parametrize("U", [1, 3, 8, 13, 17, 40])
+@pytest.mark.parametrize("own", [False, True])
+def test_average_with_a_scale_and_words_of_25_to_31_bits(E, M, U, own):
+    # a held code with twenty words of one to twenty bits and many of 25 bits and more, which differ in the low byte of the
+    # window's leading bits; most elements have one of those.  With a scale: a wavefront per chunk, the users' symbols
+    # meeting in LDS, a turn and several turns of four a wavefront.  The average of the values that co3_decode gives.
+    import torch
+    from paper_2204_08211_amd import binding as B
+    rng = np.random.default_rng(900 + 10 * E + U)
+    A, nm, b0 = 1 << (1 + E + M), orc.num_magnitudes(E, M), 2 ** (E - 1) + 3
+    seg_len = [4096 + 77, 5, 2 * 4096]
+    d, nseg = sum(seg_len), len(seg_len)
+    emit = np.array([0] + [s for s in range(A) if 0 < (s & (A // 2 - 1)) < nm])
+    order = rng.permutation(emit)
+    w = np.zeros(A, np.uint64)
+    w[order[:18]] = [1 << (58 - i) for i in range(18)]
+    rest = order[18:]
+    w[rest] = [(1 << 33) >> (3 * (i * 3 // rest.size)) for i in range(rest.size)]    # three groups of equal weights
+    lens = orc.huffman_lengths(w)
+    assert ((lens >= 25) & (lens <= 31)).sum() > 20
+    plan = B.Plan(E=E, M=M, U=U, d=d, bias=np.full((U, nseg), b0, np.int32), seg_len=seg_len, seg_book=[0, 1, 0], per_user_books=own)
+    # (above sixteen users the order of the sums is not defined: powers of two, so that they are exact)
+    inv = (2.0 ** (rng.uniform(-0.5, 0.5, (U, nseg)) if U <= 16 else rng.integers(-1, 2, (U, nseg)))).astype(np.float32)
+    gain = (np.float32(1.0) / inv).astype(np.float32)
+    plan.set_gain(gain, inv)
+    grid = orc.grid(E, M, b0).astype(np.float64)
+    p = np.where(rng.random((U, d)) < 0.8, rng.choice(rest, (U, d)), rng.choice(emit, (U, d)))
+    v = grid[p & (A // 2 - 1)] * np.where(p >= A // 2, -1.0, 1.0) * np.repeat(inv.astype(np.float64), seg_len, axis=1)
+    dev = torch.device("cuda:0")
+    stride = (d + 3) // 4 * 4
+    g = torch.zeros((U, stride), dtype=torch.float32, device=dev)
+    g[:, :d] = torch.from_numpy(v.astype(np.float32)).to(dev)
+    m = torch.zeros_like(g)
+    books = B.co3_build_codebook(E, M, plan.num_books, np.tile(w, (plan.num_books, 1)))
+    buf = B.RoundBuffers(plan, dev, max_code_len=64)
+    B.co3_encode(plan, books, g, m, m, 0.9, buf, mode=BOOK_FIXED)
+    sym = torch.zeros(plan.symbols_bytes, dtype=torch.uint8, device=dev)
+    q = torch.zeros((U, stride), dtype=torch.float32, device=dev)
+    B.co3_decode(plan, books, buf, symbols=sym, q=q)
+    out = torch.full((d,), float("nan"), dtype=torch.float32, device=dev)
+    B.co3_ps_aggregate(plan, books, buf, out)
+    torch.cuda.synchronize()
+    assert not buf.status.cpu().numpy()[2:].any()      # (a top value times its scale may be clamped by a rounding)
+    gu.assert_bits_equal(gu._sym_numpy(B.symbols_2d(plan, sym)), gu._sym_numpy(buf.symbols_2d()), "decoded symbols")
+    assert np.mean(lens[gu._sym_numpy(buf.symbols_2d())] >= 25) > 0.5
+    total = np.zeros(d)
+    for row in q[:, :d].cpu().numpy().astype(np.float64):
+        total += row
+    gu.assert_bits_equal(out.cpu().numpy(), (total * (1.0 / U)).astype(np.float32), "average")
