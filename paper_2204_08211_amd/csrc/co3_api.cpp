@@ -247,7 +247,7 @@ int co3_plan_set_gain(co3_plan *plan, const float *gain, const float *inv_gain, 
     DeviceGuard guard(plan->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (hipMemcpyAsync(plan->d_gain, pairs.data(), sizeof(float) * pairs.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+        launch_mark_scaled(plan->lay, plan->d_segs, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return CO3_ERR_HIP;
     plan->facts.has_gain = any;
     return CO3_OK;
@@ -561,8 +561,9 @@ int co3_plan_set_gain_device(co3_plan *plan, const float *gain_pairs, void *stre
     if (!plan || !gain_pairs) return CO3_ERR_ARG;
     DeviceGuard guard(plan->device);
     const size_t n = (size_t)plan->lay.U * plan->lay.nseg;
-    if (hipMemcpyAsync(plan->d_gain, gain_pairs, sizeof(float) * 2 * n, hipMemcpyDeviceToDevice,
-                       static_cast<hipStream_t>(stream)) != hipSuccess)
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (hipMemcpyAsync(plan->d_gain, gain_pairs, sizeof(float) * 2 * n, hipMemcpyDeviceToDevice, s) != hipSuccess ||
+        launch_mark_scaled(plan->lay, plan->d_segs, s) != hipSuccess)
         return CO3_ERR_HIP;
     plan->facts.has_gain = true;   // the values are not read back: a scale is taken to be there until the host setter says otherwise
     return CO3_OK;

@@ -79,7 +79,7 @@ struct SegDev {
     uint64_t length;
     uint64_t chunk_start;  // index of the segment's first chunk within a user
     int32_t book;          // code table id within a user's (or the shared) set
-    int32_t pad;
+    int32_t scaled;        // whether a user's real-valued scale of the layer is not 1 (launch_mark_scaled)
 };
 
 // How the wide coder (k_wide.hip) cuts a user's chunks into workgroups: at every change of the code table, and after
@@ -131,13 +131,15 @@ __device__ inline SegDev load_segment(const SegDev *p)
     sd.length = e[1];
     sd.chunk_start = e[2];
     sd.book = (int32_t)(uint32_t)e[3];
+    sd.scaled = (int32_t)(uint32_t)(e[3] >> 32);
     return sd;
 }
 
 }  // namespace co3
 
 namespace co3 {
-// What the host knows of a plan beside its layout.
+// What the host knows of a plan beside its layout.  It chooses between kernels by that, for speed only: a captured launch may
+// be replayed when it is out of date, so every kernel looks at the device's tables.
 struct PlanFacts {
     bool has_gain = false;     // a gain other than (1, 1) was installed
     int32_t bias_spread = 0;   // how far the users' biases of a layer lie apart at most; 0 where they came from device memory
@@ -223,6 +225,8 @@ size_t scale_workspace_bytes(const Layout &lay);
 hipError_t launch_model_scale(const Layout &lay, const co3_gennorm_params *params, int32_t *bias, float *gain_pairs,
                               double *error, double *workspace, hipStream_t s);
 hipError_t launch_decode(const Layout &lay, const co3_decode_args &a, const BookDev *books, hipStream_t s);
+// says in every layer's entry whether the plan's gain table has a scale for it
+hipError_t launch_mark_scaled(const Layout &lay, SegDev *segs, hipStream_t s);
 hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3_aggregate_args &a, const BookDev *books,
                             hipStream_t s);
 // wide alphabets (k_wide.hip): the same steps with 16-bit symbols and tables in device memory

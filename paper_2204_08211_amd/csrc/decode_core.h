@@ -202,6 +202,7 @@ struct ChunkGeom {
     uint32_t n;       // elements in the chunk
     uint64_t e0;      // first element
     int32_t book;     // table id within a user's set
+    bool scaled;      // a user of the layer carries a real-valued scale
 };
 
 __device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
@@ -218,6 +219,7 @@ __device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
     const uint64_t left = sd.offset + sd.length - g.e0;
     g.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
     g.book = sd.book;
+    g.scaled = sd.scaled != 0;
     return g;
 }
 

@@ -296,13 +296,13 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
 // The sums leave the registers: of(j) is this lane's sum of element j as a T (j a constant in [J0, J1)), `unit` what a sum of 1 is
 // worth.  kAcross: they are added up over the workgroup's wavefronts, fp64 in their order.  Where the users come in
 // several turns (first .. last), p.s_all keeps the sums.  at_element: of j = 0.
-template <bool kAcross, class T, int J0, int J1, class Of>
+template <bool kAcross, class T, int J0, int J1, bool kFewRows = false, class Of>
 __device__ inline void write_sums(const AggPart &p, double unit, Of of, bool first = true, bool last = true, int at_element = 0)
 {
     const uint32_t t = threadIdx.x, lane = t & 63;
     const double inv_u = 1.0 / (double)p.lay.U;
     const bool whole = p.g.n == (uint32_t)kChunk;
-    constexpr int rows = sizeof(T) == 4 ? (kAcross ? 64 : 16) : (kAcross ? 16 : 8);
+    constexpr int rows = sizeof(T) == 4 ? (kAcross ? 64 : 16) : (kAcross ? 16 : 8) / (kFewRows ? 2 : 1);
     constexpr uint32_t per = rows / 4;   // groups of four elements per sub-chunk
     if constexpr (kAcross) {
 #pragma unroll
@@ -370,6 +370,14 @@ struct SymbolEntry {
     __device__ inline uint32_t operator()(uint32_t s) const { return s << 8; }
 };
 
+// sum + fl32(value * inv_gain) of a symbol; val: its value at exponent bias 127, times `scale` at its own.
+template <bool kGain>
+__device__ inline double add_value(float val, double scale, float inv_gain, double sum)
+{
+    if constexpr (kGain) return sum + (double)__fmul_rn((float)((double)val * scale), inv_gain);
+    return __builtin_fma((double)val, scale, sum);   // the product is exact
+}
+
 // Integer sums in units of 2^(1 - M - bias_hi), exact while they fit 32 bits; wide: the wavefronts' sums do, the
 // workgroup's need fp64.
 template <bool kAcross>
@@ -396,38 +404,51 @@ __device__ inline void aggregate_int(const AggPart &p, int bias_hi, bool wide)
     else write_sums<kAcross, int32_t, 0, kSub>(p, unit, [&](int j) { return sum[j]; });
 }
 
-// The same users where the biases lie too far apart for that: fp64 sums, of half of every sub-chunk at a time.
-template <bool kAcross>
+// The same users where the biases lie too far apart for that (or, kGain, where one carries a scale): fp64 sums, of one of kParts
+// parts of every sub-chunk at a time.
+template <bool kAcross, bool kGain, int kParts>
 __device__ inline void aggregate_spread(const AggPart &p)
 {
+    constexpr int kPart = kSub / kParts;
     const SymbolValue val(p.lay.E, p.lay.M);
 #pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        double sum[kSub / 2];
+    for (int part = 0; part < kParts; ++part) {
+        double sum[kPart];
 #pragma unroll
-        for (int i = 0; i < kSub / 2; ++i) sum[i] = 0.0;
+        for (int i = 0; i < kPart; ++i) sum[i] = 0.0;
         each_user<kAcross, 2, 0>(
             p, 0, users_each(p, kAcross),
             [&](uint32_t, uint32_t u, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
                 u32x16 packed = 0u;
                 decode_started<false>(st, p.g, ix, p.lay.A, tab, book, SymbolEntry{},
                                       [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(packed, gr, e); });
-                const int bias = (int)uniform((uint32_t)p.lay.bias[(uint64_t)u * p.lay.nseg + p.g.seg]);
+                const uint64_t pair = (uint64_t)u * p.lay.nseg + p.g.seg;
+                const int bias = (int)uniform((uint32_t)p.lay.bias[pair]);
                 const double scale = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
-#pragma unroll
-                for (int i = 0; i < kSub / 2; ++i) {
-                    const uint32_t w = half ? packed[(kSub / 2 + i) >> 2] : packed[i >> 2];
-                    sum[i] = here(__builtin_fma((double)val(w, 8u * (uint32_t)(i & 3)), scale, sum[i]));
+                const float inv_gain = kGain ? p.lay.gain[2 * pair + 1] : 1.0f;
+                if constexpr (kGain) {   // (the products with a scale round)
+                    round_to_nearest();
+                    words_here(packed);
                 }
+#pragma unroll
+                for (int i = 0; i < kPart; ++i) {
+                    uint32_t w = packed[i >> 2];
+#pragma unroll
+                    for (int k = 1; k < kParts; ++k) w = part == k ? packed[(k * kPart + i) >> 2] : w;
+                    sum[i] = here(add_value<kGain>(val(w, 8u * (uint32_t)(i & 3)), scale, inv_gain, sum[i]));
+                }
+                if constexpr (kGain) round_toward_zero();
             });
         round_to_nearest();
-        write_sums<kAcross, double, 0, kSub / 2>(p, 1.0, [&](int j) { return sum[j]; }, true, true, half * (kSub / 2));
+        write_sums<kAcross, double, 0, kPart>(p, 1.0, [&](int j) { return sum[j]; }, true, true, part * kPart);
         round_toward_zero();
         __syncthreads();
     }
 }
 
-// Sums in fp64, from the packed symbols of up to kUsers users at a time; any format, bias and gain.
+// Sums in fp64, from the packed symbols of up to kUsers users at a time; any format, bias and scale.  kGain: the host knows
+// of a scale; else a layer that carries one all the same goes the longer way at the end, in half the rows at a time, for
+// which the registers suffice.
 template <int kUsers, bool kGain, bool kAcross>
 __device__ inline void aggregate_packed(const AggPart &p)
 {
@@ -445,32 +466,39 @@ __device__ inline void aggregate_packed(const AggPart &p)
                                              [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(pk[i], gr, e); });
             });
         round_to_nearest();
-        if constexpr (kGain) {   // (the products below round)
-#pragma unroll
-            for (int s = 0; s < kUsers; ++s) words_here(pk[s]);
-        }
+        auto pair_of = [&](int s) {
+            const uint32_t u = u0 + (kAcross ? p.wave : 0u) + (uint32_t)s * step;
+            return (uint64_t)(u < lay.U ? u : 0u) * lay.nseg + p.g.seg;
+        };
         double scale[kUsers];
-        float inv_gain[kUsers];
 #pragma unroll
         for (int s = 0; s < kUsers; ++s) {
-            const uint32_t u = u0 + (kAcross ? p.wave : 0u) + (uint32_t)s * step;
-            const uint64_t pair = (uint64_t)(u < lay.U ? u : 0u) * lay.nseg + p.g.seg;
-            const int bias = (int)uniform((uint32_t)lay.bias[pair]);
+            const int bias = (int)uniform((uint32_t)lay.bias[pair_of(s)]);
             scale[s] = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
-            inv_gain[s] = kGain ? lay.gain[2 * pair + 1] : 1.0f;
         }
-        auto sum_of = [&](int j) {   // in the users' order
-            double sum = 0.0;
-#pragma unroll
-            for (int s = 0; s < kUsers; ++s) {
-                const double v = (double)val(pk[s][j >> 2], 8u * (uint32_t)(j & 3));
-                if constexpr (kGain) sum += (double)__fmul_rn((float)(v * scale[s]), inv_gain[s]);   // fl32(value * inv_gain)
-                else sum = __builtin_fma(v, scale[s], sum);   // the product is exact
-            }
-            return sum;
-        };
         const bool last = u0 + step * kUsers >= lay.U;
-        write_sums<kAcross, double, 0, kSub>(p, 1.0, sum_of, u0 == 0, last);
+        if (kGain || __builtin_expect(p.g.scaled, 0)) {
+            float inv_gain[kUsers];
+#pragma unroll
+            for (int s = 0; s < kUsers; ++s) inv_gain[s] = lay.gain[2 * pair_of(s) + 1];
+            auto sum_of = [&](int j) {   // in the users' order; the products round: not before the mode is back
+                double sum = 0.0;
+#pragma unroll
+                for (int s = 0; s < kUsers; ++s)
+                    sum = add_value<true>(val(here(pk[s][j >> 2]), 8u * (uint32_t)(j & 3)), scale[s], inv_gain[s], sum);
+                return sum;
+            };
+            write_sums<kAcross, double, 0, kSub, !kGain>(p, 1.0, sum_of, u0 == 0, last);
+        } else {
+            auto sum_of = [&](int j) {
+                double sum = 0.0;
+#pragma unroll
+                for (int s = 0; s < kUsers; ++s)
+                    sum = add_value<false>(val(pk[s][j >> 2], 8u * (uint32_t)(j & 3)), scale[s], 1.0f, sum);
+                return sum;
+            };
+            write_sums<kAcross, double, 0, kSub>(p, 1.0, sum_of, u0 == 0, last);
+        }
         if (kAcross && !last) {
             round_toward_zero();
             __syncthreads();
@@ -486,7 +514,7 @@ constexpr uint32_t kStageUsers = 2 * kAggWaves;
 // one wavefront after the other (the others at barriers).  A small launch is one workgroup's way: a round of three users of
 // 63 112 elements in [1,4,1] with a scale 29.5 -> 23.2 us, of four of 600 001 in [1,5,2] with a table each 47 -> 40, of ten
 // of 10^6 in [1,4,3] with a scale 86 -> 70, of sixteen of 300 001 in [1,5,2] 66 -> 60.
-template <int kUsers, bool kGain>
+template <int kUsers>
 __device__ inline void aggregate_staged(const AggPart &p)
 {
     const Layout &lay = p.lay;
@@ -508,7 +536,7 @@ __device__ inline void aggregate_staged(const AggPart &p)
     if (t < lay.U) {   // a workgroup has as many threads
         const uint64_t pair = (uint64_t)t * lay.nseg + p.g.seg;
         bias = lay.bias[pair];
-        if (kGain) inv_gain = lay.gain[2 * pair + 1];
+        inv_gain = lay.gain[2 * pair + 1];
     }
     __syncthreads();   // tables and windows are done with
     if (t < lay.U) {
@@ -531,16 +559,22 @@ __device__ inline void aggregate_staged(const AggPart &p)
     for (uint32_t k = t; k < (uint32_t)kChunk / 4; k += 64 * p.waves) {   // elements 4 k .. 4 k + 3
         const uint32_t *at = p.smem + (k >> 4) * kStageStride + (k & 15u);
         double sum[4] = {0.0, 0.0, 0.0, 0.0};
+        if (p.g.scaled) {
 #pragma unroll 4
-        for (uint32_t u = 0; u < lay.U; ++u) {
-            const uint32_t w = at[u * kStageWords];
-            const double scale = s_scale[u];
-            const float inv = s_inv_gain[u];
+            for (uint32_t u = 0; u < lay.U; ++u) {
+                const uint32_t w = at[u * kStageWords];
+                const double scale = s_scale[u];
+                const float inv = s_inv_gain[u];
 #pragma unroll
-            for (uint32_t b = 0; b < 4; ++b) {
-                const double v = (double)val(w, 8u * b);
-                if constexpr (kGain) sum[b] += (double)__fmul_rn((float)(v * scale), inv);   // fl32(value * inv_gain)
-                else sum[b] = __builtin_fma(v, scale, sum[b]);   // the product is exact
+                for (uint32_t b = 0; b < 4; ++b) sum[b] = add_value<true>(val(w, 8u * b), scale, inv, sum[b]);
+            }
+        } else {
+#pragma unroll 4
+            for (uint32_t u = 0; u < lay.U; ++u) {
+                const uint32_t w = at[u * kStageWords];
+                const double scale = s_scale[u];
+#pragma unroll
+                for (uint32_t b = 0; b < 4; ++b) sum[b] = add_value<false>(val(w, 8u * b), scale, 1.0f, sum[b]);
             }
         }
         double avg[4];
@@ -565,31 +599,37 @@ __device__ inline AggPart agg_part(const Layout &lay, const AggArgs &a, uint32_t
                    chunk_geom(lay, c), c, active, wave, kAcross ? blockDim.x >> 6 : (uint32_t)kAggWaves};
 }
 
-// co3_ps_aggregate with integer sums (formats of up to four exponent bits, no real-valued scale).
+// The layer's entry and biases say which way the sums take, and not the host: a captured launch may be replayed on a plan that
+// has been given a scale or other biases since.
+// Where each wavefront has a chunk of its own: tells the others its code table, and takes the way that serves them all, the
+// largest of theirs (they meet at barriers).
+__device__ inline int common_way(const AggPart &p, int way)
+{
+    if ((threadIdx.x & 63) == 0) {
+        p.s_book[p.wave] = p.g.book;
+        p.s_book[kAggWaves + p.wave] = way;
+    }
+    __syncthreads();
+    const int other = p.s_book[kAggWaves + (threadIdx.x & (kAggWaves - 1))];
+    return __any(other == 2) ? 2 : (__any(other == 1) ? 1 : 0);
+}
+
+// co3_ps_aggregate with integer sums (formats of up to four exponent bits; layers without a real-valued scale).
 template <bool kAcross>
 __global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate_int(Layout lay, AggArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
-    const uint32_t lane = threadIdx.x & 63;
     const AggPart p = agg_part<kAcross>(lay, a, smem, 0);
     round_toward_zero();
     int lo, hi;
     bias_range(lay, p.g.seg, lo, hi);
-    bool fits = int_sum_bits(lay, hi - lo, kAcross ? (lay.U + p.waves - 1) / p.waves : lay.U) <= 31;
+    const bool fits = int_sum_bits(lay, hi - lo, kAcross ? (lay.U + p.waves - 1) / p.waves : lay.U) <= 31;
     const bool wide = int_sum_bits(lay, hi - lo, lay.U) > 31;
-    if constexpr (!kAcross) {   // the wavefronts take the same way: they meet at barriers
-        if (lane == 0) {
-            p.s_book[p.wave] = p.g.book;
-            p.s_book[kAggWaves + p.wave] = fits ? 1 : 0;
-        }
-        __syncthreads();
-        for (int w = 0; w < kAggWaves; ++w) fits = fits && p.s_book[kAggWaves + w] != 0;
-    }
-    if (fits) {
-        aggregate_int<kAcross>(p, hi, wide);
-    } else {
-        aggregate_spread<kAcross>(p);
-    }
+    int way = p.g.scaled ? 2 : (fits ? 0 : 1);
+    if constexpr (!kAcross) way = common_way(p, way);
+    if (way == 0) aggregate_int<kAcross>(p, hi, wide);
+    else if (way == 1) aggregate_spread<kAcross, false, 2>(p);
+    else aggregate_spread<kAcross, true, 4>(p);
 }
 
 // co3_ps_aggregate for everything else.  kUsers: per wavefront and turn.
@@ -607,13 +647,27 @@ __global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggrega
 }
 
 // The same where a workgroup's wavefronts take all users of a chunk in one turn, one or two each.
-template <int kUsers, bool kGain>
+template <int kUsers>
 __global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggregate_staged(Layout lay, AggArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<true>(lay, a, smem, 0);
     round_toward_zero();
-    aggregate_staged<kUsers, kGain>(p);
+    aggregate_staged<kUsers>(p);
+}
+
+__global__ __launch_bounds__(64) void k_mark_scaled(Layout lay, SegDev *__restrict__ segs)
+{
+    bool any = false;
+    for (uint32_t u = threadIdx.x; u < lay.U; u += 64) any = any || lay.gain[2 * ((uint64_t)u * lay.nseg + blockIdx.x) + 1] != 1.0f;
+    any = __any(any);
+    if (threadIdx.x == 0) segs[blockIdx.x].scaled = any ? 1 : 0;
+}
+
+hipError_t launch_mark_scaled(const Layout &lay, SegDev *segs, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_mark_scaled, dim3(lay.nseg), dim3(64), 0, s, lay, segs);
+    return hipGetLastError();
 }
 
 hipError_t launch_decode(const Layout &lay, const co3_decode_args &a, const BookDev *books, hipStream_t s)
@@ -668,8 +722,8 @@ static hipError_t launch_aggregate_packed(const Layout &lay, const AggArgs &a, u
     if (lay.U <= 2 * waves) {
         const size_t stage = 4 * (size_t)lay.U * kStageWords + kStageUsers * (sizeof(double) + sizeof(float));
         if (stage > lds) lds = stage;
-        if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1, kGain>, lay, waves, true, lds, s, a);
-        return launch_aggregate_k(k_aggregate_staged<2, kGain>, lay, waves, true, lds, s, a);
+        if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1>, lay, waves, true, lds, s, a);
+        return launch_aggregate_k(k_aggregate_staged<2>, lay, waves, true, lds, s, a);
     }
     uint32_t all_at = 0;
     if (lay.U > waves * kPackUsers) {   // several turns: the sums need a place of their own
