@@ -197,6 +197,9 @@ __device__ inline void load_table(uint32_t *dst, const void *src, uint32_t bytes
     }
 }
 
+__device__ inline uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ inline uint64_t uniform(uint64_t x) { return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x); }
+
 struct ChunkGeom {
     uint32_t seg;
     uint32_t n;       // elements in the chunk
@@ -210,21 +213,20 @@ __device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
     uint32_t lo = 0, hi = lay.nseg;
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (lay.segs[mid].chunk_start <= c) lo = mid; else hi = mid;
+        if (uniform(lay.segs[mid].chunk_start) <= c) lo = mid; else hi = mid;
     }
+    // (said to be the same in all lanes: where they are loaded outside a kernel's own body the compiler does not know)
     ChunkGeom g;
     g.seg = lo;
     const SegDev sd = load_segment(lay.segs + lo);
-    g.e0 = sd.offset + (c - sd.chunk_start) * kChunk;
-    const uint64_t left = sd.offset + sd.length - g.e0;
+    g.e0 = uniform(sd.offset + (c - sd.chunk_start) * kChunk);
+    const uint64_t left = uniform(sd.offset + sd.length) - g.e0;
     g.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
-    g.book = sd.book;
-    g.scaled = sd.scaled != 0;
+    g.book = (int32_t)uniform((uint32_t)sd.book);
+    g.scaled = uniform((uint32_t)sd.scaled) != 0;
     return g;
 }
 
-__device__ inline uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
-__device__ inline uint64_t uniform(uint64_t x) { return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x); }
 
 // What a wavefront needs to know about chunk c of user u before it can decode it.
 struct ChunkIndex {
@@ -389,9 +391,10 @@ __device__ inline void slow_group(Stream &st, uint32_t (&e)[kGroup], uint32_t n0
     }
 }
 
-// Where a wavefront decodes chunk (g, ix): `window` is the LDS address of its `rows` rows.
+// Where a wavefront decodes chunk (g, ix): `window` is the LDS address of its `rows` rows.  skip: bits of the lane's sub-chunk
+// that are passed over.
 template <int kMaxRows>
-__device__ inline void start_chunk(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t window, uint32_t rows)
+__device__ inline void start_chunk(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t window, uint32_t rows, uint32_t skip = 0)
 {
     const uint32_t lane = threadIdx.x & 63;
     st.end = wave_inclusive_scan_dpp(ix.sb);
@@ -401,7 +404,7 @@ __device__ inline void start_chunk(Stream &st, const ChunkGeom &g, const ChunkIn
     const int left = (int)g.n - (int)lane * kSub;
     st.cnt = (int)here((uint32_t)(left < 0 ? 0 : (left > kSub ? kSub : left)));
     st.bad = false;
-    load_window<kMaxRows>(st, ix, st.end - ix.sb);
+    load_window<kMaxRows>(st, ix, st.end - ix.sb + skip);
 }
 __device__ inline void finish_chunk(const Stream &st, const ChunkIndex &ix, uint64_t *__restrict__ status)
 {
@@ -410,11 +413,12 @@ __device__ inline void finish_chunk(const Stream &st, const ChunkIndex &ix, uint
     wave_lds_fence();   // the next chunk's words overwrite these
 }
 
-// on_group(gr, e) gets the entries of symbols 8 gr .. 8 gr + 7 of every lane, gr = 0 .. 7.  kUnroll: gr is a constant
-// there (sums in registers), at eight times the code, which a launch of few workgroups waits for.
+// on_group(gr, e) gets the entries of symbols 8 gr .. 8 gr + 7 of every lane, gr = 0 .. 7 (or from .. to - 1, where st stands
+// before symbol 8 from).  kUnroll: gr is a constant there (sums in registers), at eight times the code, which a launch of few
+// workgroups waits for.
 template <bool kUnroll, class Table, class Book, class Value, class OnGroup>
 __device__ inline void decode_started(Stream &st, const ChunkGeom &g, const ChunkIndex &ix, uint32_t A, const Table &tab,
-                                      const Book *__restrict__ book, Value value, OnGroup on_group)
+                                      const Book *__restrict__ book, Value value, OnGroup on_group, int from = 0, int to = kGroups)
 {
     const bool part = __any(32u * (st.first + st.rows) < st.end), full = g.n == (uint32_t)kChunk;
     auto group = [&](int gr) {
@@ -430,7 +434,7 @@ __device__ inline void decode_started(Stream &st, const ChunkGeom &g, const Chun
         for (int gr = 0; gr < kGroups; ++gr) group(gr);
     } else {
 #pragma unroll 1
-        for (int gr = 0; gr < kGroups; ++gr) group(gr);
+        for (int gr = from; gr < to; ++gr) group(gr);
     }
 }
 

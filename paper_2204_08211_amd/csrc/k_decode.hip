@@ -12,8 +12,9 @@ namespace co3 {
 
 typedef AggArgsT<BookDev> AggArgs;
 
-// Symbols 8 gr .. 8 gr + 7 of a sub-chunk: byte 1 of their entries.
-__device__ inline void pack_group(u32x16 &packed, int gr, const uint32_t (&e)[kGroup])
+// Symbols 8 gr .. 8 gr + 7 of a sub-chunk (or of the part that `packed` has room for): byte 1 of their entries.
+template <class Packed>
+__device__ inline void pack_group(Packed &packed, int gr, const uint32_t (&e)[kGroup])
 {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -191,7 +192,7 @@ struct AggPart {
     const Layout &lay;
     const AggArgs &a;
     uint32_t *smem;
-    int32_t *s_book;         // [2][kAggWaves], where a wavefront has a chunk: of its code table; notes
+    int32_t *s_book;         // [3][kAggWaves], where a wavefront has a chunk: of its code table; notes
     double *s_all;           // [kSub][kAcrossStride] where the wavefronts' users come in several turns, else nullptr
     ChunkGeom g;
     uint64_t c;
@@ -207,9 +208,13 @@ struct AggPart {
 // Decodes users u0, u0 + 1, .. (kAcross: u0 + wave, u0 + wave + waves, ..), `users` of them as far as there are, one after
 // the other: on_user(u, ix, st, tab, book) with the chunk started, on_none() in the turns that are left over.
 // kBytes: tables of values (4) or of symbols (2).  kAcross: the wavefronts of the workgroup share a chunk; else each has
-// a chunk of its own.
-template <bool kAcross, int kBytes, int kUsers, class OnUser>
-__device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, OnUser on_user)
+// a chunk of its own.  place(i): where the lane goes on in its sub-chunk (see StreamPlaces); to_end: the sub-chunks are decoded
+// to their ends.
+struct FromTheStart {
+    __device__ inline uint32_t operator()(uint32_t) const { return 0u; }
+};
+template <bool kAcross, int kBytes, int kUsers, class OnUser, class Place = FromTheStart>
+__device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, OnUser on_user, Place place = Place{}, bool to_end = true)
 {
     const Layout &lay = p.lay;
     const uint32_t t = threadIdx.x;
@@ -220,9 +225,12 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
     };
     auto decode = [&](uint32_t i, uint32_t u, const ChunkIndex &ix, uint32_t *win, const DecTable<kBytes> &tab, const BookDev *book) {
         Stream st;
-        start_chunk<kRowsByte>(st, p.g, ix, lds_address(win), window_rows(lay.A));
+        const uint32_t from = place(i);
+        start_chunk<kRowsByte>(st, p.g, ix, lds_address(win), window_rows(lay.A), from & 0x7fffu);
+        st.bad = (from & 0x8000u) != 0u;
         on_user(i, u, ix, st, tab, book);
-        finish_chunk(st, ix, p.a.status);
+        if (to_end) finish_chunk(st, ix, p.a.status);
+        else wave_lds_fence();
     };
     auto index_of = [&](uint32_t u) {
         return read_index(lay, p.c, u, p.a.words, p.a.words_stride, p.a.chunk_offset, p.a.sub_bits);
@@ -296,13 +304,13 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
 // The sums leave the registers: of(j) is this lane's sum of element j as a T (j a constant in [J0, J1)), `unit` what a sum of 1 is
 // worth.  kAcross: they are added up over the workgroup's wavefronts, fp64 in their order.  Where the users come in
 // several turns (first .. last), p.s_all keeps the sums.  at_element: of j = 0.
-template <bool kAcross, class T, int J0, int J1, bool kFewRows = false, class Of>
+template <bool kAcross, class T, int J0, int J1, class Of>
 __device__ inline void write_sums(const AggPart &p, double unit, Of of, bool first = true, bool last = true, int at_element = 0)
 {
     const uint32_t t = threadIdx.x, lane = t & 63;
     const double inv_u = 1.0 / (double)p.lay.U;
     const bool whole = p.g.n == (uint32_t)kChunk;
-    constexpr int rows = sizeof(T) == 4 ? (kAcross ? 64 : 16) : (kAcross ? 16 : 8) / (kFewRows ? 2 : 1);
+    constexpr int rows = sizeof(T) == 4 ? (kAcross ? 64 : 16) : (kAcross ? 16 : 8);
     constexpr uint32_t per = rows / 4;   // groups of four elements per sub-chunk
     if constexpr (kAcross) {
 #pragma unroll
@@ -404,51 +412,15 @@ __device__ inline void aggregate_int(const AggPart &p, int bias_hi, bool wide)
     else write_sums<kAcross, int32_t, 0, kSub>(p, unit, [&](int j) { return sum[j]; });
 }
 
-// The same users where the biases lie too far apart for that (or, kGain, where one carries a scale): fp64 sums, of one of kParts
-// parts of every sub-chunk at a time.
-template <bool kAcross, bool kGain, int kParts>
-__device__ inline void aggregate_spread(const AggPart &p)
-{
-    constexpr int kPart = kSub / kParts;
-    const SymbolValue val(p.lay.E, p.lay.M);
-#pragma unroll 1
-    for (int part = 0; part < kParts; ++part) {
-        double sum[kPart];
-#pragma unroll
-        for (int i = 0; i < kPart; ++i) sum[i] = 0.0;
-        each_user<kAcross, 2, 0>(
-            p, 0, users_each(p, kAcross),
-            [&](uint32_t, uint32_t u, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
-                u32x16 packed = 0u;
-                decode_started<false>(st, p.g, ix, p.lay.A, tab, book, SymbolEntry{},
-                                      [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(packed, gr, e); });
-                const uint64_t pair = (uint64_t)u * p.lay.nseg + p.g.seg;
-                const int bias = (int)uniform((uint32_t)p.lay.bias[pair]);
-                const double scale = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
-                const float inv_gain = kGain ? p.lay.gain[2 * pair + 1] : 1.0f;
-                if constexpr (kGain) {   // (the products with a scale round)
-                    round_to_nearest();
-                    words_here(packed);
-                }
-#pragma unroll
-                for (int i = 0; i < kPart; ++i) {
-                    uint32_t w = packed[i >> 2];
-#pragma unroll
-                    for (int k = 1; k < kParts; ++k) w = part == k ? packed[(k * kPart + i) >> 2] : w;
-                    sum[i] = here(add_value<kGain>(val(w, 8u * (uint32_t)(i & 3)), scale, inv_gain, sum[i]));
-                }
-                if constexpr (kGain) round_toward_zero();
-            });
-        round_to_nearest();
-        write_sums<kAcross, double, 0, kPart>(p, 1.0, [&](int j) { return sum[j]; }, true, true, part * kPart);
-        round_toward_zero();
-        __syncthreads();
-    }
-}
+// Where the users' streams stand between the parts that aggregate_spread takes: a lane's place in its sub-chunk (below 2^15
+// bits: half of it), in the top bit whether a code was damaged before it.  In LDS, kUsers of every wavefront's users.
+struct StreamPlaces {
+    uint16_t *at;     // behind everything else in LDS
+    uint32_t users;   // of a wavefront's; the others are decoded from the start in every part
+    __device__ inline uint16_t &of(const AggPart &p, uint32_t i) const { return at[(p.wave * users + i) * 64u + (threadIdx.x & 63u)]; }
+};
 
-// Sums in fp64, from the packed symbols of up to kUsers users at a time; any format, bias and scale.  kGain: the host knows
-// of a scale; else a layer that carries one all the same goes the longer way at the end, in half the rows at a time, for
-// which the registers suffice.
+// Sums in fp64, from the packed symbols of up to kUsers users at a time; any format and bias, kGain: and scale.
 template <int kUsers, bool kGain, bool kAcross>
 __device__ inline void aggregate_packed(const AggPart &p)
 {
@@ -477,7 +449,7 @@ __device__ inline void aggregate_packed(const AggPart &p)
             scale[s] = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
         }
         const bool last = u0 + step * kUsers >= lay.U;
-        if (kGain || __builtin_expect(p.g.scaled, 0)) {
+        if (kGain || (kUsers == 1 && p.g.scaled)) {
             float inv_gain[kUsers];
 #pragma unroll
             for (int s = 0; s < kUsers; ++s) inv_gain[s] = lay.gain[2 * pair_of(s) + 1];
@@ -488,7 +460,7 @@ __device__ inline void aggregate_packed(const AggPart &p)
                     sum = add_value<true>(val(here(pk[s][j >> 2]), 8u * (uint32_t)(j & 3)), scale[s], inv_gain[s], sum);
                 return sum;
             };
-            write_sums<kAcross, double, 0, kSub, !kGain>(p, 1.0, sum_of, u0 == 0, last);
+            write_sums<kAcross, double, 0, kSub>(p, 1.0, sum_of, u0 == 0, last);
         } else {
             auto sum_of = [&](int j) {
                 double sum = 0.0;
@@ -506,9 +478,58 @@ __device__ inline void aggregate_packed(const AggPart &p)
     }
 }
 
+// The same users where the biases lie too far apart for that, or (kGain) one carries a scale: fp64 sums, of one of kParts parts
+// of every sub-chunk at a time, for more do not fit the registers.
+// A wavefront keeps where its users' streams stand, so that every symbol is decoded once: decoded anew with every part, eight
+// users of 25 M elements in [1,4,3] with biases 14 binades apart 228 us, this way 177.
+template <bool kAcross, bool kGain, int kParts>
+__device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &places)
+{
+    constexpr int kPart = kSub / kParts, kPartGroups = kGroups / kParts;
+    const SymbolValue val(p.lay.E, p.lay.M);
+#pragma unroll 1
+    for (int part = 0; part < kParts; ++part) {
+        double sum[kPart];
+#pragma unroll
+        for (int i = 0; i < kPart; ++i) sum[i] = 0.0;
+        const int from = part * kPartGroups;
+        auto on_user = [&](uint32_t i, uint32_t u, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
+            typedef uint32_t words_t __attribute__((ext_vector_type(kPart / 4)));
+            const bool kept = i < places.users;
+            words_t packed = 0u;
+            decode_started<false>(
+                st, p.g, ix, p.lay.A, tab, book, SymbolEntry{},
+                [&](int gr, const uint32_t (&e)[kGroup]) {
+                    if (gr >= from) pack_group(packed, gr - from, e);
+                },
+                kept ? from : 0, from + kPartGroups);
+            if (kept && part + 1 < kParts)
+                places.of(p, i) = (uint16_t)(((st.bit() - (st.end - ix.sb)) & 0x7fffu) | (st.bad ? 0x8000u : 0u));
+            const uint64_t pair = (uint64_t)u * p.lay.nseg + p.g.seg;
+            const int bias = (int)uniform((uint32_t)p.lay.bias[pair]);
+            const double scale = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
+            const float inv_gain = kGain ? p.lay.gain[2 * pair + 1] : 1.0f;
+            if constexpr (kGain) round_to_nearest();   // (the products round)
+#pragma unroll
+            for (int k = 0; k < kPart; ++k) {
+                const uint32_t w = kGain ? here(packed[k >> 2]) : packed[k >> 2];
+                sum[k] = here(add_value<kGain>(val(w, 8u * (uint32_t)(k & 3)), scale, inv_gain, sum[k]));
+            }
+            if constexpr (kGain) round_toward_zero();
+        };
+        auto place = [&](uint32_t i) { return part == 0 || i >= places.users ? 0u : (uint32_t)places.of(p, i); };
+        each_user<kAcross, 2, 0>(p, 0, users_each(p, kAcross), on_user, place, part + 1 == kParts);
+        round_to_nearest();
+        write_sums<kAcross, double, 0, kPart>(p, 1.0, [&](int j) { return sum[j]; }, true, true, part * kPart);
+        round_toward_zero();
+        __syncthreads();
+    }
+}
+
 // Users whose symbols meet in LDS at most: two a wavefront, 5 KB each, so that sixteen wavefronts still fit a CU.  (Four a
 // wavefront leave room for eight: sixteen users of 12 M elements in [1,5,2], a round 600 us from the sums, 794 this way.)
 constexpr uint32_t kStageUsers = 2 * kAggWaves;
+__host__ __device__ constexpr uint32_t stage_bytes(uint32_t U) { return 4u * U * kStageWords + kStageUsers * (uint32_t)(sizeof(double) + sizeof(float)); }
 // The same sums where the workgroup's wavefronts decode all users in one turn: the symbols meet in LDS, an eighth of what
 // the fp64 sums would be, and every thread adds up its elements in the users' order, where the sums would be added up by
 // one wavefront after the other (the others at barriers).  A small launch is one workgroup's way: a round of three users of
@@ -601,22 +622,45 @@ __device__ inline AggPart agg_part(const Layout &lay, const AggArgs &a, uint32_t
 
 // The layer's entry and biases say which way the sums take, and not the host: a captured launch may be replayed on a plan that
 // has been given a scale or other biases since.
-// Where each wavefront has a chunk of its own: tells the others its code table, and takes the way that serves them all, the
-// largest of theirs (they meet at barriers).
-__device__ inline int common_way(const AggPart &p, int way)
+// Where each wavefront has a chunk of its own: tells the others its code table, and whether x; one of them takes all along
+// (they meet at barriers).  note: 1 or 2, another with each call.
+__device__ inline bool any_wave(const AggPart &p, bool x, int note)
 {
     if ((threadIdx.x & 63) == 0) {
         p.s_book[p.wave] = p.g.book;
-        p.s_book[kAggWaves + p.wave] = way;
+        p.s_book[note * kAggWaves + (int)p.wave] = x ? 1 : 0;
     }
     __syncthreads();
-    const int other = p.s_book[kAggWaves + (threadIdx.x & (kAggWaves - 1))];
-    return __any(other == 2) ? 2 : (__any(other == 1) ? 1 : 0);
+    return __any(p.s_book[note * kAggWaves + (int)(threadIdx.x & (kAggWaves - 1))] != 0);
+}
+
+// The way of what the kernels below are not made for: sums that do not fit integers, a scale that the host does not know of.
+// It reads the kernel's arguments (Layout and AggArgs come first) anew and looks its chunk up again, so that nothing of its
+// own is held in registers over the kernel's usual way (in k_aggregate_int: eight users of 10^6 elements in [1,4,3] 13.3 us
+// with the kernel's own values, 12.6 this way).
+template <bool kAcross>
+__device__ __forceinline__ void aggregate_rare(uint32_t *smem, uint32_t places_at, uint32_t places)
+{
+    struct Arguments { Layout lay; AggArgs a; };
+    uint64_t arguments = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(arguments));
+    const Arguments *k = (const Arguments *)(const __attribute__((address_space(4))) Arguments *)arguments;
+    const Layout lay = k->lay;
+    const AggArgs a = k->a;
+    const AggPart p = agg_part<kAcross>(lay, a, smem, 0);
+    const StreamPlaces sp = {reinterpret_cast<uint16_t *>(smem + places_at), places};
+    bool scaled = p.g.scaled;
+    if constexpr (!kAcross) scaled = any_wave(p, scaled, 2);
+    if constexpr (kAcross) {
+        if (lay.U <= 2u * p.waves && stage_bytes(lay.U) <= 4u * places_at) return aggregate_staged<2>(p);
+    }
+    if (scaled) aggregate_spread<kAcross, true, 4>(p, sp);
+    else aggregate_spread<kAcross, false, 2>(p, sp);
 }
 
 // co3_ps_aggregate with integer sums (formats of up to four exponent bits; layers without a real-valued scale).
 template <bool kAcross>
-__global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate_int(Layout lay, AggArgs a)
+__global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate_int(Layout lay, AggArgs a, uint32_t places_at, uint32_t places)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<kAcross>(lay, a, smem, 0);
@@ -625,23 +669,23 @@ __global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate_int(Layout lay,
     bias_range(lay, p.g.seg, lo, hi);
     const bool fits = int_sum_bits(lay, hi - lo, kAcross ? (lay.U + p.waves - 1) / p.waves : lay.U) <= 31;
     const bool wide = int_sum_bits(lay, hi - lo, lay.U) > 31;
-    int way = p.g.scaled ? 2 : (fits ? 0 : 1);
-    if constexpr (!kAcross) way = common_way(p, way);
-    if (way == 0) aggregate_int<kAcross>(p, hi, wide);
-    else if (way == 1) aggregate_spread<kAcross, false, 2>(p);
-    else aggregate_spread<kAcross, true, 4>(p);
+    bool rare = p.g.scaled || !fits;
+    if constexpr (!kAcross) rare = any_wave(p, rare, 1);
+    if (__builtin_expect(rare, 0)) aggregate_rare<kAcross>(smem, places_at, places);
+    else aggregate_int<kAcross>(p, hi, wide);
 }
 
 // co3_ps_aggregate for everything else.  kUsers: per wavefront and turn.
 template <int kUsers, bool kGain, bool kAcross>
-__global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggregate(Layout lay, AggArgs a, uint32_t all_at)
+__global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggregate(Layout lay, AggArgs a, uint32_t all_at, uint32_t places_at, uint32_t places)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<kAcross>(lay, a, smem, all_at);
     round_toward_zero();
-    if constexpr (!kAcross) {
-        if ((threadIdx.x & 63) == 0) p.s_book[p.wave] = p.g.book;
-        __syncthreads();
+    bool rare = p.g.scaled;
+    if constexpr (!kAcross) rare = any_wave(p, rare, 1);
+    if constexpr (!kGain && kUsers > 1) {
+        if (__builtin_expect(rare, 0)) return aggregate_rare<kAcross>(smem, places_at, places);
     }
     aggregate_packed<kUsers, kGain, kAcross>(p);
 }
@@ -710,17 +754,37 @@ static hipError_t launch_aggregate_k(Kernel k, const Layout &lay, uint32_t waves
     return hipGetLastError();
 }
 
+// Launches one of the kernels that has aggregate_rare, with room for what that keeps in LDS as far as it costs no workgroup that
+// the CU would hold beside (sixteen wavefronts, for the registers hold no more; a workgroup where there are no more than CUs):
+// behind the `lds` bytes a place for each of a wavefront's users, and so many in all that the users' symbols can meet there.
+template <class Kernel, class... Args>
+static hipError_t launch_aggregate_places(Kernel k, const Layout &lay, uint32_t waves, bool across, size_t lds, hipStream_t s, Args... args)
+{
+    const uint32_t piece = 1280, pieces = 128;   // LDS is given out in pieces (26 880 bytes: six workgroups, 27 136: five)
+    uint32_t groups = pieces / (((uint32_t)lds + piece - 1) / piece);
+    const uint64_t grid = across ? lay.nchunks : (lay.nchunks + waves - 1) / waves;
+    if (groups > 16 / waves) groups = 16 / waves;
+    if (groups > (grid + 255) / 256) groups = (uint32_t)((grid + 255) / 256);
+    const uint32_t share = pieces / groups * piece;
+    if (across && lay.U <= 2 * waves && stage_bytes(lay.U) <= share && stage_bytes(lay.U) > lds) lds = stage_bytes(lay.U);
+    const uint32_t at = (uint32_t)((lds + 15) / 16 * 4), per_user = waves * 64 * (uint32_t)sizeof(uint16_t);
+    uint32_t places = share > 4 * at ? (share - 4 * at) / per_user : 0;
+    const uint32_t users = across ? (lay.U + waves - 1) / waves : lay.U;
+    if (places > users) places = users;
+    return launch_aggregate_k(k, lay, waves, across, 4 * (size_t)at + (size_t)places * per_user, s, args..., at, places);
+}
+
 template <bool kGain>
 static hipError_t launch_aggregate_packed(const Layout &lay, const AggArgs &a, uint32_t waves, hipStream_t s)
 {
     if (waves <= 1) {
         const size_t lds = aggregate_lds(lay, false, kAggWaves, false);
-        if (lay.U == 1) return launch_aggregate_k(k_aggregate<1, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u);
-        return launch_aggregate_k(k_aggregate<kPackUsers, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u);
+        if (lay.U == 1) return launch_aggregate_k(k_aggregate<1, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u, 0u, 0u);
+        return launch_aggregate_places(k_aggregate<kPackUsers, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u);
     }
     size_t lds = aggregate_lds(lay, false, waves, true);
     if (lay.U <= 2 * waves) {
-        const size_t stage = 4 * (size_t)lay.U * kStageWords + kStageUsers * (sizeof(double) + sizeof(float));
+        const size_t stage = stage_bytes(lay.U);
         if (stage > lds) lds = stage;
         if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1>, lay, waves, true, lds, s, a);
         return launch_aggregate_k(k_aggregate_staged<2>, lay, waves, true, lds, s, a);
@@ -730,7 +794,7 @@ static hipError_t launch_aggregate_packed(const Layout &lay, const AggArgs &a, u
         all_at = (uint32_t)((lds + 15) / 16 * 4);
         lds = 4 * (size_t)all_at + (size_t)kSub * kAcrossStride * sizeof(double);
     }
-    return launch_aggregate_k(k_aggregate<kPackUsers, kGain, true>, lay, waves, true, lds, s, a, all_at);
+    return launch_aggregate_places(k_aggregate<kPackUsers, kGain, true>, lay, waves, true, lds, s, a, all_at);
 }
 
 hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3_aggregate_args &a, const BookDev *books, hipStream_t s)
@@ -750,8 +814,11 @@ hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3
     const bool ints = dec_value_is_int(lay.E) && !facts.has_gain && (!lay.per_user_books || lay.A <= 64u) &&
                       int_sum_bits(lay, facts.bias_spread, (lay.U + waves - 1) / waves) <= 31;
     if (ints) {
-        if (waves <= 1) return launch_aggregate_k(k_aggregate_int<false>, lay, kAggWaves, false, aggregate_lds(lay, true, kAggWaves, false), s, args);
-        return launch_aggregate_k(k_aggregate_int<true>, lay, waves, true, aggregate_lds(lay, true, waves, true), s, args);
+        const bool across = waves > 1;
+        if (!across) waves = kAggWaves;
+        const size_t lds = aggregate_lds(lay, true, waves, across);
+        return across ? launch_aggregate_places(k_aggregate_int<true>, lay, waves, true, lds, s, args)
+                      : launch_aggregate_places(k_aggregate_int<false>, lay, waves, false, lds, s, args);
     }
     while (waves * kPackUsers < lay.U && waves < kAggWaves) waves = waves < 2 ? 2 : (waves < 4 ? 4 : kAggWaves);
     return facts.has_gain ? launch_aggregate_packed<true>(lay, args, waves, s) : launch_aggregate_packed<false>(lay, args, waves, s);

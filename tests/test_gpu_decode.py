@@ -277,3 +277,87 @@ def test_average_with_a_scale_and_words_of_25_to_31_bits(E, M, U, own):
     for row in q[:, :d].cpu().numpy().astype(np.float64):
         total += row
     gu.assert_bits_equal(out.cpu().numpy(), (total * (1.0 / U)).astype(np.float32), "average")
+
+
+def device_bias(plan, bias):
+    import torch
+    from paper_2204_08211_amd import binding as B
+    t = torch.from_numpy(np.ascontiguousarray(bias, np.int32)).to("cuda:0")
+    B._check("co3_plan_set_bias_device", B.lib().co3_plan_set_bias_device(plan.handle, t.data_ptr(), B._stream()))
+    torch.cuda.synchronize()
+
+
+def coded(E, M, g, bias, own=False, seg_len=None, max_code_len=40):
+    """A round's streams of given gradients under a plan that knows the biases (memory zero)."""
+    import torch
+    from paper_2204_08211_amd import binding as B
+    U, d = g.shape
+    plan = B.Plan(E, M, U, d, bias, seg_len=seg_len, per_user_books=own)
+    books = B.co3_build_codebook(E, M, plan.num_books, None)
+    buf = B.RoundBuffers(plan, "cuda:0", max_code_len=max_code_len)
+    gt = torch.zeros((U, (d + 3) // 4 * 4), dtype=torch.float32, device="cuda:0")
+    gt[:, :d] = torch.from_numpy(g).to("cuda:0") if isinstance(g, np.ndarray) else g
+    m = torch.zeros_like(gt)
+    B.co3_encode(plan, books, gt, m, m, 0.0, buf, mode=BOOK_EMPIRICAL)
+    return plan, books, buf
+
+
+def in_order_average(plan, books, buf):
+    import torch
+    from paper_2204_08211_amd import binding as B
+    q = torch.zeros((plan.U, (plan.d + 3) // 4 * 4), dtype=torch.float32, device="cuda:0")
+    B.co3_decode(plan, books, buf, q=q)
+    total = torch.zeros(plan.d, dtype=torch.float64, device="cuda:0")
+    for u in range(plan.U):
+        total += q[u, :plan.d].double()
+    return (total * (1.0 / plan.U)).float().cpu().numpy()
+
+
+@pytest.mark.parametrize("E,M,U,chunks,own", [(4, 3, 1, 3, False), (4, 3, 3, 2, True), (4, 3, 11, 2, False), (4, 3, 40, 2, False),
+                                              (4, 3, 300, 1, False), (2, 1, 9, 2, True), (4, 3, 6, 2100, False), (3, 3, 12, 700, False)])
+def test_average_of_biases_far_apart_decodes_parts(E, M, U, chunks, own):
+    # the fp64 sums take a sub-chunk in parts and go on where a user's part ended: more users than a wavefront keeps places for,
+    # sub-chunks longer than a window in some lanes, a ragged chunk; a damaged index is counted as the integer sums count it
+    import torch
+    from paper_2204_08211_amd import binding as B
+    rng = np.random.default_rng(40 * E + U)
+    d, b0 = 4096 * chunks + 1500, 2 ** (E - 1)
+    nm = orc.num_magnitudes(E, M)
+    bias = (b0 + rng.integers(0, 22, (U, 1))).astype(np.int32)
+    bias[0], bias[-1] = b0, b0 + (21 if U > 1 else 0)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(U)
+    scale = torch.tensor([2.0 ** (b0 - int(b)) for b in bias[:, 0]], device="cuda:0")
+    x = torch.randn((U, d), generator=gen, device="cuda:0") * float(orc.grid(E, M, b0)[-1]) / 2
+    x[:, 128:128 + 640] = 0.0                                # sub-chunks of the shortest word
+    plan, books, buf = coded(E, M, (x * scale[:, None]).float(), bias, own=own)
+    if not own:                                              # a code that gives the frequent symbols long words
+        w = np.zeros(1 << (1 + E + M), np.uint64)
+        A = w.size
+        emit = sorted([0] + [s for s in range(A) if 0 < (s & (A // 2 - 1)) < nm], key=lambda s: s & (A // 2 - 1))
+        w[emit] = [max(1, int(2.0 ** (40 - 40.0 * i / len(emit)))) for i in range(len(emit))]
+        books = B.co3_build_codebook(E, M, 1, w[None, :])
+        buf = B.RoundBuffers(plan, "cuda:0", max_code_len=64)
+        g = torch.zeros((U, (d + 3) // 4 * 4), dtype=torch.float32, device="cuda:0")
+        g[:, :d] = x * scale[:, None]
+        m = torch.zeros_like(g)
+        B.co3_encode(plan, books, g, m, m, 0.0, buf, mode=BOOK_FIXED)
+    want = in_order_average(plan, books, buf)
+    near = B.Plan(E, M, U, d, np.full((U, 1), b0, np.int32), per_user_books=own)
+    device_bias(near, bias)
+    out = torch.full((d,), float("nan"), dtype=torch.float32, device="cuda:0")
+    B.co3_ps_aggregate(near, books, buf, out)
+    torch.cuda.synchronize()
+    assert not buf.status.cpu().numpy()[2:].any()
+    gu.assert_bits_equal(out.cpu().numpy(), want, "average")
+    # lanes of sub-chunks 3 and 4 of every user's second chunk start and end beside a codeword
+    buf.sub_bits[:, 64 + 3] += 1
+    buf.sub_bits[:, 64 + 4] -= 1
+    counts = []
+    for biases in (bias, np.full((U, 1), b0, np.int32)):
+        buf.status.zero_()
+        device_bias(near, biases)
+        B.co3_ps_aggregate(near, books, buf, out)
+        torch.cuda.synchronize()
+        counts.append(int(buf.status[5]))
+    assert counts[0] == counts[1] >= (U + 1) // 2 and not buf.status.cpu().numpy()[[2, 3, 6]].any()
