@@ -208,13 +208,13 @@ struct AggPart {
 // Decodes users u0, u0 + 1, .. (kAcross: u0 + wave, u0 + wave + waves, ..), `users` of them as far as there are, one after
 // the other: on_user(u, ix, st, tab, book) with the chunk started, on_none() in the turns that are left over.
 // kBytes: tables of values (4) or of symbols (2).  kAcross: the wavefronts of the workgroup share a chunk; else each has
-// a chunk of its own.  place(i): where the lane goes on in its sub-chunk (see StreamPlaces); to_end: the sub-chunks are decoded
-// to their ends.
+// a chunk of its own.  in_order: users u0, u0 + 1, .. with kAcross too.  place(i): where the lane goes on in its sub-chunk (see
+// StreamPlaces); to_end: the sub-chunks are decoded to their ends.
 struct FromTheStart {
     __device__ inline uint32_t operator()(uint32_t) const { return 0u; }
 };
 template <bool kAcross, int kBytes, int kUsers, class OnUser, class Place = FromTheStart>
-__device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, OnUser on_user, Place place = Place{}, bool to_end = true)
+__device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, OnUser on_user, bool in_order = false, Place place = Place{}, bool to_end = true)
 {
     const Layout &lay = p.lay;
     const uint32_t t = threadIdx.x;
@@ -246,7 +246,7 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
             __syncthreads();
         }
         auto turn = [&](uint32_t i) {
-            const uint32_t u = u0 + p.wave + i * p.waves;
+            const uint32_t u = u0 + (in_order ? i : p.wave + i * p.waves);
             if (u >= lay.U) return;
             const ChunkIndex ix = index_of(u);
             const BookDev *book = p.a.books + p.g.book;
@@ -479,11 +479,11 @@ __device__ inline void aggregate_packed(const AggPart &p)
 }
 
 // The same users where the biases lie too far apart for that, or (kGain) one carries a scale: fp64 sums, of one of kParts parts
-// of every sub-chunk at a time, for more do not fit the registers.
+// of every sub-chunk at a time, for more do not fit the registers.  ordered: in the users' order.
 // A wavefront keeps where its users' streams stand, so that every symbol is decoded once: decoded anew with every part, eight
 // users of 25 M elements in [1,4,3] with biases 14 binades apart 228 us, this way 177.
 template <bool kAcross, bool kGain, int kParts>
-__device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &places)
+__device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &places, bool ordered)
 {
     constexpr int kPart = kSub / kParts, kPartGroups = kGroups / kParts;
     const SymbolValue val(p.lay.E, p.lay.M);
@@ -518,7 +518,7 @@ __device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &pl
             if constexpr (kGain) round_toward_zero();
         };
         auto place = [&](uint32_t i) { return part == 0 || i >= places.users ? 0u : (uint32_t)places.of(p, i); };
-        each_user<kAcross, 2, 0>(p, 0, users_each(p, kAcross), on_user, place, part + 1 == kParts);
+        each_user<kAcross, 2, 0>(p, 0, ordered ? (p.wave ? 0u : p.lay.U) : users_each(p, kAcross), on_user, ordered, place, part + 1 == kParts);
         round_to_nearest();
         write_sums<kAcross, double, 0, kPart>(p, 1.0, [&](int j) { return sum[j]; }, true, true, part * kPart);
         round_toward_zero();
@@ -649,13 +649,17 @@ __device__ __forceinline__ void aggregate_rare(uint32_t *smem, uint32_t places_a
     const AggArgs a = k->a;
     const AggPart p = agg_part<kAcross>(lay, a, smem, 0);
     const StreamPlaces sp = {reinterpret_cast<uint16_t *>(smem + places_at), places};
-    bool scaled = p.g.scaled;
+    bool scaled = p.g.scaled, ordered = false;
     if constexpr (!kAcross) scaled = any_wave(p, scaled, 2);
     if constexpr (kAcross) {
+        // up to four users keep their order where it can make a difference: sums of more than 53 bits, or with a scale
+        int lo, hi;
+        bias_range(lay, p.g.seg, lo, hi);
+        ordered = lay.U <= 4u && p.waves < lay.U && (p.g.scaled || int_sum_bits(lay, hi - lo, lay.U) > 53);
         if (lay.U <= 2u * p.waves && stage_bytes(lay.U) <= 4u * places_at) return aggregate_staged<2>(p);
     }
-    if (scaled) aggregate_spread<kAcross, true, 4>(p, sp);
-    else aggregate_spread<kAcross, false, 2>(p, sp);
+    if (scaled) aggregate_spread<kAcross, true, 4>(p, sp, ordered);
+    else aggregate_spread<kAcross, false, 2>(p, sp, ordered);
 }
 
 // co3_ps_aggregate with integer sums (formats of up to four exponent bits; layers without a real-valued scale).

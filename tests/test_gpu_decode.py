@@ -313,6 +313,37 @@ def in_order_average(plan, books, buf):
     return (total * (1.0 / plan.U)).float().cpu().numpy()
 
 
+def cancelling(U, d, bias, top, seed):
+    """Gradients whose sums depend on the order: users 0 and 2 cancel but for a few elements, 1 and 3 are far below them."""
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    g = torch.randn((U, d), generator=gen, device="cuda:0") * (top / 4)
+    g[2] = torch.where(torch.rand(d, generator=gen, device="cuda:0") < 0.9, -g[0], g[2])
+    scale = torch.tensor([2.0 ** (int(bias[0, 0]) - int(b)) for b in bias[:, 0]], device="cuda:0")
+    return (g * scale[:, None]).float()
+
+
+@pytest.mark.parametrize("U", [3, 4])
+@pytest.mark.parametrize("E,M,chunks", [(4, 3, 5), (4, 3, 1500), (2, 1, 1500), (4, 3, 2100)])
+def test_few_users_keep_their_order(U, E, M, chunks):
+    # biases from the device so far apart that fp64 sums depend on the order: the users', with a wavefront each, two for the
+    # chunk (whose symbols meet in LDS, or do not fit there), one
+    import torch
+    from paper_2204_08211_amd import binding as B
+    d = 4096 * chunks + 100
+    bias = np.array([[10], [66], [10], [64]], np.int32)[:U]
+    plan, books, buf = coded(E, M, cancelling(U, d, bias, float(orc.grid(E, M, 10)[-1]), U + chunks), bias)
+    want = in_order_average(plan, books, buf)
+    near = B.Plan(E, M, U, d, np.full((U, 1), 10, np.int32))
+    device_bias(near, bias)
+    out = torch.zeros(d, dtype=torch.float32, device="cuda:0")
+    B.co3_ps_aggregate(near, books, buf, out)
+    torch.cuda.synchronize()
+    assert not buf.status.cpu().numpy()[2:].any()
+    gu.assert_bits_equal(out.cpu().numpy(), want, "average")
+
+
 @pytest.mark.parametrize("E,M,U,chunks,own", [(4, 3, 1, 3, False), (4, 3, 3, 2, True), (4, 3, 11, 2, False), (4, 3, 40, 2, False),
                                               (4, 3, 300, 1, False), (2, 1, 9, 2, True), (4, 3, 6, 2100, False), (3, 3, 12, 700, False)])
 def test_average_of_biases_far_apart_decodes_parts(E, M, U, chunks, own):

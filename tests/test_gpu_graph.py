@@ -81,6 +81,7 @@ def test_round_in_a_graph_equals_eager(single_sweep, E, M):
 @pytest.mark.parametrize("E,M,U,chunks,own", [
     (4, 3, 3, 3, False), (4, 3, 8, 2, False), (4, 3, 20, 2, False), (2, 1, 5, 2, True),   # integer sums, users side by side
     (4, 3, 2, 2100, False),                                                              # a wavefront per chunk
+    (4, 3, 4, 1500, False), (2, 1, 4, 1500, False),                                      # two wavefronts, four users
     (5, 2, 3, 3, False), (5, 2, 13, 2, True), (5, 2, 40, 2, False),                      # symbols met in LDS, turns of four users
     (5, 2, 4, 2100, False), (5, 2, 1, 5, True),                                          # a wavefront per chunk
     (4, 5, 3, 3, False),                                                                 # 16-bit symbols
