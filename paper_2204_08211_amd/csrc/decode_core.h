@@ -215,7 +215,8 @@ __device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
         const uint32_t mid = (lo + hi) >> 1;
         if (uniform(lay.segs[mid].chunk_start) <= c) lo = mid; else hi = mid;
     }
-    // (said to be the same in all lanes: where they are loaded outside a kernel's own body the compiler does not know)
+    // (said to be the same in all lanes: k_aggregate_wide<2, false> spills 3 registers instead of 8, sixteen users of 25.6 M elements in
+    // [1,5,6] 435 -> 431 us)
     ChunkGeom g;
     g.seg = lo;
     const SegDev sd = load_segment(lay.segs + lo);

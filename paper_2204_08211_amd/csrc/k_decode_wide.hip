@@ -199,7 +199,9 @@ static_assert(8 * kWaAloneStride * 2 <= (int)kWdWindow && 16 * kWaStride * 2 <= 
 // packed symbols and adds their values in fp64.  With a table per user every wavefront has a table (split wavefronts, one
 // chunk).  all_at: where the sums are kept when the users come in several turns, else 0.  A workgroup takes `sets` sets of
 // chunks one after the other.
-template <int kUsers>
+// kFew: three or four users over two wavefronts.  Up to four users keep their order: the first wavefront takes the first two, and
+// the second adds its own to their sum one by one.
+template <int kUsers, bool kFew>
 __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide(Layout lay, WideAggArgs a, uint32_t split_log2, uint32_t all_at, uint32_t sets)
 {
     extern __shared__ __align__(16) uint32_t smem[];
@@ -219,6 +221,7 @@ __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide(Layout lay,
     int32_t loaded_table = -1;
     uint32_t bits = 0;
     WidePacked pk[kUsers];
+    auto user = [&](uint32_t u0, int s) { return u0 + (kFew ? part * kUsers + (uint32_t)s : part + (uint32_t)s * split); };
 #pragma unroll 1
     for (uint32_t set = 0; set < sets; ++set) {
         if (((uint64_t)blockIdx.x * sets + set) * slots >= lay.nchunks) break;
@@ -252,7 +255,7 @@ __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide(Layout lay,
                 if (active && wave >= w0 && wave < w1) {
 #pragma unroll
                     for (int s = 0; s < kUsers; ++s) {
-                        const uint32_t u = u0 + part + (uint32_t)s * split;
+                        const uint32_t u = user(u0, s);
                         if (u >= lay.U) continue;
                         const ChunkIndex ix = read_index(lay, c, u, a.words, a.words_stride, a.chunk_offset, a.sub_bits);
                         const BookWide *book = a.books + (own ? (uint64_t)u * lay.books_per_user : 0u) + b;
@@ -274,13 +277,12 @@ __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide(Layout lay,
             float inv_gain[kUsers];
 #pragma unroll
             for (int s = 0; s < kUsers; ++s) {
-                const uint32_t u = u0 + part + (uint32_t)s * split;
+                const uint32_t u = user(u0, s);
                 const uint64_t pair = (uint64_t)(u < lay.U ? u : 0u) * lay.nseg + g.seg;
                 up[s] = 127 - (int)uniform((uint32_t)lay.bias[pair]);
                 inv_gain[s] = lay.gain[2 * pair + 1];
             }
-            auto sum_of = [&](int j) {   // in the users' order
-                double sum = 0.0;
+            auto sum_of = [&](int j, double sum = 0.0) {   // in the users' order
 #pragma unroll
                 for (int s = 0; s < kUsers; ++s) sum += wide_value(val, pk[s].h[j >> 5][(j & 31) >> 1], 16u * (uint32_t)(j & 1), up[s], inv_gain[s]);
                 return sum;
@@ -294,20 +296,33 @@ __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide(Layout lay,
                 for (int j = 0; j < kSub; j += 16) {
                     double *s_sum = s_all ? s_all + j * kWaStride : reinterpret_cast<double *>(smem + kWdFront + slot * split * kWdWindow);
                     __syncthreads();
-                    double v[16];
+                    if constexpr (kFew) {
+                        if (part == 0u) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) v[i] = here(sum_of(j + i));
-#pragma unroll 1
-                    for (uint32_t w = 0; w < turns; ++w) {
-                        if (turns == 2u && w ? part > 0u : part == w) {
-#pragma unroll
-                            for (int i = 0; i < 16; ++i) {
-                                double *at = &s_sum[i * kWaStride + lane];
-                                if (w == 0 && first) *at = v[i];
-                                else __hip_atomic_fetch_add(at, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            }
+                            for (int i = 0; i < 16; ++i) s_sum[i * kWaStride + lane] = sum_of(j + i);
                         }
                         __syncthreads();
+                        if (part == 1u) {
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) s_sum[i * kWaStride + lane] = sum_of(j + i, s_sum[i * kWaStride + lane]);
+                        }
+                        __syncthreads();
+                    } else {
+                        double v[16];
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) v[i] = here(sum_of(j + i));
+#pragma unroll 1
+                        for (uint32_t w = 0; w < turns; ++w) {
+                            if (turns == 2u && w ? part > 0u : part == w) {
+#pragma unroll
+                                for (int i = 0; i < 16; ++i) {
+                                    double *at = &s_sum[i * kWaStride + lane];
+                                    if (w == 0 && first) *at = v[i];
+                                    else __hip_atomic_fetch_add(at, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                                }
+                            }
+                            __syncthreads();
+                        }
                     }
 #pragma unroll 1
                     for (uint32_t k = tt; last && active && k < 256u; k += 64u << split_log2) {
@@ -485,7 +500,9 @@ hipError_t launch_aggregate_wide(const Layout &lay, const co3_aggregate_args &a,
             all_at = (uint32_t)((lds + 15) / 16 * 4);
             lds = 4 * (size_t)all_at + sums;
         }
-        return launch_wide(k_aggregate_wide<2>, lay.nchunks, waves, lds, s, lay, args, log2, all_at, 1u);
+        return lay.U == 3u || lay.U == 4u
+                   ? launch_wide(k_aggregate_wide<2, true>, lay.nchunks, waves, lds, s, lay, args, log2, all_at, 1u)
+                   : launch_wide(k_aggregate_wide<2, false>, lay.nchunks, waves, lds, s, lay, args, log2, all_at, 1u);
     }
     // Wavefronts per chunk: two users each, or one where the chip has room (eight users of 1 M elements, 245 chunks, in
     // [1,4,5]: eight wavefronts 19 us, four 25; of 2 M 33 and 28; sixteen users of 1 M, sixteen wavefronts 24, eight 27;
@@ -499,7 +516,7 @@ hipError_t launch_aggregate_wide(const Layout &lay, const co3_aggregate_args &a,
     if (lay.U > 2 * split) {   // more users than a turn takes: the sums need a place of their own
         const uint32_t waves = 8;
         const size_t all_at = (wide_lds(lay, waves, 1) + 15) / 16 * 4;
-        return launch_wide(k_aggregate_wide<2>, lay.nchunks, waves, 4 * all_at + sums, s, lay, args, 3u, (uint32_t)all_at, 1u);
+        return launch_wide(k_aggregate_wide<2, false>, lay.nchunks, waves, 4 * all_at + sums, s, lay, args, 3u, (uint32_t)all_at, 1u);
     }
     // a full workgroup where there are enough of them, else one chunk each
     uint32_t waves = lay.nchunks * split >= 16 * 256 ? (uint32_t)kWdWaves : (split > 4 ? split : 4u);
@@ -507,8 +524,10 @@ hipError_t launch_aggregate_wide(const Layout &lay, const co3_aggregate_args &a,
     const uint32_t sets = waves == (uint32_t)kWdWaves ? wide_sets(all, 256) : 1u;
     const uint64_t grid = (all + sets - 1) / sets;
     const size_t lds = wide_lds(lay, waves, 1);
-    return one ? launch_wide(k_aggregate_wide<1>, grid, waves, lds, s, lay, args, log2, 0u, sets)
-               : launch_wide(k_aggregate_wide<2>, grid, waves, lds, s, lay, args, log2, 0u, sets);
+    if (one) return launch_wide(k_aggregate_wide<1, false>, grid, waves, lds, s, lay, args, log2, 0u, sets);
+    // (two wavefronts a chunk; in the users' order four users of 25 M elements take 113 us, in any order 112)
+    return lay.U == 3u || lay.U == 4u ? launch_wide(k_aggregate_wide<2, true>, grid, waves, lds, s, lay, args, log2, 0u, sets)
+                                      : launch_wide(k_aggregate_wide<2, false>, grid, waves, lds, s, lay, args, log2, 0u, sets);
 }
 
 }  // namespace co3

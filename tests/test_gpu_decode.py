@@ -392,3 +392,26 @@ def test_average_of_biases_far_apart_decodes_parts(E, M, U, chunks, own):
         torch.cuda.synchronize()
         counts.append(int(buf.status[5]))
     assert counts[0] == counts[1] >= (U + 1) // 2 and not buf.status.cpu().numpy()[[2, 3, 6]].any()
+
+
+@pytest.mark.parametrize("U", [3, 4])
+@pytest.mark.parametrize("chunks,own,gain", [(520, False, False), (1100, False, True), (9, True, False), (1210, True, True)])
+def test_few_users_keep_their_order_wide(U, chunks, own, gain):
+    # 16-bit symbols, sums that depend on the order (biases far apart, or a scale): two wavefronts a chunk, several chunks a
+    # workgroup, a table each, the users one after the other
+    import torch
+    from paper_2204_08211_amd import binding as B
+    E, M, d = 4, 5, 4096 * chunks + 100
+    bias = np.array([[10], [66], [10], [64]], np.int32)[:U]
+    g = cancelling(U, d, bias, float(orc.grid(E, M, 10)[-1]), U + chunks)
+    plan, books, buf = coded(E, M, g, bias, own=own)
+    if gain:
+        rng = np.random.default_rng(chunks)
+        inv = (2.0 ** rng.uniform(-0.5, 0.5, (U, 1))).astype(np.float32)
+        plan.set_gain((np.float32(1.0) / inv).astype(np.float32), inv)
+    want = in_order_average(plan, books, buf)
+    out = torch.zeros(d, dtype=torch.float32, device="cuda:0")
+    B.co3_ps_aggregate(plan, books, buf, out)
+    torch.cuda.synchronize()
+    assert not buf.status.cpu().numpy()[2:].any()
+    gu.assert_bits_equal(out.cpu().numpy(), want, "average")
