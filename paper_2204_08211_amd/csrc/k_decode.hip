@@ -371,7 +371,13 @@ __device__ inline void write_sums(const AggPart &p, double unit, Of of, bool fir
     }
 }
 
-__device__ inline uint32_t users_each(const AggPart &p, bool across) { return across ? (p.lay.U + p.waves - 1) / p.waves : p.lay.U; }
+// Users a wavefront takes.  A chunk's wavefronts are as many as its users, or a power of two: no quotient, which would be found
+// by an fp32 reciprocal while the conversions round toward zero.
+__device__ inline uint32_t users_each(const Layout &lay, uint32_t waves, bool across)
+{
+    if (!across) return lay.U;
+    return lay.U <= waves ? 1u : (lay.U + waves - 1u) >> (31 - __builtin_clz(waves));
+}
 
 // The value of a decoded entry's symbol where tables hold symbols.
 struct SymbolEntry {
@@ -396,7 +402,7 @@ __device__ inline void aggregate_int(const AggPart &p, int bias_hi, bool wide)
 #pragma unroll
     for (int i = 0; i < kSub; ++i) sum[i] = 0;
     each_user<kAcross, 4, 0>(
-        p, 0, users_each(p, kAcross),
+        p, 0, users_each(p.lay, p.waves, kAcross),
         [&](uint32_t, uint32_t u, const ChunkIndex &ix, Stream &st, const DecTable<4> &tab, const BookDev *book) {
             const int shift = bias_hi - (int)uniform((uint32_t)p.lay.bias[(uint64_t)u * p.lay.nseg + p.g.seg]);
             auto value = [E, M](uint32_t s) { return dec_value_bits(s, E, M); };
@@ -518,7 +524,7 @@ __device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &pl
             if constexpr (kGain) round_toward_zero();
         };
         auto place = [&](uint32_t i) { return part == 0 || i >= places.users ? 0u : (uint32_t)places.of(p, i); };
-        each_user<kAcross, 2, 0>(p, 0, ordered ? (p.wave ? 0u : p.lay.U) : users_each(p, kAcross), on_user, ordered, place, part + 1 == kParts);
+        each_user<kAcross, 2, 0>(p, 0, ordered ? (p.wave ? 0u : p.lay.U) : users_each(p.lay, p.waves, kAcross), on_user, ordered, place, part + 1 == kParts);
         round_to_nearest();
         write_sums<kAcross, double, 0, kPart>(p, 1.0, [&](int j) { return sum[j]; }, true, true, part * kPart);
         round_toward_zero();
@@ -671,7 +677,7 @@ __global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate_int(Layout lay,
     round_toward_zero();
     int lo, hi;
     bias_range(lay, p.g.seg, lo, hi);
-    const bool fits = int_sum_bits(lay, hi - lo, kAcross ? (lay.U + p.waves - 1) / p.waves : lay.U) <= 31;
+    const bool fits = int_sum_bits(lay, hi - lo, users_each(lay, p.waves, kAcross)) <= 31;
     const bool wide = int_sum_bits(lay, hi - lo, lay.U) > 31;
     bool rare = p.g.scaled || !fits;
     if constexpr (!kAcross) rare = any_wave(p, rare, 1);

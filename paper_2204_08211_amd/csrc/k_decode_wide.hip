@@ -272,6 +272,11 @@ __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide(Layout lay,
                 w0 = w1;
             } while (w0 < waves);
             round_to_nearest();
+#pragma unroll
+            for (int s = 0; s < kUsers; ++s) {   // (the values round: not before the mode is back)
+                words_here(pk[s].h[0]);
+                words_here(pk[s].h[1]);
+            }
 
             int up[kUsers];
             float inv_gain[kUsers];
@@ -406,7 +411,7 @@ __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide_own(Layout 
 #pragma unroll
                     for (int i = 0; i < kSub / 2; ++i) {
                         const uint32_t w = half ? pk.h[1][i >> 1] : pk.h[0][i >> 1];
-                        sum[i] = here(sum[i] + wide_value(val, w, 16u * (uint32_t)(i & 1), up, inv_gain));
+                        sum[i] = here(sum[i] + wide_value(val, here(w), 16u * (uint32_t)(i & 1), up, inv_gain));
                     }
                 }
                 w0 = w1;
