@@ -48,7 +48,7 @@ struct BookDev {
     uint8_t sorted[kMaxA];       // symbols ordered by (length, symbol)
     uint32_t maxlen;
     uint32_t nactive;
-    uint32_t format;             // (E << 8) | M that dval[] was filled for
+    uint32_t format;             // (E << 8) | M that dval[] was filled for (dec_value_is_int(E), else it is not)
     // Decode tables over the complement u of the next 32 bits: entry i serves the u whose leading bits, as a floating
     // point number of log2(A) - 1 mantissa bits, are i = (exponent mod 32) * A / 2 + mantissa.
     // (symbol << 8) | length, and (what the PS sums (dec_value_bits) | length); kLenSlow: no code of up to 31 bits

@@ -72,7 +72,7 @@ static void finish_tables(BookDev *b, uint32_t A, int E, int M)
             break;
         }
         b->dsym[i] = (uint16_t)((sym << 8) | len);
-        b->dval[i] = dec_value_bits(sym, E, M) | len;
+        if (dec_value_is_int(E)) b->dval[i] = dec_value_bits(sym, E, M) | len;
     }
 }
 

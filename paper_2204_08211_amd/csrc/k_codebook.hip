@@ -40,8 +40,9 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     __shared__ uint64_t tmpw[kMaxA];      // a round's nodes in merged order: weight
     __shared__ int tmpid[kMaxA];          // and node index
     __shared__ uint32_t wcnt[kCbThreads / 64][65];   // codes of every length per wavefront of symbols
-    __shared__ uint64_t end32[33];        // codes of up to l bits lie below end32[l], left-aligned in 32 bits
-    __shared__ uint32_t entry_sym[kMaxA], entry_val[kMaxA];   // what a decode table's entry carries, by rank
+    __shared__ uint32_t limit[32];        // a window's complement <= limit[l] (and not 0): its code has more than l bits
+    __shared__ uint32_t base[65];         // a code of l bits has rank base[l] + code
+    __shared__ uint32_t entry_sym[kMaxA];   // what a decode table's entry carries, by rank
     __shared__ int err;
 
     uint64_t myw = 0;
@@ -221,8 +222,9 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
         first[l] = code;
         off[l] = o;
         const uint64_t used = __ballot(cl != 0);
-        if (l <= 32) end32[l] = (code + cl) << (32 - l);
-        if (t == 0) end32[0] = 0;
+        base[l] = o - (uint32_t)code;
+        const uint64_t end = l < 32 ? (code + cl) << (32 - l) : 0;   // codes of up to l bits lie below, left-aligned in 32 bits
+        if (l < 32) limit[l] = end >> 32 ? 0u : ~(uint32_t)end;
         if (t == 0) {
             B.maxlen = used ? 64u - (uint32_t)__clzll((long long)used) : 0u;
             B.nactive = bad ? 0 : (uint32_t)n;
@@ -237,7 +239,6 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
         code = first[L] + rank;
         sorted[off[L] + rank] = (uint32_t)t;
         entry_sym[off[L] + rank] = ((uint32_t)t << 8) | L;
-        entry_val[off[L] + rank] = dec_value_bits((uint32_t)t, E, M) | L;
         if (L <= (uint32_t)kFastLen) fast = (L << 24) | (uint32_t)code;
     }
     B.code[t] = code;
@@ -248,31 +249,36 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     B.sorted[t] = (t < n && !bad) ? (uint8_t)sorted[t] : 0;
 
     // decode tables (decode_core.h), two entries at a time: the window's complement at the entry's low end, its code's
-    // length by a binary search of the ends (they grow with the length), the rest from the code's rank
+    // length by a binary search of the limits (they fall with the length; the first steps' from registers), the rest from
+    // the code's rank
     const uint32_t nm = (uint32_t)(E + M);
-#pragma unroll 4
+    const bool values = dec_value_is_int(E);   // only integer sums read them
+    const uint32_t l8[4] = {0u, limit[8], limit[16], limit[24]}, l4[4] = {limit[4], limit[12], limit[20], limit[28]};
+#pragma unroll 8
     for (uint32_t i2 = t; i2 < dec_table_entries(A) / 2; i2 += kCbThreads) {
-        uint32_t es[2], ev[2];
+        uint32_t es[2];
 #pragma unroll
         for (uint32_t b = 0; b < 2; ++b) {
             const uint32_t i = 2 * i2 + b, binade = i >> nm;
             const uint32_t ex = binade == 31u ? 0u : binade + 1u;            // exponent of u
             const uint32_t lead = (1u << nm) | (i & ((1u << nm) - 1u));
-            const uint32_t x = ~(ex >= nm ? (uint32_t)((uint64_t)lead << (ex - nm)) : lead >> (nm - ex));
-            uint32_t l = 0;   // the largest l with x >= end32[l]: the code has l + 1 bits
-#pragma unroll
-            for (uint32_t k = 16; k; k >>= 1) l = (uint64_t)x >= end32[l + k] ? l + k : l;
+            const uint32_t u = ex >= nm ? (uint32_t)((uint64_t)lead << (ex - nm)) : lead >> (nm - ex);
+            // the largest l with u <= limit[l]: the code has l + 1 bits
+            const uint32_t q = u <= l8[2] ? (u <= l8[3] ? 3u : 2u) : (u <= l8[1] ? 1u : 0u);
+            const uint32_t at4 = q > 1u ? (q > 2u ? l4[3] : l4[2]) : (q ? l4[1] : l4[0]);
+            uint32_t l = 8u * q + (u <= at4 ? 4u : 0u);
+            l += u <= limit[l + 2u] ? 2u : 0u;
+            l += u <= limit[l + 1u] ? 1u : 0u;
             es[b] = kLenSlow;
-            ev[b] = kLenSlow;
             const uint32_t L = l + 1;
             if (binade != 0 && L < 32u) {   // (below the end of every code of up to 31 bits)
-                const uint32_t r = off[L] + ((x >> (32 - L)) - (uint32_t)first[L]);
-                es[b] = entry_sym[r & (kMaxA - 1)];
-                ev[b] = entry_val[r & (kMaxA - 1)];
+                es[b] = entry_sym[(base[L] + (~u >> (32 - L))) & (kMaxA - 1)];
             }
         }
         reinterpret_cast<uint32_t *>(B.dsym)[i2] = es[0] | (es[1] << 16);
-        reinterpret_cast<uint2 *>(B.dval)[i2] = make_uint2(ev[0], ev[1]);
+        if (values)
+            reinterpret_cast<uint2 *>(B.dval)[i2] = make_uint2(dec_value_bits(es[0] >> 8, E, M) | (es[0] & 0xffu),
+                                                              dec_value_bits(es[1] >> 8, E, M) | (es[1] & 0xffu));
     }
 }
 

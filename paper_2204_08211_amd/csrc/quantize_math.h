@@ -92,7 +92,7 @@ __device__ inline Philox4 element_random_words(uint64_t elem, uint32_t user, uin
 }
 
 // fp32 pattern of the value of a symbol (exact: every representative is an fp32).
-__device__ __host__ inline uint32_t symbol_value_bits(uint32_t sym, int E, int M, int bias)
+__device__ inline uint32_t symbol_value_bits(uint32_t sym, int E, int M, int bias)
 {
     const uint32_t sign_shift = (uint32_t)(E + M);
     const uint32_t k = sym & (((uint32_t)1 << sign_shift) - 1u);
@@ -114,13 +114,12 @@ __device__ __host__ inline uint32_t symbol_value_bits(uint32_t sym, int E, int M
     return bits | (s << 31);
 }
 
-// What a decode table's entry carries above its low byte for the PS average, of a format of up to 8 bits: the value in
-// units of the smallest subnormal, 2^(1 - bias - M), as a signed number of at most 20 bits (up to four exponent bits);
-// the top 16 bits of its fp32 pattern at bias 0 (more exponent bits: at most two mantissa bits are left).
+// What a decode table's entry carries above its low byte for integer sums of the PS average, which formats of up to 8 bits with
+// up to four exponent bits have: the value in units of the smallest subnormal, 2^(1 - bias - M), as a signed number of at
+// most 20 bits.
 __device__ __host__ inline bool dec_value_is_int(int E) { return E <= 4; }
 __device__ __host__ inline uint32_t dec_value_bits(uint32_t sym, int E, int M)
 {
-    if (!dec_value_is_int(E)) return symbol_value_bits(sym, E, M, 0) & 0xffff0000u;
     const uint32_t k = sym & ((1u << (E + M)) - 1u), f = k >> M, am = k & ((1u << M) - 1u);
     const uint32_t mag = f ? ((1u << M) | am) << (f - 1u) : am;
     return (((sym >> (E + M)) & 1u) ? 0u - mag : mag) << 8;
