@@ -103,6 +103,20 @@ __device__ inline void words_here(Words &w)
     for (int i = 0; i < 16; ++i) w[i] = here(w[i]);
 }
 
+// Where an entry lies in its table: byte alphabets, bytes from the table's start (key: u as fp32, rounded toward zero) ...
+__host__ __device__ inline uint32_t byte_table_shift(uint32_t A, uint32_t bytes)
+{
+    return 24u - (31u - (uint32_t)__builtin_clz(A)) - (bytes == 4u ? 2u : 1u);
+}
+__host__ __device__ inline uint32_t byte_table_mask(uint32_t A, uint32_t bytes) { return dec_table_entries(A) * bytes - bytes; }
+__host__ __device__ inline uint32_t byte_table_at(uint32_t key, uint32_t shift, uint32_t mask) { return (key >> shift) & mask; }
+// ... and wide ones, where the field `off`, `width` of the key (u itself, or the larger of u and this as fp32) is the index, less
+// wide_table_first(bits)
+constexpr uint32_t kWideTabLeast = 2u << kWideTabLow;   // the lowest binade holds nothing
+__host__ __device__ inline uint32_t wide_table_off(uint32_t bits) { return bits ? 23u - bits : 32u - kWidePrefixBits; }
+__host__ __device__ inline uint32_t wide_table_width(uint32_t bits) { return bits ? bits + 5u : kWidePrefixBits; }
+__host__ __device__ inline uint32_t wide_table_first(uint32_t bits) { return bits ? kWideTabLow << bits : 0u; }
+
 // Where the entries of a code lie in LDS.  Entry: code length in bits 0..7 (kLenSlow: slow path), above it what the sink
 // asks for.  kBytes 4 or 2 per entry.  The table lies at a multiple of its size.
 template <int kBytes>
@@ -112,16 +126,15 @@ struct DecTable {
     uint32_t shift, mask;
     __device__ inline void init(uint32_t address, uint32_t A)
     {
-        const uint32_t nbits = 31u - (uint32_t)__builtin_clz(A);
         base = address;
-        shift = 24u - nbits - (kBytes == 4 ? 2u : 1u);
-        mask = here(dec_table_entries(A) * (uint32_t)kBytes - (uint32_t)kBytes);   // (v_and_or_b32 takes one scalar operand)
+        shift = byte_table_shift(A, kBytes);
+        mask = here(byte_table_mask(A, kBytes));   // (v_and_or_b32 takes one scalar operand)
     }
     // u is a window's complement, whole: an entry of a code of 25 bits or more depends on its low byte too
     __device__ inline uint32_t operator()(uint32_t u) const
     {
         const float f = (float)u;
-        const uint32_t a = ((__float_as_uint(f) >> shift) & mask) | base;
+        const uint32_t a = byte_table_at(__float_as_uint(f), shift, mask) | base;
         if constexpr (kBytes == 4) return *(const lds_u32 *)a;
         else return *(const lds_u16 *)a;
     }
@@ -145,19 +158,13 @@ struct WideDecTable {
     {
         limits = limits_address;
         prefixes = bits == 0;
-        if (prefixes) {
-            base = address;
-            off = 32u - kWidePrefixBits;
-            width = here(kWidePrefixBits);
-            return;
-        }
-        base = address - (kWideTabLow << bits) * 4u;
-        off = 23u - bits;
-        width = here(bits + 5u);   // (v_bfe_u32 takes one scalar operand)
+        base = address - wide_table_first(bits) * 4u;
+        off = wide_table_off(bits);
+        width = here(wide_table_width(bits));   // (v_bfe_u32 takes one scalar operand)
     }
     __device__ inline uint32_t operator()(uint32_t u) const
     {
-        const float f = (float)(u > (2u << kWideTabLow) ? u : 2u << kWideTabLow);   // the lowest binade holds nothing
+        const float f = (float)(u > kWideTabLeast ? u : kWideTabLeast);
         const uint32_t key = prefixes ? u : __float_as_uint(f);
         return *(const lds_u32 *)(__builtin_amdgcn_ubfe(key, off, width) * 4u + base);
     }
@@ -215,8 +222,7 @@ __device__ inline ChunkGeom chunk_geom(const Layout &lay, uint64_t c)
         const uint32_t mid = (lo + hi) >> 1;
         if (uniform(lay.segs[mid].chunk_start) <= c) lo = mid; else hi = mid;
     }
-    // (said to be the same in all lanes: k_aggregate_wide<2, false> spills 3 registers instead of 8, sixteen users of 25.6 M elements in
-    // [1,5,6] 435 -> 431 us)
+    // (said to be the same in all lanes: k_aggregate_wide<2, false> spills 3 registers instead of 8)
     ChunkGeom g;
     g.seg = lo;
     const SegDev sd = load_segment(lay.segs + lo);

@@ -150,7 +150,8 @@ static void finish_wide_table(BookWide *b, uint32_t A)
         b->tab[i] = entry(~(uint32_t)((uint64_t)((1u << nm) | (i & ((1u << nm) - 1u))) << (ex - nm)), 32 - ex + nm);
         if (b->tab[i] == kLenSlow) missing += 1ull << (ex - nm);
     }
-    if (missing > (1ull << 32) - end[kWidePrefixBits]) {
+    // (the device's builder has the rule and why fewer bits never meet it)
+    if (nm == wide_tab_bits_max(A) && missing > (1ull << 32) - end[kWidePrefixBits]) {
         b->tab_bits = 0;
         std::fill(b->tab, b->tab + kWideTabMax, kLenSlow);
         for (uint32_t i = 0; i < wide_tab_entries(0); ++i) b->tab[i] = entry(~(i << (32 - kWidePrefixBits)), kWidePrefixBits);

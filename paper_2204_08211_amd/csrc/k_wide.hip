@@ -516,7 +516,9 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
         B.tab[i] = e;
     }
     bool prefixes = false;
-    if (nm == wide_tab_bits_max(A)) {   // (with fewer bits it leaves next to nothing)
+    // Fewer bits than the most resolve every code with up to ten leading ones, and what they leave of the others (eleven ones and
+    // more than nm bits behind the next) has more than twelve bits: a table by the first twelve would resolve no more.
+    if (nm == wide_tab_bits_max(A)) {
         if (missing) atomicAdd(&s_missing, (unsigned long long)missing);
         __syncthreads();
         prefixes = s_missing > (1ull << 32) - end32[kWidePrefixBits];
