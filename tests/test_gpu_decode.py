@@ -415,3 +415,30 @@ def test_few_users_keep_their_order_wide(U, chunks, own, gain):
     torch.cuda.synchronize()
     assert not buf.status.cpu().numpy()[2:].any()
     gu.assert_bits_equal(out.cpu().numpy(), want, "average")
+
+
+@pytest.mark.parametrize("U,E,M,chunks,own", [(8, 4, 5, 1100, False), (1, 5, 6, 4200, False), (18, 4, 4, 2, False),   # sets of chunks, more than a turn
+                                              (6, 4, 5, 1210, True), (2, 5, 6, 1201, True), (7, 4, 4, 30, True)])      # the users in turns, two wavefronts
+def test_wide_average_with_a_scale(U, E, M, chunks, own):
+    # 16-bit symbols with a scale where a workgroup takes several chunks or the users one after the other
+    rng = np.random.default_rng(60 + U)
+    seg_len = [4096 * chunks + 3, 4096 + 9]
+    d, b0 = sum(seg_len), 2 ** (E - 1)
+    import torch
+    from paper_2204_08211_amd import binding as B
+    bias = (b0 + rng.integers(0, 3, (U, 2))).astype(np.int32)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(U)
+    plan, books, buf = coded(E, M, torch.randn((U, d), generator=gen, device="cuda:0") * float(orc.grid(E, M, b0 + 2)[-1]) / 4, bias,
+                             own=own, seg_len=seg_len)
+    # (the order of the users is defined up to four, and where they come one after the other)
+    exact = U > 4 and not (own and chunks >= 1200)
+    inv = (2.0 ** (rng.integers(-1, 2, (U, 2)) if exact else rng.uniform(-0.5, 0.5, (U, 2)))).astype(np.float32)
+    inv[:, 1] = 1.0
+    plan.set_gain((np.float32(1.0) / inv).astype(np.float32), inv)
+    want = in_order_average(plan, books, buf)
+    out = torch.full((d,), float("nan"), dtype=torch.float32, device="cuda:0")
+    B.co3_ps_aggregate(plan, books, buf, out)
+    torch.cuda.synchronize()
+    assert not buf.status.cpu().numpy()[2:].any()
+    gu.assert_bits_equal(out.cpu().numpy(), want, "average")

@@ -835,10 +835,9 @@ def test_wide_long_codes_per_user_tables_and_device_builder():
 
 
 @pytest.mark.parametrize("per_user", [False, True])
-def test_wide_decoder_second_level_tables(per_user):
-    # a code with 500 magnitudes of about 10 bits, 1400 of 12 to 16 (more 12-bit prefixes hold only longer codes
-    # than the decoder has second-level tables: some of these codes are found there, the rest by search) and 24 of
-    # up to 40 bits; every symbol with a code about equally often in the data; the host's tables and the device's
+def test_wide_decoder_table_and_search(per_user):
+    # a code with 500 magnitudes of about 10 bits, 1400 of 12 to 16 (more bits behind their leading ones than the decoder's
+    # table has: some of these codes are found there, the rest by search) and 24 of up to 40 bits; every symbol with a code about equally often in the data; the host's tables and the device's
     import torch
     from paper_2204_08211_amd import binding as B
     E, M, U, d = 5, 6, 3, 4096 * 7 + 300
@@ -1189,8 +1188,8 @@ def test_extreme_biases_through_the_many_user_average():
 
 @pytest.mark.parametrize("K", [0, 2, 3, 4, 6, 7, 40])
 def test_device_built_decode_tables(K):
-    # a code built on the device with lengths of up to K + 8 bits: the direct table alone, the second-level tables and
-    # the search list have to lead back to the symbols that were coded
+    # a code built on the device with lengths of up to K + 8 bits: its table, and for words of more than 31 bits the slow path,
+    # have to lead back to the symbols that were coded
     import torch
     from paper_2204_08211_amd import binding as B
     E, M, d, bias = 4, 3, 4096 * 3 + 5, 12
