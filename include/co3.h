@@ -63,9 +63,12 @@ enum {
  * 1 + exp_bits + mant_bits <= 12.  Up to 8 bits a symbol is one byte.  With 9 to 12 bits ("wide"
  * alphabets) a symbol is a 16-bit word: every `symbols` buffer below then holds uint16_t (its size is
  * co3_plan_symbols_bytes() all the same), the code tables have up to 4096 entries and the library
- * runs kernels of its own for them, in which a workgroup shares one copy of a table; a fixed code
- * without a symbol buffer is coded in the same three steps as with one, the symbols kept in the
- * workspace.                                                                                    */
+ * runs kernels of its own for them, in which a workgroup shares one copy of a table.  A fixed code
+ * with neither symbol nor count buffer is coded in a single sweep as well, whose bounded wait may
+ * be counted in CO3_STAT_STALLED (see below); with a count buffer, for the stochastic conversion of
+ * layers that do not start at multiples of four elements, and for a plan whose tables change so
+ * often that the sweep's entries do not fit the workspace, it is coded in the three steps of a
+ * rebuilt code, the symbols kept in the workspace.                                              */
 typedef struct {
     int32_t exp_bits;
     int32_t mant_bits;
@@ -181,7 +184,9 @@ int co3_model_weights_device(const co3_plan *plan, const co3_gennorm_params *par
  * bias: device [U][nseg] (out); error: device [U][nseg] expected squared errors, or NULL;
  * workspace: device, co3_plan_bias_workspace_bytes().
  * co3_plan_set_bias_device installs a device bias table in the plan (device-to-device copy on
- * `stream`, no synchronisation); its values must be in the supported range, as the ones written
+ * `stream`, no synchronisation; how far the users' biases lie apart is then known to the kernels
+ * only, which average biases too far apart for integer sums by a longer way than they take for
+ * biases installed from the host); its values must be in the supported range, as the ones written
  * by co3_model_bias_device are.  co3_bias_from_model is the same argmin for one parameter triple
  * on the host.                                                                               */
 size_t co3_plan_bias_workspace_bytes(const co3_plan *plan);
@@ -319,11 +324,13 @@ typedef struct {
  * out[i] = fl32((sum over u = 0..U-1, in fp64, of ghat_i^(u)) * (1.0 / U)).
  * With `model`, also the PS model update of eq. (aggregate hat) / Algorithm 1 line 14 in the same
  * pass: model[i] = fl32(model[i] - eta * ((sum over u) * (1.0 / U))), products and difference in
- * fp64, one rounding.  With five or more users the fp64 sums are formed by atomic additions in
- * whatever order the wavefronts arrive.  The addends are representatives, so the sum is exact,
- * and independent of that order, whenever (2^exp_bits - 2) + mant_bits + 1 + (largest minus
- * smallest bias of the layer over the users) + log2 U <= 53 (add 23 - mant_bits for a plan that
- * carries a gain); beyond that the last bit of a sum may depend on the order.                 */
+ * fp64, one rounding.  Up to four users are added in their order.  With five or more the sums may
+ * be formed in integers, where those are exact, or from parts in any order.  The addends are
+ * representatives, so the sum is exact, and independent of that order, whenever (2^exp_bits - 2) +
+ * mant_bits + 1 + (largest minus smallest bias of the layer over the users) + log2 U <= 53 (add
+ * 23 - mant_bits for a plan that carries a gain); beyond that the last bit of a sum may depend on
+ * the order.  A captured call follows the biases and the gain that the plan carries when it is
+ * replayed.                                                                                     */
 int co3_ps_aggregate(const co3_plan *plan, const co3_aggregate_args *args, void *stream);
 
 /* ---- measurement aid ---------------------------------------------------------------------
