@@ -419,7 +419,7 @@ __device__ inline void aggregate_int(const AggPart &p, int bias_hi, bool wide)
 }
 
 // Where the users' streams stand between the parts that aggregate_spread takes: a lane's place in its sub-chunk (below 2^15
-// bits: half of it), in the top bit whether a code was damaged before it.  In LDS, kUsers of every wavefront's users.
+// bits: half of it), in the top bit whether a code was damaged before it.
 struct StreamPlaces {
     uint16_t *at;     // behind everything else in LDS
     uint32_t users;   // of a wavefront's; the others are decoded from the start in every part
@@ -532,8 +532,9 @@ __device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &pl
     }
 }
 
-// Users whose symbols meet in LDS at most: two a wavefront, 5 KB each, so that sixteen wavefronts still fit a CU.  (Four a
-// wavefront leave room for eight: sixteen users of 12 M elements in [1,5,2], a round 600 us from the sums, 794 this way.)
+// Users whose symbols meet in LDS at most: two a wavefront, 5 KB each, so that sixteen wavefronts still fit a CU up to fifteen
+// users, and eight with sixteen.  (Four a wavefront: sixteen users of 12 M elements in [1,5,2], a round 600 us from the sums,
+// 794 this way.)
 constexpr uint32_t kStageUsers = 2 * kAggWaves;
 __host__ __device__ constexpr uint32_t stage_bytes(uint32_t U) { return 4u * U * kStageWords + kStageUsers * (uint32_t)(sizeof(double) + sizeof(float)); }
 // The same sums where the workgroup's wavefronts decode all users in one turn: the symbols meet in LDS, an eighth of what
@@ -820,7 +821,8 @@ hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3
     uint32_t waves = lay.U <= (uint32_t)kAggWaves && lay.nchunks * lay.U <= resident ? lay.U : kAggWaves;
     while (waves > 1 && (waves > lay.U || lay.nchunks * waves > resident)) waves = waves > 4 ? 4 : waves / 2;
     while (lay.U > 12u * waves && waves < kAggWaves) waves = waves < 4 ? 4 : kAggWaves;
-    // (tables of their own in LDS per wavefront: the symbols' take half the room of the values')
+    // (tables of their own in LDS per wavefront: the symbols' take half the room of the values'.  Biases set from device memory are
+    // taken to lie close together; where they do not, the kernel takes aggregate_rare)
     const bool ints = dec_value_is_int(lay.E) && !facts.has_gain && (!lay.per_user_books || lay.A <= 64u) &&
                       int_sum_bits(lay, facts.bias_spread, (lay.U + waves - 1) / waves) <= 31;
     if (ints) {
