@@ -624,7 +624,7 @@ __device__ inline AggPart agg_part(const Layout &lay, const AggArgs &a, uint32_t
     if (!active) c = lay.nchunks - 1;
     int32_t *s_book = reinterpret_cast<int32_t *>(smem + front_words(dec_table_entries(lay.A)) + kAggWaves * stage_window_words(lay.A));
     return AggPart{lay, a, smem, s_book, all_at ? reinterpret_cast<double *>(smem + all_at) : nullptr,
-                   chunk_geom(lay, c), c, active, wave, kAcross ? blockDim.x >> 6 : (uint32_t)kAggWaves};
+                   uniform(chunk_geom(lay, c)), c, active, wave, kAcross ? blockDim.x >> 6 : (uint32_t)kAggWaves};
 }
 
 // The layer's entry and biases say which way the sums take, and not the host: a captured launch may be replayed on a plan that

@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64 * kWdWaves, 4) void k_aggregate_wide(Layout lay,
         uint64_t c = ((uint64_t)blockIdx.x * sets + set) * slots + slot;
         const bool active = c < lay.nchunks;
         if (!active) c = lay.nchunks - 1;
-        const ChunkGeom g = chunk_geom(lay, c);
+        const ChunkGeom g = uniform(chunk_geom(lay, c));
         if (several) {
             __syncthreads();
             if (lane == 0) s_book[wave] = g.book;
