@@ -549,6 +549,13 @@ __device__ inline void aggregate_staged(const AggPart &p)
     double *s_scale = reinterpret_cast<double *>(p.smem + lay.U * kStageWords);   // [kStageUsers], behind the symbols
     float *s_inv_gain = reinterpret_cast<float *>(s_scale + kStageUsers);         // [kStageUsers]
     const uint32_t t = threadIdx.x, lane = t & 63u;
+    int bias = 0;
+    float inv_gain = 1.0f;
+    if (t < lay.U) {   // a workgroup has as many threads; requested here, needed when the users are decoded
+        const uint64_t pair = (uint64_t)t * lay.nseg + p.g.seg;
+        bias = lay.bias[pair];
+        inv_gain = lay.gain[2 * pair + 1];
+    }
     u32x16 pk[kUsers];
 #pragma unroll
     for (int s = 0; s < kUsers; ++s) pk[s] = 0u;
@@ -559,13 +566,6 @@ __device__ inline void aggregate_staged(const AggPart &p)
                                          [&](int gr, const uint32_t (&e)[kGroup]) { pack_group(pk[i], gr, e); });
         });
     round_to_nearest();
-    int bias = 0;
-    float inv_gain = 1.0f;
-    if (t < lay.U) {   // a workgroup has as many threads
-        const uint64_t pair = (uint64_t)t * lay.nseg + p.g.seg;
-        bias = lay.bias[pair];
-        inv_gain = lay.gain[2 * pair + 1];
-    }
     __syncthreads();   // tables and windows are done with
     if (t < lay.U) {
         s_scale[t] = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
@@ -587,7 +587,7 @@ __device__ inline void aggregate_staged(const AggPart &p)
     for (uint32_t k = t; k < (uint32_t)kChunk / 4; k += 64 * p.waves) {   // elements 4 k .. 4 k + 3
         const uint32_t *at = p.smem + (k >> 4) * kStageStride + (k & 15u);
         double sum[4] = {0.0, 0.0, 0.0, 0.0};
-        if (p.g.scaled) {
+        if (__builtin_expect(p.g.scaled, 0)) {
 #pragma unroll 4
             for (uint32_t u = 0; u < lay.U; ++u) {
                 const uint32_t w = at[u * kStageWords];
