@@ -4,7 +4,8 @@
 //
 // HBM traffic per element: read g (4) + read m (4) + write m' (4) + write b (r/d bits).
 //
-// A workgroup of four wavefronts takes four consecutive chunks of one user:
+// A workgroup takes four consecutive chunks of one user (small inputs: one).  Two forms of the sweep and the coding share the
+// rest.  Streaming, a wavefront a chunk, for large inputs:
 //   1. wavefront w quantizes chunk w (16 KB of g and of m, requested a quarter at a time with the
 //      next quarter in flight while the current one is computed) and leaves the symbols in LDS,
 //      in the rows of 16 + 1 words the pack step reads without bank conflicts; the code's tables go
@@ -27,20 +28,26 @@
 //      (which also yields the sub-chunk sizes) and moves the rows to their bit offsets within the
 //      chunk (this needs no stream offset: chunks are word-aligned);
 //   4. the chunk's words are copied out coalesced at the offset the look-back gave.
+// Teams, four wavefronts a chunk (run_coder.h): a thread takes sixteen elements, all requested at once, and codes their run of
+// symbols from registers to its place among the chunk's words in LDS; the look-back's answers travel meanwhile.  What such a
+// launch takes is a workgroup's way, at 2 M elements of sixteen users: ticket 3.6 us, sweep 6.4, the slowest
+// wavefront of sixteen 4.3, lengths and coding 2.5, the predecessors' sizes 5.8, out 1.6.
 #include <atomic>
 
 #include "co3_internal.h"
 #include "lookback.h"
 #include "pack_core.h"
 #include "quantize_math.h"
+#include "run_coder.h"
+#include "wave_ops.h"
 
 namespace co3 {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-constexpr int kFuCpb = 4;                            // chunks (= wavefronts) per workgroup ...
-constexpr int kFuCpbSmall = 1;                       // ... and for inputs too small to fill the device that way,
-constexpr int kFuTeamSmall = 4;                      // where as many wavefronts quantize a chunk together
+constexpr int kFuCpb = 4;                            // chunks per workgroup ...
+constexpr int kFuCpbSmall = 1;                       // ... and for small inputs
+constexpr int kFuTeam = 4;                           // wavefronts that share a chunk where they do
 constexpr int kFuRow = kPcSymRow;                    // 16 words of symbols + 1 pad
 constexpr int kFuStage = kPcSymWords;                // 1088 words hold a chunk's symbols
 constexpr int kFuBatch = 4;                          // 16-byte vectors of g (and of m) a lane requests at a time
@@ -51,7 +58,6 @@ uint32_t lookback_polls() { return g_spin_limit.load(); }
 
 static_assert(kChunk % (4 * 64 * kFuBatch) == 0, "whole batches per chunk");
 static_assert(kChunk % (64 * kFuScalar) == 0, "whole element rounds per chunk");
-static_assert(kFuBatches % kFuTeamSmall == 0, "whole batches per wavefront of a team");
 
 __device__ inline uint32_t fu_find_chunk_segment(const SegDev *segs, uint32_t nseg, uint64_t chunk)
 {
@@ -80,6 +86,195 @@ __device__ inline void fu_lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// ---- a team: four wavefronts a chunk, a run of 16 symbols a thread (run_coder.h) ----
+
+// What a thread keeps of its run between the sweep and the coding.
+struct TeamRun {
+    uint32_t w[4];        // symbols
+    uint32_t e[kRun];     // their entries; 0 where there is none, or where the chunk's last ones stand in the first run
+    uint32_t tail[4];     // those
+    uint32_t from, to;    // its symbols in w
+    uint32_t excl, bits;  // bits before it in the wavefront's share of the chunk, its own
+    uint32_t total;       // that share
+    uint32_t in_order;    // bits of the wavefront's run of the lane's number
+    uint32_t tail_bits;
+    bool slow;            // an entry is not enough, or a pair too long
+};
+
+// The team's wavefront `part` quantizes vectors 256 part .. 256 part + 255 of the chunk, 64 side by side with every request.  A
+// transposition within the quads of lanes then gives lane 4 q + i the symbols of vectors 64 i + 4 q .. + 3: run 16 i + q of the
+// wavefront's (run_of_lane).
+// A chunk that starts `shift` elements behind the 16-byte grid takes the vectors from the boundary below it, and vector 0, of
+// which the first `shift` elements lie before the chunk, has the chunk's last ones in their place: every vector is whole, and the
+// runs are those `shift` elements ahead, with the last few symbols of the chunk in front of the first run.
+__device__ inline uint32_t run_of_lane(uint32_t lane) { return 16u * (lane & 3u) + (lane >> 2); }
+__device__ inline uint32_t lane_of_run(uint32_t r) { return 4u * (r & 15u) + (r >> 4); }
+
+template <bool kSR, bool kHist>
+__device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, uint32_t part, uint64_t e0, uint32_t nk, uint32_t shift,
+                                  int32_t bias, float gain, float inv_gain, const float *__restrict__ gu, const float *mu,
+                                  float *mo, float gamma, uint64_t seed, uint32_t *hist, uint64_t *__restrict__ status)
+{
+    const uint32_t lane = threadIdx.x & 63u, sign_shift = lay.E + lay.M;
+    const uint32_t v0 = 256u * part + lane;   // vectors v0, v0 + 64, + 128, + 192
+    const QConst qc = make_qconst(lay.E, lay.M, bias);
+    uint32_t n_nonfinite = 0, n_clamped = 0;
+    auto element = [&](float gj, float mj, uint32_t rnd, uint32_t in, float &eo) {
+        const float v = __fadd_rn(gj, __fmul_rn(gamma, mj));
+        const float y = __fmul_rn(v, gain);
+        uint32_t s, flags;
+        float q;
+        if constexpr (kSR) quantize_stochastic(y, qc, lay.E, lay.M, bias, sign_shift, rnd, s, q, flags);
+        else quantize(y, qc, sign_shift, s, q, flags);
+        q = __fmul_rn(q, inv_gain);
+        eo = (flags & 1u) ? 0.0f : __fsub_rn(v, q);
+        n_nonfinite += flags & in;
+        n_clamped += (flags >> 1) & in;
+        if constexpr (kHist) {
+            if (in) atomicAdd(&hist[s], 1u);
+        }
+        return s;
+    };
+    if (nk == (uint32_t)kChunk) {
+        const float *ga = gu - shift, *ma = mu - shift;
+        float *moa = mo - shift;
+        const bool turned = shift && v0 == 0;    // this lane's first vector
+        f4 gv[4], mv[4];
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            if (r == 0 && turned) {
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) {
+                    const uint32_t i = j < shift ? (uint32_t)kChunk + j : j;
+                    gv[0][j] = ga[i];
+                    mv[0][j] = ma[i];
+                }
+                continue;
+            }
+            gv[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ga + 4u * (v0 + 64u * r)));
+            mv[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ma + 4u * (v0 + 64u * r)));
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t i = 4u * (v0 + 64u * r);
+            Philox4 rw;
+            if constexpr (kSR) {
+                rw = element_random_words(e0 - shift + i, u, seed);
+                if (r == 0 && turned) {
+                    const Philox4 last = element_random_words(e0 - shift + kChunk, u, seed);
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j) rw.w[j] = j < shift ? last.w[j] : rw.w[j];
+                }
+            }
+            f4 eo;
+            uint32_t packed = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float e;
+                packed |= element(gv[r][j], mv[r][j], kSR ? rw.w[j] : 0u, 1u, e) << (8 * j);
+                eo[j] = e;
+            }
+            if (r == 0 && turned) {
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) moa[j < shift ? (uint32_t)kChunk + j : j] = eo[j];
+            } else {
+                __builtin_nontemporal_store(eo, reinterpret_cast<f4 *>(moa + i));
+            }
+            run.w[r] = packed;
+        }
+    } else {
+        // the ragged end of a layer: element by element
+        float gs[16], ms[16];
+#pragma unroll
+        for (uint32_t k = 0; k < 16; ++k) {
+            const uint32_t i = 4u * (v0 + 64u * (k >> 2)) + (k & 3u);
+            gs[k] = i < nk ? gu[i] : 0.0f;
+            ms[k] = i < nk ? mu[i] : 0.0f;
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            uint32_t packed = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t i = 4u * (v0 + 64u * r) + j;
+                uint32_t rnd = 0;
+                if constexpr (kSR) rnd = element_random_words(e0 + i, u, seed).w[(e0 + i) & 3u];
+                float e;
+                const uint32_t in = i < nk ? 1u : 0u;
+                const uint32_t s = element(gs[4 * r + j], ms[4 * r + j], rnd, in, e);
+                if (in) mo[i] = e;
+                packed |= (in ? s : 0u) << (8 * j);
+            }
+            run.w[r] = packed;
+        }
+    }
+    quad_transpose(run.w, lane);
+    if (n_nonfinite) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NONFINITE), (unsigned long long)n_nonfinite);
+    if (n_clamped) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CLAMPED), (unsigned long long)n_clamped);
+}
+
+// A run's entries, its bits and its place among the wavefront's; head: the bits of its first `shift` symbols, which belong to
+// the sub-chunk before.
+__device__ inline void team_lengths(TeamRun &run, uint32_t part, uint32_t nk, uint32_t shift, const uint32_t *entry, const BookDev &book,
+                                    uint32_t &head, uint64_t *__restrict__ status)
+{
+    const uint32_t lane = threadIdx.x & 63u, first = (uint32_t)kRun * (64u * part + run_of_lane(lane));
+    const bool opens = shift && first == 0;   // the chunk's first run
+    run.from = opens ? shift : 0u;
+    run.to = nk > first ? (nk - first < (uint32_t)kRun ? nk - first : (uint32_t)kRun) : 0u;
+    uint32_t most = 0;
+    run.bits = run.tail_bits = head = 0;
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) run.e[j] = entry[run_symbol(run.w, j)];
+    if (nk != (uint32_t)kChunk) {
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) run.e[j] = (uint32_t)j < run.to ? run.e[j] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) run.tail[j] = 0;
+    if (shift) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const bool ahead = (uint32_t)j < shift;
+            run.tail[j] = ahead && opens ? run.e[j] : 0u;
+            run.e[j] = ahead && opens ? 0u : run.e[j];
+            head += ahead ? run.e[j] & 0xffu : 0u;
+        }
+        run.tail_bits = (run.tail[0] & 0xffu) + (run.tail[1] & 0xffu) + (run.tail[2] & 0xffu);
+        most = run.tail_bits;   // at most three of 24 bits: two pairs of up to 32, or coded one by one
+    }
+#pragma unroll
+    for (int j = 0; j < kRun; j += 2) {
+        const uint32_t both = (run.e[j] & 0xffu) + (run.e[j + 1] & 0xffu);
+        run.bits += both;
+        most = most > both ? most : both;
+    }
+    run.slow = most > 32u;
+    if (__any(run.slow)) {
+        if (run.slow) {
+            uint32_t nocode = 0;
+            run.bits = run_bits_exact(run.w, (int)run.from, (int)run.to, entry, book, nocode);
+            run.tail_bits = opens ? run_bits_exact(run.w, 0, (int)shift, entry, book, nocode) : 0u;
+            if (nocode) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
+            uint32_t counted = 0;
+            head = opens ? 0u : run_bits_exact(run.w, 0, (int)shift, entry, book, counted);
+        }
+    }
+    // in the runs' order and back
+    run.in_order = (uint32_t)__shfl((int)run.bits, (int)lane_of_run(lane), 64);
+    const uint32_t incl = wave_inclusive_scan_dpp(run.in_order);
+    run.total = __builtin_amdgcn_readlane((int)incl, 63);
+    run.excl = (uint32_t)__shfl((int)(incl - run.in_order), (int)run_of_lane(lane), 64);
+}
+
+// The run's codewords, any length, with those that stand ahead of the chunk's first run at its end: words wbase .. wbase + wn - 1.
+__device__ inline void team_append_exact(const TeamRun &run, const uint32_t *entry, const BookDev &book, uint32_t pos, uint32_t chunk_bits,
+                                         uint32_t *win, uint32_t wbase, uint32_t wn)
+{
+    run_append_exact(run.w, (int)run.from, (int)run.to, entry, book, pos, win, wbase, wn);
+    if (run.from) run_append_exact(run.w, 0, (int)run.from, entry, book, chunk_bits - run.tail_bits, win, wbase, wn);
+}
+
 // kSR: the stochastic conversion (dither from Philox words of (element, user, seed)) instead of
 // the closest representative.
 // kWaves: wavefronts per SIMD the register budget is cut for.  Five (a few values spill) is what the streaming of
@@ -87,10 +282,9 @@ __device__ inline void fu_lds_barrier()
 // more state and runs faster at four without spills, and so does the stochastic conversion (1.05 against 1.29 ms).
 // kHist: also count the symbols per code table (hist_rep: kHistGlobalRep partial tables, folded afterwards), for
 // callers that hold a code but want this round's histogram, e.g. to design the next round's code from it.
-// kTeam: wavefronts per chunk.  More than one only with kCpb = 1, for inputs whose chunks are too few to fill the
-// device with a wavefront each: such a launch is a wavefront's chain of loads, quantizing and packing, so its batches
-// are spread over a team; then wavefront 0 packs while wavefront 1 looks back, and all of them copy out.  Four
-// users of 20 011 elements: 24 -> 12 us.
+// kTeam: wavefronts per chunk: 1, the streaming form, or kFuTeam.  (A former team of four quantized together, then one of them
+// packed: one user of 300 000 elements 23.3 -> 14.4 us, eight of 100 000 21.4 -> 13.7, of 300 000 30.5 -> 18.4.  Teams that take two or
+// four of the workgroup's chunks one after the other: sixteen users of 25.6 M elements 966 -> 1100 and 1070 us.)
 template <bool kSR, int kCpb, int kTeam, int kWaves, bool kHist>
 __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     Layout lay, const float *__restrict__ g, const float *m, float *m_out, uint64_t row_stride, float gamma,
@@ -99,76 +293,127 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     uint64_t *__restrict__ payload_bits, uint32_t *__restrict__ words, uint64_t words_stride,
     uint64_t *__restrict__ status, uint64_t *__restrict__ hist_rep)
 {
-    __shared__ uint32_t s_stage[kCpb][kPcRegion];     // a wavefront's symbols, then its lanes' rows, then its chunk's words
+    constexpr bool kIsTeam = kTeam > 1;
+    // a wavefront's symbols, then its lanes' rows, then its chunk's words; a team's: the words
+    __shared__ __align__(16) uint32_t s_stage[kCpb][kIsTeam ? kRunWindowStride : kPcRegion];
     __shared__ uint32_t s_fast[kCpb][kMaxA];
-    __shared__ uint8_t s_len[kCpb][kMaxA];            // code lengths (0: no code), for the chunk's size
-    __shared__ uint32_t s_hist[kHist ? kCpb : 1][kHist ? kMaxA : 1];   // a wavefront's symbol counts of its chunk
+    __shared__ uint8_t s_len[kIsTeam ? 1 : kCpb][kIsTeam ? 4 : kMaxA];   // code lengths (0: no code), for the chunk's size
+    __shared__ uint32_t s_hist[kHist ? kCpb : 1][kHist ? kMaxA : 1];   // symbol counts of a chunk
     __shared__ uint64_t s_e0[kCpb];
     __shared__ uint32_t s_n[kCpb], s_book[kCpb], s_cbits[kCpb];
     __shared__ int32_t s_bias[kCpb];
     __shared__ float s_gain[kCpb][2];
     __shared__ uint64_t s_prefix;
     __shared__ uint32_t s_ticket, s_stalled;
-    __shared__ uint32_t s_fast_ok;                    // a team's wavefront 0 packed its chunk in rows
-    __shared__ uint32_t s_part[kTeam];                // a team's shares of its chunk's size
-    static_assert(kTeam == 1 || kCpb == 1, "a team takes one chunk");
+    __shared__ uint32_t s_part[kCpb][kTeam];          // a team's wavefronts' shares of their chunk's size
+    __shared__ uint32_t s_head[kIsTeam ? kCpb : 1][kIsTeam ? kSubsPerChunk + 1 : 1];   // bits of a sub-chunk that the run before its first whole one has not
+    static_assert(kTeam == 1 || kTeam * 64 * kRun == kChunk, "a run for every thread of a team");
     constexpr uint32_t kLbWave = kTeam > 1 ? 1 : 0;   // wavefront that looks back
 
     const uint32_t t = threadIdx.x, lane = t & 63;
-    const uint32_t wave = kTeam > 1 ? 0u : t >> 6;    // chunk of the workgroup
-    const uint32_t part = kTeam > 1 ? t >> 6 : 0u;    // wavefront of the chunk's team
+    const uint32_t wave = kIsTeam ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(t / (64u * kTeam))) : t >> 6;      // chunk of the workgroup
+    const uint32_t part = kIsTeam ? (uint32_t)__builtin_amdgcn_readfirstlane((int)((t >> 6) % kTeam)) : 0u;   // wavefront of the chunk's team
     const uint32_t wv = t >> 6;
     const uint32_t u = blockIdx.y;
 
-    if (t == 0) s_ticket = atomicAdd(&tickets[kTeam > 1 ? 2 * (uint64_t)u * (nblk + 1ull) : u], 1u);
-    fu_lds_barrier();
-    const uint32_t b = s_ticket;  // position among the user's workgroups, < nblk = gridDim.x
-    const uint64_t c0 = (uint64_t)b * kCpb;
-    const uint32_t nck = lay.nchunks - c0 < (uint64_t)kCpb ? (uint32_t)(lay.nchunks - c0) : (uint32_t)kCpb;
-
-    if (t < (uint32_t)kCpb) {
-        uint64_t e0 = 0;
-        uint32_t n = 0, bk = 0;
-        int32_t bias = 0;
-        float gn = 1.0f, gi = 1.0f;
-        if (t < nck) {
-            const uint64_t c = c0 + t;
-            const uint32_t seg = fu_find_chunk_segment(lay.segs, lay.nseg, c);
-            const SegDev sd = lay.segs[seg];
-            e0 = sd.offset + (c - sd.chunk_start) * kChunk;
-            const uint64_t left = sd.offset + sd.length - e0;
-            n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
-            bk = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
-            bias = lay.bias[(uint64_t)u * lay.nseg + seg];
-            gn = lay.gain[2 * ((uint64_t)u * lay.nseg + seg)];
-            gi = lay.gain[2 * ((uint64_t)u * lay.nseg + seg) + 1];
-        }
-        s_e0[t] = e0; s_n[t] = n; s_book[t] = bk; s_bias[t] = bias; s_gain[t][0] = gn; s_gain[t][1] = gi;
+    if (t == 0) s_ticket = atomicAdd(&tickets[kCpb == 1 ? 2 * (uint64_t)u * (nblk + 1ull) : u], 1u);
+    // While a team's ticket is on its way: the first layer's entry and table (often there is no other), the window cleared.
+    SegDev sd;
+    uint32_t seg = 0, bk = 0, tab = 0;
+    if constexpr (kIsTeam) {
+        sd = load_segment(lay.segs);
+        bk = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
+        tab = books[bk].fast[t % kMaxA];
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        for (uint32_t i = 4u * (t % (64u * kTeam)); i < (uint32_t)kRunWindowStride; i += 256u * kTeam)
+            *reinterpret_cast<u4 *>(&s_stage[wave][i]) = u4{0u, 0u, 0u, 0u};
+        if constexpr (kHist) s_hist[wave][t % kMaxA] = 0u;
     }
     fu_lds_barrier();
-
-    // ---- 1. wavefront w quantizes chunk w, symbols to LDS ---------------------------------------
+    const uint32_t b = kIsTeam ? (uint32_t)__builtin_amdgcn_readfirstlane((int)s_ticket) : s_ticket;  // position among the user's workgroups, < nblk = gridDim.x
+    const uint64_t c0 = (uint64_t)b * kCpb;
+    const uint32_t nck = lay.nchunks - c0 < (uint64_t)kCpb ? (uint32_t)(lay.nchunks - c0) : (uint32_t)kCpb;
     const bool active = wave < nck;
-    const uint32_t sign_shift = lay.E + lay.M;
+
+    TeamRun run;
+    uint32_t nk = 0, shift = 0, head = 0;
     uint32_t len_sum = 0;   // code lengths of the elements this lane quantizes
-    if (active) {
-        const uint64_t e0 = s_e0[wave];
-        const uint32_t nk = s_n[wave];
-        const int bias = s_bias[wave];
-        const QConst qc = make_qconst(lay.E, lay.M, bias);
-        const float gain = s_gain[wave][0], inv_gain = s_gain[wave][1];   // real-valued scale: (1, 1) unless the plan carries one
-        const float *gu = g + (uint64_t)u * row_stride + e0;
-        const float *mu = m + (uint64_t)u * row_stride + e0;
-        float *mo = m_out + (uint64_t)u * row_stride + e0;
-        uint32_t n_nonfinite = 0, n_clamped = 0;
-        // The code's tables are requested first and stored to LDS once the first vectors of g and m are under
-        // way: the chunk's size is summed while it is quantized, so that it can be published right after.
-        uint32_t tab_fast[kMaxA / 64];
+    if constexpr (kIsTeam) {
+        // ---- 1. a team quantizes its chunk; runs of symbols and their places in the wavefront's share of its bits --------
+        static_assert(!kIsTeam || 64 * kTeam == kMaxA, "a thread for every entry");
+        run.total = run.tail_bits = 0;
+        if (active) {
+            const uint64_t c = c0 + wave;
+            if (lay.nseg > 1) {
+                seg = fu_find_chunk_segment(lay.segs, lay.nseg, c);
+                sd = load_segment(lay.segs + seg);
+                bk = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
+                tab = books[bk].fast[t % kMaxA];
+            }
+            const uint64_t e0 = sd.offset + (c - sd.chunk_start) * kChunk, left = sd.offset + sd.length - e0;
+            nk = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
+            shift = nk == (uint32_t)kChunk ? (uint32_t)(e0 & 3u) : 0u;
+            const uint64_t pair = (uint64_t)u * lay.nseg + seg, at = (uint64_t)u * row_stride + e0;
+            team_sweep<kSR, kHist>(run, lay, u, part, e0, nk, shift, lay.bias[pair], lay.gain[2 * pair], lay.gain[2 * pair + 1],
+                                          g + at, m + at, m_out + at, gamma, seed, s_hist[kHist ? wave : 0], status);
+            s_fast[wave][t % kMaxA] = run_entry(tab);
+        }
+        fu_lds_barrier();   // tables (and counts)
+        if (active) {
+            team_lengths(run, part, nk, shift, s_fast[wave], books[bk], head, status);
+            if ((lane & 15u) < 4u) s_head[wave][16u * part + (run_of_lane(lane) >> 2)] = head;
+            if (part == 0 && lane == 0) s_head[wave][kSubsPerChunk] = run.tail_bits;
+            if constexpr (kHist) {
+                // the chunk's counts go to one of the partial tables of its code table
+                uint64_t *dst = hist_rep + ((uint64_t)(blockIdx.x % kHistGlobalRep) * lay.nbooks + bk) * lay.A;
+                const uint32_t cnt = s_hist[wave][t % kMaxA];
+                if (cnt && t % kMaxA < lay.A) atomicAdd(reinterpret_cast<unsigned long long *>(dst + t % kMaxA), (unsigned long long)cnt);
+            }
+        } else if (part == 0 && lane == 0) {
+            s_head[wave][kSubsPerChunk] = 0u;
+        }
+        if (lane == 0) s_part[wave][part] = run.total;
+    } else {
+        if (t < (uint32_t)kCpb) {
+            uint64_t e0 = 0;
+            uint32_t n = 0, bk = 0;
+            int32_t bias = 0;
+            float gn = 1.0f, gi = 1.0f;
+            if (t < nck) {
+                const uint64_t c = c0 + t;
+                const uint32_t seg = fu_find_chunk_segment(lay.segs, lay.nseg, c);
+                const SegDev sd = lay.segs[seg];
+                e0 = sd.offset + (c - sd.chunk_start) * kChunk;
+                const uint64_t left = sd.offset + sd.length - e0;
+                n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
+                bk = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
+                bias = lay.bias[(uint64_t)u * lay.nseg + seg];
+                gn = lay.gain[2 * ((uint64_t)u * lay.nseg + seg)];
+                gi = lay.gain[2 * ((uint64_t)u * lay.nseg + seg) + 1];
+            }
+            s_e0[t] = e0; s_n[t] = n; s_book[t] = bk; s_bias[t] = bias; s_gain[t][0] = gn; s_gain[t][1] = gi;
+        }
+        fu_lds_barrier();
+
+        // ---- 1. wavefront w quantizes chunk w, symbols to LDS ---------------------------------------
+        const uint32_t sign_shift = lay.E + lay.M;
+        if (active) {
+            const uint64_t e0 = s_e0[wave];
+            const uint32_t nk = s_n[wave];
+            const int bias = s_bias[wave];
+            const QConst qc = make_qconst(lay.E, lay.M, bias);
+            const float gain = s_gain[wave][0], inv_gain = s_gain[wave][1];   // real-valued scale: (1, 1) unless the plan carries one
+            const float *gu = g + (uint64_t)u * row_stride + e0;
+            const float *mu = m + (uint64_t)u * row_stride + e0;
+            float *mo = m_out + (uint64_t)u * row_stride + e0;
+            uint32_t n_nonfinite = 0, n_clamped = 0;
+            // The code's tables are requested first and stored to LDS once the first vectors of g and m are under
+            // way: the chunk's size is summed while it is quantized, so that it can be published right after.
+            uint32_t tab_fast[kMaxA / 64];
 #pragma unroll
-        for (int r = 0; r < kMaxA / 64; ++r) tab_fast[r] = books[s_book[wave]].fast[lane + 64 * r];
-        const uint32_t tab_len = reinterpret_cast<const uint32_t *>(books[s_book[wave]].len)[lane];
-        auto tables_to_lds = [&]() {
-            if (part == 0) {
+            for (int r = 0; r < kMaxA / 64; ++r) tab_fast[r] = books[s_book[wave]].fast[lane + 64 * r];
+            const uint32_t tab_len = reinterpret_cast<const uint32_t *>(books[s_book[wave]].len)[lane];
+            auto tables_to_lds = [&]() {
 #pragma unroll
                 for (int r = 0; r < kMaxA / 64; ++r) s_fast[wave][lane + 64 * r] = tab_fast[r];
                 reinterpret_cast<uint32_t *>(s_len[wave])[lane] = tab_len;
@@ -176,207 +421,205 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
 #pragma unroll
                     for (int r = 0; r < kMaxA / 64; ++r) s_hist[wave][lane + 64 * r] = 0u;
                 }
-            }
-            if constexpr (kTeam > 1) fu_lds_barrier();   // reached by every wavefront: a team's workgroup has one chunk
-            else fu_wave_sync_lds();
-        };
-        const uint8_t *len_tab = s_len[wave];
-        // Four elements of a 16-byte vector: symbols packed into a word, new memory, counters and code
-        // lengths for the elements `valid` marks (bit j: element j belongs to this chunk).
-        auto quant4 = [&](const f4 &gv, const f4 &mv, uint64_t elem, uint32_t valid, f4 &eo, uint32_t &packed) {
-            packed = 0;
-            Philox4 rw;
-            if constexpr (kSR) rw = element_random_words(elem, u, seed);
+                fu_wave_sync_lds();
+            };
+            const uint8_t *len_tab = s_len[wave];
+            // Four elements of a 16-byte vector: symbols packed into a word, new memory, counters and code
+            // lengths for the elements `valid` marks (bit j: element j belongs to this chunk).
+            auto quant4 = [&](const f4 &gv, const f4 &mv, uint64_t elem, uint32_t valid, f4 &eo, uint32_t &packed) {
+                packed = 0;
+                Philox4 rw;
+                if constexpr (kSR) rw = element_random_words(elem, u, seed);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v = __fadd_rn(gv[j], __fmul_rn(gamma, mv[j]));
-                const float y = __fmul_rn(v, gain);
-                uint32_t s, flags;
-                float q;
-                if constexpr (kSR) quantize_stochastic(y, qc, lay.E, lay.M, bias, sign_shift, rw.w[j], s, q, flags);
-                else quantize(y, qc, sign_shift, s, q, flags);
-                q = __fmul_rn(q, inv_gain);
-                eo[j] = (flags & 1u) ? 0.0f : __fsub_rn(v, q);
-                const uint32_t ok = (valid >> j) & 1u;
-                n_nonfinite += flags & ok;
-                n_clamped += (flags >> 1) & ok;
-                len_sum += ok ? (uint32_t)len_tab[s] : 0u;
-                if constexpr (kHist) {
-                    if (ok) atomicAdd(&s_hist[wave][s], 1u);
-                }
-                packed |= s << (8 * j);
-            }
-        };
-        // A whole chunk takes a vector path: kFuBatch 16-byte vectors of g and of m per lane at a time,
-        // the next batch requested before the current one is computed.
-        const uint32_t shift = (uint32_t)(e0 & 3u);
-        constexpr int kShare = kFuBatches / kTeam;   // batches per wavefront
-        const int bt0 = (int)part * kShare, bt1 = bt0 + kShare;
-        if (nk == (uint32_t)kChunk && shift == 0) {
-            f4 gn[kFuBatch], mn[kFuBatch];
-#pragma unroll
-            for (int r = 0; r < kFuBatch; ++r) {
-                const uint32_t i = 4u * (lane + 64u * (uint32_t)(bt0 * kFuBatch + r));
-                gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(gu + i));
-                mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(mu + i));
-            }
-            tables_to_lds();
-#pragma unroll 1
-            for (int bt = bt0; bt < bt1; ++bt) {
-                f4 gc[kFuBatch], mc[kFuBatch];
-#pragma unroll
-                for (int r = 0; r < kFuBatch; ++r) { gc[r] = gn[r]; mc[r] = mn[r]; }
-                if (bt + 1 < bt1) {
-#pragma unroll
-                    for (int r = 0; r < kFuBatch; ++r) {
-                        const uint32_t i = 4u * (lane + 64u * (uint32_t)((bt + 1) * kFuBatch + r));
-                        gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(gu + i));
-                        mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(mu + i));
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < kFuBatch; ++r) {
-                    const uint32_t dw = lane + 64u * (uint32_t)(bt * kFuBatch + r);  // word of the chunk's symbols
-                    f4 eo;
-                    uint32_t packed;
-                    quant4(gc[r], mc[r], e0 + 4u * dw, 0xfu, eo, packed);
-                    __builtin_nontemporal_store(eo, reinterpret_cast<f4 *>(mo + 4u * dw));
-                    s_stage[wave][dw + (dw >> 4)] = packed;
-                }
-            }
-        } else if (nk == (uint32_t)kChunk) {
-            // A layer may start at any element.  The same vectors, taken from the 16-byte boundary
-            // below the chunk: vector k holds the chunk's elements 4k - shift .. 4k - shift + 3, so
-            // its symbols fall into words k - 1 and k of the stage (OR-ed in; the stage is cleared
-            // first) and the vectors at both ends are partial.
-            const float *ga = gu - shift, *ma = mu - shift;
-            float *moa = mo - shift;
-            f4 gn[kFuBatch], mn[kFuBatch];
-#pragma unroll
-            for (int r = 0; r < kFuBatch; ++r) {
-                const uint32_t i = 4u * (lane + 64u * (uint32_t)(bt0 * kFuBatch + r));
-                gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ga + i));
-                mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ma + i));
-            }
-            for (uint32_t i = lane + 64u * part; i < (uint32_t)(kFuStage + 1); i += 64 * kTeam) s_stage[wave][i] = 0;
-            tables_to_lds();
-#pragma unroll 1
-            for (int bt = bt0; bt < bt1; ++bt) {
-                f4 gc[kFuBatch], mc[kFuBatch];
-#pragma unroll
-                for (int r = 0; r < kFuBatch; ++r) { gc[r] = gn[r]; mc[r] = mn[r]; }
-                if (bt + 1 < bt1) {
-#pragma unroll
-                    for (int r = 0; r < kFuBatch; ++r) {
-                        const uint32_t i = 4u * (lane + 64u * (uint32_t)((bt + 1) * kFuBatch + r));
-                        gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ga + i));
-                        mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ma + i));
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < kFuBatch; ++r) {
-                    const uint32_t k = lane + 64u * (uint32_t)(bt * kFuBatch + r);  // vector, 0 .. 1023
-                    const uint32_t valid = k ? 0xfu : (0xfu << shift) & 0xfu;      // vector 0 starts before the chunk
-                    f4 eo;
-                    uint32_t packed;
-                    quant4(gc[r], mc[r], e0 - shift + 4u * k, valid, eo, packed);
-                    if (k) {
-                        __builtin_nontemporal_store(eo, reinterpret_cast<f4 *>(moa + 4u * k));
-                        atomicOr(&s_stage[wave][(k - 1u) + ((k - 1u) >> 4)], packed << (8u * (4u - shift)));
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if ((valid >> j) & 1u) moa[j] = eo[j];
-                    }
-                    atomicOr(&s_stage[wave][k + (k >> 4)], packed >> (8u * shift));
-                }
-            }
-            if (lane == 0 && part == kTeam - 1) {
-                // vector 1024: the chunk's last `shift` elements
-                f4 gv = {0.0f, 0.0f, 0.0f, 0.0f}, mv = {0.0f, 0.0f, 0.0f, 0.0f}, eo;
-                for (uint32_t j = 0; j < shift; ++j) { gv[j] = ga[kChunk + j]; mv[j] = ma[kChunk + j]; }
-                uint32_t packed;
-                quant4(gv, mv, e0 - shift + kChunk, (1u << shift) - 1u, eo, packed);
-                for (uint32_t j = 0; j < shift; ++j) moa[kChunk + j] = eo[j];
-                const uint32_t last = kChunk / 4 - 1;
-                atomicOr(&s_stage[wave][last + (last >> 4)], (packed & ((1u << (8u * shift)) - 1u)) << (8u * (4u - shift)));
-            }
-        } else {
-            // ragged chunk (the end of a layer): a lane takes one element of every 64, kFuScalar rounds requested together; four neighbouring lanes then gather
-            // their symbols into one word of the stage
-            tables_to_lds();
-            for (uint32_t base = 64u * kFuScalar * part; base < nk; base += 64u * kFuScalar * kTeam) {
-                float gs[kFuScalar], ms[kFuScalar];
-#pragma unroll
-                for (int r = 0; r < kFuScalar; ++r) {
-                    const uint32_t j = base + lane + 64u * r;
-                    gs[r] = j < nk ? gu[j] : 0.0f;
-                    ms[r] = j < nk ? mu[j] : 0.0f;
-                }
-#pragma unroll
-                for (int r = 0; r < kFuScalar; ++r) {
-                    const uint32_t j = base + lane + 64u * r;  // < kChunk: base is a multiple of 64 kFuScalar
-                    const bool in = j < nk;
-                    const float v = __fadd_rn(gs[r], __fmul_rn(gamma, ms[r]));
+                for (int j = 0; j < 4; ++j) {
+                    const float v = __fadd_rn(gv[j], __fmul_rn(gamma, mv[j]));
                     const float y = __fmul_rn(v, gain);
                     uint32_t s, flags;
                     float q;
-                    if constexpr (kSR)
-                        quantize_stochastic(y, qc, lay.E, lay.M, bias, sign_shift,
-                                            element_random_words(e0 + j, u, seed).w[(e0 + j) & 3u], s, q, flags);
+                    if constexpr (kSR) quantize_stochastic(y, qc, lay.E, lay.M, bias, sign_shift, rw.w[j], s, q, flags);
                     else quantize(y, qc, sign_shift, s, q, flags);
                     q = __fmul_rn(q, inv_gain);
-                    if (in) {
-                        mo[j] = (flags & 1u) ? 0.0f : __fsub_rn(v, q);
-                        n_nonfinite += flags & 1u;
-                        n_clamped += (flags >> 1) & 1u;
-                        len_sum += (uint32_t)len_tab[s];
-                        if constexpr (kHist) atomicAdd(&s_hist[wave][s], 1u);
+                    eo[j] = (flags & 1u) ? 0.0f : __fsub_rn(v, q);
+                    const uint32_t ok = (valid >> j) & 1u;
+                    n_nonfinite += flags & ok;
+                    n_clamped += (flags >> 1) & ok;
+                    len_sum += ok ? (uint32_t)len_tab[s] : 0u;
+                    if constexpr (kHist) {
+                        if (ok) atomicAdd(&s_hist[wave][s], 1u);
                     }
-                    s = in ? s : 0u;
-                    const uint32_t s4 = s | (__shfl_down(s, 1, 64) << 8) | (__shfl_down(s, 2, 64) << 16) |
-                                        (__shfl_down(s, 3, 64) << 24);
-                    const uint32_t dw = j >> 2;
-                    if ((lane & 3u) == 0 && in) s_stage[wave][dw + (dw >> 4)] = s4;
+                    packed |= s << (8 * j);
+                }
+            };
+            // A whole chunk takes a vector path: kFuBatch 16-byte vectors of g and of m per lane at a time,
+            // the next batch requested before the current one is computed.
+            const uint32_t shift = (uint32_t)(e0 & 3u);
+            if (nk == (uint32_t)kChunk && shift == 0) {
+                f4 gn[kFuBatch], mn[kFuBatch];
+#pragma unroll
+                for (int r = 0; r < kFuBatch; ++r) {
+                    const uint32_t i = 4u * (lane + 64u * (uint32_t)r);
+                    gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(gu + i));
+                    mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(mu + i));
+                }
+                tables_to_lds();
+#pragma unroll 1
+                for (int bt = 0; bt < kFuBatches; ++bt) {
+                    f4 gc[kFuBatch], mc[kFuBatch];
+#pragma unroll
+                    for (int r = 0; r < kFuBatch; ++r) { gc[r] = gn[r]; mc[r] = mn[r]; }
+                    if (bt + 1 < kFuBatches) {
+#pragma unroll
+                        for (int r = 0; r < kFuBatch; ++r) {
+                            const uint32_t i = 4u * (lane + 64u * (uint32_t)((bt + 1) * kFuBatch + r));
+                            gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(gu + i));
+                            mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(mu + i));
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < kFuBatch; ++r) {
+                        const uint32_t dw = lane + 64u * (uint32_t)(bt * kFuBatch + r);  // word of the chunk's symbols
+                        f4 eo;
+                        uint32_t packed;
+                        quant4(gc[r], mc[r], e0 + 4u * dw, 0xfu, eo, packed);
+                        __builtin_nontemporal_store(eo, reinterpret_cast<f4 *>(mo + 4u * dw));
+                        s_stage[wave][dw + (dw >> 4)] = packed;
+                    }
+                }
+            } else if (nk == (uint32_t)kChunk) {
+                // A layer may start at any element.  The same vectors, taken from the 16-byte boundary
+                // below the chunk: vector k holds the chunk's elements 4k - shift .. 4k - shift + 3, so
+                // its symbols fall into words k - 1 and k of the stage (OR-ed in; the stage is cleared
+                // first) and the vectors at both ends are partial.
+                const float *ga = gu - shift, *ma = mu - shift;
+                float *moa = mo - shift;
+                f4 gn[kFuBatch], mn[kFuBatch];
+#pragma unroll
+                for (int r = 0; r < kFuBatch; ++r) {
+                    const uint32_t i = 4u * (lane + 64u * (uint32_t)r);
+                    gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ga + i));
+                    mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ma + i));
+                }
+                for (uint32_t i = lane; i < (uint32_t)(kFuStage + 1); i += 64) s_stage[wave][i] = 0;
+                tables_to_lds();
+#pragma unroll 1
+                for (int bt = 0; bt < kFuBatches; ++bt) {
+                    f4 gc[kFuBatch], mc[kFuBatch];
+#pragma unroll
+                    for (int r = 0; r < kFuBatch; ++r) { gc[r] = gn[r]; mc[r] = mn[r]; }
+                    if (bt + 1 < kFuBatches) {
+#pragma unroll
+                        for (int r = 0; r < kFuBatch; ++r) {
+                            const uint32_t i = 4u * (lane + 64u * (uint32_t)((bt + 1) * kFuBatch + r));
+                            gn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ga + i));
+                            mn[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(ma + i));
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < kFuBatch; ++r) {
+                        const uint32_t k = lane + 64u * (uint32_t)(bt * kFuBatch + r);  // vector, 0 .. 1023
+                        const uint32_t valid = k ? 0xfu : (0xfu << shift) & 0xfu;      // vector 0 starts before the chunk
+                        f4 eo;
+                        uint32_t packed;
+                        quant4(gc[r], mc[r], e0 - shift + 4u * k, valid, eo, packed);
+                        if (k) {
+                            __builtin_nontemporal_store(eo, reinterpret_cast<f4 *>(moa + 4u * k));
+                            atomicOr(&s_stage[wave][(k - 1u) + ((k - 1u) >> 4)], packed << (8u * (4u - shift)));
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                if ((valid >> j) & 1u) moa[j] = eo[j];
+                        }
+                        atomicOr(&s_stage[wave][k + (k >> 4)], packed >> (8u * shift));
+                    }
+                }
+                if (lane == 0) {
+                    // vector 1024: the chunk's last `shift` elements
+                    f4 gv = {0.0f, 0.0f, 0.0f, 0.0f}, mv = {0.0f, 0.0f, 0.0f, 0.0f}, eo;
+                    for (uint32_t j = 0; j < shift; ++j) { gv[j] = ga[kChunk + j]; mv[j] = ma[kChunk + j]; }
+                    uint32_t packed;
+                    quant4(gv, mv, e0 - shift + kChunk, (1u << shift) - 1u, eo, packed);
+                    for (uint32_t j = 0; j < shift; ++j) moa[kChunk + j] = eo[j];
+                    const uint32_t last = kChunk / 4 - 1;
+                    atomicOr(&s_stage[wave][last + (last >> 4)], (packed & ((1u << (8u * shift)) - 1u)) << (8u * (4u - shift)));
+                }
+            } else {
+                // ragged chunk (the end of a layer): a lane takes one element of every 64, kFuScalar rounds requested together; four neighbouring lanes then gather
+                // their symbols into one word of the stage
+                tables_to_lds();
+                for (uint32_t base = 0; base < nk; base += 64u * kFuScalar) {
+                    float gs[kFuScalar], ms[kFuScalar];
+#pragma unroll
+                    for (int r = 0; r < kFuScalar; ++r) {
+                        const uint32_t j = base + lane + 64u * r;
+                        gs[r] = j < nk ? gu[j] : 0.0f;
+                        ms[r] = j < nk ? mu[j] : 0.0f;
+                    }
+#pragma unroll
+                    for (int r = 0; r < kFuScalar; ++r) {
+                        const uint32_t j = base + lane + 64u * r;  // < kChunk: base is a multiple of 64 kFuScalar
+                        const bool in = j < nk;
+                        const float v = __fadd_rn(gs[r], __fmul_rn(gamma, ms[r]));
+                        const float y = __fmul_rn(v, gain);
+                        uint32_t s, flags;
+                        float q;
+                        if constexpr (kSR)
+                            quantize_stochastic(y, qc, lay.E, lay.M, bias, sign_shift,
+                                                element_random_words(e0 + j, u, seed).w[(e0 + j) & 3u], s, q, flags);
+                        else quantize(y, qc, sign_shift, s, q, flags);
+                        q = __fmul_rn(q, inv_gain);
+                        if (in) {
+                            mo[j] = (flags & 1u) ? 0.0f : __fsub_rn(v, q);
+                            n_nonfinite += flags & 1u;
+                            n_clamped += (flags >> 1) & 1u;
+                            len_sum += (uint32_t)len_tab[s];
+                            if constexpr (kHist) atomicAdd(&s_hist[wave][s], 1u);
+                        }
+                        s = in ? s : 0u;
+                        const uint32_t s4 = s | (__shfl_down(s, 1, 64) << 8) | (__shfl_down(s, 2, 64) << 16) |
+                                            (__shfl_down(s, 3, 64) << 24);
+                        const uint32_t dw = j >> 2;
+                        if ((lane & 3u) == 0 && in) s_stage[wave][dw + (dw >> 4)] = s4;
+                    }
+                }
+            }
+            if (n_nonfinite)
+                atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NONFINITE),
+                          (unsigned long long)n_nonfinite);
+            if (n_clamped)
+                atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CLAMPED), (unsigned long long)n_clamped);
+            if constexpr (kHist) {
+                // the chunk's counts go to one of the partial tables of its code table
+                fu_wave_sync_lds();
+                uint64_t *dst = hist_rep + ((uint64_t)(blockIdx.x % kHistGlobalRep) * lay.nbooks + s_book[wave]) * lay.A;
+#pragma unroll
+                for (int r = 0; r < kMaxA / 64; ++r) {
+                    const uint32_t bin = lane + 64u * (uint32_t)r;
+                    const uint32_t cnt = s_hist[wave][bin];
+                    if (cnt && bin < lay.A) atomicAdd(reinterpret_cast<unsigned long long *>(dst + bin), (unsigned long long)cnt);
                 }
             }
         }
-        if (n_nonfinite)
-            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NONFINITE),
-                      (unsigned long long)n_nonfinite);
-        if (n_clamped)
-            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CLAMPED), (unsigned long long)n_clamped);
-        if constexpr (kHist) {
-            // the chunk's counts go to one of the partial tables of its code table
-            if constexpr (kTeam > 1) fu_lds_barrier();
-            else fu_wave_sync_lds();
-            uint64_t *dst = hist_rep + ((uint64_t)(blockIdx.x % kHistGlobalRep) * lay.nbooks + s_book[wave]) * lay.A;
+        // the chunk's size: every lane summed the code lengths of the elements it quantized
 #pragma unroll
-            for (int r = 0; r < kMaxA / 64 / kTeam; ++r) {
-                const uint32_t bin = lane + 64u * (part + (uint32_t)(r * kTeam));
-                const uint32_t cnt = s_hist[wave][bin];
-                if (cnt && bin < lay.A) atomicAdd(reinterpret_cast<unsigned long long *>(dst + bin), (unsigned long long)cnt);
-            }
-        }
-    }
-    // the chunk's size: every lane summed the code lengths of the elements it quantized
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) len_sum += __shfl_xor(len_sum, o, 64);
-    if (lane == 0) {
-        if constexpr (kTeam > 1) s_part[part] = len_sum;
-        else s_cbits[wave] = len_sum;        // 0 for a wavefront without a chunk
+        for (int o = 32; o > 0; o >>= 1) len_sum += __shfl_xor(len_sum, o, 64);
+        if (lane == 0) s_cbits[wave] = len_sum;  // 0 for a wavefront without a chunk
     }
     fu_lds_barrier();                        // also: every wavefront's symbols are staged
 
     // ---- 2. publish the workgroup's size; request the predecessors' ------------------------------
     uint32_t before = 0;  // 32-bit-rounded sizes of the workgroup's chunks ahead of this wavefront's
     uint32_t own = 0, pay = 0;
+    uint32_t chunk_bits = 0, windows = 0;   // (a team's) of its chunk; that the longest chunk of the workgroup takes
 #pragma unroll
     for (int k = 0; k < kCpb; ++k) {
-        uint32_t cbits = 0;
-        if constexpr (kTeam > 1) {
+        uint32_t cbits;
+        if constexpr (kIsTeam) {
+            cbits = s_head[k][kSubsPerChunk];
 #pragma unroll
-            for (int i = 0; i < kTeam; ++i) cbits += s_part[i];
+            for (int i = 0; i < kTeam; ++i) cbits += s_part[k][i];
+            const uint32_t nw = (cbits + 31u) >> 5, wins = (nw + kRunWindow - 1) / kRunWindow;
+            windows = windows > wins ? windows : wins;
+            if ((uint32_t)k == wave) chunk_bits = cbits;
         } else {
             cbits = s_cbits[k];
         }
@@ -385,7 +628,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
         own += a;
         pay += cbits;
     }
-    uint64_t *state = lb_state + (uint64_t)u * (kTeam > 1 ? nblk + 1ull : nblk);
+    uint64_t *state = lb_state + (uint64_t)u * (kCpb == 1 ? nblk + 1ull : nblk);
     // By the lane that replaces the entry with the running total (or the stalled mark) below: the two stores are
     // relaxed, only one lane's program order keeps the size from landing last.
     if (t == 64u * kLbWave)
@@ -399,35 +642,57 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     // ---- 3. wavefront = chunk, lane = sub-chunk: the chunk's words, built in LDS ---------------------
     // A chunk starts on a word boundary, so its words do not depend on where it lands in the stream.
     const uint64_t c = c0 + wave;
-    const uint32_t n = active ? s_n[wave] : 0u;
-    const int first = (int)lane * kSub;
-    const int cnt = (int)n - first < 0 ? 0 : ((int)n - first > kSub ? kSub : (int)n - first);
     uint32_t *region = s_stage[wave];
+    uint32_t nwords = 0;
+    uint32_t excl = 0;
     const uint32_t *fast = s_fast[wave];
-    const BookDev &book = books[s_book[wave]];
-    uint32_t symw[kSub / 4];
-    uint32_t my_bits = 0;
+    int cnt = 0;
     bool fast_ok = true;
-    if (active && part == 0) {
-        const uint32_t *row = region + kFuRow * lane;
+    if constexpr (kIsTeam) {
+        // every thread codes its run at its place among the chunk's words
+        uint32_t base = 0;
 #pragma unroll
-        for (int jj = 0; jj < kSub / 4; ++jj) symw[jj] = row[jj];
-        fu_wave_sync_lds();  // every lane has its symbols: the region is free
-        fast_ok = n == (uint32_t)kChunk ? pc_pack_rows<true>(symw, cnt, fast, region, lane, my_bits)
-                                        : pc_pack_rows<false>(symw, cnt, fast, region, lane, my_bits);
-        if (!fast_ok) {
-            uint32_t nocode = 0;
-            my_bits = pc_general_count(symw, cnt, fast, book, region, lane, nocode);
-            if (nocode)
-                atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
+        for (uint32_t i = 0; i < (uint32_t)kTeam; ++i) base += i < part ? s_part[wave][i] : 0u;
+        excl = base + run.excl;
+        nwords = (chunk_bits + 31u) >> 5;
+        if (active) {
+            if (windows == 1u) {
+                if (run.slow) team_append_exact(run, fast, books[bk], excl, chunk_bits, region, 0, kRunWindow);
+                else run_append(run.e, excl, region);
+                if (shift && run.from && !run.slow) run_append(run.tail, chunk_bits - run.tail_bits, region);
+            }
+            // a sub-chunk has what its four runs hold, but for the symbols ahead of the first, and with those ahead of the next
+            const uint32_t sub = 16u * part + (lane >> 2);
+            const uint32_t bits = quad_sum(run.in_order) + (shift ? s_head[wave][sub + 1] - s_head[wave][sub] : 0u);
+            if ((lane & 3u) == 0) sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + sub] = (uint16_t)bits;
         }
-        sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + lane] = (uint16_t)my_bits;
+    } else {
+        const uint32_t n = active ? s_n[wave] : 0u;
+        const int first = (int)lane * kSub;
+        cnt = (int)n - first < 0 ? 0 : ((int)n - first > kSub ? kSub : (int)n - first);
+        uint32_t symw[kSub / 4];
+        uint32_t my_bits = 0;
+        if (active) {
+            const uint32_t *row = region + kFuRow * lane;
+#pragma unroll
+            for (int jj = 0; jj < kSub / 4; ++jj) symw[jj] = row[jj];
+            fu_wave_sync_lds();  // every lane has its symbols: the region is free
+            fast_ok = n == (uint32_t)kChunk ? pc_pack_rows<true>(symw, cnt, fast, region, lane, my_bits)
+                                            : pc_pack_rows<false>(symw, cnt, fast, region, lane, my_bits);
+            if (!fast_ok) {
+                uint32_t nocode = 0;
+                my_bits = pc_general_count(symw, cnt, fast, books[s_book[wave]], region, lane, nocode);
+                if (nocode)
+                    atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
+            }
+            sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + lane] = (uint16_t)my_bits;
+        }
+        const uint32_t incl = pc_wave_inclusive_scan(my_bits, lane);
+        excl = incl - my_bits;
+        const uint32_t chunk_total = __shfl(incl, 63, 64);   // equals s_cbits[wave]: the same lengths, summed in another order
+        nwords = (chunk_total + 31u) >> 5;
+        if (active && fast_ok) pc_rows_to_window(region, lane, my_bits, excl, nwords);
     }
-    const uint32_t incl = pc_wave_inclusive_scan(my_bits, lane);
-    const uint32_t excl = incl - my_bits;
-    const uint32_t chunk_total = __shfl(incl, 63, 64);   // equals s_cbits[wave]: the same lengths, summed in another order
-    uint32_t nwords = (chunk_total + 31u) >> 5;
-    if (active && part == 0 && fast_ok) pc_rows_to_window(region, lane, my_bits, excl, nwords);
 
     if (wv == kLbWave) {
         uint64_t prefix = 0;
@@ -471,38 +736,51 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
             atomicAdd(reinterpret_cast<unsigned long long *>(payload_bits + u), (unsigned long long)pay);
         }
     }
-    if constexpr (kTeam > 1) {
-        if (t == 0) s_fast_ok = fast_ok ? 1u : 0u;
-    }
     fu_lds_barrier();
-    if (!active || s_stalled) return;  // whole wavefronts; no workgroup barrier below
+    if (s_stalled) return;
+    if constexpr (!kIsTeam) {
+        if (!active) return;  // whole wavefronts; no workgroup barrier below but a team's
+    }
 
     // ---- 4. the chunk's words go to their place in the stream -----------------------------------
-    if constexpr (kTeam > 1) {
-        nwords = own >> 5;
-        fast_ok = s_fast_ok != 0u;
-        if (!fast_ok && part != 0) return;
-    }
     const uint64_t off = s_prefix + before;
-    if (lane == 0 && part == 0) {
+    if (active && lane == 0 && part == 0) {
         uint64_t *co = chunk_offset + (uint64_t)u * (lay.nchunks + 1);
         co[c] = off;
         if (c + 1 == lay.nchunks) co[lay.nchunks] = off + ((uint64_t)nwords << 5);
     }
     const uint64_t off_words = off >> 5;
+    bool fits = active;
     if (off_words + nwords > words_stride) {
-        if (lane == 0 && part == 0) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CAPACITY), 1ull);
-        return;
+        if (active && lane == 0 && part == 0) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CAPACITY), 1ull);
+        fits = false;
+        if constexpr (!kIsTeam) return;
     }
     uint32_t *dst = words + (uint64_t)u * words_stride + off_words;
-    if (fast_ok) {
-        for (uint32_t i = lane + 64u * part; i < nwords; i += 64 * kTeam) __builtin_nontemporal_store(region[i], dst + i);
+    if constexpr (kIsTeam) {
+        const uint32_t th = lane + 64u * part;
+        if (windows == 1u) {
+            for (uint32_t i = th; fits && i < nwords; i += 64 * kTeam) __builtin_nontemporal_store(region[i], dst + i);
+        } else {
+            // a chunk of the workgroup does not fit its window: window by window, in step
+            for (uint32_t k = 0; k < windows; ++k) {
+                const uint32_t wbase = k * kRunWindow, wn = nwords <= wbase ? 0u : (nwords - wbase < (uint32_t)kRunWindow ? nwords - wbase : (uint32_t)kRunWindow);
+                fu_lds_barrier();
+                for (uint32_t i = th; i < (uint32_t)kRunWindow; i += 64 * kTeam) region[i] = 0u;
+                fu_lds_barrier();
+                if (active) team_append_exact(run, fast, books[bk], excl, chunk_bits, region, wbase, wn);
+                fu_lds_barrier();
+                for (uint32_t i = th; fits && i < wn; i += 64 * kTeam) __builtin_nontemporal_store(region[i], dst + wbase + i);
+            }
+        }
+    } else if (fast_ok) {
+        for (uint32_t i = lane; i < nwords; i += 64) __builtin_nontemporal_store(region[i], dst + i);
     } else {
         // the general coder: the symbols are back in LDS, the words pass through a small window
         const uint32_t *win = region + kPcSymWords;
         for (uint32_t wbase = 0; wbase < nwords; wbase += kPcWin) {
             const uint32_t wn = nwords - wbase < (uint32_t)kPcWin ? nwords - wbase : (uint32_t)kPcWin;
-            pc_general_window(cnt, fast, book, region, lane, excl, wbase, wn);
+            pc_general_window(cnt, fast, books[s_book[wave]], region, lane, excl, wbase, wn);
             for (uint32_t i = lane; i < wn; i += 64) __builtin_nontemporal_store(win[i], dst + wbase + i);
             fu_wave_sync_lds();
         }
@@ -518,25 +796,33 @@ __global__ void k_zero_fused(uint64_t *p, uint64_t n, uint64_t *q, uint64_t nq)
     if (i < nq) q[i] = 0;
 }
 
-// Chunks per workgroup.  The small form wins while a launch is one workgroup's latency: it quantizes a chunk in a
-// quarter of the time.  It loses once the chunks are many, for three of its four wavefronts wait while one packs, and
-// once a user's are, for a user has one ticket counter and one chain of look-back entries, here one a chunk.  In
-// groups of kFuCpb chunks the two meet, for the conversion to the nearest representative, near 185 of one user, 320 of
-// four, 400 of eight, 450 of 24 (encode of one user, small and large form: 160 groups 27 and 28 us, 256 groups 38 and
-// 31; of eight users: 320 groups 31 and 38, 496 groups 46 and 44; of five users: 1895 groups 197 and 105): a line in
-// groups and groups per user.  The stochastic conversion is the longer part of its sweep and keeps the small form for
-// longer (eight users, 600 groups: 56 and 66 us, 720 groups: 68 and 69; one user, 320 groups: 55 and 52).
-constexpr uint64_t kFuSmallLine = 960, kFuSmallLineStochastic = 1650;
-static int fused_chunks_per_workgroup(const Layout &lay, bool stochastic)
+// Which form.  Small: a chunk and one team a workgroup.  A user has one ticket counter, whose atomics take turns (some 15 ns
+// each), and one chain of look-back entries, here one a chunk, so it is for launches that are one workgroup's way: encode of
+// eight users of 100 000 elements 13.7 us, in the next form 15.2; of 300 000 18.4 and 18.0; of 650 000 31 and 25.5; of one user of
+// 3.1 M 31 and 20.  Teams: four chunks a workgroup, a team each.  All of a chunk's vectors are requested at once, so a launch of
+// few workgroups is short and chunks off the 16-byte grid cost nothing more: eight users of 10^6 elements, in this form and in the
+// streaming form, 30 and 49 us; one of 8 M 32 and 48; sixteen of 2 M 89 and 107; eight of 6 M 132 and 143; sixteen of
+// 6.4 M 260 and 260; of 12 M 466 and 462; of 25.6 M 966 and 942, in three layers at odd elements 1048 and 1076; eight of 138 M so
+// 2635 and 2718.  The stochastic conversion, teams and streaming: sixteen users of 2 M elements 99 and 106 us, of 6.4 M 289 and 271.
+enum class FusedForm { kSmall, kTeams, kStream };
+constexpr uint64_t kFuSmallLine = 960, kFuSmallLineStochastic = 1650;     // in groups of kFuCpb chunks and groups per user
+constexpr uint64_t kFuStreamLine = 7000, kFuStreamLineStochastic = 4000;   // in groups
+static FusedForm fused_form(const Layout &lay, bool stochastic)
 {
     const uint64_t per_user = (lay.nchunks + kFuCpb - 1) / kFuCpb, groups = (uint64_t)lay.U * per_user;
-    return 2 * groups + 3 * per_user < (stochastic ? kFuSmallLineStochastic : kFuSmallLine) ? kFuCpbSmall : kFuCpb;
+    if (2 * groups + 3 * per_user < (stochastic ? kFuSmallLineStochastic : kFuSmallLine)) return FusedForm::kSmall;
+    if (stochastic) return groups < kFuStreamLineStochastic ? FusedForm::kTeams : FusedForm::kStream;
+    return groups < kFuStreamLine || !lay.vec_aligned ? FusedForm::kTeams : FusedForm::kStream;
+}
+static uint64_t fused_chunks_per_workgroup(const Layout &lay, bool stochastic)
+{
+    return fused_form(lay, stochastic) == FusedForm::kSmall ? kFuCpbSmall : kFuCpb;
 }
 
 size_t fused_workspace_bytes(const Layout &lay)
 {
     static_assert(kFuSmallLineStochastic >= kFuSmallLine, "a plan's workspace serves both conversions");
-    const uint64_t cpb = (uint64_t)fused_chunks_per_workgroup(lay, true);
+    const uint64_t cpb = fused_chunks_per_workgroup(lay, true);
     const uint64_t nblk = (lay.nchunks + cpb - 1) / cpb;
     // the look-back entries and a ticket counter (one 64-bit slot per user), the partial symbol-count tables of the
     // histogram option, plus alignment slack
@@ -553,31 +839,25 @@ static void launch_fused_waves(const Layout &lay, const co3_encode_args &a, cons
                        a.chunk_offset, a.sub_bits, a.payload_bits, a.words, a.words_stride, a.status, hist_rep);
 }
 
-// Wavefronts per SIMD the kernel is cut for: five only for the conversion to the nearest representative without symbol
-// counts, and in the large form only where no chunk needs shifted vectors (k_encode_fused's comment).  The team's
-// wavefronts hold a quarter of a chunk each: 85 registers either way, so there is no second cut of it.
-template <bool kSR, int kCpb, int kTeam>
-static void launch_fused_variant(const Layout &lay, const co3_encode_args &a, const BookDev *books, uint32_t *tickets,
-                                 uint64_t *lb_state, uint32_t nblk, uint64_t *hist_rep, hipStream_t s)
+// Wavefronts per SIMD the kernel is cut for.  A team's threads hold sixteen elements: two workgroups of 1024 threads fit a CU up
+// to 64 registers (the stochastic conversion spills fifteen for that: sixteen users of 2 M elements 110 -> 99 us).  The
+// streaming form: five only for the conversion to the nearest representative without symbol counts (k_encode_fused's comment).
+template <bool kSR, bool kHist>
+static void launch_fused_variant(FusedForm form, const Layout &lay, const co3_encode_args &a, const BookDev *books,
+                                 uint32_t *tickets, uint64_t *lb_state, uint32_t nblk, uint64_t *hist_rep, hipStream_t s)
 {
-    if (a.hist) {
-        launch_fused_waves<kSR, kCpb, kTeam, 4, true>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-    } else if constexpr (kSR) {
-        launch_fused_waves<kSR, kCpb, kTeam, 4, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-    } else if constexpr (kTeam > 1) {
-        launch_fused_waves<kSR, kCpb, kTeam, 5, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-    } else {
-        if (lay.vec_aligned) launch_fused_waves<kSR, kCpb, kTeam, 5, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-        else launch_fused_waves<kSR, kCpb, kTeam, 4, false>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-    }
+    if (form == FusedForm::kSmall) launch_fused_waves<kSR, kFuCpbSmall, kFuTeam, kSR ? 6 : 8, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    else if (form == FusedForm::kTeams) launch_fused_waves<kSR, kFuCpb, kFuTeam, 8, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    else launch_fused_waves<kSR, kFuCpb, 1, kSR || kHist ? 4 : 5, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
 }
 
 hipError_t launch_encode_fused(const Layout &lay, const co3_encode_args &a, const BookDev *books, hipStream_t s)
 {
     if (lay.U == 0) return hipSuccess;
     const bool sr = a.rounding == CO3_ROUND_STOCHASTIC;
-    const int cpb = fused_chunks_per_workgroup(lay, sr);
-    const uint64_t nblk = (lay.nchunks + (uint64_t)cpb - 1) / (uint64_t)cpb;
+    const FusedForm form = fused_form(lay, sr);
+    const uint64_t cpb = fused_chunks_per_workgroup(lay, sr);
+    const uint64_t nblk = (lay.nchunks + cpb - 1) / cpb;
     uint64_t *base = reinterpret_cast<uint64_t *>((reinterpret_cast<uintptr_t>(a.workspace) + 255u) & ~(uintptr_t)255u);
     // A ticket counter per user and the look-back entries.  Atomics on one cache line take turns whichever word they
     // add to.  In the small form all users' workgroups start together, so a user's counter lies in front of its own
@@ -607,12 +887,12 @@ hipError_t launch_encode_fused(const Layout &lay, const co3_encode_args &a, cons
     {
         ProfScope prof(K_FUSED, s);
         uint32_t *tickets = reinterpret_cast<uint32_t *>(base);
-        if (cpb == kFuCpb) {
-            if (sr) launch_fused_variant<true, kFuCpb, 1>(lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
-            else launch_fused_variant<false, kFuCpb, 1>(lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
+        if (a.hist) {
+            if (sr) launch_fused_variant<true, true>(form, lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
+            else launch_fused_variant<false, true>(form, lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
         } else {
-            if (sr) launch_fused_variant<true, kFuCpbSmall, kFuTeamSmall>(lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
-            else launch_fused_variant<false, kFuCpbSmall, kFuTeamSmall>(lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
+            if (sr) launch_fused_variant<true, false>(form, lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
+            else launch_fused_variant<false, false>(form, lay, a, books, tickets, lb_state, (uint32_t)nblk, hist_rep, s);
         }
     }
     if (a.hist) return launch_reduce_hist(hist_rep, a.hist, hist_n, s);

@@ -1384,3 +1384,61 @@ def test_wide_single_sweep_bounded_wait_gives_up():
     written = gpu["chunk_offset"] != np.uint64(0xFFFFFFFFFFFFFFFF)
     assert written.any() and not written.all()
     assert np.array_equal(gpu["chunk_offset"][written], ref["chunk_offset"][written])
+
+
+@pytest.mark.parametrize("U,seg_len", [(3, [4096 * 2 + 5]), (240, [3, 4096, 2, 4098, 1, 4097])], ids=["small", "teams"])
+@pytest.mark.parametrize("code", ["near", "long", "dense"])
+@pytest.mark.parametrize("seed", [None, 17])
+def test_single_sweep_runs_of_symbols(U, seg_len, code, seed):
+    # four wavefronts a chunk, a run of sixteen symbols a thread, a chunk and four chunks a workgroup: layers at every
+    # place of the 16-byte grid (a chunk's last symbols stand in front of its first run), a few codes of up to 61 bits (runs
+    # coded symbol by symbol), codes of 40 bits and more throughout (chunks of several windows)
+    E, M, A = 4, 1, 64
+    d = sum(seg_len)
+    rng = np.random.default_rng(2300 + U)
+    bias = 16
+    nm = orc.num_magnitudes(E, M)
+    grid = orc.grid(E, M, bias)
+    emit = np.array([s for s in range(A) if (s & 31) < nm and s != 32])
+    w = np.zeros(A, np.uint64)
+    k = np.minimum(rng.geometric(0.35, (U, d)) - 1, nm - 1)
+    if code == "near":
+        k = rng.integers(0, nm, (U, d))
+        w[emit] = 1
+    elif code == "long":
+        w[emit] = [1 << max(0, 60 - (int(s) & 31) * 2 - (int(s) >> 5)) for s in emit]
+    else:
+        few = [int(s) for s in emit if (int(s) & 31) < 8]
+        k = rng.integers(0, 8, (U, d))
+        rest = [int(s) for s in emit if int(s) not in few]
+        w[few] = 1
+        w[rest] = [1 << (5 + i) for i in range(len(rest))]
+    g = (grid[k] * rng.choice([-1.0, 1.0], (U, d))).astype(np.float32)
+    m = np.zeros_like(g)
+    n = len(seg_len)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias] * n] * U, seg_len=seg_len, seg_book=[0] * n)
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=w[None, :], stochastic_seed=seed)
+    used = ref["lens"].reshape(-1)[np.flatnonzero(ref["hist"].reshape(-1))]
+    assert {"near": used.max() <= 8, "long": used.max() > 24, "dense": used.min() >= 33}[code], used
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w[None, :], single_sweep=True, stochastic_seed=seed, max_code_len=64)
+    gu.compare_round(gpu, ref, d, single_sweep=True)
+
+
+@pytest.mark.parametrize("U,seg_len,seed,hist", [(7001, [4100], None, False), (7001, [4100], None, True), (4001, [4099, 70], 3, False)])
+def test_single_sweep_streaming_form(U, seg_len, seed, hist):
+    # a wavefront a chunk, which large inputs take: whole and ragged chunks, of the stochastic conversion also shifted ones
+    E, M = 3, 2
+    d = sum(seg_len)
+    rng = np.random.default_rng(2400 + U)
+    g = (rng.standard_normal((U, d), dtype=np.float32) * np.float32(1e-3))
+    m = np.roll(g, 1, axis=0) * np.float32(0.3)
+    bias = syn.bias_for_max(np.abs(g + np.float32(0.9) * m).max(), E)
+    n = len(seg_len)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias] * n] * U, seg_len=seg_len, seg_book=[0] * n)
+    few = dict(kw, U=4, bias=kw["bias"][:4])
+    weights = np.maximum(gu.oracle_round(few, g[:4], m[:4], 0.9)["hist"], 1)
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=weights, stochastic_seed=seed)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=weights, single_sweep=True, stochastic_seed=seed, single_sweep_hist=hist)
+    gu.compare_round(gpu, ref, d, single_sweep=True)
+    if hist:
+        gu.assert_bits_equal(gpu["hist"], ref["hist"], "histogram")
