@@ -88,28 +88,12 @@ __device__ inline void fu_lds_barrier()
 
 // ---- a team: four wavefronts a chunk, a run of 16 symbols a thread (run_coder.h) ----
 
-// What a thread keeps of its run between the sweep and the coding.
-struct TeamRun {
-    uint32_t w[4];        // symbols
-    uint32_t e[kRun];     // their entries; 0 where there is none, or where the chunk's last ones stand in the first run
-    uint32_t tail[4];     // those
-    uint32_t from, to;    // its symbols in w
-    uint32_t excl, bits;  // bits before it in the wavefront's share of the chunk, its own
-    uint32_t total;       // that share
-    uint32_t in_order;    // bits of the wavefront's run of the lane's number
-    uint32_t tail_bits;
-    bool slow;            // an entry is not enough, or a pair too long
-};
-
 // The team's wavefront `part` quantizes vectors 256 part .. 256 part + 255 of the chunk, 64 side by side with every request.  A
 // transposition within the quads of lanes then gives lane 4 q + i the symbols of vectors 64 i + 4 q .. + 3: run 16 i + q of the
 // wavefront's (run_of_lane).
 // A chunk that starts `shift` elements behind the 16-byte grid takes the vectors from the boundary below it, and vector 0, of
 // which the first `shift` elements lie before the chunk, has the chunk's last ones in their place: every vector is whole, and the
 // runs are those `shift` elements ahead, with the last few symbols of the chunk in front of the first run.
-__device__ inline uint32_t run_of_lane(uint32_t lane) { return 16u * (lane & 3u) + (lane >> 2); }
-__device__ inline uint32_t lane_of_run(uint32_t r) { return 4u * (r & 15u) + (r >> 4); }
-
 template <bool kSR, bool kHist>
 __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, uint32_t part, uint64_t e0, uint32_t nk, uint32_t shift,
                                   int32_t bias, float gain, float inv_gain, const float *__restrict__ gu, const float *mu,
@@ -213,68 +197,6 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
     if (n_clamped) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CLAMPED), (unsigned long long)n_clamped);
 }
 
-// A run's entries, its bits and its place among the wavefront's; head: the bits of its first `shift` symbols, which belong to
-// the sub-chunk before.
-__device__ inline void team_lengths(TeamRun &run, uint32_t part, uint32_t nk, uint32_t shift, const uint32_t *entry, const BookDev &book,
-                                    uint32_t &head, uint64_t *__restrict__ status)
-{
-    const uint32_t lane = threadIdx.x & 63u, first = (uint32_t)kRun * (64u * part + run_of_lane(lane));
-    const bool opens = shift && first == 0;   // the chunk's first run
-    run.from = opens ? shift : 0u;
-    run.to = nk > first ? (nk - first < (uint32_t)kRun ? nk - first : (uint32_t)kRun) : 0u;
-    uint32_t most = 0;
-    run.bits = run.tail_bits = head = 0;
-#pragma unroll
-    for (int j = 0; j < kRun; ++j) run.e[j] = entry[run_symbol(run.w, j)];
-    if (nk != (uint32_t)kChunk) {
-#pragma unroll
-        for (int j = 0; j < kRun; ++j) run.e[j] = (uint32_t)j < run.to ? run.e[j] : 0u;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) run.tail[j] = 0;
-    if (shift) {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const bool ahead = (uint32_t)j < shift;
-            run.tail[j] = ahead && opens ? run.e[j] : 0u;
-            run.e[j] = ahead && opens ? 0u : run.e[j];
-            head += ahead ? run.e[j] & 0xffu : 0u;
-        }
-        run.tail_bits = (run.tail[0] & 0xffu) + (run.tail[1] & 0xffu) + (run.tail[2] & 0xffu);
-        most = run.tail_bits;   // at most three of 24 bits: two pairs of up to 32, or coded one by one
-    }
-#pragma unroll
-    for (int j = 0; j < kRun; j += 2) {
-        const uint32_t both = (run.e[j] & 0xffu) + (run.e[j + 1] & 0xffu);
-        run.bits += both;
-        most = most > both ? most : both;
-    }
-    run.slow = most > 32u;
-    if (__any(run.slow)) {
-        if (run.slow) {
-            uint32_t nocode = 0;
-            run.bits = run_bits_exact(run.w, (int)run.from, (int)run.to, entry, book, nocode);
-            run.tail_bits = opens ? run_bits_exact(run.w, 0, (int)shift, entry, book, nocode) : 0u;
-            if (nocode) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
-            uint32_t counted = 0;
-            head = opens ? 0u : run_bits_exact(run.w, 0, (int)shift, entry, book, counted);
-        }
-    }
-    // in the runs' order and back
-    run.in_order = (uint32_t)__shfl((int)run.bits, (int)lane_of_run(lane), 64);
-    const uint32_t incl = wave_inclusive_scan_dpp(run.in_order);
-    run.total = __builtin_amdgcn_readlane((int)incl, 63);
-    run.excl = (uint32_t)__shfl((int)(incl - run.in_order), (int)run_of_lane(lane), 64);
-}
-
-// The run's codewords, any length, with those that stand ahead of the chunk's first run at its end: words wbase .. wbase + wn - 1.
-__device__ inline void team_append_exact(const TeamRun &run, const uint32_t *entry, const BookDev &book, uint32_t pos, uint32_t chunk_bits,
-                                         uint32_t *win, uint32_t wbase, uint32_t wn)
-{
-    run_append_exact(run.w, (int)run.from, (int)run.to, entry, book, pos, win, wbase, wn);
-    if (run.from) run_append_exact(run.w, 0, (int)run.from, entry, book, chunk_bits - run.tail_bits, win, wbase, wn);
-}
-
 // kSR: the stochastic conversion (dither from Philox words of (element, user, seed)) instead of
 // the closest representative.
 // kWaves: wavefronts per SIMD the register budget is cut for.  Five (a few values spill) is what the streaming of
@@ -360,7 +282,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
         }
         fu_lds_barrier();   // tables (and counts)
         if (active) {
-            team_lengths(run, part, nk, shift, s_fast[wave], books[bk], head, status);
+            team_lengths<true>(run, part, nk, shift, s_fast[wave], books[bk], head, status);
             if ((lane & 15u) < 4u) s_head[wave][16u * part + (run_of_lane(lane) >> 2)] = head;
             if (part == 0 && lane == 0) s_head[wave][kSubsPerChunk] = run.tail_bits;
             if constexpr (kHist) {

@@ -17,6 +17,7 @@
 // Nothing in these kernels needs a workgroup barrier.
 #include "co3_internal.h"
 #include "pack_core.h"
+#include "run_coder.h"
 
 namespace co3 {
 
@@ -136,93 +137,126 @@ __global__ __launch_bounds__(kPkThreads) void k_chunk_bits_hist(Layout lay, cons
     if (lane == 0) chunk_bits[(uint64_t)u * lay.nchunks + c] = total;
 }
 
-// The coder proper.  chunk_offset comes from k_scan_chunks.
-__global__ __launch_bounds__(kPkThreads) void k_pack_chunk(
+// The coder proper.  chunk_offset comes from k_scan_chunks, or (kOffsets) every workgroup adds up the sizes of its user's chunks ahead
+// of its own and writes its chunks' offsets, the last one the payload.  A workgroup takes `per_wg` consecutive chunks of a user, a team of four
+// wavefronts on each in turn: a thread loads the 16 symbols of its run at once, at any byte, those of the next chunk before
+// it codes these.  Two windows take turns; a thread clears the words that it has copied out.
+// What bounds it: vector instructions, some @@ per symbol (17.5 where a lane coded 64 symbols into a row of its own and moved it).
+// Sixteen users of 25.6 M elements in [1,4,3]: 208 -> @@ us.
+template <bool kOffsets>
+__global__ __launch_bounds__(kPkThreads, 8) void k_pack_chunk(
     Layout lay, const uint8_t *__restrict__ sym, uint64_t sym_stride, const BookDev *__restrict__ books,
-    const uint64_t *__restrict__ chunk_offset, uint16_t *__restrict__ sub_bits, uint32_t *__restrict__ words,
-    uint64_t words_stride, uint64_t *__restrict__ status)
+    uint64_t *__restrict__ chunk_offset, uint16_t *__restrict__ sub_bits, uint32_t *__restrict__ words,
+    uint64_t words_stride, uint64_t *__restrict__ status, uint32_t per_wg, const uint32_t *__restrict__ chunk_bits,
+    uint64_t *__restrict__ payload_bits)
 {
-    __shared__ uint32_t s_region_all[kPkWaves][kPcRegion];
-    __shared__ uint32_t s_fast_all[kPkWaves][kMaxA];
+    __shared__ __align__(16) uint32_t s_win[2][kRunWindowStride];
+    __shared__ uint32_t s_entry[kMaxA];
+    __shared__ uint32_t s_part[2][kPkWaves];
+    static_assert(kPkThreads == kMaxA && kPkThreads * kRun == kChunk, "an entry and a run for every thread");
 
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t c = (uint64_t)blockIdx.x * kPkWaves + wave;
+    const uint32_t t = threadIdx.x, lane = t & 63;
+    const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
     const uint32_t u = blockIdx.y;
-    if (c >= lay.nchunks) return;  // whole wavefront; no workgroup barriers below
-    uint32_t *region = s_region_all[wave];
-    uint32_t *s_fast = s_fast_all[wave];
-    const PkChunk k = pk_chunk(lay, c, u, sym_stride);
-    const BookDev &book = books[k.book];
-
-    // what the wavefront needs from memory, requested together: table, symbols, stream offset
-    uint32_t tab[kMaxA / 64];
-#pragma unroll
-    for (int r = 0; r < kMaxA / 64; ++r) tab[r] = book.fast[lane + 64 * r];
-    const uint64_t off = chunk_offset[(uint64_t)u * (lay.nchunks + 1) + c];
-    uint32_t symw[kSub / 4];   // the lane's 64 symbols, four per word
-    {
-        // any byte offset, any length: coalesced dwords from the 4-byte boundary below the chunk, staged in LDS
-        // rows of 16 + 1 words, from which every lane funnels its 64 bytes
-        const uint32_t shift = (uint32_t)(k.byte0 & 3u);
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(sym + (k.byte0 - shift));
-        const uint32_t ndw = (shift + k.n + 3u) >> 2;
-        uint32_t tmp[kSymLoads];
-#pragma unroll
-        for (int r = 0; r < kSymLoads; ++r) {
-            const uint32_t i = lane + 64u * r;
-            tmp[r] = i < ndw ? __builtin_nontemporal_load(src + i) : 0u;
+    const uint64_t c0 = (uint64_t)blockIdx.x * per_wg;
+    const uint32_t n = lay.nchunks - c0 < per_wg ? (uint32_t)(lay.nchunks - c0) : per_wg;
+    uint64_t *offsets = chunk_offset + (uint64_t)u * (lay.nchunks + 1) + c0;
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    typedef u4 u4_any __attribute__((aligned(1)));
+    auto request = [&](const PkChunk &k) {
+        return (uint32_t)kRun * t < k.n ? __builtin_nontemporal_load(reinterpret_cast<const u4_any *>(sym + k.byte0 + (uint32_t)kRun * t))
+                                        : u4{0u, 0u, 0u, 0u};
+    };
+    PkChunk k = pk_chunk(lay, c0, u, sym_stride);
+    u4 next = request(k);
+    uint32_t tab = books[k.book].fast[t];
+    for (uint32_t i = 4u * t; i < (uint32_t)kRunWindowStride; i += 4u * kPkThreads)
+        *reinterpret_cast<u4 *>(&s_win[0][i]) = *reinterpret_cast<u4 *>(&s_win[1][i]) = u4{0u, 0u, 0u, 0u};
+    uint32_t ahead = 0, payload = 0;   // (kOffsets) bits of the chunks before this one, rounded up to words each, and as they are
+    if constexpr (kOffsets) {
+        __shared__ uint32_t s_ahead[kPkWaves], s_payload[kPkWaves];
+        const uint32_t *size = chunk_bits + (uint64_t)u * lay.nchunks;
+        for (uint32_t i = t; i < (uint32_t)c0; i += kPkThreads) {
+            ahead += (size[i] + 31u) & ~31u;
+            payload += size[i];
         }
-#pragma unroll
-        for (int r = 0; r < kMaxA / 64; ++r) s_fast[lane + 64 * r] = tab[r];
-#pragma unroll
-        for (int r = 0; r < kSymLoads; ++r) {
-            const uint32_t i = lane + 64u * r;
-            if (i < kChunk / 4 + 1) region[i + (i >> 4)] = tmp[r];  // word 1024 lands at 1088
+        ahead = wave_sum(ahead);
+        payload = wave_sum(payload);
+        if (lane == 0) {
+            s_ahead[part] = ahead;
+            s_payload[part] = payload;
         }
-        pc_wave_sync_lds();
-        const uint32_t *row = region + kPcSymRow * lane;   // dwords 16 lane .. 16 lane + 15; dword 16 lane + 16 is row[17]
-        uint32_t cur = row[0];
+        __syncthreads();
+        ahead = payload = 0;
 #pragma unroll
-        for (int jj = 0; jj < kSub / 4; ++jj) {
-            const uint32_t nxt = row[jj + 1 + (jj == kSub / 4 - 1 ? 1 : 0)];
-            symw[jj] = __builtin_amdgcn_alignbit(nxt, cur, 8u * shift);
-            cur = nxt;
+        for (int j = 0; j < kPkWaves; ++j) {
+            ahead += s_ahead[j];
+            payload += s_payload[j];
         }
-        pc_wave_sync_lds();                                // the region is free again
     }
-    const int first = (int)lane * kSub;
-    const int cnt = (int)k.n - first < 0 ? 0 : ((int)k.n - first > kSub ? kSub : (int)k.n - first);
-
-    uint32_t bits = 0;
-    const bool fast_ok = k.n == (uint32_t)kChunk ? pc_pack_rows<true>(symw, cnt, s_fast, region, lane, bits)
-                                                 : pc_pack_rows<false>(symw, cnt, s_fast, region, lane, bits);
-    if (!fast_ok) {
-        uint32_t nocode = 0;
-        bits = pc_general_count(symw, cnt, s_fast, book, region, lane, nocode);
-        if (nocode)
-            atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NOCODE), (unsigned long long)nocode);
+    uint32_t book = ~0u;
+    for (uint32_t i = 0; i < n; ++i) {
+        const PkChunk cur = k;
+        const BookDev &table = books[cur.book];
+        if (cur.book != book) {   // the same in all threads
+            if (i) {
+                __syncthreads();   // the table before is done with
+                tab = table.fast[t];
+            }
+            s_entry[t] = run_entry(tab);
+            book = cur.book;
+            __syncthreads();
+        }
+        TeamRun run;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) run.w[j] = next[j];
+        if (i + 1 < n) {
+            k = pk_chunk(lay, c0 + i + 1, u, sym_stride);
+            next = request(k);
+        }
+        uint64_t off_words = 0;
+        if constexpr (!kOffsets) off_words = offsets[i] >> 5;
+        uint32_t head;
+        team_lengths<false>(run, part, cur.n, 0, s_entry, table, head, status);
+        uint32_t *win = s_win[i & 1u], *share = s_part[i & 1u];
+        if (lane == 0) share[part] = run.total;
+        __syncthreads();
+        uint32_t base = 0, bits = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < (uint32_t)kPkWaves; ++j) {
+            base += j < part ? share[j] : 0u;
+            bits += share[j];
+        }
+        const uint32_t excl = base + run.excl, nwords = (bits + 31u) >> 5;
+        if constexpr (kOffsets) {
+            off_words = ahead >> 5;
+            if (t == 0) offsets[i] = ahead;
+            ahead += nwords << 5;
+            payload += bits;
+        }
+        const uint32_t sub = quad_sum(run.bits);
+        if ((lane & 3u) == 0) sub_bits[((uint64_t)u * lay.nchunks + c0 + i) * kSubsPerChunk + (t >> 2)] = (uint16_t)sub;
+        const bool fits = off_words + nwords <= words_stride;
+        if (!fits && t == 0) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CAPACITY), 1ull);
+        uint32_t *dst = words + (uint64_t)u * words_stride + off_words;
+        // window by window where the chunk's words are more than one holds
+        for (uint32_t wbase = 0; wbase < nwords; wbase += kRunWindow) {
+            if (wbase) __syncthreads();   // the window before is out
+            if (run.slow || nwords > (uint32_t)kRunWindow) run_append_exact(run.w, 0, (int)run.to, s_entry, table, excl, win, wbase, kRunWindow);
+            else run_append(run.e, excl, win);
+            __syncthreads();
+            const uint32_t left = nwords - wbase, wn = left < (uint32_t)kRunWindow ? left : (uint32_t)kRunWindow;
+            for (uint32_t j = t; j < wn; j += kPkThreads) {
+                if (fits) __builtin_nontemporal_store(win[j], dst + wbase + j);
+                win[j] = 0u;
+            }
+        }
+        if (t < 1) win[kRunWindow] = 0u;
     }
-    sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + lane] = (uint16_t)bits;
-    const uint32_t incl = wave_inclusive_scan(bits);
-    const uint32_t excl = incl - bits;
-    const uint32_t chunk_total = __shfl(incl, 63, 64);
-    const uint32_t nwords = (chunk_total + 31u) >> 5;
-    const uint64_t off_words = off >> 5;
-    if (off_words + nwords > words_stride) {
-        if (lane == 0) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CAPACITY), 1ull);
-        return;
-    }
-    uint32_t *dst = words + (uint64_t)u * words_stride + off_words;
-    if (fast_ok) {
-        pc_rows_to_window(region, lane, bits, excl, nwords);
-        for (uint32_t i = lane; i < nwords; i += 64) __builtin_nontemporal_store(region[i], dst + i);
-    } else {
-        const uint32_t *win = region + kPcSymWords;
-        for (uint32_t wbase = 0; wbase < nwords; wbase += kPcWin) {
-            const uint32_t wn = nwords - wbase < (uint32_t)kPcWin ? nwords - wbase : (uint32_t)kPcWin;
-            pc_general_window(cnt, s_fast, book, region, lane, excl, wbase, wn);
-            for (uint32_t i = lane; i < wn; i += 64) __builtin_nontemporal_store(win[i], dst + wbase + i);
-            pc_wave_sync_lds();
+    if constexpr (kOffsets) {
+        if (t == 0 && c0 + n == lay.nchunks) {
+            offsets[n] = ahead;
+            payload_bits[u] = payload;
         }
     }
 }
@@ -271,6 +305,16 @@ hipError_t launch_scan_chunks(const Layout &lay, const uint32_t *chunk_bits, uin
     return hipGetLastError();
 }
 
+// One while the workgroups fit the device at a time; then several, whose symbols are requested ahead (k_pack_chunk of 256 chunks with
+// one, two and four a workgroup 3.8, 5.1, 7.9 us; of 10 360 25.3, 22.4, 22.1; of 28 540 62, 57, 54; of 99 840 227, 203, 200; with
+// eight 13.4, 25.4, 55, 203).
+constexpr uint64_t kPkSums = 1024;
+static uint32_t pack_chunks_per_workgroup(const Layout &lay)
+{
+    const uint64_t chunks = lay.nchunks * lay.U;
+    return chunks >= 8192 ? 4 : (chunks >= 4096 ? 2 : 1);
+}
+
 hipError_t launch_pack(const Layout &lay, const co3_encode_args &a, const BookDev *books, const EncodeWs &ws,
                        hipStream_t s)
 {
@@ -286,11 +330,16 @@ hipError_t launch_pack(const Layout &lay, const co3_encode_args &a, const BookDe
             hipLaunchKernelGGL(k_chunk_bits, dim3(gx, lay.U), dim3(kPkThreads), 0, s, lay, a.symbols, sym_stride, books,
                                ws.chunk_bits);
     }
-    if (launch_scan_chunks(lay, ws.chunk_bits, a.chunk_offset, a.payload_bits, s) != hipSuccess) return hipGetLastError();
+    // Up to kPkSums chunks a user the coder's workgroups add up the sizes themselves: a launch less (one user of 256 chunks in [1,3,0], a
+    // round @@ us; a workgroup's loads, four a thread at most, are answered while its symbols are on their way).
+    const bool sums = lay.nchunks && lay.nchunks <= kPkSums;
+    if (!sums && launch_scan_chunks(lay, ws.chunk_bits, a.chunk_offset, a.payload_bits, s) != hipSuccess) return hipGetLastError();
     if (lay.nchunks) {
         ProfScope prof(K_PACK, s);
-        hipLaunchKernelGGL(k_pack_chunk, dim3(gx, lay.U), dim3(kPkThreads), 0, s, lay, a.symbols, sym_stride, books,
-                           a.chunk_offset, a.sub_bits, a.words, a.words_stride, a.status);
+        const uint32_t per_wg = pack_chunks_per_workgroup(lay);
+        hipLaunchKernelGGL(sums ? k_pack_chunk<true> : k_pack_chunk<false>, dim3((uint32_t)((lay.nchunks + per_wg - 1) / per_wg), lay.U),
+                           dim3(kPkThreads), 0, s, lay, a.symbols, sym_stride, books, a.chunk_offset, a.sub_bits, a.words, a.words_stride,
+                           a.status, per_wg, ws.chunk_bits, a.payload_bits);
     }
     return hipGetLastError();
 }
