@@ -532,10 +532,9 @@ __device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &pl
     }
 }
 
-// Users whose symbols meet in LDS at most: two a wavefront, 5 KB each, so that sixteen wavefronts still fit a CU up to fifteen
-// users, and eight with sixteen.  (Four a wavefront: sixteen users of 12 M elements in [1,5,2], a round 600 us from the sums,
-// 794 this way.)
-constexpr uint32_t kStageUsers = 2 * kAggWaves;
+// Users whose symbols meet in LDS at most: two a wavefront, 5 KB each.  (Four a wavefront: sixteen users of 12 M elements in
+// [1,5,2], a round 600 us from the sums, 794 this way.)
+constexpr uint32_t kStageWaves = 16, kStageUsers = 2 * kStageWaves;
 __host__ __device__ constexpr uint32_t stage_bytes(uint32_t U) { return 4u * U * kStageWords + kStageUsers * (uint32_t)(sizeof(double) + sizeof(float)); }
 // The same sums where the workgroup's wavefronts decode all users in one turn: the symbols meet in LDS, an eighth of what
 // the fp64 sums would be, and every thread adds up its elements in the users' order, where the sums would be added up by
@@ -703,7 +702,7 @@ __global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggrega
 
 // The same where a workgroup's wavefronts take all users of a chunk in one turn, one or two each.
 template <int kUsers>
-__global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggregate_staged(Layout lay, AggArgs a)
+__global__ __launch_bounds__(64 * kStageWaves, kUsers == 1 ? 6 : 4) void k_aggregate_staged(Layout lay, AggArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<true>(lay, a, smem, 0);
@@ -785,6 +784,44 @@ static hipError_t launch_aggregate_places(Kernel k, const Layout &lay, uint32_t 
     return launch_aggregate_k(k, lay, waves, across, 4 * (size_t)at + (size_t)places * per_user, s, args..., at, places);
 }
 
+static size_t staged_lds(const Layout &lay, uint32_t waves)
+{
+    const size_t lds = aggregate_lds(lay, false, waves, true), stage = stage_bytes(lay.U);
+    return lds > stage ? lds : stage;
+}
+static hipError_t launch_aggregate_staged(const Layout &lay, const AggArgs &a, uint32_t waves, hipStream_t s)
+{
+    const size_t lds = staged_lds(lay, waves);
+    if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1>, lay, waves, true, lds, s, a);
+    return launch_aggregate_k(k_aggregate_staged<2>, lay, waves, true, lds, s, a);
+}
+
+// Wavefronts of a workgroup that takes all users of a chunk in one turn, one each or two, where that is the better way (else 0).  A launch
+// of few chunks is a workgroup's way: one turn of decoding, and sums by all threads.  us, this way and the others, formats of
+// four and of five exponent bits:
+//   chunks a user    2 users         4               8               10              16              24
+//   5                -               10.2 11.7       10.8 12.3       11.6 16.6       13.4 17.8       19.7 23.3, 19.7 29.2
+//   245              11.4 12.9       10.7 11.9       11.2 12.6       12.5 16.7       13.7 18.0       20.4 24.3, 20.5 29.3
+//   367              12.4 13.7       11.5 12.9       13.7 14.7       16.9 19.0       23.9 21.5, 24.2 32.6   37.4 28.9, 37.6 38.6
+//   1026             15.5 16.2       16.9 22.0       26.6 34.2, 41.4   37 41, 57     58 59, 57 68    90 83, 88 93
+//   2198             24 27, 34       28 39, 46       43 66, 68       68 79, 87       104 82, 103 104  159 113, 158 160
+//   3907             33 28, 32 34    43 38, 43 44    70 64, 70 86    113 78, 113 133   188 132, 182 162  295 184, 293 285
+// Formats whose sums are integers go over to those from 2500 chunks on, many users from more than the device holds; the others
+// stay with up to ten users (four of 10^8 elements in [1,5,2] 234 and 265).  A table for every wavefront leaves less room in LDS.
+static uint32_t staged_waves(const Layout &lay, bool ints)
+{
+    const uint32_t each = (lay.U + kStageWaves - 1) / kStageWaves;
+    if (lay.U < 2 || each > 2) return 0;
+    const uint32_t waves = (lay.U + each - 1) / each;
+    const uint64_t pieces = (staged_lds(lay, waves) + 1279) / 1280;   // LDS is given out in pieces, 128 of them
+    const uint64_t per_cu = 128 / pieces < 32 / waves ? 128 / pieces : 32 / waves;
+    if (per_cu == 0) return 0;
+    const bool few = lay.nchunks <= 256 * per_cu;
+    if (lay.per_user_books) return few ? waves : 0;
+    if (lay.U <= 10) return few || !ints || lay.nchunks <= 2500 ? waves : 0;
+    return few || (!ints && lay.nchunks <= 2300) ? waves : 0;
+}
+
 template <bool kGain>
 static hipError_t launch_aggregate_packed(const Layout &lay, const AggArgs &a, uint32_t waves, hipStream_t s)
 {
@@ -793,13 +830,8 @@ static hipError_t launch_aggregate_packed(const Layout &lay, const AggArgs &a, u
         if (lay.U == 1) return launch_aggregate_k(k_aggregate<1, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u, 0u, 0u);
         return launch_aggregate_places(k_aggregate<kPackUsers, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u);
     }
+    if (lay.U <= 2 * waves) return launch_aggregate_staged(lay, a, waves, s);
     size_t lds = aggregate_lds(lay, false, waves, true);
-    if (lay.U <= 2 * waves) {
-        const size_t stage = stage_bytes(lay.U);
-        if (stage > lds) lds = stage;
-        if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1>, lay, waves, true, lds, s, a);
-        return launch_aggregate_k(k_aggregate_staged<2>, lay, waves, true, lds, s, a);
-    }
     uint32_t all_at = 0;
     if (lay.U > waves * kPackUsers) {   // several turns: the sums need a place of their own
         all_at = (uint32_t)((lds + 15) / 16 * 4);
@@ -812,6 +844,7 @@ hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3
 {
     if (lay.U == 0 || lay.nchunks == 0) return hipSuccess;
     const AggArgs args = {a.words, a.words_stride, a.chunk_offset, a.sub_bits, books, a.out, a.model, (double)a.eta, a.status};
+    if (const uint32_t w = staged_waves(lay, dec_value_is_int(lay.E) && !facts.has_gain)) return launch_aggregate_staged(lay, args, w, s);
     // A wavefront per user where 4096 are resident at a time (sixteen a CU) and more would wait: what bounds a small
     // launch is one wavefront's way through its users (eight users of 10^6 elements in [1,4,3], eight, four, two
     // wavefronts and one a chunk: 13, 18, 28 and 53 us; of 4 M elements 30, 24, 33, 53).  Beyond, a wavefront per chunk
