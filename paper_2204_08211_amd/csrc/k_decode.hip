@@ -31,13 +31,16 @@ constexpr int kStageStride = 20;   // words per staged sub-chunk row (16, and 4 
 constexpr uint32_t kStageWords = kSubsPerChunk * kStageStride;
 static_assert(kStageWords % 64 == 0, "windows are whole rows");
 __host__ __device__ constexpr uint32_t stage_window_words(uint32_t A) { return window_words(A) > kStageWords ? window_words(A) : kStageWords; }
+// kOne: the average of a single user, which is its values: out and model of `one` instead of symbols and q (one of the averages'
+// kernels with sums in registers took 12.2 us for 300 000 elements in [1,4,3] and 134 for 10^8; this 10.8 and 96).
+template <bool kOne>
 __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uint32_t *__restrict__ words,
                                                            uint64_t words_stride,
                                                            const uint64_t *__restrict__ chunk_offset,
                                                            const uint16_t *__restrict__ sub_bits,
                                                            const BookDev *__restrict__ books, uint8_t *__restrict__ sym,
                                                            uint64_t sym_stride, float *__restrict__ q, uint64_t q_stride,
-                                                           uint64_t *__restrict__ status, uint32_t by_chunk)
+                                                           uint64_t *__restrict__ status, uint32_t by_chunk, AggArgs one)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const uint32_t tab_words = dec_table_entries(lay.A) / 2;
@@ -102,6 +105,25 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(Layout lay, const uin
     wave_lds_fence();
     const uint8_t *stage_b = reinterpret_cast<const uint8_t *>(s_stage);
     const bool full = g.n == (uint32_t)kChunk;
+    if constexpr (kOne) {
+        const SymbolValue val(lay.E, lay.M);
+        const int up = 127 - (int)uniform((uint32_t)lay.bias[g.seg]);
+        const float inv_gain = lay.gain[2 * g.seg + 1];   // 1 unless the plan carries a scale
+        auto four = [&](uint32_t e, bool whole) {
+            const uint32_t w = s_stage[(e >> 6) * kStageStride + ((e & 63u) >> 2)];
+            double avg[4];
+#pragma unroll
+            for (uint32_t b = 0; b < 4; ++b) avg[b] = 0.0 + (double)__fmul_rn(ldexpf(val(w, 8u * b), up), inv_gain);
+            write_four(g, one, e, avg, whole);
+        };
+        if (full) {
+#pragma unroll 4
+            for (uint32_t e = 4 * lane; e < (uint32_t)kChunk; e += 256) four(e, true);
+        } else {
+            for (uint32_t e = 4 * lane; e < g.n; e += 256) four(e, false);
+        }
+        return;
+    }
     if (sym) {
         uint8_t *dst = sym + (uint64_t)u * sym_stride + g.e0;
         if (full) {   // layers start anywhere
@@ -455,7 +477,7 @@ __device__ inline void aggregate_packed(const AggPart &p)
             scale[s] = __longlong_as_double((long long)(1023 + 127 - bias) << 52);
         }
         const bool last = u0 + step * kUsers >= lay.U;
-        if (kGain || (kUsers == 1 && p.g.scaled)) {
+        if (kGain) {
             float inv_gain[kUsers];
 #pragma unroll
             for (int s = 0; s < kUsers; ++s) inv_gain[s] = lay.gain[2 * pair_of(s) + 1];
@@ -687,14 +709,14 @@ __global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate_int(Layout lay,
 
 // co3_ps_aggregate for everything else.  kUsers: per wavefront and turn.
 template <int kUsers, bool kGain, bool kAcross>
-__global__ __launch_bounds__(64 * kAggWaves, kUsers == 1 ? 6 : 4) void k_aggregate(Layout lay, AggArgs a, uint32_t all_at, uint32_t places_at, uint32_t places)
+__global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate(Layout lay, AggArgs a, uint32_t all_at, uint32_t places_at, uint32_t places)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<kAcross>(lay, a, smem, all_at);
     round_toward_zero();
     bool rare = p.g.scaled;
     if constexpr (!kAcross) rare = any_wave(p, rare, 1);
-    if constexpr (!kGain && kUsers > 1) {
+    if constexpr (!kGain) {
         if (__builtin_expect(rare, 0)) return aggregate_rare<kAcross>(smem, places_at, places);
     }
     aggregate_packed<kUsers, kGain, kAcross>(p);
@@ -724,13 +746,17 @@ hipError_t launch_mark_scaled(const Layout &lay, SegDev *segs, hipStream_t s)
     return hipGetLastError();
 }
 
+static size_t decode_lds(const Layout &lay)
+{
+    return 4 * ((size_t)front_words(dec_table_entries(lay.A) / 2) + kDecWaves * stage_window_words(lay.A) + kBehindWords);
+}
+
 hipError_t launch_decode(const Layout &lay, const co3_decode_args &a, const BookDev *books, hipStream_t s)
 {
     if (lay.U == 0 || lay.nchunks == 0) return hipSuccess;
     const uint64_t sym_stride = symbol_row_stride(lay.d);
-    const size_t lds = 4 * ((size_t)front_words(dec_table_entries(lay.A) / 2) +
-                            kDecWaves * stage_window_words(lay.A) + kBehindWords);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_decode),
+    const size_t lds = decode_lds(lay);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_decode<false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ProfScope prof(K_DECODE, s);
@@ -739,8 +765,8 @@ hipError_t launch_decode(const Layout &lay, const co3_decode_args &a, const Book
     const bool by_chunk = lay.books_per_user > 1 && !lay.per_user_books;
     const uint64_t chunks = by_chunk ? lay.nchunks * lay.U : lay.nchunks;
     const dim3 grid((uint32_t)((chunks + kDecWaves - 1) / kDecWaves), by_chunk ? 1u : lay.U);
-    hipLaunchKernelGGL(k_decode, grid, dim3(64 * kDecWaves), lds, s, lay, a.words, a.words_stride, a.chunk_offset, a.sub_bits,
-                       books, a.symbols, sym_stride, a.q, a.q_stride, a.status, by_chunk ? 1u : 0u);
+    hipLaunchKernelGGL(k_decode<false>, grid, dim3(64 * kDecWaves), lds, s, lay, a.words, a.words_stride, a.chunk_offset, a.sub_bits,
+                       books, a.symbols, sym_stride, a.q, a.q_stride, a.status, by_chunk ? 1u : 0u, AggArgs{});
     return hipGetLastError();
 }
 
@@ -806,8 +832,9 @@ static hipError_t launch_aggregate_staged(const Layout &lay, const AggArgs &a, u
 //   1026             15.5 16.2       16.9 22.0       26.6 34.2, 41.4   37 41, 57     58 59, 57 68    90 83, 88 93
 //   2198             24 27, 34       28 39, 46       43 66, 68       68 79, 87       104 82, 103 104  159 113, 158 160
 //   3907             33 28, 32 34    43 38, 43 44    70 64, 70 86    113 78, 113 133   188 132, 182 162  295 184, 293 285
-// Formats whose sums are integers go over to those from 2500 chunks on, many users from more than the device holds; the others
-// stay with up to ten users (four of 10^8 elements in [1,5,2] 234 and 265).  A table for every wavefront leaves less room in LDS.
+// Formats whose sums are integers go over to those from 2500 chunks on, more than ten users from more than the device holds; the
+// others stay with up to ten users (four of 10^8 elements in [1,5,2] 234 and 265), and up to 1400 chunks with more (1538 of
+// sixteen 78 and 77).  A table for every wavefront leaves less room in LDS.
 static uint32_t staged_waves(const Layout &lay, bool ints)
 {
     const uint32_t each = (lay.U + kStageWaves - 1) / kStageWaves;
@@ -819,7 +846,19 @@ static uint32_t staged_waves(const Layout &lay, bool ints)
     const bool few = lay.nchunks <= 256 * per_cu;
     if (lay.per_user_books) return few ? waves : 0;
     if (lay.U <= 10) return few || !ints || lay.nchunks <= 2500 ? waves : 0;
-    return few || (!ints && lay.nchunks <= 2300) ? waves : 0;
+    return few || (!ints && lay.nchunks <= 1400) ? waves : 0;
+}
+
+static hipError_t launch_average_of_one(const Layout &lay, const AggArgs &a, hipStream_t s)
+{
+    const size_t lds = decode_lds(lay);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_decode<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    ProfScope prof(K_AGGREGATE, s);
+    hipLaunchKernelGGL(k_decode<true>, dim3((uint32_t)((lay.nchunks + kDecWaves - 1) / kDecWaves)), dim3(64 * kDecWaves), lds, s, lay, a.words,
+                       a.words_stride, a.chunk_offset, a.sub_bits, a.books, static_cast<uint8_t *>(nullptr), (uint64_t)0,
+                       static_cast<float *>(nullptr), (uint64_t)0, a.status, 0u, a);
+    return hipGetLastError();
 }
 
 template <bool kGain>
@@ -827,7 +866,6 @@ static hipError_t launch_aggregate_packed(const Layout &lay, const AggArgs &a, u
 {
     if (waves <= 1) {
         const size_t lds = aggregate_lds(lay, false, kAggWaves, false);
-        if (lay.U == 1) return launch_aggregate_k(k_aggregate<1, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u, 0u, 0u);
         return launch_aggregate_places(k_aggregate<kPackUsers, kGain, false>, lay, kAggWaves, false, lds, s, a, 0u);
     }
     if (lay.U <= 2 * waves) return launch_aggregate_staged(lay, a, waves, s);
@@ -844,6 +882,7 @@ hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3
 {
     if (lay.U == 0 || lay.nchunks == 0) return hipSuccess;
     const AggArgs args = {a.words, a.words_stride, a.chunk_offset, a.sub_bits, books, a.out, a.model, (double)a.eta, a.status};
+    if (lay.U == 1) return launch_average_of_one(lay, args, s);
     if (const uint32_t w = staged_waves(lay, dec_value_is_int(lay.E) && !facts.has_gain)) return launch_aggregate_staged(lay, args, w, s);
     // A wavefront per user where 4096 are resident at a time (sixteen a CU) and more would wait: what bounds a small
     // launch is one wavefront's way through its users (eight users of 10^6 elements in [1,4,3], eight, four, two

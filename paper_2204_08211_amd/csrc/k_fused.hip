@@ -178,14 +178,28 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
 #pragma unroll
         for (uint32_t r = 0; r < 4; ++r) {
             uint32_t packed = 0;
+            uint32_t rnd[8] = {};   // the words from the vector's first element on
+            if constexpr (kSR) {
+                const uint64_t first = e0 + 4u * (v0 + 64u * r);
+                const Philox4 rw = element_random_words(first, u, seed);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) rnd[k] = rw.w[k];
+                if (e0 & 3u) {   // the same in all lanes
+                    const Philox4 more = element_random_words(first + 4u, u, seed);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) rnd[4 + k] = more.w[k];
+#pragma unroll
+                    for (int k = 0; k < 7; ++k) rnd[k] = e0 & 1u ? rnd[k + 1] : rnd[k];
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) rnd[k] = e0 & 2u ? rnd[k + 2] : rnd[k];
+                }
+            }
 #pragma unroll
             for (uint32_t j = 0; j < 4; ++j) {
                 const uint32_t i = 4u * (v0 + 64u * r) + j;
-                uint32_t rnd = 0;
-                if constexpr (kSR) rnd = element_random_words(e0 + i, u, seed).w[(e0 + i) & 3u];
                 float e;
                 const uint32_t in = i < nk ? 1u : 0u;
-                const uint32_t s = element(gs[4 * r + j], ms[4 * r + j], rnd, in, e);
+                const uint32_t s = element(gs[4 * r + j], ms[4 * r + j], rnd[j], in, e);
                 if (in) mo[i] = e;
                 packed |= (in ? s : 0u) << (8 * j);
             }
