@@ -24,7 +24,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMoWaves = 4;                 // wavefronts (chunks) per workgroup
 constexpr int kMoThreads = 64 * kMoWaves;
-constexpr int kFitThreads = 256;
 
 __device__ inline uint32_t fit_find_chunk_segment(const SegDev *segs, uint32_t nseg, uint64_t chunk)
 {
@@ -93,43 +92,51 @@ __global__ __launch_bounds__(kMoThreads) void k_moments(Layout lay, const float 
 }
 
 // beta_of_kurtosis() by the workgroup: the same bisection, kFitDepth steps at a time.  An evaluation is three
-// log-gammas, some 2 us that depend on the step before, so the midpoints of the next kFitDepth steps, whichever way
-// those turn out, are evaluated side by side: thread k takes node k of the binary tree of intervals (heap order), and
-// every thread then walks down the tree with the answers.  Midpoints and decisions are the serial bisection's, bit
-// for bit; it ends once a whole walk leaves the interval as it was, which the serial one's remaining steps would, too.
-// (One thread, 80 evaluations one after the other: k_fit_params 168 us; this way 40 us.)
+// log-gammas, which depend on the step before, so the midpoints of the next kFitDepth steps, whichever way
+// those turn out, are evaluated side by side, each log-gamma by a thread of its own: threads k, k + 256 and k + 512 take
+// those of node k of the binary tree of intervals (heap order; node 0 is the range's lower end in the first round and its upper
+// one in the second), and every thread then walks down the tree with the answers.  Midpoints, sums and
+// decisions are the serial bisection's, bit for bit; it ends once a whole walk leaves the interval as it was, which the
+// serial one's remaining steps would, too.
+// (One thread, 80 evaluations one after the other: k_fit_params 168 us; the three log-gammas one after the other in 256
+// threads 37; this way 32.)
 constexpr int kFitDepth = 8;
-static_assert(kFitThreads == 1 << kFitDepth, "a thread per node of the tree");
-__device__ inline double fit_beta_of_kurtosis(double kappa, uint32_t t, uint8_t *s_flag)
+constexpr int kFitNodes = 1 << kFitDepth;
+constexpr int kFitThreads = 3 * kFitNodes;
+struct FitGammas { double lg[3][kFitNodes]; uint8_t right[kFitNodes]; };
+__device__ inline double fit_log_gamma(uint32_t which, double b) { return lgamma((which == 0 ? 5.0 : which == 1 ? 1.0 : 3.0) / b); }
+__device__ inline double fit_beta_of_kurtosis(double kappa, uint32_t t, FitGammas *s)
 {
     if (!(kappa == kappa) || isinf(kappa)) return kBetaMin;   // the same in every thread
     const double lk = log(kappa);
-    if ((t & 63u) == 0u && t < 128u) s_flag[t >> 6] = t ? lk <= log_kurtosis_of_beta(kBetaMax) : lk >= log_kurtosis_of_beta(kBetaMin);
-    __syncthreads();
-    const bool at_min = s_flag[0], at_max = s_flag[1];
-    __syncthreads();
-    if (at_min) return kBetaMin;
-    if (at_max) return kBetaMax;
+    const uint32_t which = t / kFitNodes, node = t % kFitNodes;
     double lo = log(kBetaMin), hi = log(kBetaMax);
     for (int i = 0; i < 80; i += kFitDepth) {
-        if (t) {
+        double at_beta = i ? kBetaMax : kBetaMin;
+        if (node) {
             double a = lo, b = hi;
-            for (int l = 30 - __clz((int)t); l >= 0; --l) {   // from the bit below the leading one of t down
+            for (int l = 30 - __clz((int)node); l >= 0; --l) {   // from the bit below the leading one down
                 const double mid = 0.5 * (a + b);
-                if ((t >> l) & 1u) a = mid; else b = mid;
+                if ((node >> l) & 1u) a = mid; else b = mid;
             }
-            s_flag[t] = log_kurtosis_of_beta(exp(0.5 * (a + b))) > lk;
+            at_beta = exp(0.5 * (a + b));
         }
+        if (node || i <= kFitDepth) s->lg[which][node] = fit_log_gamma(which, at_beta);
+        __syncthreads();
+        if (i <= kFitDepth) {   // two rounds take place in any case
+            const double end = s->lg[0][0] + s->lg[1][0] - 2.0 * s->lg[2][0];
+            if (i == 0 ? lk >= end : lk <= end) return i ? kBetaMax : kBetaMin;   // the same in every thread
+        }
+        if (t < (uint32_t)kFitNodes && node) s->right[node] = s->lg[0][node] + s->lg[1][node] - 2.0 * s->lg[2][node] > lk;
         __syncthreads();
         const double lo0 = lo, hi0 = hi;
-        uint32_t node = 1;
+        uint32_t at = 1;
         for (int l = 0; l < kFitDepth; ++l) {
             const double mid = 0.5 * (lo + hi);
-            const uint32_t right = s_flag[node];
+            const uint32_t right = s->right[at];
             if (right) lo = mid; else hi = mid;
-            node = 2 * node + right;
+            at = 2 * at + right;
         }
-        __syncthreads();
         if (lo == lo0 && hi == hi0) break;
     }
     return exp(0.5 * (lo + hi));
@@ -138,25 +145,25 @@ __device__ inline double fit_beta_of_kurtosis(double kappa, uint32_t t, uint8_t 
 __global__ __launch_bounds__(kFitThreads) void k_fit_params(Layout lay, const double *__restrict__ partial,
                                                             co3_gennorm_params *__restrict__ params)
 {
-    __shared__ double s_red[4][kFitThreads];
-    __shared__ uint8_t s_flag[kFitThreads];
+    constexpr int kFold = 256;   // threads that fold the chunks' sums
+    __shared__ double s_red[4][kFold];
+    __shared__ FitGammas s_gammas;
     const uint32_t seg = blockIdx.x, u = blockIdx.y, t = threadIdx.x;
     const uint64_t cs = lay.segs[seg].chunk_start, ce = lay.segs[seg + 1].chunk_start;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    if (t < (uint32_t)kFold) {
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 8
-    for (uint64_t c = cs + t; c < ce; c += kFitThreads) {   // eight chunks' sums requested together, added in order
-        const double *p = partial + ((uint64_t)u * lay.nchunks + c) * 4;
+        for (uint64_t c = cs + t; c < ce; c += kFold) {   // eight chunks' sums requested together, added in order
+            const double *p = partial + ((uint64_t)u * lay.nchunks + c) * 4;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) a[j] += p[j];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s_red[j][t] = a[j];
-    __syncthreads();
-    for (int o = kFitThreads / 2; o > 0; o >>= 1) {
-        if (t < (uint32_t)o) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s_red[j][t] += s_red[j][t + o];
+            for (int j = 0; j < 4; ++j) a[j] += p[j];
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s_red[j][t] = a[j];
+    }
+    __syncthreads();
+    for (int o = kFold / 2; o > 0; o >>= 1) {   // a thread for every sum of a pair
+        if (t < 4u * (uint32_t)o) s_red[t / o][t % o] += s_red[t / o][t % o + o];
         __syncthreads();
     }
     co3_gennorm_params out = {0.0, 0.0, 0.0, 0.0};
@@ -171,8 +178,12 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_params(Layout lay, const do
         // a variance below 2^-40 of the mean square is rounding noise of the raw sums: constant layer
         if (m2 > ms * 9.094947017729282e-13) {
             out.kurtosis = m4 / (m2 * m2);
-            out.beta = fit_beta_of_kurtosis(out.kurtosis, t, s_flag);
-            out.alpha = sqrt(m2 / variance_factor(out.beta));
+            out.beta = fit_beta_of_kurtosis(out.kurtosis, t, &s_gammas);
+            // variance_factor(), its two log-gammas side by side
+            __syncthreads();
+            if (t == 0 || t == 64) s_gammas.lg[0][t / 64] = fit_log_gamma(t ? 1u : 2u, out.beta);
+            __syncthreads();
+            out.alpha = sqrt(m2 / exp(s_gammas.lg[0][0] - s_gammas.lg[0][1]));
         }
     }
     if (t == 0) params[(uint64_t)u * lay.nseg + seg] = out;
@@ -258,15 +269,16 @@ __global__ __launch_bounds__(kMwThreads) void k_model_weights(Layout lay, const 
 }
 
 // Exponent bias from the model, eq. (exp bias) with integer b.  The expected squared error of a candidate
-// bias is a sum of non-negative shares, one per symbol's cell, so any few shares bound it from below:
+// bias is a sum of non-negative shares, one per symbol's cell, so any few shares bound it from below; and
+// what lies in a binade is at most half its gap away from its representative, which bounds it from above:
 //   k_model_bias_bounds  per (user, layer), a workgroup per kBoundCands candidates: the shares of the zero cell and
-//                        of the two outermost cells (too coarse a set loses in the first, too narrow a one in the others)
-//   k_model_bias_ref     per (user, layer): the candidate with the smallest bound, evaluated in full; no
-//                        candidate whose bound exceeds that error can be the minimum or tie with it
-//   k_model_bias_errors  workgroup per (candidate bias, layer, user): the integral of (x - r)^2 f(x) over
-//                        every symbol's cell in closed form, folded in a fixed order -> expected squared
-//                        error of the candidate; candidates ruled out by their bound leave at once (a
-//                        handful of the 226 remain)
+//                        of the two outermost cells (too coarse a set loses in the first, too narrow a one in the others),
+//                        and, for few pairs, from the shares of the binades the least upper bound of its candidates
+//   k_model_bias_ref     for many: per (user, layer), the candidate with the smallest lower bound, evaluated in full
+//   k_model_bias_errors  err_slots() workgroups per (layer, user) take the candidates whose lower bound does not exceed that
+//                        (a handful of the 226; no other can be the minimum or tie with it): the
+//                        integral of (x - r)^2 f(x) over every symbol's cell in closed form, folded in a fixed order -> expected
+//                        squared error of the candidate
 //   k_model_bias_pick    wavefront per (user, layer): the smallest bias whose error is within kBiasTie of the
 //                        minimum (a format with many binades has a plateau of equally good biases;
 //                        the smallest has the most headroom).  No model (alpha = 0): the IEEE bias.
@@ -285,12 +297,17 @@ constexpr double kBiasPrune = 1e-6;  // margin of the bound test, far above the 
 constexpr int kErrPlaces = kMaxA + 1;               // where the cells of a block of 256 symbols meet, and the next one's
 constexpr int kErrThreads = 768;                    // 3 x 252 places for the largest alphabet of up to 8 bits
 constexpr int kErrThreadsMany = kMaxA;
-// Pairs from which a workgroup takes kErrThreadsMany: the candidates' search, some six of whose 226 workgroups a pair
-// evaluate (40 pairs: 118 us with kErrThreads, 120 with kErrThreadsMany; 96 pairs: 196 and 154), and the kernels with
+// Pairs from which a workgroup takes kErrThreadsMany: the candidates' search, some six of whose 226 workgroups a pair (as
+// they then were) evaluated (40 pairs: 118 us with kErrThreads, 120 with kErrThreadsMany; 96 pairs: 196 and 154), and the kernels with
 // one workgroup a pair, which from then on are one on every CU (the scale search of 192 pairs: 2340 and 3170 us; of
 // 384: 4390 and 4070).
+// Alphabets of up to 64 symbols have no more than 174 places and moments.
 constexpr uint64_t kErrManySearch = 40, kErrManyOne = 256;
-inline uint32_t err_threads(const Layout &lay, uint64_t many) { return (uint64_t)lay.U * lay.nseg < many ? kErrThreads : kErrThreadsMany; }
+inline uint32_t err_threads(const Layout &lay, uint64_t many)
+{
+    return (uint64_t)lay.U * lay.nseg < many && lay.A > 64u ? kErrThreads : kErrThreadsMany;
+}
+constexpr uint64_t kUpperPairs = 64;   // pairs from which the candidates are compared with one that is evaluated first
 
 // What the cells of one (mu, alpha, beta) share: per moment the log-gamma of its shape and the moment's factor.
 struct ErrModel { double lg[3], ck[3]; };
@@ -399,15 +416,23 @@ __device__ inline double err_total(double *s_red, ErrPlaces<kErrPlaces> *pl, uin
     return r;
 }
 
+// Places where a workgroup of the bounds' kernel evaluates: four a candidate and moment, and for the upper bounds, of the
+// distribution function, the ends of all binades that its candidates' sets have, on both axes.
 constexpr int kBoundCands = 16;               // candidates per workgroup, four places each ...
 constexpr int kBoundPlaces = 4 * kBoundCands; // ... and a wavefront per moment
 static_assert(kBoundPlaces == 64, "a wavefront per moment");
-__global__ __launch_bounds__(3 * kBoundPlaces) void k_model_bias_bounds(
+constexpr int kMaxEdges = (1 << 7) - 1 + kBoundCands;   // (exponent fields of more than seven bits have no candidates)
+constexpr int kBoundThreads = 3 * kBoundPlaces + 128;   // up to five exponent bits: an evaluation each
+constexpr double kProbSlack = 1e-15;          // of differences of the distribution function
+template <bool kUppers>
+__global__ __launch_bounds__(kUppers ? kBoundThreads : 3 * kBoundPlaces) void k_model_bias_bounds(
     Layout lay, const co3_gennorm_params *__restrict__ params, double *__restrict__ bounds)
 {
     __shared__ ErrModel s_em;
     __shared__ ErrPlaces<kBoundPlaces> s_pl;
     __shared__ double s_share[kBoundCands][3];
+    __shared__ double s_F[2][kUppers ? kMaxEdges : 1];      // distribution function at -2^e and 2^e
+    __shared__ double s_upper[kBoundCands];
     const uint32_t seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x;
     const uint32_t cand0 = blockIdx.x * kBoundCands;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
@@ -415,14 +440,37 @@ __global__ __launch_bounds__(3 * kBoundPlaces) void k_model_bias_bounds(
     const uint32_t ncand = (uint32_t)(kBiasMax - bias_min_supported(lay.E) + 1);
     const int bias0 = bias_min_supported(lay.E) + (int)cand0;
     const bool model = p.alpha > 0.0 && p.beta > 0.0;   // the same in every thread
+    const uint32_t binades = (1u << lay.E) - 2u, edges = binades + kBoundCands;
+    const int edge0 = 1 - (bias0 + kBoundCands - 1);    // exponent of the lowest edge
     if (model) {
         err_log_gammas(&s_em, t, p.beta);
         err_factors(&s_em, t, p.alpha);
         const uint32_t top = (((1u << lay.E) - 1u) << lay.M) - 1u;        // largest magnitude code
-        const uint32_t place = t % kBoundPlaces, which = place & 3u;      // above and below zero, before the outermost cells
-        if (cand0 + (place >> 2) < ncand)
-            err_eval(&s_pl, place, t / kBoundPlaces, err_place((which & 1u) != 0u, (which & 2u) ? (int)top - 1 : 0, lay.M, bias0 + (int)(place >> 2)),
-                     p.mu, p.alpha, p.beta, &s_em);
+        if constexpr (!kUppers) {
+            const uint32_t place = t % kBoundPlaces, which = place & 3u;      // above and below zero, before the outermost cells
+            if (cand0 + (place >> 2) < ncand)
+                err_eval(&s_pl, place, t / kBoundPlaces, err_place((which & 1u) != 0u, (which & 2u) ? (int)top - 1 : 0, lay.M, bias0 + (int)(place >> 2)),
+                         p.mu, p.alpha, p.beta, &s_em);
+        } else {
+#pragma unroll 1
+            for (uint32_t job = t; job < 3u * kBoundPlaces + 2u * edges; job += kBoundThreads) {
+                const bool cell = job < 3u * kBoundPlaces;
+                const uint32_t place = job % kBoundPlaces, which = place & 3u;    // above and below zero, before the outermost cells
+                const uint32_t edge = (job - 3u * kBoundPlaces) >> 1, plus = (job - 3u * kBoundPlaces) & 1u;
+                if (cell && cand0 + (place >> 2) >= ncand) continue;
+                const uint32_t k = cell ? job / kBoundPlaces : 0u;
+                const double x = cell ? err_place((which & 1u) != 0u, (which & 2u) ? (int)top - 1 : 0, lay.M, bias0 + (int)(place >> 2))
+                                      : (plus ? ldexp(1.0, edge0 + (int)edge) : -ldexp(1.0, edge0 + (int)edge));
+                double P, Q;
+                inc_gamma(((double)k + 1.0) / p.beta, pow(fabs(x - p.mu) / p.alpha, p.beta), s_em.lg[k], &P, &Q);
+                if (cell) {
+                    s_pl.P[k][place] = P;
+                    s_pl.Q[k][place] = Q;
+                } else {
+                    s_F[plus][edge] = x >= p.mu ? 0.5 + 0.5 * P : 0.5 * Q;
+                }
+            }
+        }
         __syncthreads();
         if (t < 3u * kBoundCands && cand0 + t / 3u < ncand) {
             const uint32_t cl = t / 3u, w = t % 3u, pc = 4u * cl;
@@ -431,8 +479,33 @@ __global__ __launch_bounds__(3 * kBoundPlaces) void k_model_bias_bounds(
         }
         __syncthreads();
     }
-    if (t < (uint32_t)kBoundCands && cand0 + t < ncand)
-        bounds[pair * kBiasSlots + cand0 + t] = model ? s_share[t][0] + s_share[t][1] + s_share[t][2] : INFINITY;
+    if (t < (uint32_t)kBoundCands) {
+        double lower = INFINITY, upper = INFINITY;
+        if (model && cand0 + t < ncand) {
+            lower = s_share[t][0] + s_share[t][1] + s_share[t][2];
+        }
+        if (kUppers && model && cand0 + t < ncand) {
+            // an element lies at most half a gap from its representative, but for those in the outermost cells
+            upper = s_share[t][1] + s_share[t][2];
+            const uint32_t e0 = (uint32_t)(kBoundCands - 1) - t;             // the edge 2^(1 - bias)
+            double half_gap = ldexp(0.5, 1 - (bias0 + (int)t) - lay.M), below = 0.0;
+            for (uint32_t f = 0; f <= binades; ++f) {
+                const double inside = s_F[1][e0 + f] - s_F[0][e0 + f];
+                upper += half_gap * half_gap * (inside - below + kProbSlack);
+                below = inside;
+                if (f) half_gap *= 2.0;
+            }
+        }
+        if (cand0 + t < ncand) bounds[pair * kBiasSlots + cand0 + t] = lower;
+        s_upper[t] = upper;
+    }
+    __syncthreads();
+    if (kUppers && t == 0) {   // behind the candidates' slots
+        double least = INFINITY;
+#pragma unroll
+        for (int i = 0; i < kBoundCands; ++i) least = s_upper[i] < least ? s_upper[i] : least;
+        bounds[pair * kBiasSlots + kBiasSlots - 1 - blockIdx.x] = least;
+    }
 }
 
 __global__ __launch_bounds__(kErrThreads) void k_model_bias_ref(Layout lay, const co3_gennorm_params *__restrict__ params,
@@ -470,26 +543,55 @@ __global__ __launch_bounds__(kErrThreads) void k_model_bias_ref(Layout lay, cons
     if (t == 0) ref[pair] = total;
 }
 
+// The candidates that are left of a pair, taken by the workgroups of the pair.  ref: the error of one, or nullptr and the least upper bounds say it.
+// As many as a plateau of equally good biases is long, a binade each, and some.  (Not a multiple of eight: the first few, which find
+// candidates, would all lie on the same dies: 384 pairs in [1,4,3] 494 us, 245 so.)
+inline uint32_t err_slots(int E) { return E < 6 ? (1u << E) + 5u : 61u; }
 __global__ __launch_bounds__(kErrThreads) void k_model_bias_errors(Layout lay, const co3_gennorm_params *__restrict__ params,
-                                                                   const double *__restrict__ bounds,
+                                                                   const double *__restrict__ bounds, uint32_t nbounds,
                                                                    const double *__restrict__ ref, double *__restrict__ errors)
 {
     __shared__ double s_red[kMaxA];
     __shared__ ErrPlaces<kErrPlaces> s_pl;
     __shared__ ErrModel s_em;
-    const uint32_t cand = blockIdx.x, seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x;
+    __shared__ uint8_t s_left[kBiasSlots];
+    __shared__ uint32_t s_count[kBiasSlots / 64];
+    const uint32_t seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x, lane = t & 63u;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
     const co3_gennorm_params p = params[pair];
     const bool model = p.alpha > 0.0 && p.beta > 0.0;
-    // uniform over the workgroup: a candidate whose lower bound lies above the reference error cannot win or tie
-    if (!model || bounds[pair * kBiasSlots + cand] > ref[pair] * (1.0 + kBiasPrune)) {
-        if (t == 0) errors[pair * kBiasSlots + cand] = INFINITY;
-        return;
+    const uint32_t ncand = (uint32_t)(kBiasMax - bias_min_supported(lay.E) + 1);
+    const double *lb = bounds + pair * kBiasSlots;
+    const double mine = t < ncand ? lb[t] : INFINITY;
+    double limit = INFINITY;
+    if (ref) {
+        limit = ref[pair];
+    } else {
+        for (uint32_t i = 0; i < nbounds; ++i) {
+            const double x = lb[kBiasSlots - 1 - i];
+            limit = x < limit ? x : limit;
+        }
     }
+    // a candidate whose lower bound lies above another's error, or upper bound, cannot win or tie
+    const bool left = model && t < ncand && !(mine > limit * (1.0 + kBiasPrune));
+    const uint64_t mask = __ballot(left);
+    if (lane == 0 && t < (uint32_t)kBiasSlots) s_count[t >> 6] = (uint32_t)__popcll(mask);
+    if (blockIdx.x == 0 && t < ncand && !left) errors[pair * kBiasSlots + t] = INFINITY;
+    __syncthreads();
+    uint32_t n = 0, rank = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+    for (uint32_t k = 0; k < (uint32_t)kBiasSlots / 64u; ++k) {
+        rank += k < (t >> 6) ? s_count[k] : 0u;
+        n += s_count[k];
+    }
+    if (left) s_left[rank] = (uint8_t)t;
+    if (blockIdx.x >= n) return;   // the same in every thread
     err_log_gammas(&s_em, t, p.beta);
     err_factors(&s_em, t, p.alpha);
-    const double total = err_total(s_red, &s_pl, t, blockDim.x, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em);
-    if (t == 0) errors[pair * kBiasSlots + cand] = total;
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const uint32_t cand = s_left[i];
+        const double total = err_total(s_red, &s_pl, t, blockDim.x, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em);
+        if (t == 0) errors[pair * kBiasSlots + cand] = total;
+    }
 }
 
 __global__ __launch_bounds__(64) void k_model_bias_pick(Layout lay, const double *__restrict__ errors,
@@ -548,12 +650,22 @@ hipError_t launch_model_bias(const Layout &lay, const co3_gennorm_params *params
     const int ncand = kBiasMax - bias_min_supported(lay.E) + 1;
     ProfScope prof(K_MODEL_BIAS, s);
     const uint64_t pairs = (uint64_t)lay.U * lay.nseg;
-    double *bounds = errors_ws + pairs * kBiasSlots, *ref = bounds + pairs * kBiasSlots;
-    hipLaunchKernelGGL(k_model_bias_bounds, dim3((uint32_t)(ncand + kBoundCands - 1) / kBoundCands, lay.nseg, lay.U),
-                       dim3(3 * kBoundPlaces), 0, s, lay, params, bounds);
-    hipLaunchKernelGGL(k_model_bias_ref, dim3(lay.nseg, lay.U), dim3(err_threads(lay, kErrManyOne)), 0, s, lay, params, bounds, ref);
-    hipLaunchKernelGGL(k_model_bias_errors, dim3((uint32_t)ncand, lay.nseg, lay.U), dim3(err_threads(lay, kErrManySearch)), 0, s, lay, params,
-                       bounds, ref, errors_ws);
+    double *bounds = errors_ws + pairs * kBiasSlots;
+    const uint32_t nbounds = (uint32_t)(ncand + kBoundCands - 1) / kBoundCands;
+    static_assert(kBiasSlots - (226 + kBoundCands - 1) / kBoundCands >= 226, "a slot for every workgroup's least upper bound behind the candidates'");
+    // Few pairs wait for a chain of kernels, many for their evaluations, which one candidate's error rules out more of than an
+    // upper bound does.  Bias search in [1,4,3] and [1,5,2], us: 8 pairs by an error 64 and 69, by upper bounds 46 and 46; 48 pairs 105
+    // and 134, 75 and 107; 96 pairs 119 and 178, 173 and 178; 384 pairs 305 and 536, 587 and 575.
+    const bool uppers = pairs < kUpperPairs;
+    double *ref = uppers ? nullptr : bounds + pairs * kBiasSlots;
+    if (uppers) {
+        hipLaunchKernelGGL(k_model_bias_bounds<true>, dim3(nbounds, lay.nseg, lay.U), dim3(kBoundThreads), 0, s, lay, params, bounds);
+    } else {
+        hipLaunchKernelGGL(k_model_bias_bounds<false>, dim3(nbounds, lay.nseg, lay.U), dim3(3 * kBoundPlaces), 0, s, lay, params, bounds);
+        hipLaunchKernelGGL(k_model_bias_ref, dim3(lay.nseg, lay.U), dim3(err_threads(lay, kErrManyOne)), 0, s, lay, params, bounds, ref);
+    }
+    hipLaunchKernelGGL(k_model_bias_errors, dim3(err_slots(lay.E), lay.nseg, lay.U), dim3(err_threads(lay, kErrManySearch)), 0, s, lay, params,
+                       bounds, nbounds, ref, errors_ws);
     hipLaunchKernelGGL(k_model_bias_pick, dim3((uint32_t)pairs), dim3(64), 0, s, lay, errors_ws, bias,
                        error);
     return hipGetLastError();
