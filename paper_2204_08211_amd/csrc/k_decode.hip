@@ -254,23 +254,25 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
         if (to_end) finish_chunk(st, ix, p.a.status);
         else wave_lds_fence();
     };
-    auto index_of = [&](uint32_t u) {
-        return read_index(lay, p.c, u, p.a.words, p.a.words_stride, p.a.chunk_offset, p.a.sub_bits);
-    };
+    auto request_of = [&](uint32_t u) { return request_index(lay, p.c, uniform(u), p.a.chunk_offset, p.a.sub_bits); };
     DecTable<kBytes> tab;
     if constexpr (kAcross) {
         const bool own = lay.per_user_books != 0;
         uint32_t *my_tab = p.smem + (own ? p.wave * tab_words : 0u);
         uint32_t *win = p.smem + front_words((own ? p.waves : 1u) * tab_words) + p.wave * window_words(lay.A);
         tab.init(lds_address(my_tab), lay.A);
+        auto user_of = [&](uint32_t i) { return u0 + (in_order ? i : p.wave + i * p.waves); };
+        IndexAhead ahead;
+        if (user_of(0) < lay.U) ahead = request_of(user_of(0));
         if (!own) {
             load(my_tab, p.a.books + p.g.book, t, 64 * p.waves);
             __syncthreads();
         }
         auto turn = [&](uint32_t i) {
-            const uint32_t u = u0 + (in_order ? i : p.wave + i * p.waves);
+            const uint32_t u = user_of(i);
             if (u >= lay.U) return;
-            const ChunkIndex ix = index_of(u);
+            const ChunkIndex ix = take_index(ahead, u, p.a.words, p.a.words_stride);
+            if (user_of(i + 1) < lay.U && i + 1 < users) ahead = request_of(user_of(i + 1));
             const BookDev *book = p.a.books + p.g.book;
             if (own) {
                 book += (uint64_t)u * lay.books_per_user;
@@ -298,11 +300,16 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
                 for (w1 = w0 + 1; w1 < kAggWaves && __builtin_amdgcn_readfirstlane(p.s_book[w1]) == b;) ++w1;
             }
             const bool mine = p.active && p.wave >= w0 && p.wave < w1;
+            IndexAhead ahead;
+            if (mine && u0 < lay.U) ahead = request_of(u0);
             auto turn = [&](uint32_t i) {
                 const uint32_t u = u0 + i;
                 if (u >= lay.U) return;
                 ChunkIndex ix;
-                if (mine) ix = index_of(u);
+                if (mine) {
+                    ix = take_index(ahead, u, p.a.words, p.a.words_stride);
+                    if (u + 1 < lay.U && i + 1 < users) ahead = request_of(u + 1);
+                }
                 const BookDev *book = p.a.books + (lay.per_user_books ? (uint64_t)u * lay.books_per_user : 0u) + b;
                 if (i == 0 || lay.per_user_books) {
                     if (i || w0) __syncthreads();   // the table before is done with
