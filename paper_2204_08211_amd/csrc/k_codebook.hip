@@ -17,6 +17,13 @@ namespace co3 {
 
 constexpr int kCbThreads = 256;
 
+// x of a lane, the same in all of them.
+__device__ inline uint64_t lane_value(uint64_t x, int lane)
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane) << 32;
+}
+
 // counts: `weights` are the sweep's kHistGlobalRep partial tables of symbol counts, one table of all codes after the
 // other; their sum is the weight and is left in `counts` (a kernel of its own for it was another 3.4 to 5 us).
 __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict__ books, int E, int M,
@@ -37,8 +44,6 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     __shared__ uint32_t cnt[65], off[65];
     __shared__ uint64_t first[65];
     __shared__ uint32_t sorted[kMaxA];
-    __shared__ uint64_t tmpw[kMaxA];      // a round's nodes in merged order: weight
-    __shared__ int tmpid[kMaxA];          // and node index
     __shared__ uint32_t wcnt[kCbThreads / 64][65];   // codes of every length per wavefront of symbols
     __shared__ uint32_t limit[32];        // a window's complement <= limit[l] (and not 0): its code has more than l bits
     __shared__ uint32_t base[65];         // a code of l bits has rank base[l] + code
@@ -92,25 +97,24 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
     // The two-queue merge in rounds.  With T the sum of the two lightest nodes alive, every internal node alive and
     // every leaf of weight <= T is taken before any node created from now on (their weights are >= T; on equal
     // weights a leaf goes before an internal node and an older internal node before a newer one).  So the merged
-    // order of those nodes — a leaf's rank is its own index plus the number of lighter internal nodes, an internal
-    // node's its own plus the number of leaves that are not heavier — pairs off two by two exactly as the serial
-    // merge would; an odd one out stays at the head of its queue.  One wavefront runs the rounds, 64 nodes at a time:
-    // the rounds of a table average n / 10 nodes, and without the other wavefronts a round needs no barrier.
+    // order of those nodes pairs off two by two exactly as the serial merge would; an odd one out stays at the head of
+    // its queue.  One wavefront runs the rounds, a pair a lane: the rounds of a table average n / 10 nodes, and without
+    // the other wavefronts a round needs no barrier.
+    // A lane finds where its pair begins in the two queues by bisection over the merged order's diagonal, a load from
+    // each queue a step, and takes the two lightest of the four nodes there: the merged order is never written down.
+    // The whole builder, us, with every node's rank looked up by one of two searches and the order kept in LDS, and so:
+    // [1,4,3] 32.2 and 28.0, [1,5,2] 28.7 and 25.4, 16 symbols 12.2 and 10.7.  (The odd one known from its lane instead of
+    // two weights read back: 28.5, 26.0, 11.2.)
     if (t < 64) {
         const uint64_t kNone = ~0ull;
         int li = 0, ii = n, made = n;   // next leaf, next internal node, next node to create
-        auto lower_bound = [&](int lo, int hi, uint64_t x) {   // first index in [lo, hi) with nw[index] >= x
-            while (lo < hi) { const int mid = (lo + hi) >> 1; if (nw[mid] < x) lo = mid + 1; else hi = mid; }
-            return lo;
-        };
-        auto upper_bound = [&](int lo, int hi, uint64_t x) {   // first index in [lo, hi) with nw[index] > x
-            while (lo < hi) { const int mid = (lo + hi) >> 1; if (nw[mid] <= x) lo = mid + 1; else hi = mid; }
-            return lo;
-        };
         bool over = err != 0;   // the weights of this table sum to 2^64 - 1 or more
         while (n >= 2 && !over && (n - li) + (made - ii) > 1) {   // the same in every lane
-            const uint64_t c0 = li < n ? nw[li] : kNone, c1 = li + 1 < n ? nw[li + 1] : kNone;
-            const uint64_t c2 = ii < made ? nw[ii] : kNone, c3 = ii + 1 < made ? nw[ii + 1] : kNone;
+            // the leaf li + t and the internal node ii + t; the lightest two of each queue are lanes 0 and 1
+            uint64_t leaf = li + t < n ? nw[li + t] : kNone;
+            const uint64_t inner = ii + t < made ? nw[ii + t] : kNone;
+            const uint64_t c0 = lane_value(leaf, 0), c1 = lane_value(leaf, 1);
+            const uint64_t c2 = lane_value(inner, 0), c3 = lane_value(inner, 1);
             // the two lightest of two sorted pairs
             const uint64_t m1 = c0 < c2 ? c0 : c2;
             const uint64_t r1 = c0 < c2 ? c1 : c0, r2 = c0 < c2 ? c2 : c3;
@@ -120,36 +124,40 @@ __global__ __launch_bounds__(kCbThreads) void k_build_books(BookDev *__restrict_
                 over = true;
                 break;
             }
-            // leaves of weight <= T: they are sorted, so counting them (lane t looks at leaf lj + t) gives the end
+            // leaves of weight <= T: they are sorted, so counting them (lane t looks at leaf lj + t) gives the end; no
+            // leaf is as heavy as what stands for none, and T is below it
             int lj = li, c;
-            do {
-                c = __popcll(__ballot(lj + t < n && nw[lj + t] <= T));
+            for (;;) {
+                c = __popcll(__ballot(leaf <= T));
                 lj += c;
-            } while (c == 64);
+                if (c < 64) break;
+                leaf = lj + t < n ? nw[lj + t] : kNone;
+            }
             const int bL = lj - li;
             const int bI = made - ii, nb = bL + bI;   // 2 <= nb <= 256: the two lightest are among them
-            for (int k = t; k < nb; k += 64) {
-                int node, r;
-                if (k < bL) {
-                    node = li + k;
-                    r = k + (lower_bound(ii, made, nw[node]) - ii);
-                } else {
-                    node = ii + (k - bL);
-                    r = (k - bL) + (upper_bound(li, lj, nw[node]) - li);
-                }
-                tmpw[r] = nw[node];
-                tmpid[r] = node;
-            }
-            pc_wave_sync_lds();
             const int npair = nb >> 1;
             bool wrapped = false;
             for (int k = t; k < npair; k += 64) {
-                const uint64_t wa = tmpw[2 * k], wb = tmpw[2 * k + 1];
+                // of the first d nodes of the merged order, i are leaves
+                const int d = 2 * k;
+                int i = d > bI ? d - bI : 0, hi = d < bL ? d : bL;
+                while (i < hi) {
+                    const int mid = (i + hi) >> 1;
+                    if (nw[li + mid] <= nw[ii + (d - 1 - mid)]) i = mid + 1; else hi = mid;
+                }
+                const int j = d - i;
+                const uint64_t l0 = i < bL ? nw[li + i] : kNone, l1 = i + 1 < bL ? nw[li + i + 1] : kNone;
+                const uint64_t i0 = j < bI ? nw[ii + j] : kNone, i1 = j + 1 < bI ? nw[ii + j + 1] : kNone;
+                const bool leaf1 = l0 <= i0;
+                const uint64_t wa = leaf1 ? l0 : i0;
+                const uint64_t ln = leaf1 ? l1 : l0, in = leaf1 ? i0 : i1;
+                const bool leaf2 = ln <= in;
+                const uint64_t wb = leaf2 ? ln : in;
                 const uint64_t sum = wa + wb;
                 wrapped |= sum < wb || sum == kNone;
                 nw[made + k] = sum;
-                parent[tmpid[2 * k]] = made + k;
-                parent[tmpid[2 * k + 1]] = made + k;
+                parent[leaf1 ? li + i : ii + j] = made + k;
+                parent[leaf2 ? li + i + leaf1 : ii + j + !leaf1] = made + k;
             }
             over = __any(wrapped);
             pc_wave_sync_lds();

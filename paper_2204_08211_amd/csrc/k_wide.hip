@@ -270,7 +270,7 @@ __global__ void k_zero_wide(uint64_t *p, uint64_t n, uint64_t *q, uint32_t nq)  
 // ---- code tables ------------------------------------------------------------------------------------------
 
 // One workgroup per table.  A is a power of two (512 .. 4096).  Dynamic LDS: node weights (2 A x 8 bytes),
-// parents (2 A x 4 bytes), the leaves' symbols (A x 2 bytes), a round's merged nodes (A x 10 bytes).  Steps: bitonic
+// parents (2 A x 4 bytes), the leaves' symbols and the symbols by rank (A x 2 bytes each).  Steps: bitonic
 // sort of the symbols by (weight, symbol) with the unused ones last; the two-queue merge in rounds of many pairs;
 // depth of every leaf; canonical order, the rank of a symbol among those of its length from wavefront ballots
 // (wavefront w owns symbols w A/16 .. (w + 1) A/16 - 1, in order).
@@ -283,12 +283,12 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
     uint64_t *nw = wb_smem;                                        // [2 A] sorted leaves, then internal nodes
     int *parent = reinterpret_cast<int *>(nw + 2 * (size_t)A);      // [2 A]
     uint16_t *leaf_sym = reinterpret_cast<uint16_t *>(parent + 2 * (size_t)A);   // [A] sorted leaf -> symbol
-    uint64_t *tmpw = reinterpret_cast<uint64_t *>(leaf_sym + A);                 // [A] a round's nodes in merged order: weight
-    uint16_t *tmpid = reinterpret_cast<uint16_t *>(tmpw + A);                    // [A] and node index
+    uint16_t *by_rank = leaf_sym + A;                                            // [A] symbols in canonical order
     __shared__ uint32_t cnt[65], off[65];
     __shared__ uint64_t first[65];
     __shared__ uint32_t wcnt[kWbWaves][65];   // symbols of each length in a wavefront's range; then running ranks
     __shared__ int err, s_n;
+    __shared__ int s_wrapped[2];   // a sum of a round wrapped, by the round's parity
     __shared__ uint32_t s_maxlen, s_bits;
     __shared__ unsigned long long s_missing;
     __shared__ uint64_t end32[33];   // codes of up to l bits lie below end32[l], left-aligned in 32 bits
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
 
     if (t < 65) { cnt[t] = 0; off[t] = 0; first[t] = 0; }
     for (uint32_t i = t; i < (uint32_t)kWbWaves * 65u; i += kWbThreads) wcnt[i / 65u][i % 65u] = 0;
-    if (t == 0) { err = 0; s_maxlen = 0; s_n = 0; s_bits = 2; s_missing = 0; end32[0] = 0; }
+    if (t == 0) { err = s_wrapped[0] = s_wrapped[1] = 0; s_maxlen = 0; s_n = 0; s_bits = 2; s_missing = 0; end32[0] = 0; }
     for (uint32_t i = t; i < 2 * A; i += kWbThreads) parent[i] = -1;
     __syncthreads();
     int active = 0;
@@ -341,56 +341,63 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
     // The two-queue merge in rounds.  With T the sum of the two lightest nodes alive, every internal node alive and
     // every leaf of weight <= T is taken before any node created from now on (their weights are >= T; on equal
     // weights a leaf goes before an internal node and an older internal node before a newer one).  So the merged
-    // order of those nodes — a leaf's rank is its own index plus the number of lighter internal nodes, an internal
-    // node's its own plus the number of leaves that are not heavier — pairs off two by two exactly as the serial
-    // merge would; an odd one out stays at the head of its queue.  Every thread keeps the queue positions itself.
+    // order of those nodes pairs off two by two exactly as the serial merge would; an odd one out stays at the head of
+    // its queue.  Every thread keeps the queue positions itself and finds its pair as the byte builder's lanes do
+    // (k_codebook.hip): one meeting of the workgroup a round.  A wrapped sum is marked in the round's own word of two, as
+    // a thread may be a round ahead of one that has yet to look.
+    // With every node's rank looked up and the merged order kept in LDS, two meetings a round: 61 us for 1024 symbols and
+    // 126 for 4096, so 50 and 114.
     {
         int li = 0, ii = nact, made = nact;   // next leaf, next internal node, next node to create
-        auto lower_bound = [&](int lo, int hi, uint64_t x) {   // first index in [lo, hi) with nw[index] >= x
-            while (lo < hi) { const int mid = (lo + hi) >> 1; if (nw[mid] < x) lo = mid + 1; else hi = mid; }
-            return lo;
-        };
-        auto upper_bound = [&](int lo, int hi, uint64_t x) {   // first index in [lo, hi) with nw[index] > x
-            while (lo < hi) { const int mid = (lo + hi) >> 1; if (nw[mid] <= x) lo = mid + 1; else hi = mid; }
-            return lo;
-        };
-        while (nact >= 2 && !err && (nact - li) + (made - ii) > 1) {   // the same in every thread
-            uint64_t c[4] = {li < nact ? nw[li] : kNone, li + 1 < nact ? nw[li + 1] : kNone,
-                             ii < made ? nw[ii] : kNone, ii + 1 < made ? nw[ii + 1] : kNone};
+        bool over = err != 0;
+        for (int round = 0; nact >= 2 && !over && (nact - li) + (made - ii) > 1; round ^= 1) {   // the same in every thread
+            const uint64_t c0 = li < nact ? nw[li] : kNone, c1 = li + 1 < nact ? nw[li + 1] : kNone;
+            const uint64_t c2 = ii < made ? nw[ii] : kNone, c3 = ii + 1 < made ? nw[ii + 1] : kNone;
+            // leaves of weight <= T, every wavefront by itself: of the 64 at equal distances, then of those between two
+            const int apart = (nact - li + 63) >> 6;
+            const int far = li + (int)lane * apart;
+            const uint64_t wide = far < nact ? nw[far] : kNone;
             // the two lightest of two sorted pairs
-            const uint64_t m1 = c[0] < c[2] ? c[0] : c[2];
-            const uint64_t r1 = c[0] < c[2] ? c[1] : c[0], r2 = c[0] < c[2] ? c[2] : c[3];
+            const uint64_t m1 = c0 < c2 ? c0 : c2;
+            const uint64_t r1 = c0 < c2 ? c1 : c0, r2 = c0 < c2 ? c2 : c3;
             const uint64_t m2 = r1 < r2 ? r1 : r2;
             const uint64_t T = m1 + m2;
             if (T < m2 || T == kNone) {   // the table's weights sum to 2^64 - 1 or more
                 if (t == 0) err = 1;
                 break;
             }
-            const int lj = upper_bound(li, nact, T);
-            const int bL = lj - li, bI = made - ii, nb = bL + bI;   // nb >= 2: the two lightest are among them
-            for (int e = (int)t; e < nb; e += kWbThreads) {
-                int node, r;
-                if (e < bL) {
-                    node = li + e;
-                    r = e + (lower_bound(ii, made, nw[node]) - ii);
-                } else {
-                    node = ii + (e - bL);
-                    r = (e - bL) + (upper_bound(li, lj, nw[node]) - li);
-                }
-                tmpw[r] = nw[node];
-                tmpid[r] = (uint16_t)node;
+            int lj = li;
+            if (const int c = __popcll(__ballot(wide <= T))) {   // leaf (c - 1) apart is among them, leaf c apart is not
+                lj += (c - 1) * apart;
+                const int near = lj + (int)lane;
+                lj += __popcll(__ballot((int)lane < apart && near < nact && nw[near] <= T));
             }
-            __syncthreads();
+            const int bL = lj - li, bI = made - ii, nb = bL + bI;   // nb >= 2: the two lightest are among them
             const int npair = nb >> 1;
             for (int k = (int)t; k < npair; k += kWbThreads) {
-                const uint64_t wa = tmpw[2 * k], wb = tmpw[2 * k + 1];
+                // of the first d nodes of the merged order, i are leaves
+                const int d = 2 * k;
+                int i = d > bI ? d - bI : 0, hi = d < bL ? d : bL;
+                while (i < hi) {
+                    const int mid = (i + hi) >> 1;
+                    if (nw[li + mid] <= nw[ii + (d - 1 - mid)]) i = mid + 1; else hi = mid;
+                }
+                const int j = d - i;
+                const uint64_t l0 = i < bL ? nw[li + i] : kNone, l1 = i + 1 < bL ? nw[li + i + 1] : kNone;
+                const uint64_t i0 = j < bI ? nw[ii + j] : kNone, i1 = j + 1 < bI ? nw[ii + j + 1] : kNone;
+                const bool leaf1 = l0 <= i0;
+                const uint64_t wa = leaf1 ? l0 : i0;
+                const uint64_t ln = leaf1 ? l1 : l0, in = leaf1 ? i0 : i1;
+                const bool leaf2 = ln <= in;
+                const uint64_t wb = leaf2 ? ln : in;
                 const uint64_t sum = wa + wb;
-                if (sum < wb || sum == kNone) err = 1;
+                if (sum < wb || sum == kNone) s_wrapped[round] = 1;
                 nw[made + k] = sum;
-                parent[tmpid[2 * k]] = made + k;
-                parent[tmpid[2 * k + 1]] = made + k;
+                parent[leaf1 ? li + i : ii + j] = made + k;
+                parent[leaf2 ? li + i + leaf1 : ii + j + !leaf1] = made + k;
             }
             __syncthreads();
+            over = s_wrapped[round] != 0;
             int next_li = lj, next_ii = made;
             if (nb & 1) {   // the heaviest of the batch stays: the last internal node unless a leaf is heavier
                 if (bI > 0 && (bL == 0 || nw[made - 1] >= nw[lj - 1])) next_ii = made - 1;
@@ -400,6 +407,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
             ii = next_ii;
             made += npair;
         }
+        if (over && t == 0) err = 1;
     }
     __syncthreads();
 
@@ -464,7 +472,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
         if (t < 32) end32[t + 1] = ((sum << 1) + cnt[t + 1]) << (31u - t);
     }
     __syncthreads();
-    // canonical order: rank among the symbols of the same length, ascending symbol (and, in tmpid, for the table below)
+    // canonical order: rank among the symbols of the same length, ascending symbol (and, in by_rank, for the table below)
     uint32_t bits = 0;
     for (uint32_t sb = 0; sb < per_wave; sb += 64) {
         const uint32_t i = sb + lane;
@@ -478,7 +486,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
                 B.code[s_i] = code;
                 if (L0 <= kWFastCodeBits) B.fast[s_i] = (L0 << kWFastCodeBits) | (uint32_t)code;
                 B.sorted[off[L0] + rank] = (uint16_t)s_i;
-                tmpid[off[L0] + rank] = (uint16_t)s_i;
+                by_rank[off[L0] + rank] = (uint16_t)s_i;
                 // mantissa bits that a code with up to ten leading ones asks of the decode table
                 const uint32_t ones = (uint32_t)__clzll((long long)~(code << (64u - L0)));   // (a 64-bit code: code itself)
                 if (ones <= 10u && ones < L0 && L0 - ones - 1u > bits) bits = L0 - ones - 1u;
@@ -504,7 +512,7 @@ __global__ __launch_bounds__(kWbThreads) void k_build_books_wide(BookWide *__res
         const uint32_t L = l + 1u;
         uint32_t e = kLenSlow;
         if (L < 32u && L <= longest)
-            e = ((uint32_t)tmpid[(off[L] + ((x >> (32u - L)) - (uint32_t)first[L])) & (A - 1u)] << 8) | L;
+            e = ((uint32_t)by_rank[(off[L] + ((x >> (32u - L)) - (uint32_t)first[L])) & (A - 1u)] << 8) | L;
         return e;
     };
     uint64_t missing = 0;   // share of the code space the table leaves to the search, in 2^-32
@@ -1228,7 +1236,7 @@ hipError_t launch_build_books_wide(BookWide *books, uint32_t nbooks, uint32_t A,
                                    uint64_t *status, hipStream_t s)
 {
     if (nbooks == 0) return hipSuccess;
-    const size_t lds = (size_t)2 * A * (sizeof(uint64_t) + sizeof(int)) + (size_t)A * (2 * sizeof(uint16_t) + sizeof(uint64_t));   // 144 KB at A = 4096
+    const size_t lds = (size_t)2 * A * (sizeof(uint64_t) + sizeof(int)) + (size_t)A * 2 * sizeof(uint16_t);   // 112 KB at A = 4096
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_build_books_wide),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

@@ -110,3 +110,31 @@ def test_rounds_are_few_on_counts_and_many_on_a_path():
     path = np.zeros(A, np.uint64); path[:40] = [1 << i for i in range(40)]
     _, r = lengths_by_rounds(path)
     assert r == 39                       # one pair per round: the serial merge
+
+
+@pytest.mark.parametrize("bL,bI", [(1, 1), (2, 0), (0, 2), (1, 0), (5, 1), (1, 6), (63, 64), (64, 65), (130, 70)])
+def test_pairs_by_the_diagonals_are_the_merged_order(bL, bI):
+    # a lane bisects the diagonal 2k of the two queues, with every index inside them, and takes the two lightest of the
+    # four nodes there: the merged order of leaves first on equal weights, and the odd one the heaviest
+    rng = np.random.default_rng(1800 + 256 * bL + bI)
+    for top in (1, 3, 1000):
+        lw, iw = sorted(rng.integers(1, top + 1, bL).tolist()), sorted(rng.integers(1, top + 1, bI).tolist())
+        want = sorted([(w, 0, i) for i, w in enumerate(lw)] + [(w, 1, j) for j, w in enumerate(iw)])
+        for k in range((bL + bI) // 2):
+            d = 2 * k
+            i, hi = max(0, d - bI), min(d, bL)
+            while i < hi:
+                mid = (i + hi) >> 1
+                assert 0 <= mid < bL and 0 <= d - 1 - mid < bI
+                if lw[mid] <= iw[d - 1 - mid]:
+                    i = mid + 1
+                else:
+                    hi = mid
+            j = d - i
+            leaf = [lw[x] if x < bL else NONE for x in (i, i + 1)]
+            inner = [iw[x] if x < bI else NONE for x in (j, j + 1)]
+            first = leaf[0] <= inner[0]
+            second = (leaf[1] if first else leaf[0]) <= (inner[0] if first else inner[1])
+            got = [(leaf[0], 0, i) if first else (inner[0], 1, j)]
+            got.append((leaf[1 if first else 0], 0, i + first) if second else (inner[0 if first else 1], 1, j + (not first)))
+            assert got == want[d:d + 2]
