@@ -841,7 +841,10 @@ static hipError_t launch_aggregate_staged(const Layout &lay, const AggArgs &a, u
 //   3907             33 28, 32 34    43 38, 43 44    70 64, 70 86    113 78, 113 133   188 132, 182 162  295 184, 293 285
 // Formats whose sums are integers go over to those from 2500 chunks on, more than ten users from more than the device holds; the
 // others stay with up to ten users (four of 10^8 elements in [1,5,2] 234 and 265), and up to 1400 chunks with more (1538 of
-// sixteen 78 and 77).  A table for every wavefront leaves less room in LDS.
+// sixteen 78 and 77).  A table for every wavefront leaves less room in LDS and is a load more before every chunk's first symbol:
+// beyond what the device holds only tables of up to 64 symbols, to 1250 chunks (of [1,2,1] and [1,3,1], this way and integer
+// sums: 1036 chunks of ten users 35 39, of eight 25 33; 1221 of ten 39 41; 1587 of ten 48 44, of eight 33 37; 1954 of ten 57 44,
+// of six 34 31).
 static uint32_t staged_waves(const Layout &lay, bool ints)
 {
     const uint32_t each = (lay.U + kStageWaves - 1) / kStageWaves;
@@ -851,7 +854,7 @@ static uint32_t staged_waves(const Layout &lay, bool ints)
     const uint64_t per_cu = 128 / pieces < 32 / waves ? 128 / pieces : 32 / waves;
     if (per_cu == 0) return 0;
     const bool few = lay.nchunks <= 256 * per_cu;
-    if (lay.per_user_books) return few ? waves : 0;
+    if (lay.per_user_books) return few || (lay.U <= 10 && lay.A <= 64u && lay.nchunks <= 1250) ? waves : 0;
     if (lay.U <= 10) return few || !ints || lay.nchunks <= 2500 ? waves : 0;
     return few || (!ints && lay.nchunks <= 1400) ? waves : 0;
 }
@@ -891,6 +894,7 @@ hipError_t launch_aggregate(const Layout &lay, const PlanFacts &facts, const co3
     const AggArgs args = {a.words, a.words_stride, a.chunk_offset, a.sub_bits, books, a.out, a.model, (double)a.eta, a.status};
     if (lay.U == 1) return launch_average_of_one(lay, args, s);
     if (const uint32_t w = staged_waves(lay, dec_value_is_int(lay.E) && !facts.has_gain)) return launch_aggregate_staged(lay, args, w, s);
+    // What staged_waves() leaves: many users, or chunks enough to fill the device.
     // A wavefront per user where 4096 are resident at a time (sixteen a CU) and more would wait: what bounds a small
     // launch is one wavefront's way through its users (eight users of 10^6 elements in [1,4,3], eight, four, two
     // wavefronts and one a chunk: 13, 18, 28 and 53 us; of 4 M elements 30, 24, 33, 53).  Beyond, a wavefront per chunk

@@ -442,3 +442,45 @@ def test_wide_average_with_a_scale(U, E, M, chunks, own):
     torch.cuda.synchronize()
     assert not buf.status.cpu().numpy()[2:].any()
     gu.assert_bits_equal(out.cpu().numpy(), want, "average")
+
+
+@pytest.mark.parametrize("U,chunks,E,M,own,gain", [
+    (1, 1, 5, 2, False, False), (1, 9, 4, 3, False, True), (1, 2051, 2, 1, True, False),                     # the decoder writes them
+    (10, 2500, 4, 3, False, False), (10, 2501, 4, 3, False, False), (11, 515, 5, 2, False, False),           # in LDS, integer sums
+    (17, 1400, 5, 2, False, False), (17, 1401, 5, 2, False, False), (32, 250, 3, 2, False, False), (33, 250, 3, 2, False, False),
+    (10, 1250, 3, 1, True, False), (10, 1251, 3, 1, True, False), (6, 1100, 5, 2, True, False), (31, 70, 4, 3, True, False)])
+def test_average_at_the_edges_of_its_rules(U, chunks, E, M, own, gain):
+    # one user, users of a chunk in one workgroup and the other forms, on both sides of where they change; a ragged chunk in
+    # front, so that the others lie at an odd offset, and one behind; two tables.  Values and sums are exact in fp64.
+    import torch
+    from paper_2204_08211_amd import binding as B
+    seg_len = [5, 4096 * max(chunks - 2, 0), 3001] if chunks > 1 else [3001]
+    d, nseg = sum(seg_len), len(seg_len)
+    rng = np.random.default_rng(U + chunks)
+    bias = rng.integers(14, 18, (U, nseg)).astype(np.int32)
+    plan = B.Plan(E=E, M=M, U=U, d=d, bias=bias, seg_len=seg_len, seg_book=[0, 1, 0][:nseg], per_user_books=own)
+    if gain:
+        inv = (2.0 ** rng.uniform(-0.5, 0.5, (U, nseg))).astype(np.float32)
+        plan.set_gain((np.float32(1.0) / inv).astype(np.float32), inv)
+    dev, stride = torch.device("cuda:0"), (d + 3) // 4 * 4
+    top = float(orc.grid(E, M, 16)[-1])
+    gen = torch.Generator(device=dev); gen.manual_seed(chunks)
+    g = torch.randn((U, stride), device=dev, generator=gen) * (top / 4)
+    m = torch.zeros_like(g)
+    books = B.co3_build_codebook(E, M, plan.num_books, None)
+    buf = B.RoundBuffers(plan, dev, max_code_len=16)
+    buf.status.zero_()
+    B.co3_encode(plan, books, g, m, m, 0.9, buf, mode=BOOK_EMPIRICAL)
+    del g
+    B.co3_decode(plan, books, buf, q=m)
+    out = torch.full((d,), float("nan"), dtype=torch.float32, device=dev)
+    model = torch.randn((d,), device=dev, generator=gen)
+    before = model.double()
+    B.co3_ps_aggregate(plan, books, buf, out, model=model, eta=0.25)
+    total = torch.zeros(d, dtype=torch.float64, device=dev)
+    for u in range(U):
+        total += m[u, :d].double()
+    mean = total * (1.0 / U)
+    assert not buf.status[2:].any()      # (the words in front count clipped values)
+    assert torch.equal(out, mean.float()) and torch.equal(model, (before - 0.25 * mean).float())
+    assert bool((out != 0).any())

@@ -1442,3 +1442,36 @@ def test_single_sweep_streaming_form(U, seg_len, seed, hist):
     gu.compare_round(gpu, ref, d, single_sweep=True)
     if hist:
         gu.assert_bits_equal(gpu["hist"], ref["hist"], "histogram")
+
+
+@pytest.mark.parametrize("U,chunks,layers,E,M", [
+    (1, 1024, 1, 3, 0), (1, 1025, 1, 3, 0),          # a user's sizes added up by the coder; by a launch of their own
+    (4, 1023, 5, 4, 3), (4, 1024, 5, 5, 2),          # a chunk a workgroup; two, with tables that change between them
+    (8, 1023, 7, 4, 3), (8, 1024, 7, 4, 3), (8, 1030, 7, 2, 1)])   # two; four; four behind the scan
+def test_coder_for_stored_symbols_at_the_edges_of_its_rules(U, chunks, layers, E, M):
+    # the streams of a code of the round's own against the single sweep's with that code held, whose words, offsets and sizes
+    # other tests compare with the oracle's; layers of odd lengths, tables that alternate
+    import torch
+    from paper_2204_08211_amd import binding as B
+    rng = np.random.default_rng(chunks + layers)
+    seg_len = [4096 * int(rng.integers(1, 4)) + 1 + k for k in range(layers - 1)]
+    left = chunks - sum((n + 4095) // 4096 for n in seg_len)
+    seg_len.append(4096 * (left - 1) + 77)
+    d = sum(seg_len)
+    bias = np.full((U, layers), 2 ** (E - 1) + 8, np.int32)
+    plan = B.Plan(E=E, M=M, U=U, d=d, bias=bias, seg_len=seg_len, seg_book=[k % 2 for k in range(layers)] if layers > 1 else [0])
+    dev, stride = torch.device("cuda:0"), (d + 3) // 4 * 4
+    gen = torch.Generator(device=dev); gen.manual_seed(chunks)
+    g = torch.randn((U, stride), device=dev, generator=gen) * (float(orc.grid(E, M, int(bias[0, 0]))[-1]) / 4)
+    m1, m2 = torch.zeros_like(g), torch.zeros_like(g)
+    books = B.co3_build_codebook(E, M, plan.num_books, None)
+    bufs = [B.RoundBuffers(plan, dev, max_code_len=32) for _ in range(2)]
+    for buf in bufs:
+        buf.status.zero_(); buf.words.zero_()
+    B.co3_encode(plan, books, g, m1, m1, 0.9, bufs[0], mode=BOOK_EMPIRICAL)
+    B.co3_encode(plan, books, g, m2, m2, 0.9, bufs[1], mode=BOOK_FIXED, single_sweep=True)
+    torch.cuda.synchronize()
+    assert torch.equal(bufs[0].status, bufs[1].status) and not bufs[0].status[2:].any()   # (the words in front count clipped values)
+    for name in ("payload_bits", "chunk_offset", "sub_bits", "words"):
+        assert torch.equal(getattr(bufs[0], name), getattr(bufs[1], name)), name
+    assert torch.equal(m1[:, :d], m2[:, :d]) and int(bufs[0].payload_bits[0]) > d
