@@ -10,11 +10,11 @@
 //   k_chunk_bits   sum of the code lengths of every chunk: a wavefront per chunk, coalesced loads, a
 //                  byte table of lengths in LDS (k_chunk_bits_hist: the same sums from the per-chunk symbol
 //                  counts the quantize sweep writes for single-layer vectors, without touching the symbols)
-//   k_scan_chunks  exclusive scan of the 32-bit-rounded chunk sizes (64-bit offsets), payload r
-//   k_pack_chunk   a wavefront per chunk, lane j owns sub-chunk j (64 elements), exactly as in the
-//                  decoder: the wavefront-level coder of pack_core.h builds the chunk's words in LDS,
-//                  which are then copied out coalesced; the lanes' bit counts are the sub-chunk index
-// Nothing in these kernels needs a workgroup barrier.
+//   k_scan_chunks  exclusive scan of the 32-bit-rounded chunk sizes (64-bit offsets), payload r; left out where a user has so
+//                  few chunks that the coder's workgroups add the sizes up themselves
+//   k_pack_chunk   four wavefronts per chunk, a thread a run of sixteen symbols: the codewords go to their place in the
+//                  chunk's words in LDS (run_coder.h), which are then copied out coalesced; the sums over four threads are
+//                  the sub-chunk index
 #include "co3_internal.h"
 #include "pack_core.h"
 #include "run_coder.h"
@@ -33,11 +33,6 @@ __device__ inline uint32_t find_chunk_segment(const SegDev *segs, uint32_t nseg,
         if (segs[mid].chunk_start <= chunk) lo = mid; else hi = mid;
     }
     return lo;
-}
-
-__device__ inline uint32_t wave_inclusive_scan(uint32_t x)
-{
-    return pc_wave_inclusive_scan(x, threadIdx.x & 63);
 }
 
 __device__ inline uint32_t wave_sum(uint32_t x)
@@ -140,7 +135,7 @@ __global__ __launch_bounds__(kPkThreads) void k_chunk_bits_hist(Layout lay, cons
 // The coder proper.  chunk_offset comes from k_scan_chunks, or (kOffsets) every workgroup adds up the sizes of its user's chunks ahead
 // of its own and writes its chunks' offsets, the last one the payload.  A workgroup takes `per_wg` consecutive chunks of a user, a team of four
 // wavefronts on each in turn: a thread loads the 16 symbols of its run at once, at any byte, those of the next chunk before
-// it codes these.  Two windows take turns; a thread clears the words that it has copied out.
+// it codes these.  (A ragged chunk's last run is loaded whole as well: the symbols' buffer ends 16 bytes behind the last row.)  Two windows take turns; a thread clears the words that it has copied out.
 // What bounds it: vector instructions, some 13 per symbol (17.5 where a lane coded 64 symbols into a row of its own and moved it).
 // Sixteen users of 25.6 M elements in [1,4,3]: 229 -> 200 us.
 template <bool kOffsets>
@@ -277,7 +272,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_chunks(uint64_t nchunks, 
         const uint64_t i = base + t;
         const uint32_t b = (i < nchunks) ? cb[i] : 0u;
         const uint32_t a = (b + 31u) & ~31u;
-        const uint32_t incl_w = wave_inclusive_scan(a);
+        const uint32_t incl_w = pc_wave_inclusive_scan(a, lane);
         const uint32_t pay = wave_sum(b);
         __syncthreads();  // previous iteration's reads of s_wave are done
         if (lane == 63) { s_wave[wave] = incl_w; s_pay[wave] = pay; }

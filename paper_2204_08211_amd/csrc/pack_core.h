@@ -1,6 +1,7 @@
 // Wavefront-level core of h_Hf (Sec. II-B (iii), Sec. IV-A (ii); Algorithm 1 line 9): the codewords of
-// one chunk (4096 symbols) concatenated MSB-first into 32-bit words.  Shared by the coder for stored
-// symbols (k_pack.hip) and the single-sweep encoder (k_fused.hip).
+// one chunk (4096 symbols) concatenated MSB-first into 32-bit words.  The streaming form of the
+// single-sweep encoder (k_fused.hip) uses it; the other forms and the coder for stored symbols give a
+// chunk to four wavefronts (run_coder.h) and take the wave operations from here.
 //
 // A wavefront owns a chunk, lane j owns sub-chunk j (64 symbols, held in 16 registers).
 //
