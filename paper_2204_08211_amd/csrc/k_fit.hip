@@ -98,18 +98,24 @@ __global__ __launch_bounds__(kMoThreads) void k_moments(Layout lay, const float 
 // one in the second), and every thread then walks down the tree with the answers.  Midpoints, sums and
 // decisions are the serial bisection's, bit for bit; it ends once a whole walk leaves the interval as it was, which the
 // serial one's remaining steps would, too.
-// (One thread, 80 evaluations one after the other: k_fit_params 168 us; the three log-gammas one after the other in 256
-// threads 37; this way 32.)
+// Two workgroups of 768 threads fit a CU up to 80 registers, which the log-gamma takes as a function of its own (inlined, its
+// constants stay in registers over the loop: 168 and spills, and one workgroup a CU).  With more pairs than CUs the
+// evaluations bound it and not their chain, and a workgroup has 256 threads, thread k all three of node k.
+// (One thread, 80 evaluations one after the other: k_fit_params 168 us; 256 threads 37; 768 32.  The whole fit of 8 pairs of
+// 20 000 elements, 256 threads and 768: 43.8 and 38.5 us; of 256 pairs 51.4 and 46.4; 257 57.1 and 61.5; 384 63 and 67; 1200 123
+// and 152; inlined, 768 threads took 58 us for 256 pairs, 90 for 384 and 198 for 1200.)
 constexpr int kFitDepth = 8;
 constexpr int kFitNodes = 1 << kFitDepth;
-constexpr int kFitThreads = 3 * kFitNodes;
+constexpr int kFitThreads = 3 * kFitNodes, kFitThreadsMany = kFitNodes;
+constexpr uint64_t kFitPairsWide = 256;   // as many as CUs
 struct FitGammas { double lg[3][kFitNodes]; uint8_t right[kFitNodes]; };
-__device__ inline double fit_log_gamma(uint32_t which, double b) { return lgamma((which == 0 ? 5.0 : which == 1 ? 1.0 : 3.0) / b); }
+__device__ __attribute__((noinline)) double fit_log_gamma(uint32_t which, double b) { return lgamma((which == 0 ? 5.0 : which == 1 ? 1.0 : 3.0) / b); }
+template <int kThreads>
 __device__ inline double fit_beta_of_kurtosis(double kappa, uint32_t t, FitGammas *s)
 {
     if (!(kappa == kappa) || isinf(kappa)) return kBetaMin;   // the same in every thread
     const double lk = log(kappa);
-    const uint32_t which = t / kFitNodes, node = t % kFitNodes;
+    const uint32_t node = t % kFitNodes;
     double lo = log(kBetaMin), hi = log(kBetaMax);
     for (int i = 0; i < 80; i += kFitDepth) {
         double at_beta = i ? kBetaMax : kBetaMin;
@@ -121,7 +127,10 @@ __device__ inline double fit_beta_of_kurtosis(double kappa, uint32_t t, FitGamma
             }
             at_beta = exp(0.5 * (a + b));
         }
-        if (node || i <= kFitDepth) s->lg[which][node] = fit_log_gamma(which, at_beta);
+        if (node || i <= kFitDepth) {
+#pragma unroll 1
+            for (uint32_t which = t / kFitNodes; which < 3u; which += kThreads / kFitNodes) s->lg[which][node] = fit_log_gamma(which, at_beta);
+        }
         __syncthreads();
         if (i <= kFitDepth) {   // two rounds take place in any case
             const double end = s->lg[0][0] + s->lg[1][0] - 2.0 * s->lg[2][0];
@@ -142,7 +151,8 @@ __device__ inline double fit_beta_of_kurtosis(double kappa, uint32_t t, FitGamma
     return exp(0.5 * (lo + hi));
 }
 
-__global__ __launch_bounds__(kFitThreads) void k_fit_params(Layout lay, const double *__restrict__ partial,
+template <int kThreads>
+__global__ __launch_bounds__(kThreads, kThreads == kFitThreads ? 6 : 7) void k_fit_params(Layout lay, const double *__restrict__ partial,
                                                             co3_gennorm_params *__restrict__ params)
 {
     constexpr int kFold = 256;   // threads that fold the chunks' sums
@@ -178,7 +188,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_params(Layout lay, const do
         // a variance below 2^-40 of the mean square is rounding noise of the raw sums: constant layer
         if (m2 > ms * 9.094947017729282e-13) {
             out.kurtosis = m4 / (m2 * m2);
-            out.beta = fit_beta_of_kurtosis(out.kurtosis, t, &s_gammas);
+            out.beta = fit_beta_of_kurtosis<kThreads>(out.kurtosis, t, &s_gammas);
             // variance_factor(), its two log-gammas side by side
             __syncthreads();
             if (t == 0 || t == 64) s_gammas.lg[0][t / 64] = fit_log_gamma(t ? 1u : 2u, out.beta);
@@ -788,7 +798,8 @@ hipError_t launch_fit(const Layout &lay, const float *g, const float *m, uint64_
         hipLaunchKernelGGL(k_moments, dim3(gx, lay.U), dim3(kMoThreads), 0, s, lay, g, m, row_stride, gamma, partial);
     }
     ProfScope prof(K_FIT, s);
-    hipLaunchKernelGGL(k_fit_params, dim3(lay.nseg, lay.U), dim3(kFitThreads), 0, s, lay, partial, params);
+    if ((uint64_t)lay.U * lay.nseg <= kFitPairsWide) hipLaunchKernelGGL(k_fit_params<kFitThreads>, dim3(lay.nseg, lay.U), dim3(kFitThreads), 0, s, lay, partial, params);
+    else hipLaunchKernelGGL(k_fit_params<kFitThreadsMany>, dim3(lay.nseg, lay.U), dim3(kFitThreadsMany), 0, s, lay, partial, params);
     return hipGetLastError();
 }
 

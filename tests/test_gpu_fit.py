@@ -137,6 +137,24 @@ def test_fit_closed_form_samples():
     assert abs(par[1, 0, 1] - 0.5 * np.sqrt(2.0 / 3.0)) < 1e-10
 
 
+@pytest.mark.parametrize("nseg", [256, 257, 400])
+def test_fit_of_as_many_pairs_as_cus_and_more(nseg):
+    # a pair's log-gammas by three threads a node of its tree, or one after the other where the pairs are more than the CUs: the
+    # fit of a layer does not depend on how many there are, bit for bit, and is the oracle's
+    rng = np.random.default_rng(90)
+    betas = rng.uniform(0.3, 6.0, 400)
+    n = 1000
+    g = np.concatenate([syn.gennorm_numpy(rng, n, b, 1e-3) for b in betas])[None, : nseg * n].astype(np.float32)
+    m = np.roll(g, 7, axis=1) * np.float32(0.25)
+    kw = dict(E=4, M=3, U=1, d=nseg * n, bias=[[16] * nseg], seg_len=[n] * nseg, seg_book=[0] * nseg)
+    _, got, _, _ = gpu_fit(kw, g, m, 0.5)
+    last = dict(kw, d=20 * n, bias=[[16] * 20], seg_len=[n] * 20, seg_book=[0] * 20)
+    tail = slice((nseg - 20) * n, nseg * n)
+    _, few, _, _ = gpu_fit(last, g[:, tail], m[:, tail], 0.5)
+    assert np.array_equal(got[:, -20:].copy().view(np.uint64), few.view(np.uint64))
+    check_params(got, fitm.fit_round(g, m, 0.5, kw["seg_len"]))
+
+
 def test_fit_is_deterministic_and_gamma_zero_ignores_memory():
     E, M, U, d = 4, 3, 3, 4096 * 7 + 11
     rng = np.random.default_rng(3)
