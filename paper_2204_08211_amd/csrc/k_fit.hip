@@ -285,8 +285,8 @@ __global__ __launch_bounds__(kMwThreads) void k_model_weights(Layout lay, const 
 //                        of the two outermost cells (too coarse a set loses in the first, too narrow a one in the others),
 //                        and, for few pairs, from the shares of the binades the least upper bound of its candidates
 //   k_model_bias_ref     for many: per (user, layer), the candidate with the smallest lower bound, evaluated in full
-//   k_model_bias_errors  err_slots() workgroups per (layer, user) take the candidates whose lower bound does not exceed that
-//                        (a handful of the 226; no other can be the minimum or tie with it): the
+//   k_model_bias_errors  err_slots() workgroups per (layer, user), or one per candidate, take those whose lower bound does not
+//                        exceed that (a handful of the 226; no other can be the minimum or tie with it): the
 //                        integral of (x - r)^2 f(x) over every symbol's cell in closed form, folded in a fixed order -> expected
 //                        squared error of the candidate
 //   k_model_bias_pick    wavefront per (user, layer): the smallest bias whose error is within kBiasTie of the
@@ -297,8 +297,8 @@ __global__ __launch_bounds__(kMwThreads) void k_model_weights(Layout lay, const 
 // thread of its own, for both cells that meet there, the moments one after the other so that a wavefront's lanes run
 // the same shape at neighbouring places; what they share, the log-gammas of the three shapes, once per workgroup.
 // For few pairs that is a chain, so a workgroup has a thread for each place and moment of 256 symbols; many pairs fill
-// the device and take four wavefronts (and nearly all workgroups of the search only find that their candidate is
-// ruled out).  us, a thread per symbol with its six integrals one after the other / eight threads per symbol, 1024 to
+// the device and take four wavefronts (in the formats in which the search has a workgroup for
+// every candidate, most only find that theirs is ruled out).  us, a thread per symbol with its six integrals one after the other / eight threads per symbol, 1024 to
 // a workgroup, every place twice / this way: the bias search of 8 pairs in [1,5,2] 324 / 109 / 75, 384 pairs in
 // [1,4,3] 862 / 990 / 347, 2400 pairs 4180 / 5740 / 1650, 384 pairs in [1,5,6] 8050 / 9800 / 3620; the scale search of 8 pairs in
 // [1,4,3] 6190 / 3630 / 2160, 2400 pairs 33 900 / 41 500 / 15 300.
@@ -311,7 +311,7 @@ constexpr int kErrThreadsMany = kMaxA;
 // they then were) evaluated (40 pairs: 118 us with kErrThreads, 120 with kErrThreadsMany; 96 pairs: 196 and 154), and the kernels with
 // one workgroup a pair, which from then on are one on every CU (the scale search of 192 pairs: 2340 and 3170 us; of
 // 384: 4390 and 4070).
-// Alphabets of up to 64 symbols have no more than 174 places and moments.
+// Alphabets of up to 64 symbols have no more than 180 places and moments ([1,5,0]).
 constexpr uint64_t kErrManySearch = 40, kErrManyOne = 256;
 inline uint32_t err_threads(const Layout &lay, uint64_t many)
 {
@@ -553,10 +553,17 @@ __global__ __launch_bounds__(kErrThreads) void k_model_bias_ref(Layout lay, cons
     if (t == 0) ref[pair] = total;
 }
 
-// The candidates that are left of a pair, taken by the workgroups of the pair.  ref: the error of one, or nullptr and the least upper bounds say it.
+// The candidates that are left of a pair, taken by the workgroups of the pair: kEach, one for each of all candidates, which leaves at
+// once where that is ruled out, or err_slots() that share those left.  ref: the error of one, or nullptr and the least upper bounds say it.
 // As many as a plateau of equally good biases is long, a binade each, and some.  (Not a multiple of eight: the first few, which find
-// candidates, would all lie on the same dies: 384 pairs in [1,4,3] 494 us, 245 so.)
+// candidates, would all lie on the same dies: 384 pairs in [1,4,3] 494 us, 245 so.)  Where the plateau is half of the candidates, or a
+// quarter with many pairs, what a workgroup does to find its own costs more than the workgroups that leave, and the loop over
+// them registers (99, four wavefronts a SIMD, and 96, five).  Bias search with 61 that
+// share and with one each, us: [1,7,0] 1 pair 55 and 38, 32 pairs 237 and 213, 384 pairs 1241 and 1239; [1,7,4] 32 pairs 1479 and 1281,
+// 96 pairs 2905 and 2613; [1,6,1] 32 pairs 163 and 174, 63 187 and 196, 64 197 and 197, 384 906 and 872.
 inline uint32_t err_slots(int E) { return E < 6 ? (1u << E) + 5u : 61u; }
+inline bool err_each(int E, uint64_t pairs) { return E > 6 || (E == 6 && pairs >= kUpperPairs); }
+template <bool kEach>
 __global__ __launch_bounds__(kErrThreads) void k_model_bias_errors(Layout lay, const co3_gennorm_params *__restrict__ params,
                                                                    const double *__restrict__ bounds, uint32_t nbounds,
                                                                    const double *__restrict__ ref, double *__restrict__ errors)
@@ -564,15 +571,14 @@ __global__ __launch_bounds__(kErrThreads) void k_model_bias_errors(Layout lay, c
     __shared__ double s_red[kMaxA];
     __shared__ ErrPlaces<kErrPlaces> s_pl;
     __shared__ ErrModel s_em;
-    __shared__ uint8_t s_left[kBiasSlots];
-    __shared__ uint32_t s_count[kBiasSlots / 64];
     const uint32_t seg = blockIdx.y, u = blockIdx.z, t = threadIdx.x, lane = t & 63u;
     const uint64_t pair = (uint64_t)u * lay.nseg + seg;
     const co3_gennorm_params p = params[pair];
     const bool model = p.alpha > 0.0 && p.beta > 0.0;
     const uint32_t ncand = (uint32_t)(kBiasMax - bias_min_supported(lay.E) + 1);
     const double *lb = bounds + pair * kBiasSlots;
-    const double mine = t < ncand ? lb[t] : INFINITY;
+    const uint32_t of = kEach ? blockIdx.x : t;   // the candidate that is compared here
+    const double mine = of < ncand ? lb[of] : INFINITY;
     double limit = INFINITY;
     if (ref) {
         limit = ref[pair];
@@ -583,24 +589,36 @@ __global__ __launch_bounds__(kErrThreads) void k_model_bias_errors(Layout lay, c
         }
     }
     // a candidate whose lower bound lies above another's error, or upper bound, cannot win or tie
-    const bool left = model && t < ncand && !(mine > limit * (1.0 + kBiasPrune));
-    const uint64_t mask = __ballot(left);
-    if (lane == 0 && t < (uint32_t)kBiasSlots) s_count[t >> 6] = (uint32_t)__popcll(mask);
-    if (blockIdx.x == 0 && t < ncand && !left) errors[pair * kBiasSlots + t] = INFINITY;
-    __syncthreads();
-    uint32_t n = 0, rank = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-    for (uint32_t k = 0; k < (uint32_t)kBiasSlots / 64u; ++k) {
-        rank += k < (t >> 6) ? s_count[k] : 0u;
-        n += s_count[k];
-    }
-    if (left) s_left[rank] = (uint8_t)t;
-    if (blockIdx.x >= n) return;   // the same in every thread
-    err_log_gammas(&s_em, t, p.beta);
-    err_factors(&s_em, t, p.alpha);
-    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
-        const uint32_t cand = s_left[i];
+    const bool left = model && of < ncand && !(mine > limit * (1.0 + kBiasPrune));
+    auto evaluate = [&](uint32_t cand) {
         const double total = err_total(s_red, &s_pl, t, blockDim.x, lay.A, lay.E, lay.M, bias_min_supported(lay.E) + (int)cand, p.mu, p.alpha, p.beta, &s_em);
         if (t == 0) errors[pair * kBiasSlots + cand] = total;
+    };
+    if constexpr (kEach) {
+        if (!left) {   // the same in every thread
+            if (t == 0) errors[pair * kBiasSlots + of] = INFINITY;
+            return;
+        }
+        err_log_gammas(&s_em, t, p.beta);
+        err_factors(&s_em, t, p.alpha);
+        evaluate(of);
+    } else {
+        __shared__ uint8_t s_left[kBiasSlots];
+        __shared__ uint32_t s_count[kBiasSlots / 64];
+        const uint64_t mask = __ballot(left);
+        if (lane == 0 && t < (uint32_t)kBiasSlots) s_count[t >> 6] = (uint32_t)__popcll(mask);
+        if (blockIdx.x == 0 && t < ncand && !left) errors[pair * kBiasSlots + t] = INFINITY;
+        __syncthreads();
+        uint32_t n = 0, rank = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+        for (uint32_t k = 0; k < (uint32_t)kBiasSlots / 64u; ++k) {
+            rank += k < (t >> 6) ? s_count[k] : 0u;
+            n += s_count[k];
+        }
+        if (left) s_left[rank] = (uint8_t)t;
+        if (blockIdx.x >= n) return;   // the same in every thread
+        err_log_gammas(&s_em, t, p.beta);
+        err_factors(&s_em, t, p.alpha);
+        for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) evaluate(s_left[i]);
     }
 }
 
@@ -674,8 +692,9 @@ hipError_t launch_model_bias(const Layout &lay, const co3_gennorm_params *params
         hipLaunchKernelGGL(k_model_bias_bounds<false>, dim3(nbounds, lay.nseg, lay.U), dim3(3 * kBoundPlaces), 0, s, lay, params, bounds);
         hipLaunchKernelGGL(k_model_bias_ref, dim3(lay.nseg, lay.U), dim3(err_threads(lay, kErrManyOne)), 0, s, lay, params, bounds, ref);
     }
-    hipLaunchKernelGGL(k_model_bias_errors, dim3(err_slots(lay.E), lay.nseg, lay.U), dim3(err_threads(lay, kErrManySearch)), 0, s, lay, params,
-                       bounds, nbounds, ref, errors_ws);
+    const bool each = err_each(lay.E, pairs);
+    hipLaunchKernelGGL(each ? k_model_bias_errors<true> : k_model_bias_errors<false>, dim3(each ? (uint32_t)ncand : err_slots(lay.E), lay.nseg, lay.U),
+                       dim3(err_threads(lay, kErrManySearch)), 0, s, lay, params, bounds, nbounds, ref, errors_ws);
     hipLaunchKernelGGL(k_model_bias_pick, dim3((uint32_t)pairs), dim3(64), 0, s, lay, errors_ws, bias,
                        error);
     return hipGetLastError();

@@ -366,9 +366,11 @@ def test_real_valued_scale_on_the_device_and_a_round_with_it(E, M):
 
 
 @pytest.mark.parametrize("E,M,U,nseg", [(2, 0, 3, 13), (2, 0, 2, 20), (7, 0, 8, 5), (6, 1, 1, 7), (4, 3, 16, 17), (4, 4, 4, 11), (5, 6, 2, 3),
-                                        (3, 8, 8, 33)])
+                                        (3, 8, 8, 33), (4, 1, 9, 7), (5, 2, 8, 8), (6, 1, 9, 7), (6, 1, 8, 8), (7, 0, 9, 7), (7, 2, 13, 5)])
 def test_bias_and_scale_search_of_few_and_many_pairs(E, M, U, nseg):
-    # the searches' workgroups shrink with the number of (user, layer) pairs (39 and 40; below and above 256): every pair's
+    # the searches' workgroups shrink with the number of (user, layer) pairs (39 and 40; below and above 256), and from 64 on
+    # candidates are compared with another's error instead of an upper bound, in formats of six exponent bits by a workgroup
+    # each, as in formats of seven at any number: every pair's
     # result is, bit for bit, that of a plan with this pair alone, and the host routine's; the smallest alphabet, those
     # with the most cells in one block of 256 symbols, and those of several blocks; means on either side, in a cell's
     # middle and where two cells meet, and pairs without a model
