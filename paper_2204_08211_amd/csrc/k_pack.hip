@@ -45,21 +45,50 @@ __device__ inline uint32_t wave_sum(uint32_t x)
 // Where chunk c of user u lies: first symbol byte (within the symbol buffer), element count, code table.
 struct PkChunk {
     uint64_t byte0;
+    uint64_t left;   // elements from there to the layer's end
     uint32_t n;
     uint32_t book;
+    uint32_t seg;
 };
+
+__device__ inline PkChunk pk_layer_chunk(const Layout &lay, uint32_t seg, const SegDev &sd, uint64_t first, uint32_t u, uint64_t sym_stride)
+{
+    // the same in all lanes of a wavefront, and kept so: k_pack_chunk has no vector registers to spare
+    auto scalar = [](uint64_t x) {
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
+               (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32;
+    };
+    PkChunk k;
+    k.byte0 = scalar((uint64_t)u * sym_stride + sd.offset + first);
+    k.left = scalar(sd.length - first);
+    k.n = k.left < (uint64_t)kChunk ? (uint32_t)k.left : (uint32_t)kChunk;
+    k.book = (uint32_t)__builtin_amdgcn_readfirstlane((int)((lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book));
+    k.seg = (uint32_t)__builtin_amdgcn_readfirstlane((int)seg);
+    return k;
+}
 
 __device__ inline PkChunk pk_chunk(const Layout &lay, uint64_t c, uint32_t u, uint64_t sym_stride)
 {
     const uint32_t seg = find_chunk_segment(lay.segs, lay.nseg, c);
-    const SegDev sd = lay.segs[seg];
-    const uint64_t e0 = sd.offset + (c - sd.chunk_start) * kChunk;
-    const uint64_t left = sd.offset + sd.length - e0;
-    PkChunk k;
-    k.byte0 = (uint64_t)u * sym_stride + e0;
-    k.n = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
-    k.book = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
-    return k;
+    const SegDev sd = load_segment(lay.segs + seg);
+    return pk_layer_chunk(lay, seg, sd, (c - sd.chunk_start) * kChunk, u, sym_stride);
+}
+
+// The user's chunk behind k, of which there is one; only where k ends its layer is a layer's entry read.  (Searched for with every
+// chunk, three loads that the next symbols' waited for: k_pack_chunk of ten users of 8 M elements in [1,3,0] in one layer 39 us,
+// in three at odd elements 48; so 36.5 and 39.)
+__device__ inline void pk_next_chunk(PkChunk &k, const Layout &lay, uint32_t u, uint64_t sym_stride)
+{
+    if (k.left > (uint64_t)kChunk) {
+        k.byte0 += kChunk;
+        k.left -= kChunk;
+        k.n = k.left < (uint64_t)kChunk ? (uint32_t)k.left : (uint32_t)kChunk;
+        return;
+    }
+    SegDev sd;
+    uint32_t seg = k.seg;
+    do sd = load_segment(lay.segs + ++seg); while (sd.length == 0);
+    k = pk_layer_chunk(lay, seg, sd, 0, u, sym_stride);
 }
 
 // chunk_bits[u][c] = sum of the code lengths of the chunk's symbols (symbols without a code add nothing;
@@ -188,6 +217,8 @@ __global__ __launch_bounds__(kPkThreads, 8) void k_pack_chunk(
             ahead += s_ahead[j];
             payload += s_payload[j];
         }
+        ahead = (uint32_t)__builtin_amdgcn_readfirstlane((int)ahead);
+        payload = (uint32_t)__builtin_amdgcn_readfirstlane((int)payload);
     }
     uint32_t book = ~0u;
     for (uint32_t i = 0; i < n; ++i) {
@@ -206,7 +237,7 @@ __global__ __launch_bounds__(kPkThreads, 8) void k_pack_chunk(
 #pragma unroll
         for (int j = 0; j < 4; ++j) run.w[j] = next[j];
         if (i + 1 < n) {
-            k = pk_chunk(lay, c0 + i + 1, u, sym_stride);
+            pk_next_chunk(k, lay, u, sym_stride);
             next = request(k);
         }
         uint64_t off_words = 0;
@@ -222,6 +253,7 @@ __global__ __launch_bounds__(kPkThreads, 8) void k_pack_chunk(
             base += j < part ? share[j] : 0u;
             bits += share[j];
         }
+        bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)bits);
         const uint32_t excl = base + run.excl, nwords = (bits + 31u) >> 5;
         if constexpr (kOffsets) {
             off_words = ahead >> 5;

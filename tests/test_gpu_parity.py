@@ -1475,3 +1475,41 @@ def test_coder_for_stored_symbols_at_the_edges_of_its_rules(U, chunks, layers, E
     for name in ("payload_bits", "chunk_offset", "sub_bits", "words"):
         assert torch.equal(getattr(bufs[0], name), getattr(bufs[1], name)), name
     assert torch.equal(m1[:, :d], m2[:, :d]) and int(bufs[0].payload_bits[0]) > d
+
+
+@pytest.mark.parametrize("U,chunks", [(3, 1024), (4, 1024), (4, 1030), (8, 1024), (8, 1030)])   # a chunk a workgroup, two, four
+@pytest.mark.parametrize("code", ["long", "dense"])
+def test_coder_for_stored_symbols_over_many_layers(U, chunks, code):
+    # against the oracle, offsets by the coder's workgroups (up to 1024 chunks a user) and by a launch of their own: a workgroup
+    # goes from one layer to the next, over empty ones and ends off the 16-byte grid; tables that change between its chunks; runs
+    # coded symbol by symbol, and chunks of several windows while the other window holds the chunk before
+    E, M, A = 4, 1, 64
+    rng = np.random.default_rng(2600 + U + chunks)
+    seg_len, left = [], chunks
+    while left:
+        n = int(rng.choice([0, rng.integers(1, 60), 4096 + rng.integers(0, 9), 8192 + rng.integers(1, 70)], p=[0.1, 0.7, 0.15, 0.05]))
+        if (n + 4095) // 4096 <= left:
+            seg_len.append(n)
+            left -= (n + 4095) // 4096
+    d, n = sum(seg_len), len(seg_len)
+    bias, nm = 16, orc.num_magnitudes(E, M)
+    emit = np.array([s for s in range(A) if (s & 31) < nm and s != 32])
+    w = np.zeros((2, A), np.uint64)
+    w[0, emit] = 1                          # layers of about five bits a symbol in between
+    if code == "long":
+        k = np.minimum(rng.geometric(0.35, (U, d)) - 1, nm - 1)
+        w[1, emit] = [1 << max(0, 60 - (int(s) & 31) * 2 - (int(s) >> 5)) for s in emit]
+    else:
+        k = rng.integers(0, 8, (U, d))
+        few = [int(s) for s in emit if (int(s) & 31) < 8]
+        rest = [int(s) for s in emit if int(s) not in few]
+        w[1, few] = 1
+        w[1, rest] = [1 << (5 + i) for i in range(len(rest))]
+    g = (orc.grid(E, M, bias)[k] * rng.choice([-1.0, 1.0], (U, d))).astype(np.float32)
+    m = np.zeros_like(g)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias] * n] * U, seg_len=seg_len, seg_book=[int(x) for x in rng.integers(0, 2, n)])
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=w)
+    used = ref["lens"][1][np.flatnonzero(ref["hist"][1])]
+    assert used.max() > 24 if code == "long" else used.min() >= 33, used
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w, max_code_len=64)
+    gu.compare_round(gpu, ref, d)
