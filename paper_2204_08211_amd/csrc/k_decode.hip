@@ -262,8 +262,11 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
         uint32_t *win = p.smem + front_words((own ? p.waves : 1u) * tab_words) + p.wave * window_words(lay.A);
         tab.init(lds_address(my_tab), lay.A);
         auto user_of = [&](uint32_t i) { return u0 + (in_order ? i : p.wave + i * p.waves); };
+        // ahead of the user before; not where there is none, for the table's first words come behind what is asked for before them
+        // (the average of two users, one a wavefront, in [1,5,2]: 11.65 us ahead of the table, 11.55 behind it, 11.4 with the user)
+        constexpr bool kAhead = kUsers != 1;
         IndexAhead ahead;
-        if (user_of(0) < lay.U) ahead = request_of(user_of(0));
+        if (kAhead && user_of(0) < lay.U) ahead = request_of(user_of(0));
         if (!own) {
             load(my_tab, p.a.books + p.g.book, t, 64 * p.waves);
             __syncthreads();
@@ -271,8 +274,9 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
         auto turn = [&](uint32_t i) {
             const uint32_t u = user_of(i);
             if (u >= lay.U) return;
-            const ChunkIndex ix = take_index(ahead, u, p.a.words, p.a.words_stride);
-            if (user_of(i + 1) < lay.U && i + 1 < users) ahead = request_of(user_of(i + 1));
+            const ChunkIndex ix = kAhead ? take_index(ahead, u, p.a.words, p.a.words_stride)
+                                         : read_index(lay, p.c, u, p.a.words, p.a.words_stride, p.a.chunk_offset, p.a.sub_bits);
+            if (kAhead && user_of(i + 1) < lay.U && i + 1 < users) ahead = request_of(user_of(i + 1));
             const BookDev *book = p.a.books + p.g.book;
             if (own) {
                 book += (uint64_t)u * lay.books_per_user;
