@@ -565,10 +565,11 @@ __device__ inline void aggregate_spread(const AggPart &p, const StreamPlaces &pl
     }
 }
 
-// Users whose symbols meet in LDS at most: two a wavefront, 5 KB each.  (Four a wavefront: sixteen users of 12 M elements in
-// [1,5,2], a round 600 us from the sums, 794 this way.)
-constexpr uint32_t kStageWaves = 16, kStageUsers = 2 * kStageWaves;
+// Users whose symbols meet in LDS at most: two a wavefront, 5 KB each, as many as a CU's 160 KB hold.  (Four a wavefront: sixteen
+// users of 12 M elements in [1,5,2], a round 600 us from the sums, 794 this way.)
+constexpr uint32_t kStageWaves = 16, kStageUsers = 31;
 __host__ __device__ constexpr uint32_t stage_bytes(uint32_t U) { return 4u * U * kStageWords + kStageUsers * (uint32_t)(sizeof(double) + sizeof(float)); }
+static_assert(kStageUsers <= 2 * kStageWaves && stage_bytes(kStageUsers) <= 160 * 1024, "a turn, and a CU");
 // The same sums where the workgroup's wavefronts decode all users in one turn: the symbols meet in LDS, an eighth of what
 // the fp64 sums would be, and every thread adds up its elements in the users' order, where the sums would be added up by
 // one wavefront after the other (the others at barriers).  A small launch is one workgroup's way: a round of three users of
@@ -834,33 +835,47 @@ static hipError_t launch_aggregate_staged(const Layout &lay, const AggArgs &a, u
 }
 
 // Wavefronts of a workgroup that takes all users of a chunk in one turn, one each or two, where that is the better way (else 0).  A launch
-// of few chunks is a workgroup's way: one turn of decoding, and sums by all threads.  us, this way and the others, formats of
-// four and of five exponent bits:
-//   chunks a user    2 users         4               8               10              16              24
-//   5                -               10.2 11.7       10.8 12.3       11.6 16.6       13.4 17.8       19.7 23.3, 19.7 29.2
-//   245              11.4 12.9       10.7 11.9       11.2 12.6       12.5 16.7       13.7 18.0       20.4 24.3, 20.5 29.3
-//   367              12.4 13.7       11.5 12.9       13.7 14.7       16.9 19.0       23.9 21.5, 24.2 32.6   37.4 28.9, 37.6 38.6
-//   1026             15.5 16.2       16.9 22.0       26.6 34.2, 41.4   37 41, 57     58 59, 57 68    90 83, 88 93
-//   2198             24 27, 34       28 39, 46       43 66, 68       68 79, 87       104 82, 103 104  159 113, 158 160
-//   3907             33 28, 32 34    43 38, 43 44    70 64, 70 86    113 78, 113 133   188 132, 182 162  295 184, 293 285
-// Formats whose sums are integers go over to those from 2500 chunks on, more than ten users from more than the device holds; the
-// others stay with up to ten users (four of 10^8 elements in [1,5,2] 234 and 265), and up to 1400 chunks with more (1538 of
-// sixteen 78 and 77).  A table for every wavefront leaves less room in LDS and is a load more before every chunk's first symbol:
-// beyond what the device holds only tables of up to 64 symbols, to 1250 chunks (of [1,2,1] and [1,3,1], this way and integer
+// of few chunks is a workgroup's way: one turn of decoding, and sums by all threads.  Beyond, it takes what the busiest CU does, a
+// workgroup for every 256 chunks ("rounds"); nine to twelve wavefronts cost what twelve do, as one SIMD has three of them, and of
+// thirteen and more a CU was seen to hold one workgroup, not two.  us in [1,4,3], this way and integer sums (launch_aggregate(): eight
+// wavefronts a chunk up to 512 chunks, four to 1024, two to 2048, then one; each best at the end of its range, where its launch just
+// fits the device):
+//   rounds       1      2      3      4         5      6      7      8      9
+//   8 users    11 12  14 15  18 21  24 23     28 36  32 39  37 58  41 60  45 67
+//   10 users   12 17  17 20  25 27  30-34 29  38 42  47 46  53 68  60 71  70 80
+//   12 users   12 17  18 20  26 27  31 31     39 48  45 52  51 78  58 82  64 93
+//   14 users   14 18  24 22  35 33  47 37     57 53  68 58
+// Tables of up to 64 symbols leave room in LDS for all workgroups of two wavefronts to 2048 chunks ([1,2,1], 6 to 8 rounds: 8 users
+// 29 36, 34 36, 37 38; 9 users 37-40 41, 43 42, 48-52 43; 10 users 42-46 42, 49 43, 54-59 44).  The sums of other formats are
+// left for more than twelve users where a workgroup of them takes sixteen in eight wavefronts and two such fit a CU (two rounds of
+// 13 to 15 users, [1,5,2]: 24 22), at four rounds (16 users 50 48) and beyond 1280 or 1400 chunks.
+// A table for every wavefront leaves less room in LDS and is a load more before every chunk's first symbol: beyond what the
+// device holds only tables of up to 64 symbols, to 1250 chunks (of [1,2,1] and [1,3,1], this way and integer
 // sums: 1036 chunks of ten users 35 39, of eight 25 33; 1221 of ten 39 41; 1587 of ten 48 44, of eight 33 37; 1954 of ten 57 44,
 // of six 34 31).
 static uint32_t staged_waves(const Layout &lay, bool ints)
 {
+    if (lay.U < 2 || lay.U > kStageUsers) return 0;
     const uint32_t each = (lay.U + kStageWaves - 1) / kStageWaves;
-    if (lay.U < 2 || each > 2) return 0;
     const uint32_t waves = (lay.U + each - 1) / each;
     const uint64_t pieces = (staged_lds(lay, waves) + 1279) / 1280;   // LDS is given out in pieces, 128 of them
-    const uint64_t per_cu = 128 / pieces < 32 / waves ? 128 / pieces : 32 / waves;
+    const uint64_t per_cu = 128 / pieces < 24 / waves ? 128 / pieces : 24 / waves;
     if (per_cu == 0) return 0;
-    const bool few = lay.nchunks <= 256 * per_cu;
-    if (lay.per_user_books) return few || (lay.U <= 10 && lay.A <= 64u && lay.nchunks <= 1250) ? waves : 0;
-    if (lay.U <= 10) return few || !ints || lay.nchunks <= 2500 ? waves : 0;
-    return few || (!ints && lay.nchunks <= 1400) ? waves : 0;
+    const uint64_t rounds = (lay.nchunks + 255) / 256;   // workgroups of the busiest CU
+    const bool few = rounds <= per_cu, small = lay.A <= 64u;
+    if (lay.per_user_books && !few && !(lay.U <= 10 && small && lay.nchunks <= 1250)) return 0;
+    if (lay.per_user_books && (few || !ints)) return waves;
+    if (ints) {
+        if (lay.U > 10) return few ? waves : 0;
+        if (lay.nchunks > 2500 || (lay.U > 8 && rounds > 9)) return 0;
+        if (lay.U > 6 && rounds == 4) return 0;
+        if (lay.U > 4 && small && rounds == 8) return 0;
+        if (lay.U > 8 && (small ? rounds == 7 || (lay.U > 9 && rounds == 6) : rounds == 6)) return 0;
+        return waves;
+    }
+    if (lay.U <= 12) return lay.U <= 10 || lay.nchunks <= 1400 ? waves : 0;
+    if (rounds == 2) return lay.U > 15 ? waves : 0;
+    return rounds != 4 && lay.nchunks <= (lay.U <= 16 ? 1400u : 1280u) ? waves : 0;
 }
 
 static hipError_t launch_average_of_one(const Layout &lay, const AggArgs &a, hipStream_t s)
