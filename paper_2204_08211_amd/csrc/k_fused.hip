@@ -733,20 +733,39 @@ __global__ void k_zero_fused(uint64_t *p, uint64_t n, uint64_t *q, uint64_t nq)
 }
 
 // Which form.  Small: a chunk and one team a workgroup.  A user has one ticket counter, whose atomics take turns (some 15 ns
-// each), and one chain of look-back entries, here one a chunk, so it is for launches that are one workgroup's way: encode of
-// eight users of 100 000 elements 13.7 us, in the next form 15.2; of 300 000 18.4 and 18.0; of 650 000 31 and 25.5; of one user of
-// 3.1 M 31 and 20.  Teams: four chunks a workgroup, a team each.  All of a chunk's vectors are requested at once, so a launch of
+// each), and one chain of look-back entries, here one a chunk, so it is for launches that are one workgroup's way.  The next form is
+// best while no CU has two of its workgroups.  Encode in this form and in that, us, by groups of four chunks:
+//   groups          96         150        200        256        280        320        350
+//   4 users      14.9 14.6  19 16      23 18      28 20      31 24      33 26      36 26
+//   8            14.3 14.2  18 16      22 17      26 19      28 24      32 25      33 26
+//   16           13.6 14.2  16.1 15.6  18 17      22 19      23.6 24.4  26.2 25.3  28 26
+//   24           13.8 14.0  15.6 14.8  17 16      20 18      22 23      23.3 23.2  25.6 24.2
+//   off the grid of 16 bytes
+//   8            14.8 16.0  18.6 17.8  22 18      26 21      29 26      32 27      34 29
+//   16           13.6 16.6  16.8 16.9  18.8 18.9  23 21      24 28      27.0 27.4  28.5 29.3
+//   stochastic conversion
+//   8            15.6 18.4  18.4 20.5  22 21      26 22      28.6 28.3  31 30      34 30
+//   16           15.4 19.8  17.3 20.4  19 20      23.4 22.5  24.6 28.5  27 30      29 30
+//   24           15.6 18.5  17.8 20.1  19 20      20.6 20.5  22.5 27.4  24 28      26 29
+// (one user of 56 groups 13.4 and 13.6, of 80 16.6 and 14.6, of 190 31 and 18.)
+// Teams: four chunks a workgroup, a team each.  All of a chunk's vectors are requested at once, so a launch of
 // few workgroups is short and chunks off the 16-byte grid cost nothing more: eight users of 10^6 elements, in this form and in the
 // streaming form, 30 and 49 us; one of 8 M 32 and 48; sixteen of 2 M 89 and 107; eight of 6 M 132 and 143; sixteen of
-// 6.4 M 260 and 260; of 12 M 466 and 462; of 25.6 M 966 and 942, in three layers at odd elements 1048 and 1076; eight of 138 M so
-// 2635 and 2718.  The stochastic conversion, teams and streaming: sixteen users of 2 M elements 99 and 106 us, of 6.4 M 289 and 271.
+// 6.4 M 260 and 260; of 12 M 466 and 462; of 25.6 M 966 and 942; with a third of the chunks off the grid, of 8 M 333 and 382, of 12 M
+// 483 and 560.  With symbol counts the teams are ahead at every size with layers off the grid (sixteen users of 6.5 M 294 and 303,
+// of 28 M 1170 and 1206).  The stochastic conversion, teams and streaming: sixteen users of 2 M elements 99 and 106 us, of 6.4 M 289 and 271.
 enum class FusedForm { kSmall, kTeams, kStream };
-constexpr uint64_t kFuSmallLine = 960, kFuSmallLineStochastic = 1650;     // in groups of kFuCpb chunks and groups per user
+// In groups of kFuCpb chunks and groups per user: 2 groups + 3 of a user's up to a workgroup of teams for every CU, groups + 5 of a
+// user's beyond, where a user's counter is what the small form waits for; later off the grid.
+constexpr uint64_t kFuSmallLine = 280, kFuSmallLineStochastic = 460;
+constexpr uint64_t kFuSmallLineBeyond = 400, kFuSmallLineBeyondStochastic = 475, kFuSmallLineOff = 60;
 constexpr uint64_t kFuStreamLine = 7000, kFuStreamLineStochastic = 4000;   // in groups
 static FusedForm fused_form(const Layout &lay, bool stochastic)
 {
-    const uint64_t per_user = (lay.nchunks + kFuCpb - 1) / kFuCpb, groups = (uint64_t)lay.U * per_user;
-    if (2 * groups + 3 * per_user < (stochastic ? kFuSmallLineStochastic : kFuSmallLine)) return FusedForm::kSmall;
+    const uint64_t per_user = (lay.nchunks + kFuCpb - 1) / kFuCpb, groups = (uint64_t)lay.U * per_user, off = lay.vec_aligned ? 0 : kFuSmallLineOff;
+    const bool small = groups <= 256 ? 2 * groups + 3 * per_user < (stochastic ? kFuSmallLineStochastic : kFuSmallLine) + off
+                                     : groups + 5 * per_user < (stochastic ? kFuSmallLineBeyondStochastic : kFuSmallLineBeyond) + off;
+    if (small) return FusedForm::kSmall;
     if (stochastic) return groups < kFuStreamLineStochastic ? FusedForm::kTeams : FusedForm::kStream;
     return groups < kFuStreamLine || !lay.vec_aligned ? FusedForm::kTeams : FusedForm::kStream;
 }
@@ -757,7 +776,8 @@ static uint64_t fused_chunks_per_workgroup(const Layout &lay, bool stochastic)
 
 size_t fused_workspace_bytes(const Layout &lay)
 {
-    static_assert(kFuSmallLineStochastic >= kFuSmallLine, "a plan's workspace serves both conversions");
+    static_assert(kFuSmallLineStochastic >= kFuSmallLine && kFuSmallLineBeyondStochastic >= kFuSmallLineBeyond,
+                  "a plan's workspace serves both conversions");
     const uint64_t cpb = fused_chunks_per_workgroup(lay, true);
     const uint64_t nblk = (lay.nchunks + cpb - 1) / cpb;
     // the look-back entries and a ticket counter (one 64-bit slot per user), the partial symbol-count tables of the

@@ -1293,11 +1293,14 @@ def test_wide_coder_runs_of_layers_under_one_table(U, per_user):
     gu.compare_round(gpu, ref, d)
 
 
-@pytest.mark.parametrize("U,groups,seed,hist,small", [(1, 191, None, False, True), (1, 192, None, True, False), (1, 329, 5, False, True),
-                                                      (1, 330, 5, False, False), (3, 106, None, True, True), (3, 107, None, False, False)])
+@pytest.mark.parametrize("U,groups,seed,hist,small", [(1, 55, None, False, True), (1, 56, None, True, False), (1, 91, 5, False, True),
+                                                      (1, 92, 5, False, False), (3, 31, None, True, True), (3, 32, None, False, False),
+                                                      (3, 51, 5, True, True), (3, 52, 5, True, False),
+                                                      (16, 19, None, True, True), (16, 20, None, False, False), (16, 22, 5, False, True),
+                                                      (16, 23, 5, True, False)])
 def test_single_sweep_on_both_sides_of_the_forms_line(U, groups, seed, hist, small):
     # `groups` of four chunks a user: the last size of the small form and the first of the large one, for both
-    # conversions; a user's ticket counter says how many workgroups took it
+    # conversions, up to as many groups as CUs and beyond; a user's ticket counter says how many workgroups took it
     E, M = 3, 2
     d = groups * 4 * 4096 - 4096 - 37          # the last group has three chunks, the last chunk is ragged
     rng = np.random.default_rng(2000 + groups)
@@ -1386,7 +1389,7 @@ def test_wide_single_sweep_bounded_wait_gives_up():
     assert np.array_equal(gpu["chunk_offset"][written], ref["chunk_offset"][written])
 
 
-@pytest.mark.parametrize("U,seg_len", [(3, [4096 * 2 + 5]), (240, [3, 4096, 2, 4098, 1, 4097])], ids=["small", "teams"])
+@pytest.mark.parametrize("U,seg_len", [(3, [4096 * 2 + 5]), (300, [3, 4096, 2, 4098, 1, 4097])], ids=["small", "teams"])
 @pytest.mark.parametrize("code", ["near", "long", "dense"])
 @pytest.mark.parametrize("seed", [None, 17])
 def test_single_sweep_runs_of_symbols(U, seg_len, code, seed):
@@ -1420,13 +1423,19 @@ def test_single_sweep_runs_of_symbols(U, seg_len, code, seed):
     ref = gu.oracle_round(kw, g, m, 0.9, weights=w[None, :], stochastic_seed=seed)
     used = ref["lens"].reshape(-1)[np.flatnonzero(ref["hist"].reshape(-1))]
     assert {"near": used.max() <= 8, "long": used.max() > 24, "dense": used.min() >= 33}[code], used
-    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w[None, :], single_sweep=True, stochastic_seed=seed, max_code_len=64)
+    gpu, (plan, _, buf, _, _) = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w[None, :], single_sweep=True, stochastic_seed=seed,
+                                             max_code_len=64)
     gu.compare_round(gpu, ref, d, single_sweep=True)
+    skip = (-buf.workspace.data_ptr()) % 256   # the first user's ticket counter: a workgroup a chunk, or four chunks
+    ticket = int(buf.workspace[skip:skip + 4].cpu().numpy().view(np.uint32)[0])
+    assert ticket == (plan.num_chunks if U == 3 else (plan.num_chunks + 3) // 4)
 
 
-@pytest.mark.parametrize("U,seg_len,seed,hist", [(7001, [4100], None, False), (7001, [4100], None, True), (4001, [4099, 70], 3, False)])
+@pytest.mark.parametrize("U,seg_len,seed,hist", [(7001, [4100], None, False), (7001, [4100], None, True), (4001, [4099, 70], 3, False),
+                                                 (4001, [5, 4099], 3, False), (4001, [3, 2, 4098], 3, True)])
 def test_single_sweep_streaming_form(U, seg_len, seed, hist):
-    # a wavefront a chunk, which large inputs take: whole and ragged chunks, of the stochastic conversion also shifted ones
+    # a wavefront a chunk, which large inputs take: whole and ragged chunks, of the stochastic conversion also whole ones off the
+    # 16-byte grid
     E, M = 3, 2
     d = sum(seg_len)
     rng = np.random.default_rng(2400 + U)
