@@ -83,7 +83,8 @@ __device__ inline uint32_t run_bits_exact(const uint32_t (&w)[4], int from, int 
 __device__ inline uint32_t pair_bits(uint32_t e0, uint32_t e1) { return (e0 + e1) & 0xffu; }
 
 // Codewords of a run's entries (pairs of less than 32 bits) from bit pos on; 0 stands for no symbol.  A word is ORed in with every
-// pair: what it holds so far is in its place already.
+// pair: what it holds so far is in its place already.  Not for a run without bits: all those behind a short chunk's end would OR
+// nothing into the same word, one after the other (k_pack_chunk of 24 000 chunks of 1237 symbols 162 us, of whole ones 60; without 52).
 template <int kN>
 __device__ inline void run_append(const uint32_t (&e)[kN], uint32_t pos, uint32_t *win)
 {
