@@ -281,7 +281,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
         if (active) {
             const uint64_t c = c0 + wave;
             if (lay.nseg > 1) {
-                seg = fu_find_chunk_segment(lay.segs, lay.nseg, c);
+                seg = wave_find_chunk_segment(lay.segs, lay.nseg, c);
                 sd = load_segment(lay.segs + seg);
                 bk = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
                 tab = books[bk].fast[t % kMaxA];

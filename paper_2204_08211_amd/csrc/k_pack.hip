@@ -25,16 +25,6 @@ constexpr int kPkWaves = 4;                         // wavefronts (chunks) per w
 constexpr int kPkThreads = 64 * kPkWaves;
 constexpr int kSymLoads = (kChunk / 4 + 1 + 63) / 64;  // dword loads per lane to cover a chunk at any byte offset (17)
 
-__device__ inline uint32_t find_chunk_segment(const SegDev *segs, uint32_t nseg, uint64_t chunk)
-{
-    uint32_t lo = 0, hi = nseg;  // segs[nseg].chunk_start = nchunks > chunk
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (segs[mid].chunk_start <= chunk) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 __device__ inline uint32_t wave_sum(uint32_t x)
 {
 #pragma unroll
@@ -69,7 +59,7 @@ __device__ inline PkChunk pk_layer_chunk(const Layout &lay, uint32_t seg, const 
 
 __device__ inline PkChunk pk_chunk(const Layout &lay, uint64_t c, uint32_t u, uint64_t sym_stride)
 {
-    const uint32_t seg = find_chunk_segment(lay.segs, lay.nseg, c);
+    const uint32_t seg = wave_find_chunk_segment(lay.segs, lay.nseg, c);
     const SegDev sd = load_segment(lay.segs + seg);
     return pk_layer_chunk(lay, seg, sd, (c - sd.chunk_start) * kChunk, u, sym_stride);
 }

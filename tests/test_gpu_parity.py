@@ -1489,7 +1489,7 @@ def test_coder_for_stored_symbols_at_the_edges_of_its_rules(U, chunks, layers, E
     assert torch.equal(m1[:, :d], m2[:, :d]) and int(bufs[0].payload_bits[0]) > d
 
 
-@pytest.mark.parametrize("U,chunks", [(3, 1024), (4, 1024), (4, 1030), (8, 1024), (8, 1030)])   # a chunk a workgroup, two, four
+@pytest.mark.parametrize("U,chunks", [(1, 90), (3, 1024), (4, 1024), (4, 1030), (8, 1024), (8, 1030)])   # a chunk a workgroup, two, four
 @pytest.mark.parametrize("code", ["long", "dense"])
 def test_coder_for_stored_symbols_over_many_layers(U, chunks, code):
     # against the oracle, offsets by the coder's workgroups (up to 1024 chunks a user) and by a launch of their own: a workgroup
@@ -1525,3 +1525,5 @@ def test_coder_for_stored_symbols_over_many_layers(U, chunks, code):
     assert used.max() > 24 if code == "long" else used.min() >= 33, used
     gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w, max_code_len=64)
     gu.compare_round(gpu, ref, d)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w, single_sweep=True, max_code_len=64)   # more layers than lanes
+    gu.compare_round(gpu, ref, d, single_sweep=True)
