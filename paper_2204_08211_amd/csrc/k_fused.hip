@@ -44,6 +44,7 @@
 namespace co3 {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef f4 f4_any __attribute__((aligned(4)));   // at any element
 
 constexpr int kFuCpb = 4;                            // chunks per workgroup ...
 constexpr int kFuCpbSmall = 1;                       // ... and for small inputs
@@ -94,8 +95,11 @@ __device__ inline void fu_lds_barrier()
 // A chunk that starts `shift` elements behind the 16-byte grid takes the vectors from the boundary below it, and vector 0, of
 // which the first `shift` elements lie before the chunk, has the chunk's last ones in their place: every vector is whole, and the
 // runs are those `shift` elements ahead, with the last few symbols of the chunk in front of the first run.
+// The ragged end of a layer has `vecs` vectors a lane (conversion to the nearest representative), as few as hold it, so that all
+// four wavefronts share it; the runs behind it are empty.  (Sixteen elements a lane whatever its length, one by one: encode of
+// eight users of fifty layers of 1000 elements 15.4 us, of four of 3000 layers of 5333 elements 239, of 6000 of 1237 214; so 14, 209 and 177.)
 template <bool kSR, bool kHist>
-__device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, uint32_t part, uint64_t e0, uint32_t nk, uint32_t shift,
+__device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, uint32_t part, uint64_t e0, uint32_t nk, uint32_t vecs, uint32_t shift,
                                   int32_t bias, float gain, float inv_gain, const float *__restrict__ gu, const float *mu,
                                   float *mo, float gamma, uint64_t seed, uint32_t *hist, uint64_t *__restrict__ status)
 {
@@ -166,8 +170,8 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
             }
             run.w[r] = packed;
         }
-    } else {
-        // the ragged end of a layer: element by element
+    } else if constexpr (kSR) {
+        // the ragged end of a layer, element by element (shared as below, the whole chunks' registers spill: 32 M elements 104 -> 108 us)
         float gs[16], ms[16];
 #pragma unroll
         for (uint32_t k = 0; k < 16; ++k) {
@@ -179,20 +183,18 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
         for (uint32_t r = 0; r < 4; ++r) {
             uint32_t packed = 0;
             uint32_t rnd[8] = {};   // the words from the vector's first element on
-            if constexpr (kSR) {
-                const uint64_t first = e0 + 4u * (v0 + 64u * r);
-                const Philox4 rw = element_random_words(first, u, seed);
+            const uint64_t first = e0 + 4u * (v0 + 64u * r);
+            const Philox4 rw = element_random_words(first, u, seed);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) rnd[k] = rw.w[k];
-                if (e0 & 3u) {   // the same in all lanes
-                    const Philox4 more = element_random_words(first + 4u, u, seed);
+            for (int k = 0; k < 4; ++k) rnd[k] = rw.w[k];
+            if (e0 & 3u) {   // the same in all lanes
+                const Philox4 more = element_random_words(first + 4u, u, seed);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) rnd[4 + k] = more.w[k];
+                for (int k = 0; k < 4; ++k) rnd[4 + k] = more.w[k];
 #pragma unroll
-                    for (int k = 0; k < 7; ++k) rnd[k] = e0 & 1u ? rnd[k + 1] : rnd[k];
+                for (int k = 0; k < 7; ++k) rnd[k] = e0 & 1u ? rnd[k + 1] : rnd[k];
 #pragma unroll
-                    for (int k = 0; k < 5; ++k) rnd[k] = e0 & 2u ? rnd[k + 2] : rnd[k];
-                }
+                for (int k = 0; k < 5; ++k) rnd[k] = e0 & 2u ? rnd[k + 2] : rnd[k];
             }
 #pragma unroll
             for (uint32_t j = 0; j < 4; ++j) {
@@ -202,6 +204,59 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
                 const uint32_t s = element(gs[4 * r + j], ms[4 * r + j], rnd[j], in, e);
                 if (in) mo[i] = e;
                 packed |= (in ? s : 0u) << (8 * j);
+            }
+            run.w[r] = packed;
+        }
+    } else {
+        // the ragged end of a layer, at any element: vectors, and its last few elements one by one; all one by one where the
+        // registers are for counts
+        constexpr bool kVectors = !kHist;
+        const uint32_t i0 = 4u * (64u * vecs * part + lane);
+        float gs[16], ms[16];
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t i = i0 + 256u * r;
+            if (kVectors && r < vecs && i + 4u <= nk) {
+                const f4 gv = *reinterpret_cast<const f4_any *>(gu + i), mv = *reinterpret_cast<const f4_any *>(mu + i);
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) {
+                    gs[4 * r + j] = gv[j];
+                    ms[4 * r + j] = mv[j];
+                }
+            } else {
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) {
+                    const bool in = r < vecs && i + j < nk;
+                    gs[4 * r + j] = in ? gu[i + j] : 0.0f;
+                    ms[4 * r + j] = in ? mu[i + j] : 0.0f;
+                }
+            }
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            run.w[r] = 0u;
+            if (r >= vecs) continue;   // the same in all lanes
+            uint32_t packed = 0;
+            f4 eo;
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t i = i0 + 256u * r + j;
+                float e;
+                const uint32_t in = i < nk ? 1u : 0u;
+                const uint32_t s = element(gs[4 * r + j], ms[4 * r + j], 0u, in, e);
+                if constexpr (kVectors) eo[j] = e;
+                else if (in) mo[i] = e;
+                packed |= (in ? s : 0u) << (8 * j);
+            }
+            if constexpr (kVectors) {
+                const uint32_t i = i0 + 256u * r;
+                if (i + 4u <= nk) {
+                    *reinterpret_cast<f4_any *>(mo + i) = eo;
+                } else {
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j)
+                        if (i + j < nk) mo[i + j] = eo[j];
+                }
             }
             run.w[r] = packed;
         }
@@ -272,7 +327,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     const bool active = wave < nck;
 
     TeamRun run;
-    uint32_t nk = 0, shift = 0, head = 0;
+    uint32_t nk = 0, shift = 0, head = 0, vecs = 4;
     uint32_t len_sum = 0;   // code lengths of the elements this lane quantizes
     if constexpr (kIsTeam) {
         // ---- 1. a team quantizes its chunk; runs of symbols and their places in the wavefront's share of its bits --------
@@ -289,14 +344,18 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
             const uint64_t e0 = sd.offset + (c - sd.chunk_start) * kChunk, left = sd.offset + sd.length - e0;
             nk = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
             shift = nk == (uint32_t)kChunk ? (uint32_t)(e0 & 3u) : 0u;
+            if constexpr (!kSR) vecs = (nk + 1023u) >> 10;
             const uint64_t pair = (uint64_t)u * lay.nseg + seg, at = (uint64_t)u * row_stride + e0;
-            team_sweep<kSR, kHist>(run, lay, u, part, e0, nk, shift, lay.bias[pair], lay.gain[2 * pair], lay.gain[2 * pair + 1],
+            team_sweep<kSR, kHist>(run, lay, u, part, e0, nk, vecs, shift, lay.bias[pair], lay.gain[2 * pair], lay.gain[2 * pair + 1],
                                           g + at, m + at, m_out + at, gamma, seed, s_hist[kHist ? wave : 0], status);
             s_fast[wave][t % kMaxA] = run_entry(tab);
         }
         fu_lds_barrier();   // tables (and counts)
         if (active) {
-            team_lengths<true>(run, part, nk, shift, s_fast[wave], books[bk], head, status);
+            const bool whole = nk == (uint32_t)kChunk;
+            const uint32_t from = kSR || whole ? 1024u * part : 256u * vecs * part;
+            const uint32_t end = kSR || from + 256u * vecs > nk ? nk : from + 256u * vecs;
+            team_lengths<true>(run, from, end, whole, shift, s_fast[wave], books[bk], head, status);
             if ((lane & 15u) < 4u) s_head[wave][16u * part + (run_of_lane(lane) >> 2)] = head;
             if (part == 0 && lane == 0) s_head[wave][kSubsPerChunk] = run.tail_bits;
             if constexpr (kHist) {
@@ -598,7 +657,9 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
                 if (shift && run.from && !run.slow) run_append(run.tail, chunk_bits - run.tail_bits, region);
             }
             // a sub-chunk has what its four runs hold, but for the symbols ahead of the first, and with those ahead of the next
-            const uint32_t sub = 16u * part + (lane >> 2);
+            // (behind those of the chunk's elements the empty ones, as many from every wavefront)
+            const uint32_t j = lane >> 2, subs = 4u * vecs;
+            const uint32_t sub = kSR || j < subs ? subs * part + j : 4u * subs + (16u - subs) * part + (j - subs);
             const uint32_t bits = quad_sum(run.in_order) + (shift ? s_head[wave][sub + 1] - s_head[wave][sub] : 0u);
             if ((lane & 3u) == 0) sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + sub] = (uint16_t)bits;
         }

@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kPkThreads, 8) void k_pack_chunk(
         uint64_t off_words = 0;
         if constexpr (!kOffsets) off_words = offsets[i] >> 5;
         uint32_t head;
-        team_lengths<false>(run, part, cur.n, 0, s_entry, table, head, status);
+        team_lengths<false>(run, 64u * kRun * part, cur.n, cur.n == (uint32_t)kChunk, 0, s_entry, table, head, status);
         uint32_t *win = s_win[i & 1u], *share = s_part[i & 1u];
         if (lane == 0) share[part] = run.total;
         __syncthreads();

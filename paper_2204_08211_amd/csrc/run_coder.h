@@ -168,21 +168,22 @@ struct TeamRun {
 __device__ inline uint32_t run_of_lane(uint32_t lane) { return 16u * (lane & 3u) + (lane >> 2); }
 __device__ inline uint32_t lane_of_run(uint32_t r) { return 4u * (r & 15u) + (r >> 4); }
 
+// The wavefront's share is the chunk's elements base .. end - 1, all of its runs whole where `whole`.
 // A run's entries, its bits and its place among the wavefront's; head: the bits of its first `shift` symbols, which belong to
 // the sub-chunk before.
 template <bool kQuads>
-__device__ inline void team_lengths(TeamRun &run, uint32_t part, uint32_t nk, uint32_t shift, const uint32_t *entry, const BookDev &book,
-                                    uint32_t &head, uint64_t *__restrict__ status)
+__device__ inline void team_lengths(TeamRun &run, uint32_t base, uint32_t end, bool whole, uint32_t shift, const uint32_t *entry,
+                                    const BookDev &book, uint32_t &head, uint64_t *__restrict__ status)
 {
-    const uint32_t lane = threadIdx.x & 63u, first = (uint32_t)kRun * (64u * part + (kQuads ? run_of_lane(lane) : lane));
+    const uint32_t lane = threadIdx.x & 63u, first = base + (uint32_t)kRun * (kQuads ? run_of_lane(lane) : lane);
     const bool opens = shift && first == 0;   // the chunk's first run
     run.from = opens ? shift : 0u;
-    run.to = nk > first ? (nk - first < (uint32_t)kRun ? nk - first : (uint32_t)kRun) : 0u;
+    run.to = end > first ? (end - first < (uint32_t)kRun ? end - first : (uint32_t)kRun) : 0u;
     uint32_t over = 0;   // 32 or more: an entry is not enough
     run.bits = run.tail_bits = head = 0;
 #pragma unroll
     for (int j = 0; j < kRun; ++j) run.e[j] = entry[run_symbol(run.w, j)];
-    if (nk != (uint32_t)kChunk) {
+    if (!whole) {
 #pragma unroll
         for (int j = 0; j < kRun; ++j) run.e[j] = (uint32_t)j < run.to ? run.e[j] : 0u;
     }
