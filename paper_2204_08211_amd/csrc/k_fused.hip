@@ -95,13 +95,16 @@ __device__ inline void fu_lds_barrier()
 // A chunk that starts `shift` elements behind the 16-byte grid takes the vectors from the boundary below it, and vector 0, of
 // which the first `shift` elements lie before the chunk, has the chunk's last ones in their place: every vector is whole, and the
 // runs are those `shift` elements ahead, with the last few symbols of the chunk in front of the first run.
+// odd: non-finite and clamped elements of the workgroup, which has one addition to each of the status words: all wavefronts of a
+// launch add to the same two words, some 11 ns each, one after the other (sixteen a workgroup: twenty users of 4.4 M elements
+// in [1,3,0] with 2 of 1000 beyond the largest 920 us, four, in the streaming form, 340).
 // The ragged end of a layer has `vecs` vectors a lane (conversion to the nearest representative), as few as hold it, so that all
 // four wavefronts share it; the runs behind it are empty.  (Sixteen elements a lane whatever its length, one by one: encode of
 // eight users of fifty layers of 1000 elements 15.4 us, of four of 3000 layers of 5333 elements 239, of 6000 of 1237 214; so 14, 209 and 177.)
 template <bool kSR, bool kHist>
 __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, uint32_t part, uint64_t e0, uint32_t nk, uint32_t vecs, uint32_t shift,
                                   int32_t bias, float gain, float inv_gain, const float *__restrict__ gu, const float *mu,
-                                  float *mo, float gamma, uint64_t seed, uint32_t *hist, uint64_t *__restrict__ status)
+                                  float *mo, float gamma, uint64_t seed, uint32_t *hist, uint32_t *odd)
 {
     const uint32_t lane = threadIdx.x & 63u, sign_shift = lay.E + lay.M;
     const uint32_t v0 = 256u * part + lane;   // vectors v0, v0 + 64, + 128, + 192
@@ -262,8 +265,8 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
         }
     }
     quad_transpose(run.w, lane);
-    if (n_nonfinite) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_NONFINITE), (unsigned long long)n_nonfinite);
-    if (n_clamped) atomicAdd(reinterpret_cast<unsigned long long *>(status + CO3_STAT_CLAMPED), (unsigned long long)n_clamped);
+    if (n_nonfinite) atomicAdd(&odd[0], n_nonfinite);
+    if (n_clamped) atomicAdd(&odd[1], n_clamped);
 }
 
 // kSR: the stochastic conversion (dither from Philox words of (element, user, seed)) instead of
@@ -296,6 +299,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     __shared__ float s_gain[kCpb][2];
     __shared__ uint64_t s_prefix;
     __shared__ uint32_t s_ticket, s_stalled;
+    __shared__ uint32_t s_odd[2];                     // (a team's) non-finite and clamped elements of the workgroup
     __shared__ uint32_t s_part[kCpb][kTeam];          // a team's wavefronts' shares of their chunk's size
     __shared__ uint32_t s_head[kIsTeam ? kCpb : 1][kIsTeam ? kSubsPerChunk + 1 : 1];   // bits of a sub-chunk that the run before its first whole one has not
     static_assert(kTeam == 1 || kTeam * 64 * kRun == kChunk, "a run for every thread of a team");
@@ -312,6 +316,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
     SegDev sd;
     uint32_t seg = 0, bk = 0, tab = 0;
     if constexpr (kIsTeam) {
+        if (t < 2) s_odd[t] = 0u;
         sd = load_segment(lay.segs);
         bk = (lay.per_user_books ? u * lay.books_per_user : 0u) + (uint32_t)sd.book;
         tab = books[bk].fast[t % kMaxA];
@@ -347,10 +352,11 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
             if constexpr (!kSR) vecs = (nk + 1023u) >> 10;
             const uint64_t pair = (uint64_t)u * lay.nseg + seg, at = (uint64_t)u * row_stride + e0;
             team_sweep<kSR, kHist>(run, lay, u, part, e0, nk, vecs, shift, lay.bias[pair], lay.gain[2 * pair], lay.gain[2 * pair + 1],
-                                          g + at, m + at, m_out + at, gamma, seed, s_hist[kHist ? wave : 0], status);
+                                          g + at, m + at, m_out + at, gamma, seed, s_hist[kHist ? wave : 0], s_odd);
             s_fast[wave][t % kMaxA] = run_entry(tab);
         }
-        fu_lds_barrier();   // tables (and counts)
+        fu_lds_barrier();   // tables, counts
+        if (t < 2 && s_odd[t]) atomicAdd(reinterpret_cast<unsigned long long *>(status + (t ? CO3_STAT_CLAMPED : CO3_STAT_NONFINITE)), (unsigned long long)s_odd[t]);
         if (active) {
             const bool whole = nk == (uint32_t)kChunk;
             const uint32_t from = kSR || whole ? 1024u * part : 256u * vecs * part;

@@ -1434,6 +1434,28 @@ def test_single_sweep_runs_of_symbols(U, seg_len, code, seed):
     assert ticket == (plan.num_chunks if U < 10 else (plan.num_chunks + 3) // 4)
 
 
+@pytest.mark.parametrize("U,seg_len", [(3, [4096 * 2 + 5, 70, 4096 + 3]), (300, [3, 4096, 2, 4098, 1, 4097])], ids=["small", "teams"])
+@pytest.mark.parametrize("seed,hist", [(None, False), (None, True), (17, False)])
+def test_single_sweep_counts_odd_elements_once(U, seg_len, seed, hist):
+    # non-finite and clamped elements everywhere, in whole and ragged chunks: a workgroup adds up those of its wavefronts
+    E, M = 3, 2
+    d, n = sum(seg_len), len(seg_len)
+    rng = np.random.default_rng(2900 + U)
+    g = rng.standard_normal((U, d), dtype=np.float32)
+    g[rng.random((U, d)) < 0.01] = np.nan
+    g[rng.random((U, d)) < 0.01] = -np.inf
+    g[rng.random((U, d)) < 0.05] = 1e30
+    g[0, -1] = g[-1, 0] = np.inf
+    m = np.zeros_like(g)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[3] * n] * U, seg_len=seg_len, seg_book=[0] * n)
+    weights = np.ones((1, 64), np.uint64)
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=weights, stochastic_seed=seed)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=weights, single_sweep=True, stochastic_seed=seed, single_sweep_hist=hist)
+    gu.compare_round(gpu, ref, d, single_sweep=True)
+    assert int(gpu["status_encode"][0]) == (~np.isfinite(g)).sum() and int(gpu["status_encode"][1]) >= (g == np.float32(1e30)).sum()
+
+
+
 @pytest.mark.parametrize("U,seg_len,seed,hist", [(7001, [4100], None, False), (7001, [4100], None, True), (4001, [4099, 70], 3, False),
                                                  (4001, [5, 4099], 3, False), (4001, [3, 2, 4098], 3, True)])
 def test_single_sweep_streaming_form(U, seg_len, seed, hist):
