@@ -659,8 +659,9 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
         if (active) {
             if (windows == 1u) {
                 if (run.slow) team_append_exact(run, fast, books[bk], excl, chunk_bits, region, 0, kRunWindow);
-                else if (run.bits) run_append(run.e, excl, region);
-                if (shift && run.from && !run.slow) run_append(run.tail, chunk_bits - run.tail_bits, region);
+                else if (run.wide) run_append<1>(run.e, excl, region);
+                else if (run.bits) run_append<2>(run.e, excl, region);
+                if (shift && run.from && !run.slow) run_append<1>(run.tail, chunk_bits - run.tail_bits, region);
             }
             // a sub-chunk has what its four runs hold, but for the symbols ahead of the first, and with those ahead of the next
             // (behind those of the chunk's elements the empty ones, as many from every wavefront)

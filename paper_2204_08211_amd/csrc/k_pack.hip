@@ -260,7 +260,8 @@ __global__ __launch_bounds__(kPkThreads, 8) void k_pack_chunk(
         for (uint32_t wbase = 0; wbase < nwords; wbase += kRunWindow) {
             if (wbase) __syncthreads();   // the window before is out
             if (run.slow || nwords > (uint32_t)kRunWindow) run_append_exact(run.w, 0, (int)run.to, s_entry, table, excl, win, wbase, kRunWindow);
-            else if (run.bits) run_append(run.e, excl, win);
+            else if (run.wide) run_append<1>(run.e, excl, win);
+            else if (run.bits) run_append<2>(run.e, excl, win);
             __syncthreads();
             const uint32_t left = nwords - wbase, wn = left < (uint32_t)kRunWindow ? left : (uint32_t)kRunWindow;
             for (uint32_t j = t; j < wn; j += kPkThreads) {

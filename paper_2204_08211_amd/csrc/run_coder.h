@@ -8,9 +8,9 @@
 // all wavefronts of the chunk share it.
 //
 // Entries in LDS are the table's turned round: the codeword (up to 24 bits) from the top bit on, its length in the low
-// byte; kRunSlow alone for a longer code or none.  A run that has one, or a pair of neighbours of 32 bits or more together,
-// is coded symbol by symbol from the full table (run_append_exact); so is a chunk of more words than the window holds,
-// window by window.
+// byte; kRunSlow alone for a longer code or none.  Codewords are placed two at a time; one by one in a run that has a pair of
+// 32 bits or more together.  A run with a code that its entry does not hold is coded symbol by symbol from the full table
+// (run_append_exact); so is a chunk of more words than the window holds, window by window.
 #pragma once
 
 #include "co3_internal.h"
@@ -82,13 +82,13 @@ __device__ inline uint32_t run_bits_exact(const uint32_t (&w)[4], int from, int 
 // The two lengths of a pair of entries.
 __device__ inline uint32_t pair_bits(uint32_t e0, uint32_t e1) { return (e0 + e1) & 0xffu; }
 
-// Codewords of a run's entries (pairs of less than 32 bits) from bit pos on; 0 stands for no symbol.  A word is ORed in with every
-// pair: what it holds so far is in its place already.  Not for a run without bits: all those behind a short chunk's end would OR
+// Codewords of a run's entries, kStep at a time (together less than 32 bits), from bit pos on; 0 stands for no symbol.  A word is ORed
+// in with every step: what it holds so far is in its place already.  Not for a run without bits: all those behind a short chunk's end would OR
 // nothing into the same word, one after the other (k_pack_chunk of 24 000 chunks of 1237 symbols 162 us, of whole ones 60; without 52).
-template <int kN>
+template <int kStep, int kN>
 __device__ inline void run_append(const uint32_t (&e)[kN], uint32_t pos, uint32_t *win)
 {
-    static_assert(kN % 2 == 0, "pairs");
+    static_assert((kStep == 1 || kStep == 2) && kN % kStep == 0, "single codewords or pairs");
     typedef __attribute__((address_space(3))) uint32_t lds_word_t;
     auto or_in = [](uint32_t at, uint32_t x) {
         __hip_atomic_fetch_or((lds_word_t *)at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -97,12 +97,13 @@ __device__ inline void run_append(const uint32_t (&e)[kN], uint32_t pos, uint32_
     uint32_t bit = pos + 8u * (uint32_t)(uintptr_t)(const lds_word_t *)win;
     uint32_t at = (bit >> 3) & ~3u, cur = 0u;   // cur: the run's bits in that word
 #pragma unroll
-    for (int j = 0; j < kN; j += 2) {
-        const uint32_t c = (e[j] & 0xffffff00u) | ((e[j + 1] & 0xffffff00u) >> (e[j] & 31u));
+    for (int j = 0; j < kN; j += kStep) {
+        uint32_t c = e[j] & 0xffffff00u;
+        if constexpr (kStep == 2) c |= (e[j + 1] & 0xffffff00u) >> (e[j] & 31u);
         cur |= c >> (bit & 31u);
         or_in(at, cur);
         const uint32_t rest = __builtin_amdgcn_alignbit(c, 0u, bit);
-        bit += pair_bits(e[j], e[j + 1]);
+        bit += kStep == 2 ? pair_bits(e[j], e[j + kStep - 1]) : e[j] & 0xffu;
         const uint32_t next = (bit >> 3) & ~3u;
         cur = next != at ? rest : cur;
         at = next;
@@ -161,7 +162,8 @@ struct TeamRun {
     uint32_t total;       // that share
     uint32_t in_order;    // bits of the wavefront's run of the lane's number
     uint32_t tail_bits;
-    bool slow;            // an entry is not enough, or a pair too long
+    bool slow;            // an entry is not enough
+    bool wide;            // that, or a pair is too long to be placed at once
 };
 
 // Where the lanes' runs come from a transposition within quads (kQuads), lane 4 q + i has run 16 i + q; else they come in the lanes' order.
@@ -179,7 +181,7 @@ __device__ inline void team_lengths(TeamRun &run, uint32_t base, uint32_t end, b
     const bool opens = shift && first == 0;   // the chunk's first run
     run.from = opens ? shift : 0u;
     run.to = end > first ? (end - first < (uint32_t)kRun ? end - first : (uint32_t)kRun) : 0u;
-    uint32_t over = 0;   // 32 or more: an entry is not enough
+    uint32_t over = 0;   // 32 or more: a pair is too long; 64 or more: an entry is not enough (up to 48 without such, or in the tail it does no harm)
     run.bits = run.tail_bits = head = 0;
 #pragma unroll
     for (int j = 0; j < kRun; ++j) run.e[j] = entry[run_symbol(run.w, j)];
@@ -206,7 +208,11 @@ __device__ inline void team_lengths(TeamRun &run, uint32_t base, uint32_t end, b
         run.bits += both;
         over |= both;
     }
-    run.slow = over > 31u;
+    // A pair of 32 bits and more is two of the rarest symbols side by side, one or a few in a launch, but a small launch waits for
+    // its slowest thread: symbol by symbol from the full table such a run took 3 us (encode of four users of 66 000 elements
+    // 10.7 -> 13 us, of twelve of 30 000 11 -> 13.5).
+    run.wide = over > 31u;
+    run.slow = over > 63u;
     if (__any(run.slow)) {
         if (run.slow) {
             uint32_t nocode = 0;

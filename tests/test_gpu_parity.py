@@ -1435,6 +1435,35 @@ def test_single_sweep_runs_of_symbols(U, seg_len, code, seed):
 
 
 @pytest.mark.parametrize("U,seg_len", [(3, [4096 * 2 + 5, 70, 4096 + 3]), (300, [3, 4096, 2, 4098, 1, 4097])], ids=["small", "teams"])
+@pytest.mark.parametrize("seed", [None, 17])
+def test_pairs_of_codewords_of_32_bits_and_more(U, seg_len, seed):
+    # codes of 17 bits and more beside short ones: pairs of neighbours that are placed one by one, in some runs, as the first and
+    # last symbols of a chunk and as those that stand in front of its first run
+    E, M, A = 4, 1, 64
+    d, n, bias = sum(seg_len), len(seg_len), 16
+    rng = np.random.default_rng(2700 + U)
+    nm = orc.num_magnitudes(E, M)
+    emit = [s for s in range(A) if (s & 31) < nm and s != 32]
+    rare, chain = [s for s in emit if (s & 31) < 8], [s for s in emit if (s & 31) >= 8]
+    w = np.zeros(A, np.uint64)
+    w[rare] = 1
+    w[chain[:14]] = [1 << (5 + i) for i in range(14)]
+    k = np.where(rng.random((U, d)) < 0.3, rng.integers(0, 8, (U, d)), chain[13] & 31)
+    k[::3] = chain[13] & 31                                   # every third user: a pair or two a chunk
+    k[::3, :2] = k[::3, d // 2:d // 2 + 3] = k[::3, -3:] = 5
+    g = orc.grid(E, M, bias)[k].astype(np.float32)
+    m = np.zeros_like(g)
+    kw = dict(E=E, M=M, U=U, d=d, bias=[[bias] * n] * U, seg_len=seg_len, seg_book=[0] * n)
+    ref = gu.oracle_round(kw, g, m, 0.9, weights=w[None, :], stochastic_seed=seed)
+    used = ref["lens"].reshape(-1)[np.flatnonzero(ref["hist"].reshape(-1))]
+    assert used.max() <= 24 and np.sort(used)[-1] >= 16 and np.diff(ref["chunk_offset"].astype(np.int64)).max() <= 32 * 2048, used
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w[None, :], single_sweep=True, stochastic_seed=seed, max_code_len=32)
+    gu.compare_round(gpu, ref, d, single_sweep=True)
+    gpu, _ = gu.gpu_round(kw, g, m, 0.9, BOOK_FIXED, weights=w[None, :], stochastic_seed=seed, max_code_len=32)
+    gu.compare_round(gpu, ref, d)
+
+
+@pytest.mark.parametrize("U,seg_len", [(3, [4096 * 2 + 5, 70, 4096 + 3]), (300, [3, 4096, 2, 4098, 1, 4097])], ids=["small", "teams"])
 @pytest.mark.parametrize("seed,hist", [(None, False), (None, True), (17, False)])
 def test_single_sweep_counts_odd_elements_once(U, seg_len, seed, hist):
     # non-finite and clamped elements everywhere, in whole and ragged chunks: a workgroup adds up those of its wavefronts
