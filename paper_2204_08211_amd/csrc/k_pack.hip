@@ -259,8 +259,8 @@ __global__ __launch_bounds__(kPkThreads, 8) void k_pack_chunk(
         // window by window where the chunk's words are more than one holds
         for (uint32_t wbase = 0; wbase < nwords; wbase += kRunWindow) {
             if (wbase) __syncthreads();   // the window before is out
-            if (run.slow || nwords > (uint32_t)kRunWindow) run_append_exact(run.w, 0, (int)run.to, s_entry, table, excl, win, wbase, kRunWindow);
-            else if (run.wide) run_append<1>(run.e, excl, win);
+            // (a pair too long takes that way as well: singly from the entries, which the next symbols leave no registers for, 32 spill)
+            if (run.wide || nwords > (uint32_t)kRunWindow) run_append_exact(run.w, 0, (int)run.to, s_entry, table, excl, win, wbase, kRunWindow);
             else if (run.bits) run_append<2>(run.e, excl, win);
             __syncthreads();
             const uint32_t left = nwords - wbase, wn = left < (uint32_t)kRunWindow ? left : (uint32_t)kRunWindow;
