@@ -5,7 +5,7 @@
 // HBM traffic per element: read g (4) + read m (4) + write m' (4) + write b (r/d bits).
 //
 // A workgroup takes four consecutive chunks of one user (small inputs: one).  Two forms of the sweep and the coding share the
-// rest.  Streaming, a wavefront a chunk, for large inputs:
+// rest.  Streaming, a wavefront a chunk, for large inputs and for layers of few elements:
 //   1. wavefront w quantizes chunk w (16 KB of g and of m, requested a quarter at a time with the
 //      next quarter in flight while the current one is computed) and leaves the symbols in LDS,
 //      in the rows of 16 + 1 words the pack step reads without bank conflicts; the code's tables go
@@ -98,9 +98,10 @@ __device__ inline void fu_lds_barrier()
 // odd: non-finite and clamped elements of the workgroup, which has one addition to each of the status words: all wavefronts of a
 // launch add to the same two words, some 11 ns each, one after the other (sixteen a workgroup: twenty users of 4.4 M elements
 // in [1,3,0] with 2 of 1000 beyond the largest 920 us, four, in the streaming form, 340).
-// The ragged end of a layer has `vecs` vectors a lane (conversion to the nearest representative), as few as hold it, so that all
-// four wavefronts share it; the runs behind it are empty.  (Sixteen elements a lane whatever its length, one by one: encode of
-// eight users of fifty layers of 1000 elements 15.4 us, of four of 3000 layers of 5333 elements 239, of 6000 of 1237 214; so 14, 209 and 177.)
+// The ragged end of a layer has `vecs` vectors a lane, as few as hold it, so that all four wavefronts share it; the runs behind it
+// are empty.  (Sixteen elements a lane whatever its length, one by one: encode of eight users of fifty layers of 1000 elements 15.4 us,
+// of four of 3000 layers of 5333 elements 239, of 6000 of 1237 214; so 14, 209 and 177.  Stochastic, forty users of thirty layers of 100
+// elements 38 and 28.)
 template <bool kSR, bool kHist>
 __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, uint32_t part, uint64_t e0, uint32_t nk, uint32_t vecs, uint32_t shift,
                                   int32_t bias, float gain, float inv_gain, const float *__restrict__ gu, const float *mu,
@@ -174,19 +175,23 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
             run.w[r] = packed;
         }
     } else if constexpr (kSR) {
-        // the ragged end of a layer, element by element (shared as below, the whole chunks' registers spill: 32 M elements 104 -> 108 us)
+        // the ragged end of a layer, element by element
+        const uint32_t i0 = 4u * (64u * vecs * part + lane);
         float gs[16], ms[16];
 #pragma unroll
         for (uint32_t k = 0; k < 16; ++k) {
-            const uint32_t i = 4u * (v0 + 64u * (k >> 2)) + (k & 3u);
-            gs[k] = i < nk ? gu[i] : 0.0f;
-            ms[k] = i < nk ? mu[i] : 0.0f;
+            const uint32_t i = i0 + 256u * (k >> 2) + (k & 3u);
+            const bool in = (k >> 2) < vecs && i < nk;
+            gs[k] = in ? gu[i] : 0.0f;
+            ms[k] = in ? mu[i] : 0.0f;
         }
 #pragma unroll
         for (uint32_t r = 0; r < 4; ++r) {
             uint32_t packed = 0;
+            run.w[r] = 0u;
+            if (r >= vecs) continue;   // the same in all lanes
             uint32_t rnd[8] = {};   // the words from the vector's first element on
-            const uint64_t first = e0 + 4u * (v0 + 64u * r);
+            const uint64_t first = e0 + i0 + 256u * r;
             const Philox4 rw = element_random_words(first, u, seed);
 #pragma unroll
             for (int k = 0; k < 4; ++k) rnd[k] = rw.w[k];
@@ -201,7 +206,7 @@ __device__ inline void team_sweep(TeamRun &run, const Layout &lay, uint32_t u, u
             }
 #pragma unroll
             for (uint32_t j = 0; j < 4; ++j) {
-                const uint32_t i = 4u * (v0 + 64u * r) + j;
+                const uint32_t i = i0 + 256u * r + j;
                 float e;
                 const uint32_t in = i < nk ? 1u : 0u;
                 const uint32_t s = element(gs[4 * r + j], ms[4 * r + j], rnd[j], in, e);
@@ -349,7 +354,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
             const uint64_t e0 = sd.offset + (c - sd.chunk_start) * kChunk, left = sd.offset + sd.length - e0;
             nk = left < (uint64_t)kChunk ? (uint32_t)left : (uint32_t)kChunk;
             shift = nk == (uint32_t)kChunk ? (uint32_t)(e0 & 3u) : 0u;
-            if constexpr (!kSR) vecs = (nk + 1023u) >> 10;
+            vecs = (nk + 1023u) >> 10;
             const uint64_t pair = (uint64_t)u * lay.nseg + seg, at = (uint64_t)u * row_stride + e0;
             team_sweep<kSR, kHist>(run, lay, u, part, e0, nk, vecs, shift, lay.bias[pair], lay.gain[2 * pair], lay.gain[2 * pair + 1],
                                           g + at, m + at, m_out + at, gamma, seed, s_hist[kHist ? wave : 0], s_odd);
@@ -359,8 +364,8 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
         if (t < 2 && s_odd[t]) atomicAdd(reinterpret_cast<unsigned long long *>(status + (t ? CO3_STAT_CLAMPED : CO3_STAT_NONFINITE)), (unsigned long long)s_odd[t]);
         if (active) {
             const bool whole = nk == (uint32_t)kChunk;
-            const uint32_t from = kSR || whole ? 1024u * part : 256u * vecs * part;
-            const uint32_t end = kSR || from + 256u * vecs > nk ? nk : from + 256u * vecs;
+            const uint32_t from = 256u * vecs * part;
+            const uint32_t end = from + 256u * vecs > nk ? nk : from + 256u * vecs;
             team_lengths<true>(run, from, end, whole, shift, s_fast[wave], books[bk], head, status);
             if ((lane & 15u) < 4u) s_head[wave][16u * part + (run_of_lane(lane) >> 2)] = head;
             if (part == 0 && lane == 0) s_head[wave][kSubsPerChunk] = run.tail_bits;
@@ -487,7 +492,8 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
                     }
                 }
             } else if (nk == (uint32_t)kChunk) {
-                // A layer may start at any element.  The same vectors, taken from the 16-byte boundary
+                // A layer may start at any element.  (Never in the cut for five wavefronts, which only plans on the grid take; but without
+                // this path its registers come out worse, sixteen users of 25.6 M elements 942 -> 969 to 998 us.)  The same vectors, taken from the 16-byte boundary
                 // below the chunk: vector k holds the chunk's elements 4k - shift .. 4k - shift + 3, so
                 // its symbols fall into words k - 1 and k of the stage (OR-ed in; the stage is cleared
                 // first) and the vectors at both ends are partial.
@@ -666,7 +672,7 @@ __global__ __launch_bounds__(64 * kCpb * kTeam, kWaves) void k_encode_fused(
             // a sub-chunk has what its four runs hold, but for the symbols ahead of the first, and with those ahead of the next
             // (behind those of the chunk's elements the empty ones, as many from every wavefront)
             const uint32_t j = lane >> 2, subs = 4u * vecs;
-            const uint32_t sub = kSR || j < subs ? subs * part + j : 4u * subs + (16u - subs) * part + (j - subs);
+            const uint32_t sub = j < subs ? subs * part + j : 4u * subs + (16u - subs) * part + (j - subs);
             const uint32_t bits = quad_sum(run.in_order) + (shift ? s_head[wave][sub + 1] - s_head[wave][sub] : 0u);
             if ((lane & 3u) == 0) sub_bits[((uint64_t)u * lay.nchunks + c) * kSubsPerChunk + sub] = (uint16_t)bits;
         }
@@ -820,33 +826,48 @@ __global__ void k_zero_fused(uint64_t *p, uint64_t n, uint64_t *q, uint64_t nq)
 // few workgroups is short and chunks off the 16-byte grid cost nothing more: eight users of 10^6 elements, in this form and in the
 // streaming form, 30 and 49 us; one of 8 M 32 and 48; sixteen of 2 M 89 and 107; eight of 6 M 132 and 143; sixteen of
 // 6.4 M 260 and 260; of 12 M 466 and 462; of 25.6 M 966 and 942; with a third of the chunks off the grid, of 8 M 333 and 382, of 12 M
-// 483 and 560.  With symbol counts the teams are ahead at every size with layers off the grid (sixteen users of 6.5 M 294 and 303,
-// of 28 M 1170 and 1206).  The stochastic conversion, teams and streaming: sixteen users of 2 M elements 99 and 106 us, of 6.4 M 289 and 271.
+// 483 and 560.  With symbol counts and layers off the grid, sixteen users of 28 M in [1,4,3] 1170 and 1206, but ten of 8.3 M in [1,2,0],
+// where more of a wavefront's lanes count the same symbol, 287 and 252.  The stochastic conversion, teams and streaming: sixteen users of 2 M elements 99 and 106 us, of 6.4 M 289 and 271.
 enum class FusedForm { kSmall, kTeams, kStream };
-// In groups of kFuCpb chunks and groups per user: 2 groups + 3 of a user's up to a workgroup of teams for every CU, groups + 5 of a
-// user's beyond, where a user's counter is what the small form waits for; later off the grid.
-constexpr uint64_t kFuSmallLine = 280, kFuSmallLineStochastic = 460;
-constexpr uint64_t kFuSmallLineBeyond = 400, kFuSmallLineBeyondStochastic = 475, kFuSmallLineOff = 60;
-constexpr uint64_t kFuStreamLine = 7000, kFuStreamLineStochastic = 4000;   // in groups
-static FusedForm fused_form(const Layout &lay, bool stochastic)
+// In groups of kFuCpb chunks and groups per user.  Small: 2 groups + 3 of a user's up to a workgroup of teams for every CU, groups + 5
+// of a user's beyond, where a user's counter is what the small form waits for; later off the grid.  Streaming: from a number of
+// groups, and sooner where chunks are short on average (layers of few elements), for which a wavefront each is enough.
+// us, small, teams, streaming:
+//   with symbol counts, which take turns in LDS: [1,2,0], 24 users of 72 groups 17.5 22.3 24.9, of 288 29.8 36.6 38.2, of 2400
+//   162 145 138; [1,4,3], eight users of 256 groups 32.5 26.1 29.1, 24 of 2400 163 116 122
+//   stochastic, eight users of 296 groups 31.5 30.5 32.8, of 3200 298 163 157
+//   layers of one chunk each, off the grid where their length is odd: of 20 elements, 40 users of 600 groups 27 23 20, of 9000 413 205 141;
+//   of 301 27 24 19, 427 200 147; of 701, of 600 27 24 21; of 1001 28 24 23, 474 222 200; of 3101, of 9000 - 356 372
+//   with counts, of 701, 40 users of 600 groups 34 29 26; of 3101, of 1520 105 79 77
+//   stochastic, twelve users, of 701, of 156 groups 25 23 22, of 600 51 39 35, of 1500 105 66 65; of 1500, of 1500 112 75 76; with counts,
+//   of 701, of 600 56 44 47, of 301, 40 users of 600 43 42 39.  (From 400 groups on: of layers that differ, a launch waits for the longest's
+//   wavefront, fourteen users of sixty layers of 974 elements on average 43 and 52 streaming.)
+//   layers of 13 333 at odd elements, 40 users of 9000 groups, teams and streaming 341 324; with counts 376 338
+// short_chunk, short_off: the average of a chunk's elements, where all layers are on the grid, and else.
+struct FormLines { uint64_t small, small_beyond, stream, short_chunk, short_off, short_stream; };
+constexpr FormLines kFuNearest = {280, 400, 7000, 350, 1050, 400};
+constexpr FormLines kFuCounts = {400, 550, 2000, 3150, 3150, 400};
+constexpr FormLines kFuStochastic = {520, 550, 2600, 1050, 1050, 400};
+constexpr FormLines kFuStochasticCounts = {520, 550, 2600, 350, 350, 600};
+constexpr uint64_t kFuSmallOff = 60, kFuWhole = 3500;
+static FusedForm fused_form(const Layout &lay, bool stochastic, bool counts)
 {
-    const uint64_t per_user = (lay.nchunks + kFuCpb - 1) / kFuCpb, groups = (uint64_t)lay.U * per_user, off = lay.vec_aligned ? 0 : kFuSmallLineOff;
-    const bool small = groups <= 256 ? 2 * groups + 3 * per_user < (stochastic ? kFuSmallLineStochastic : kFuSmallLine) + off
-                                     : groups + 5 * per_user < (stochastic ? kFuSmallLineBeyondStochastic : kFuSmallLineBeyond) + off;
+    const FormLines &line = stochastic ? (counts ? kFuStochasticCounts : kFuStochastic) : (counts ? kFuCounts : kFuNearest);
+    const uint64_t per_user = (lay.nchunks + kFuCpb - 1) / kFuCpb, groups = (uint64_t)lay.U * per_user, off = lay.vec_aligned ? 0 : kFuSmallOff;
+    if (groups >= line.short_stream && lay.d <= (lay.vec_aligned ? line.short_chunk : line.short_off) * lay.nchunks) return FusedForm::kStream;
+    const bool small = groups <= 256 ? 2 * groups + 3 * per_user < line.small + off : groups + 5 * per_user < line.small_beyond + off;
     if (small) return FusedForm::kSmall;
-    if (stochastic) return groups < kFuStreamLineStochastic ? FusedForm::kTeams : FusedForm::kStream;
-    return groups < kFuStreamLine || !lay.vec_aligned ? FusedForm::kTeams : FusedForm::kStream;
-}
-static uint64_t fused_chunks_per_workgroup(const Layout &lay, bool stochastic)
-{
-    return fused_form(lay, stochastic) == FusedForm::kSmall ? kFuCpbSmall : kFuCpb;
+    if (groups < line.stream) return FusedForm::kTeams;
+    // of the closest representative, the teams stay ahead where nearly all chunks are whole and off the grid
+    return stochastic || counts || lay.vec_aligned || lay.d <= kFuWhole * lay.nchunks ? FusedForm::kStream : FusedForm::kTeams;
 }
 
 size_t fused_workspace_bytes(const Layout &lay)
 {
-    static_assert(kFuSmallLineStochastic >= kFuSmallLine && kFuSmallLineBeyondStochastic >= kFuSmallLineBeyond,
-                  "a plan's workspace serves both conversions");
-    const uint64_t cpb = fused_chunks_per_workgroup(lay, true);
+    // a plan's workspace serves both conversions, with and without counts: the small form, a workgroup a chunk, takes the most
+    const bool small = fused_form(lay, false, false) == FusedForm::kSmall || fused_form(lay, false, true) == FusedForm::kSmall ||
+                       fused_form(lay, true, false) == FusedForm::kSmall || fused_form(lay, true, true) == FusedForm::kSmall;
+    const uint64_t cpb = small ? kFuCpbSmall : kFuCpb;
     const uint64_t nblk = (lay.nchunks + cpb - 1) / cpb;
     // the look-back entries and a ticket counter (one 64-bit slot per user), the partial symbol-count tables of the
     // histogram option, plus alignment slack
@@ -865,22 +886,23 @@ static void launch_fused_waves(const Layout &lay, const co3_encode_args &a, cons
 
 // Wavefronts per SIMD the kernel is cut for.  A team's threads hold sixteen elements: two workgroups of 1024 threads fit a CU up
 // to 64 registers (the stochastic conversion spills fifteen for that: sixteen users of 2 M elements 110 -> 99 us).  The
-// streaming form: five only for the conversion to the nearest representative without symbol counts (k_encode_fused's comment).
+// streaming form: five only for the conversion to the nearest representative without symbol counts, on the grid (k_encode_fused's comment).
 template <bool kSR, bool kHist>
 static void launch_fused_variant(FusedForm form, const Layout &lay, const co3_encode_args &a, const BookDev *books,
                                  uint32_t *tickets, uint64_t *lb_state, uint32_t nblk, uint64_t *hist_rep, hipStream_t s)
 {
     if (form == FusedForm::kSmall) launch_fused_waves<kSR, kFuCpbSmall, kFuTeam, kSR ? 6 : 8, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
     else if (form == FusedForm::kTeams) launch_fused_waves<kSR, kFuCpb, kFuTeam, 8, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
-    else launch_fused_waves<kSR, kFuCpb, 1, kSR || kHist ? 4 : 5, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    else if (kSR || kHist || !lay.vec_aligned) launch_fused_waves<kSR, kFuCpb, 1, 4, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
+    else if constexpr (!kSR && !kHist) launch_fused_waves<kSR, kFuCpb, 1, 5, kHist>(lay, a, books, tickets, lb_state, nblk, hist_rep, s);
 }
 
 hipError_t launch_encode_fused(const Layout &lay, const co3_encode_args &a, const BookDev *books, hipStream_t s)
 {
     if (lay.U == 0) return hipSuccess;
     const bool sr = a.rounding == CO3_ROUND_STOCHASTIC;
-    const FusedForm form = fused_form(lay, sr);
-    const uint64_t cpb = fused_chunks_per_workgroup(lay, sr);
+    const FusedForm form = fused_form(lay, sr, a.hist != nullptr);
+    const uint64_t cpb = form == FusedForm::kSmall ? kFuCpbSmall : kFuCpb;
     const uint64_t nblk = (lay.nchunks + cpb - 1) / cpb;
     uint64_t *base = reinterpret_cast<uint64_t *>((reinterpret_cast<uintptr_t>(a.workspace) + 255u) & ~(uintptr_t)255u);
     // A ticket counter per user and the look-back entries.  Atomics on one cache line take turns whichever word they
