@@ -172,8 +172,8 @@ __global__ __launch_bounds__(kThreads, kThreads == kFitThreads ? 6 : 7) void k_f
         for (int j = 0; j < 4; ++j) s_red[j][t] = a[j];
     }
     __syncthreads();
-    for (int o = kFold / 2; o > 0; o >>= 1) {   // a thread for every sum of a pair
-        if (t < 4u * (uint32_t)o) s_red[t / o][t % o] += s_red[t / o][t % o + o];
+    for (uint32_t o = kFold / 2; o > 0; o >>= 1) {   // every sum of a pair by a thread: in the first step more than the smaller workgroup has
+        for (uint32_t k = t; k < 4u * o; k += kThreads) s_red[k / o][k % o] += s_red[k / o][k % o + o];
         __syncthreads();
     }
     co3_gennorm_params out = {0.0, 0.0, 0.0, 0.0};

@@ -155,6 +155,24 @@ def test_fit_of_as_many_pairs_as_cus_and_more(nseg):
     check_params(got, fitm.fit_round(g, m, 0.5, kw["seg_len"]))
 
 
+@pytest.mark.parametrize("n", [128 * 4096, 128 * 4096 + 1, 300 * 4096 + 77])
+def test_fit_of_many_pairs_with_a_layer_of_many_chunks(n):
+    # more pairs than CUs: every chunk of a layer of 128, 129 and 301 is in all four of its sums, as where the pairs are few
+    rng = np.random.default_rng(91)
+    short = 40
+    for nseg in (257, 300):
+        d = n + short * (nseg - 1)
+        g = syn.gennorm_numpy(rng, d, 1.3, 1e-3).astype(np.float32)[None, :]
+        g[0, :n] += np.linspace(0.0, 2e-3, n).astype(np.float32)      # chunks that differ
+        m = np.roll(g, 5, axis=1) * np.float32(0.25)
+        kw = dict(E=4, M=3, U=1, d=d, bias=[[16] * nseg], seg_len=[n] + [short] * (nseg - 1), seg_book=[0] * nseg)
+        _, got, _, _ = gpu_fit(kw, g, m, 0.5)
+        few = dict(kw, d=n + short, bias=[[16] * 2], seg_len=[n, short], seg_book=[0] * 2)
+        _, alone, _, _ = gpu_fit(few, g[:, : n + short], m[:, : n + short], 0.5)
+        assert np.array_equal(got[:, :2].copy().view(np.uint64), alone.view(np.uint64)), nseg
+        check_params(alone, fitm.fit_round(g[:, : n + short], m[:, : n + short], 0.5, few["seg_len"]))
+
+
 def test_fit_is_deterministic_and_gamma_zero_ignores_memory():
     E, M, U, d = 4, 3, 3, 4096 * 7 + 11
     rng = np.random.default_rng(3)
