@@ -231,11 +231,12 @@ struct AggPart {
 // the other: on_user(u, ix, st, tab, book) with the chunk started, on_none() in the turns that are left over.
 // kBytes: tables of values (4) or of symbols (2).  kAcross: the wavefronts of the workgroup share a chunk; else each has
 // a chunk of its own.  in_order: users u0, u0 + 1, .. with kAcross too.  place(i): where the lane goes on in its sub-chunk (see
-// StreamPlaces); to_end: the sub-chunks are decoded to their ends.
+// StreamPlaces); to_end: the sub-chunks are decoded to their ends.  kAhead: (kAcross) a user's index is asked for ahead of the user
+// before, the first one's ahead of the table.
 struct FromTheStart {
     __device__ inline uint32_t operator()(uint32_t) const { return 0u; }
 };
-template <bool kAcross, int kBytes, int kUsers, class OnUser, class Place = FromTheStart>
+template <bool kAcross, int kBytes, int kUsers, bool kAhead = true, class OnUser, class Place = FromTheStart>
 __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, OnUser on_user, bool in_order = false, Place place = Place{}, bool to_end = true)
 {
     const Layout &lay = p.lay;
@@ -262,9 +263,6 @@ __device__ inline void each_user(const AggPart &p, uint32_t u0, uint32_t users, 
         uint32_t *win = p.smem + front_words((own ? p.waves : 1u) * tab_words) + p.wave * window_words(lay.A);
         tab.init(lds_address(my_tab), lay.A);
         auto user_of = [&](uint32_t i) { return u0 + (in_order ? i : p.wave + i * p.waves); };
-        // ahead of the user before; not where there is none, for the table's first words come behind what is asked for before them
-        // (the average of two users, one a wavefront, in [1,5,2]: 11.65 us ahead of the table, 11.55 behind it, 11.4 with the user)
-        constexpr bool kAhead = kUsers != 1;
         IndexAhead ahead;
         if (kAhead && user_of(0) < lay.U) ahead = request_of(user_of(0));
         if (!own) {
@@ -575,7 +573,7 @@ static_assert(kStageUsers <= 2 * kStageWaves && stage_bytes(kStageUsers) <= 160 
 // one wavefront after the other (the others at barriers).  A small launch is one workgroup's way: a round of three users of
 // 63 112 elements in [1,4,1] with a scale 29.5 -> 23.2 us, of four of 600 001 in [1,5,2] with a table each 47 -> 40, of ten
 // of 10^6 in [1,4,3] with a scale 86 -> 70, of sixteen of 300 001 in [1,5,2] 66 -> 60.
-template <int kUsers>
+template <int kUsers, bool kAhead>
 __device__ inline void aggregate_staged(const AggPart &p)
 {
     const Layout &lay = p.lay;
@@ -592,7 +590,7 @@ __device__ inline void aggregate_staged(const AggPart &p)
     u32x16 pk[kUsers];
 #pragma unroll
     for (int s = 0; s < kUsers; ++s) pk[s] = 0u;
-    each_user<true, 2, kUsers>(
+    each_user<true, 2, kUsers, kAhead>(
         p, 0, kUsers,
         [&](uint32_t i, uint32_t, const ChunkIndex &ix, Stream &st, const DecTable<2> &tab, const BookDev *book) {
             decode_started<false>(st, p.g, ix, lay.A, tab, book, SymbolEntry{},
@@ -696,7 +694,7 @@ __device__ __forceinline__ void aggregate_rare(uint32_t *smem, uint32_t places_a
         int lo, hi;
         bias_range(lay, p.g.seg, lo, hi);
         ordered = lay.U <= 4u && p.waves < lay.U && (p.g.scaled || int_sum_bits(lay, hi - lo, lay.U) > 53);
-        if (lay.U <= 2u * p.waves && stage_bytes(lay.U) <= 4u * places_at) return aggregate_staged<2>(p);
+        if (lay.U <= 2u * p.waves && stage_bytes(lay.U) <= 4u * places_at) return aggregate_staged<2, true>(p);
     }
     if (scaled) aggregate_spread<kAcross, true, 4>(p, sp, ordered);
     else aggregate_spread<kAcross, false, 2>(p, sp, ordered);
@@ -735,13 +733,13 @@ __global__ __launch_bounds__(64 * kAggWaves, 4) void k_aggregate(Layout lay, Agg
 }
 
 // The same where a workgroup's wavefronts take all users of a chunk in one turn, one or two each.
-template <int kUsers>
+template <int kUsers, bool kAhead>
 __global__ __launch_bounds__(64 * kStageWaves, kUsers == 1 ? 6 : 4) void k_aggregate_staged(Layout lay, AggArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const AggPart p = agg_part<true>(lay, a, smem, 0);
     round_toward_zero();
-    aggregate_staged<kUsers>(p);
+    aggregate_staged<kUsers, kAhead>(p);
 }
 
 __global__ __launch_bounds__(64) void k_mark_scaled(Layout lay, SegDev *__restrict__ segs)
@@ -830,8 +828,13 @@ static size_t staged_lds(const Layout &lay, uint32_t waves)
 static hipError_t launch_aggregate_staged(const Layout &lay, const AggArgs &a, uint32_t waves, hipStream_t s)
 {
     const size_t lds = staged_lds(lay, waves);
-    if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1>, lay, waves, true, lds, s, a);
-    return launch_aggregate_k(k_aggregate_staged<2>, lay, waves, true, lds, s, a);
+    // One user a wavefront: there is none before to ask ahead of, and a launch of up to eight wavefronts a CU waits for the table's
+    // first words behind the index (the average in [1,5,2], index ahead of the table and with the user: two users of 10^6 elements
+    // 11.1 and 10.85 us, three of 2 M 12.9 and 12.75, four 12.0 and 12.05; eight 14.4 and 14.7; four of 10^7 33.0 and 33.3, of 25 10^7
+    // 557 and 571).
+    if (lay.U <= waves && (uint64_t)lay.U * lay.nchunks <= 2048) return launch_aggregate_k(k_aggregate_staged<1, false>, lay, waves, true, lds, s, a);
+    if (lay.U <= waves) return launch_aggregate_k(k_aggregate_staged<1, true>, lay, waves, true, lds, s, a);
+    return launch_aggregate_k(k_aggregate_staged<2, true>, lay, waves, true, lds, s, a);
 }
 
 // Wavefronts of a workgroup that takes all users of a chunk in one turn, one each or two, where that is the better way (else 0).  A launch
