@@ -853,7 +853,7 @@ static hipError_t launch_aggregate_staged(const Layout &lay, const AggArgs &a, u
 // left for more than twelve users where a workgroup of them takes sixteen in eight wavefronts and two such fit a CU (two rounds of
 // 13 to 15 users, [1,5,2]: 24 22), at four rounds (16 users 50 48) and beyond 1280 or 1400 chunks.
 // A table for every wavefront leaves less room in LDS and is a load more before every chunk's first symbol: beyond what the
-// device holds only tables of up to 64 symbols, to 1250 chunks (of [1,2,1] and [1,3,1], this way and integer
+// device holds (five users of 1264 chunks in [1,2,1] 22, integer sums 29) only tables of up to 64 symbols, to 1250 chunks (of [1,2,1] and [1,3,1], this way and integer
 // sums: 1036 chunks of ten users 35 39, of eight 25 33; 1221 of ten 39 41; 1587 of ten 48 44, of eight 33 37; 1954 of ten 57 44,
 // of six 34 31).
 static uint32_t staged_waves(const Layout &lay, bool ints)
@@ -862,7 +862,8 @@ static uint32_t staged_waves(const Layout &lay, bool ints)
     const uint32_t each = (lay.U + kStageWaves - 1) / kStageWaves;
     const uint32_t waves = (lay.U + each - 1) / each;
     const uint64_t pieces = (staged_lds(lay, waves) + 1279) / 1280;   // LDS is given out in pieces, 128 of them
-    const uint64_t per_cu = 128 / pieces < 24 / waves ? 128 / pieces : 24 / waves;
+    const uint32_t resident = (waves <= 12 ? 32 : 24) / waves;
+    const uint64_t per_cu = 128 / pieces < resident ? 128 / pieces : resident;
     if (per_cu == 0) return 0;
     const uint64_t rounds = (lay.nchunks + 255) / 256;   // workgroups of the busiest CU
     const bool few = rounds <= per_cu, small = lay.A <= 64u;

@@ -826,30 +826,35 @@ __global__ void k_zero_fused(uint64_t *p, uint64_t n, uint64_t *q, uint64_t nq)
 // few workgroups is short and chunks off the 16-byte grid cost nothing more: eight users of 10^6 elements, in this form and in the
 // streaming form, 30 and 49 us; one of 8 M 32 and 48; sixteen of 2 M 89 and 107; eight of 6 M 132 and 143; sixteen of
 // 6.4 M 260 and 260; of 12 M 466 and 462; of 25.6 M 966 and 942; with a third of the chunks off the grid, of 8 M 333 and 382, of 12 M
-// 483 and 560.  With symbol counts and layers off the grid, sixteen users of 28 M in [1,4,3] 1170 and 1206, but ten of 8.3 M in [1,2,0],
-// where more of a wavefront's lanes count the same symbol, 287 and 252.  The stochastic conversion, teams and streaming: sixteen users of 2 M elements 99 and 106 us, of 6.4 M 289 and 271.
+// 483 and 560.  The stochastic conversion, teams and streaming: sixteen users of 2 M elements 99 and 106 us, of 6.4 M 289 and 271.
 enum class FusedForm { kSmall, kTeams, kStream };
 // In groups of kFuCpb chunks and groups per user.  Small: 2 groups + 3 of a user's up to a workgroup of teams for every CU, groups + 5
 // of a user's beyond, where a user's counter is what the small form waits for; later off the grid.  Streaming: from a number of
 // groups, and sooner where chunks are short on average (layers of few elements), for which a wavefront each is enough.
 // us, small, teams, streaming:
 //   with symbol counts, which take turns in LDS: [1,2,0], 24 users of 72 groups 17.5 22.3 24.9, of 288 29.8 36.6 38.2, of 2400
-//   162 145 138; [1,4,3], eight users of 256 groups 32.5 26.1 29.1, 24 of 2400 163 116 122
-//   stochastic, eight users of 296 groups 31.5 30.5 32.8, of 3200 298 163 157
+//   162 145 138; [1,4,3], eight users of 256 groups 32.5 26.1 29.1, 24 of 2400 163 116 122; [1,3,2], eight of 6980 - 342 316; [1,5,2],
+//   four of 2168 - 113 133
+//   stochastic, eight users of 296 groups 31.5 30.5 32.8, of 3200 298 163 157, five of 3225 - 187 253
 //   layers of one chunk each, off the grid where their length is odd: of 20 elements, 40 users of 600 groups 27 23 20, of 9000 413 205 141;
 //   of 301 27 24 19, 427 200 147; of 701, of 600 27 24 21; of 1001 28 24 23, 474 222 200; of 3101, of 9000 - 356 372
 //   with counts, of 701, 40 users of 600 groups 34 29 26; of 3101, of 1520 105 79 77
 //   stochastic, twelve users, of 701, of 156 groups 25 23 22, of 600 51 39 35, of 1500 105 66 65; of 1500, of 1500 112 75 76; with counts,
 //   of 701, of 600 56 44 47, of 301, 40 users of 600 43 42 39.  (From 400 groups on: of layers that differ, a launch waits for the longest's
 //   wavefront, fourteen users of sixty layers of 974 elements on average 43 and 52 streaming.)
-//   layers of 13 333 at odd elements, 40 users of 9000 groups, teams and streaming 341 324; with counts 376 338
+// Off the grid, where streaming has shifted vectors, layers of many chunks, teams and streaming:
+//   six users of 2730, 5010 and 8010 groups 135 159, 228 260, 348 381; 40 of 14 000 601 595: the teams at every size; but layers of 13 333
+//   elements, of which a quarter of the chunks are ragged, 40 users of 9000 groups 341 324
+//   with counts, of 5010 groups in [1,5,2] 240 269; in [1,2,0] 285 287, 40 users of 3680 209 195, of 8080 436 383
+//   stochastic, 40 users of 2720 groups 138 183, of 5040 245 298, of 8080 388 376, of 14 080 668 635; six of 8010 398 457
 // short_chunk, short_off: the average of a chunk's elements, where all layers are on the grid, and else.
 struct FormLines { uint64_t small, small_beyond, stream, short_chunk, short_off, short_stream; };
 constexpr FormLines kFuNearest = {280, 400, 7000, 350, 1050, 400};
-constexpr FormLines kFuCounts = {400, 550, 2000, 3150, 3150, 400};
-constexpr FormLines kFuStochastic = {520, 550, 2600, 1050, 1050, 400};
-constexpr FormLines kFuStochasticCounts = {520, 550, 2600, 350, 350, 600};
-constexpr uint64_t kFuSmallOff = 60, kFuWhole = 3500;
+constexpr FormLines kFuCounts = {400, 550, 7000, 3150, 3150, 400};
+constexpr FormLines kFuStochastic = {520, 550, 4000, 1050, 1050, 400};
+constexpr FormLines kFuStochasticCounts = {520, 550, 4000, 350, 350, 600};
+constexpr uint64_t kFuFewSymbols = 2000, kFuMoreSymbols = 4000;   // counts, alphabets of up to 16 and up to 64
+constexpr uint64_t kFuSmallOff = 60, kFuFewOff = 3500, kFuStreamOff = 7000, kFuWhole = 3500;
 static FusedForm fused_form(const Layout &lay, bool stochastic, bool counts)
 {
     const FormLines &line = stochastic ? (counts ? kFuStochasticCounts : kFuStochastic) : (counts ? kFuCounts : kFuNearest);
@@ -857,9 +862,10 @@ static FusedForm fused_form(const Layout &lay, bool stochastic, bool counts)
     if (groups >= line.short_stream && lay.d <= (lay.vec_aligned ? line.short_chunk : line.short_off) * lay.nchunks) return FusedForm::kStream;
     const bool small = groups <= 256 ? 2 * groups + 3 * per_user < line.small + off : groups + 5 * per_user < line.small_beyond + off;
     if (small) return FusedForm::kSmall;
-    if (groups < line.stream) return FusedForm::kTeams;
-    // of the closest representative, the teams stay ahead where nearly all chunks are whole and off the grid
-    return stochastic || counts || lay.vec_aligned || lay.d <= kFuWhole * lay.nchunks ? FusedForm::kStream : FusedForm::kTeams;
+    const uint64_t stream = counts && !stochastic && lay.A <= 64 ? (lay.A <= 16 ? kFuFewSymbols : kFuMoreSymbols) : line.stream;
+    if (lay.vec_aligned) return groups < stream ? FusedForm::kTeams : FusedForm::kStream;
+    if (counts && !stochastic && lay.A <= 16) return groups < kFuFewOff ? FusedForm::kTeams : FusedForm::kStream;
+    return groups >= kFuStreamOff && (stochastic || lay.d <= kFuWhole * lay.nchunks) ? FusedForm::kStream : FusedForm::kTeams;
 }
 
 size_t fused_workspace_bytes(const Layout &lay)

@@ -452,7 +452,7 @@ def test_wide_average_with_a_scale(U, E, M, chunks, own):
     (7, 768, 3, 2, False, False), (7, 769, 3, 2, False, False), (7, 1025, 3, 2, False, False),               # in LDS, integer sums
     (10, 1280, 2, 1, False, False), (10, 1281, 2, 1, False, False), (14, 256, 4, 3, False, True), (14, 257, 4, 3, False, True),
     (12, 1400, 5, 2, False, False), (12, 1401, 5, 2, False, False), (17, 1280, 5, 2, False, False), (17, 1281, 5, 2, False, False),
-    (8, 256, 5, 2, False, False), (8, 257, 5, 2, False, False), (2, 1024, 4, 3, False, True), (2, 1025, 4, 3, True, False),   # one a wavefront
+    (8, 256, 5, 2, False, False), (8, 257, 5, 2, False, False), (2, 1024, 4, 3, False, True), (2, 1025, 4, 3, True, False), (5, 1264, 2, 1, True, False),   # one a wavefront
     (31, 250, 3, 2, False, False), (31, 120, 5, 2, False, True), (32, 120, 5, 2, False, True),
     (10, 1250, 3, 1, True, False), (10, 1251, 3, 1, True, False), (6, 1100, 5, 2, True, False), (31, 70, 4, 3, True, False)])
 def test_average_at_the_edges_of_its_rules(U, chunks, E, M, own, gain):

@@ -1513,7 +1513,8 @@ def test_single_sweep_counts_odd_elements_once(U, seg_len, seed, hist):
 
 
 @pytest.mark.parametrize("U,seg_len,seed,hist", [(7001, [4100], None, False), (7001, [4100], None, True), (4001, [4099, 70], 3, False),
-                                                 (4001, [5, 4099], 3, False), (4001, [3, 2, 4098], 3, True)])
+                                                 (4001, [5, 4099], 3, False), (4001, [3, 2, 4098], 3, True),
+                                                 (7001, [5, 4099], 3, False), (7001, [3, 4098], 3, True)])
 def test_single_sweep_streaming_form(U, seg_len, seed, hist):
     # a wavefront a chunk, which large inputs take: whole and ragged chunks, of the stochastic conversion also whole ones off the
     # 16-byte grid
