@@ -847,6 +847,9 @@ enum class FusedForm { kSmall, kTeams, kStream };
 //   elements, of which a quarter of the chunks are ragged, 40 users of 9000 groups 341 324
 //   with counts, of 5010 groups in [1,5,2] 240 269; in [1,2,0] 285 287, 40 users of 3680 209 195, of 8080 436 383
 //   stochastic, 40 users of 2720 groups 138 183, of 5040 245 298, of 8080 388 376, of 14 080 668 635; six of 8010 398 457
+// Users of up to eight chunks, whose counters are not waited for, small, teams, streaming: of one chunk, 500 users 10 11 19, 2500 31 42 46; of two 18
+//   18 24, 54 57 69; of eight 47 48 52, 193 202 202; of one of 300 elements 9 10 13, 16 31 26, of four of 300 16 15 15, 51 54 38; with counts, of
+//   eight 52 86 91, 201 349 346, of four of 300 28 56 59, 86 229 232; stochastic, of eight 49 53 52, 194 212 205, of one of 300 23 24 15, 32 50 36
 // short_chunk, short_off: the average of a chunk's elements, where all layers are on the grid, and else.
 struct FormLines { uint64_t small, small_beyond, stream, short_chunk, short_off, short_stream; };
 constexpr FormLines kFuNearest = {280, 400, 7000, 350, 1050, 400};
@@ -854,12 +857,15 @@ constexpr FormLines kFuCounts = {400, 550, 7000, 3150, 3150, 400};
 constexpr FormLines kFuStochastic = {520, 550, 4000, 1050, 1050, 400};
 constexpr FormLines kFuStochasticCounts = {520, 550, 4000, 350, 350, 600};
 constexpr uint64_t kFuFewSymbols = 2000, kFuMoreSymbols = 4000;   // counts, alphabets of up to 16 and up to 64
+constexpr uint64_t kFuFewGroups = 2;   // of a user's
 constexpr uint64_t kFuSmallOff = 60, kFuFewOff = 3500, kFuStreamOff = 7000, kFuWhole = 3500;
 static FusedForm fused_form(const Layout &lay, bool stochastic, bool counts)
 {
     const FormLines &line = stochastic ? (counts ? kFuStochasticCounts : kFuStochastic) : (counts ? kFuCounts : kFuNearest);
     const uint64_t per_user = (lay.nchunks + kFuCpb - 1) / kFuCpb, groups = (uint64_t)lay.U * per_user, off = lay.vec_aligned ? 0 : kFuSmallOff;
-    if (groups >= line.short_stream && lay.d <= (lay.vec_aligned ? line.short_chunk : line.short_off) * lay.nchunks) return FusedForm::kStream;
+    const bool shorts = groups >= line.short_stream && lay.d <= (lay.vec_aligned ? line.short_chunk : line.short_off) * lay.nchunks;
+    if (per_user <= kFuFewGroups && groups < line.stream && (counts || !shorts || (!stochastic && lay.nchunks < 4))) return FusedForm::kSmall;
+    if (shorts) return FusedForm::kStream;
     const bool small = groups <= 256 ? 2 * groups + 3 * per_user < line.small + off : groups + 5 * per_user < line.small_beyond + off;
     if (small) return FusedForm::kSmall;
     const uint64_t stream = counts && !stochastic && lay.A <= 64 ? (lay.A <= 16 ? kFuFewSymbols : kFuMoreSymbols) : line.stream;
